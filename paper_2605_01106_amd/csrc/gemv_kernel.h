@@ -17,7 +17,7 @@ template <int BF16> struct W8;
 template <> struct W8<1> {
   uint4 v;
   __device__ __forceinline__ void load(const void* row, int k) {
-    v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(row) + k);
+    v = load_once16(static_cast<const uint16_t*>(row) + k);
   }
   __device__ __forceinline__ float dot(const float4& a, const float4& b, float s) const {
     s = fmaf(bf16lo(v.x), a.x, s); s = fmaf(bf16hi(v.x), a.y, s);

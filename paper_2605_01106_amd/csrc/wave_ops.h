@@ -6,6 +6,16 @@
 
 namespace hh {
 
+// 16 bytes of a matrix that one workgroup of a launch reads, once: a streaming load, so that the weights of a pass (0.9 GB
+// and more) do not push out of the caches what the next small launches start with - activations, launch arguments, code.
+// Decode passes of one sequence, two rounds: 0.5B shape, k = 2, 7.18 -> 6.69 ms; 3B shape, k = 4, 10.08 -> 9.59 ms.  Not for
+// float32 weights: models of that size stay in the cache from pass to pass (2 % slower).
+__device__ __forceinline__ uint4 load_once16(const void* p) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 v = __builtin_nontemporal_load(static_cast<const u32x4*>(p));
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // v of lane l combined with the lane that a DPP control selects (row_shr, quad_perm, row_bcast ...)
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float v) {
