@@ -66,7 +66,8 @@ enum {
   HH_KF_ROWS_LDS = 32,     /* with HH_KF_MID_OFF: 17..96 activation rows through the LDS-staged many-row GEMM */
   HH_KF_SSM_SEQUENTIAL = 64, /* passes of 16 and more positions: the position-by-position scan instead of the matmul form */
   HH_KF_NO_HANDOVER = 128, /* many-row passes: the SwiGLU result goes through float32 and a split kernel to the down projection */
-  HH_KF_SSM_MATMUL = 512,  /* the matmul form of the scan also for launches of fewer than 128 workgroups (default: the sequential kernel there) */
+  HH_KF_SSM_MATMUL = 512,  /* one walk of the matmul form per head pair also for launches of fewer than 128 workgroups (default there: segments
+                              of a long pass side by side, or the sequential kernel) */
   HH_KF_MID_WIDE = 1024,   /* 17..80 activation rows: the 8-wavefront, 128-column-window shape of the 81..96-row products (one workgroup per compute unit) */
   HH_KF_CANARIES = 256     /* every region the library carves from the workspace is followed by 256 guard bytes (see hh_check_canaries) */
 };

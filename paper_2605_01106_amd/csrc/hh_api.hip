@@ -80,7 +80,7 @@ struct hh_ctx {
   uint16_t* planes_act;  // SwiGLU result of a many-row pass, handed to the down projection as split planes
   float* gemm_partial_side;
   float* ho;             // [Mmax][D] attention branch after its output projection (full mode)
-  float *rope, *h, *zx, *qkv, *g, *o, *act, *logits_d, *logits_v, *logits_p, *lasth, *part_o, *part_ml, *export_buf;
+  float *rope, *h, *zx, *qkv, *g, *o, *act, *logits_d, *logits_v, *logits_p, *lasth, *part_o, *part_ml, *export_buf, *seg_scratch;
   int max_passes;
   // host state
   int phase = PH_CREATED;
@@ -228,6 +228,7 @@ size_t carve(hh_ctx* x, char* base) {
   x->part_o = c.take<float>(Mv * d.Hq * kMaxSplits * d.Dh);
   x->part_ml = c.take<float>(Mv * d.Hq * kMaxSplits * 2);
   x->export_buf = c.take<float>(B * d.conv_dim * 3);
+  x->seg_scratch = ssd_segment_elems(d) > 0 ? c.take<float>(ssd_segment_elems(d)) : nullptr;
   const size_t state = B * d.Hm * d.P * d.N;
   const size_t ring = B * d.ring_slots * d.ring_w;
   const size_t pool = (size_t)d.n_pages * d.Hkv * d.page_tokens * d.Dh * esz;
@@ -387,7 +388,7 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
       SsmArgs a{};
       a.layers = nullptr; a.one = w; a.layer0 = 0; a.n_layers_z = 1;
       a.zx = x->zx; a.g = x->g; a.pos0 = x->pos0; a.n_tok = n_tok; a.T = T; a.B = B;
-      a.state_in = state_in; a.state_out = state_out; a.write_ring = 1;
+      a.state_in = state_in; a.state_out = state_out; a.write_ring = 1; a.seg_scratch = x->seg_scratch;
       HH_LAUNCH(HH_K_SSM, launch_ssm(d, a, s));
     }
     {  // h += W_out * gated_norm(g)

@@ -103,9 +103,11 @@ struct SsmArgs {
   int T, B;
   int state_in, state_out;   // in: 0 committed S, 1 S_draft, 2 zeros.  out: 0 none, 1 S, 2 S_draft
   int write_ring;
+  float* seg_scratch;        // ssd_segment_elems() floats for the segmented form of long passes over few sequences (nullptr: not available)
 };
 hipError_t launch_ssm(const Dims& d, const SsmArgs& a, hipStream_t s);
 // matmul-form kernel for passes with many positions (ssd_mfma.hip); true if it took the pass
+size_t ssd_segment_elems(const Dims& d);
 bool launch_ssd_mfma(const Dims& d, const SsmArgs& a, hipStream_t s, hipError_t* err);
 
 // ---- attention branch

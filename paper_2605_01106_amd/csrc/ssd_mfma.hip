@@ -26,6 +26,8 @@
 // padded so that the operand reads of the two large products are free of bank conflicts.
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "hh_internal.h"
 #include "wave_ops.h"
 #include "trace.h"
@@ -52,8 +54,19 @@ struct SsdLds {
   static constexpr int kFloats = kCum + 2 * kSsdL;
 };
 
-template <int N>
-__global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmArgs a) {
+// SEG_WALK: a workgroup walks the whole pass.  With few sequences that leaves most of the chip idle, so the pass is
+// cut into segments of `len` positions (blockIdx.z): SEG_LOCAL computes every segment's own contribution to the state
+// (as if zeros entered it) and its log-decay sum, ssd_combine_kernel chains them and leaves the state that enters each
+// segment in the same place, and SEG_OUT computes the outputs of every segment from the state entering it.
+enum { SEG_WALK = 0, SEG_LOCAL = 1, SEG_OUT = 2 };
+struct SsdSeg {
+  float* states;   // [B][n][Hm][P][N]
+  float* decay;    // [B][n][Hm] log-decay sums
+  int len, n;
+};
+
+template <int N, int MODE>
+__global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmArgs a, const SsdSeg seg) {
   typedef SsdLds<N> Lds;
   constexpr int L = kSsdL, P = kSsdP, NT = N / 16, HALF = L / 2;
   constexpr int LDB = Lds::LDB, LDT = Lds::LDT, LDX = Lds::LDX, LDM = Lds::LDM;
@@ -75,6 +88,10 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
   int nt = a.T;
   if (a.n_tok != nullptr) nt = a.n_tok[b];
   if (nt <= 0) return;
+  // positions t0 .. t1 - 1 of the pass (seg.len is a multiple of the chunk length)
+  const int t0 = MODE == SEG_WALK ? 0 : (int)blockIdx.z * seg.len, t1 = MODE == SEG_WALK ? nt : min(nt, t0 + seg.len);
+  if (MODE != SEG_WALK && t0 >= nt) return;
+  float* const seg_state = MODE == SEG_WALK ? nullptr : seg.states + (((size_t)b * seg.n + blockIdx.z) * d.Hm + h) * P * N;
   const int pos0 = a.pos0[b];
   const int rmask = d.ring_slots - 1;
   float* ring = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
@@ -84,8 +101,9 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
   ssd_f32x4 S[NT];
   {
     const float* src = a.state_in == 0 ? ly.S : (a.state_in == 1 ? ly.S_draft : nullptr);
-    if (src != nullptr) {
-      const float* sp = src + (((size_t)b * d.Hm + h) * P + 16 * wq + j) * N + 4 * g;
+    if (MODE == SEG_LOCAL) src = nullptr;
+    if (MODE == SEG_OUT || src != nullptr) {
+      const float* sp = (MODE == SEG_OUT ? seg_state : src + ((size_t)b * d.Hm + h) * P * N) + (16 * wq + j) * N + 4 * g;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const float4 v = *reinterpret_cast<const float4*>(sp + 16 * t);
@@ -102,7 +120,8 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
   // wavefronts (WPH of them), so that the row a wavefront loads is uniform and its address scalar
   constexpr int WPH = (NG + 63) / 64;
   const int sh = w / WPH < 2 ? w / WPH : 0, sg_raw = tid - 64 * WPH * sh;
-  const bool stager = w < 2 * WPH && sg_raw < NG;
+  const bool stager = w < 2 * WPH && sg_raw < (MODE == SEG_LOCAL ? NG - N / 4 : NG);   // (the state alone does not need C)
+  const bool keep_raw = MODE != SEG_LOCAL && a.write_ring;
   const int sg = stager ? sg_raw : 0;
   // first of the 4 channels (index into xBC) and where its outputs go
   const int ch = sg < P / 4 ? (2 * blockIdx.x) * P + 4 * sg : sg < 2 * (P / 4) ? (2 * blockIdx.x + 1) * P + 4 * (sg - P / 4) : d.d_inner + 4 * (sg - 2 * (P / 4));
@@ -124,11 +143,12 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
       rows[u] = pos_ < 0 ? make_float4(0.f, 0.f, 0.f, 0.f) : v_;                                         \
     }                                                                                                    \
   } while (0)
-  if (stager) HH_SSD_REQUEST(HALF * sh, 0);
+  if (stager) HH_SSD_REQUEST(t0 + HALF * sh, 0);
+  float total = 0.f;                                   // SEG_LOCAL: log-decay sum of the segment
 
   TR(0);
-  for (int j0 = 0; j0 < nt; j0 += L) {
-    const int tc = min(L, nt - j0);
+  for (int j0 = t0; j0 < t1; j0 += L) {
+    const int tc = min(L, t1 - j0);
     if (j0 == 0) TR(1);
     // ================= staging: conv + SiLU of x, B, C; dt and its running log-decay sum
     if (stager) {
@@ -171,12 +191,12 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
           }
           // the raw inputs stay in the ring for the next pass's window and for rollbacks (x of this pair
           // of heads by every workgroup, B and C by the workgroup of the first pair)
-          if (on && a.write_ring && (sg < 2 * (P / 4) || blockIdx.x == 0))
+          if (on && keep_raw && (sg < 2 * (P / 4) || blockIdx.x == 0))
             *reinterpret_cast<float4*>(ring + (size_t)((pos0 + j0 + jj) & rmask) * d.ring_w + ch) = q3;
         }
       }
       asm volatile("" ::: "memory");                   // (not before this chunk's rows are dead: registers)
-      if (j0 + L < nt) HH_SSD_REQUEST(j0 + L + HALF * sh, 0);   // the next chunk's first rows travel while this one is multiplied
+      if (j0 + L < t1) HH_SSD_REQUEST(j0 + L + HALF * sh, 0);   // the next chunk's first rows travel while this one is multiplied
     } else if (w >= 6 && lane < L) {
       // wavefront 6 + hh': step sizes and log-decay sums of head hh' (= this wavefront's own head: 6 >> 2 = 7 >> 2 = 1
       // does not hold, so index explicitly)
@@ -184,7 +204,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
       const bool on = lane < tc;
       const float rawdt = zx[(size_t)(j0 + min(lane, tc - 1)) * d.ldzx + d.d_inner + d.conv_dim + hd];
       const float dt = on ? ssd_softplus(rawdt + ly.dt_bias[hd]) : 0.f;
-      if (on && a.write_ring) ring[(size_t)((pos0 + j0 + lane) & rmask) * d.ring_w + d.conv_dim + hd] = rawdt;
+      if (on && keep_raw) ring[(size_t)((pos0 + j0 + lane) & rmask) * d.ring_w + d.conv_dim + hd] = rawdt;
       float c = -expf(ly.a_log[hd]) * dt;              // log a_t, summed over the positions up to t
 #pragma unroll
       for (int o = 1; o < L; o <<= 1) {
@@ -197,6 +217,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
     __syncthreads();
     if (j0 == 0) TR(2);
 
+    if (MODE != SEG_LOCAL) {
     // ================= G = C B^T on the tiles at or below the diagonal, M = G * decay * dt to LDS
     {
       const int tt = wq == 0 ? 0 : 1, it = wq == 2 ? 1 : 0;        // slice 3: the tile above the diagonal is zero
@@ -263,10 +284,12 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
       }
     }
 
+    }
     if (j0 == 0) TR(4);
     // ================= state update: S' = exp(cum_L) S + sum_i w_i x_i (outer) B_i
-    {
+    if (MODE != SEG_OUT || j0 + L < t1) {
       const float cl = cums[L - 1], el = expf(cl);
+      total += cl;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -286,8 +309,9 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
   }
   TR(6);
 
-  if (a.state_out != 0) {
-    float* dp = (a.state_out == 1 ? ly.S : ly.S_draft) + (((size_t)b * d.Hm + h) * P + 16 * wq + j) * N + 4 * g;
+  if (MODE == SEG_LOCAL && wq == 0 && lane == 0) seg.decay[((size_t)b * seg.n + blockIdx.z) * d.Hm + h] = total;
+  if (MODE == SEG_LOCAL || (MODE == SEG_WALK && a.state_out != 0)) {
+    float* dp = (MODE == SEG_LOCAL ? seg_state : (a.state_out == 1 ? ly.S : ly.S_draft) + ((size_t)b * d.Hm + h) * P * N) + (16 * wq + j) * N + 4 * g;
 #pragma unroll
     for (int t = 0; t < NT; ++t) *reinterpret_cast<float4*>(dp + 16 * t) = make_float4(S[t][0], S[t][1], S[t][2], S[t][3]);
   }
@@ -296,9 +320,47 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
 #undef HH_SSD_REQUEST
 }
 
-template <int N>
-static hipError_t ssd_launch(const Dims& d, const SsmArgs& a, hipStream_t s) {
-  auto kern = ssd_mfma_kernel<N>;
+// Chains the segments of a pass: the state entering segment q+1 is exp(decay_q) times the one entering q plus what
+// segment q adds.  A thread owns 4 elements of one sequence's state; the segments' contributions are replaced by the
+// states that enter them, and the state behind the last one becomes the sequence's state.
+__global__ __launch_bounds__(256) void ssd_combine_kernel(const Dims d, const SsmArgs a, const SsdSeg seg) {
+  const int b = blockIdx.y;
+  int nt = a.T;
+  if (a.n_tok != nullptr) nt = a.n_tok[b];
+  if (nt <= 0) return;
+  const int ns = (nt + seg.len - 1) / seg.len, per_head = d.P * d.N;
+  const size_t at = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4, state = (size_t)d.Hm * per_head;   // per_head % 1024 == 0
+  const int h = (int)((size_t)blockIdx.x * 1024 / per_head);
+  const LayerDev& ly = a.one;
+  const float* src = a.state_in == 0 ? ly.S : (a.state_in == 1 ? ly.S_draft : nullptr);
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (src != nullptr) s = *reinterpret_cast<const float4*>(src + (size_t)b * state + at);
+  float* p = seg.states + (size_t)b * seg.n * state + at;
+  const float* dec = seg.decay + (size_t)b * seg.n * d.Hm + h;
+  for (int q0 = 0; q0 < ns; q0 += 8) {
+    float4 v[8];
+    float e[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int q = min(q0 + u, ns - 1);
+      v[u] = *reinterpret_cast<const float4*>(p + (size_t)q * state);
+      e[u] = dec[(size_t)q * d.Hm];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (q0 + u >= ns) break;
+      *reinterpret_cast<float4*>(p + (size_t)(q0 + u) * state) = s;
+      const float f = expf(e[u]);
+      s.x = fmaf(f, s.x, v[u].x); s.y = fmaf(f, s.y, v[u].y); s.z = fmaf(f, s.z, v[u].z); s.w = fmaf(f, s.w, v[u].w);
+    }
+  }
+  float* dst = a.state_out == 1 ? ly.S : (a.state_out == 2 ? ly.S_draft : nullptr);
+  if (dst != nullptr) *reinterpret_cast<float4*>(dst + (size_t)b * state + at) = s;
+}
+
+template <int N, int MODE>
+static hipError_t ssd_launch_mode(const Dims& d, const SsmArgs& a, const SsdSeg& seg, hipStream_t s) {
+  auto kern = ssd_mfma_kernel<N, MODE>;
   constexpr int lds = SsdLds<N>::kFloats * (int)sizeof(float);
   static bool enabled = false;
   if (!enabled && lds > 48 * 1024) {
@@ -306,8 +368,54 @@ static hipError_t ssd_launch(const Dims& d, const SsmArgs& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     enabled = true;
   }
-  hipLaunchKernelGGL(kern, dim3(d.Hm / 2, a.B), dim3(512), lds, s, d, a);
+  hipLaunchKernelGGL(kern, dim3(d.Hm / 2, a.B, MODE == SEG_WALK ? 1 : seg.n), dim3(512), lds, s, d, a, seg);
   return hipGetLastError();
+}
+template <int N>
+static hipError_t ssd_launch(const Dims& d, const SsmArgs& a, const SsdSeg& seg, hipStream_t s) {
+  if (seg.n <= 1) return ssd_launch_mode<N, SEG_WALK>(d, a, seg, s);
+  hipError_t e = ssd_launch_mode<N, SEG_LOCAL>(d, a, seg, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(ssd_combine_kernel, dim3(d.Hm * d.P * d.N / 1024, a.B), dim3(256), 0, s, d, a, seg);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return ssd_launch_mode<N, SEG_OUT>(d, a, seg, s);
+}
+
+// When the segmented form is taken.  Fewer than 128 workgroups (sequence, pair of heads) leave half the chip idle in a
+// walk, and the position-by-position kernel that served them is a serial chain of 0.36 us (0.5B shape) or 0.59 us (3B
+// shape) per position.  As many segments as give kSegWorkgroups workgroups (two per compute unit; one at state size 256,
+// where the staged chunk takes 101 KB of LDS), at least one chunk each.  One sequence, pass of 512 positions: 0.5B shape
+// 186 -> 43 us (16.0 + 7.8 + 19.6), 3B shape 300 -> 90 us (31.5 + 10.4 + 48.2); prefill of 509 tokens at the 0.5B shape
+// 13.8 -> 8.7 ms, of 4096 tokens through four 3B blocks 20.8 -> 15.0 ms, 8 sequences of 512 at 12 0.5B blocks 11.2 -> 9.7.
+// The local pass repeats the staging and the state products, so at state size 256 fewer than three segments give nothing
+// (6 sequences at the 3B shape: 4.22 against 4.20 ms with the position-by-position kernel).  From 96 positions on the
+// three launches pay (100 positions: 5 % per prefill at either shape); below, the chain is short enough.
+static constexpr int kSegWorkgroups = 512, kSegMinT = 96;
+
+static bool ssd_shape(const Dims& d) {
+  return d.P == kSsdP && d.Hm % 2 == 0 && d.d_inner % 4 == 0 && d.ldzx % 4 == 0 && d.ring_w % 4 == 0 && d.conv_dim % 4 == 0 &&
+         (d.N == 64 || d.N == 128 || d.N == 256);
+}
+static SsdSeg ssd_segments(const Dims& d, int B, int T) {
+  SsdSeg seg{nullptr, nullptr, 0, 1};
+  const int wgs = (d.Hm / 2) * B, chunks = (T + kSsdL - 1) / kSsdL;
+  const int most = (d.N == 256 ? kSegWorkgroups / 2 : kSegWorkgroups) / wgs;
+  if (wgs >= 128 || T < kSegMinT || most < (d.N == 256 ? 3 : 2)) return seg;
+  const int per = (chunks + most - 1) / most;      // chunks per segment
+  seg.len = per * kSsdL;
+  seg.n = (chunks + per - 1) / per;
+  return seg;
+}
+// floats of scratch for the segment states of any pass of this context
+size_t ssd_segment_elems(const Dims& d) {
+  if (!ssd_shape(d) || d.Tmax < kSegMinT) return 0;
+  size_t most = 0;
+  for (int B = 1; B <= d.Bmax && (d.Hm / 2) * B < 128; ++B) {
+    const size_t n = std::min((size_t)kSegWorkgroups / ((d.Hm / 2) * B), (size_t)(d.Tmax + kSsdL - 1) / kSsdL);
+    most = std::max(most, (size_t)B * n * d.Hm * ((size_t)d.P * d.N + 1));
+  }
+  return most;
 }
 
 // true if the pass was taken by the matmul-form kernel: a single layer's pass over this call's
@@ -315,18 +423,19 @@ static hipError_t ssd_launch(const Dims& d, const SsmArgs& a, hipStream_t s) {
 // 16-byte aligned rows
 bool launch_ssd_mfma(const Dims& d, const SsmArgs& a, hipStream_t s, hipError_t* err) {
   if ((d.flags & HH_KF_SSM_SEQUENTIAL) || a.layers != nullptr || a.zx == nullptr || a.g == nullptr || a.n_acc != nullptr ||
-      a.skip != nullptr || a.T < 16 || d.P != kSsdP || d.Hm % 2 != 0 || d.d_inner % 4 != 0 || d.ldzx % 4 != 0 || d.ring_w % 4 != 0 ||
-      d.conv_dim % 4 != 0 || (reinterpret_cast<uintptr_t>(a.zx) & 15) != 0 || (reinterpret_cast<uintptr_t>(a.g) & 15) != 0)
+      a.skip != nullptr || a.T < 16 || !ssd_shape(d) || (reinterpret_cast<uintptr_t>(a.zx) & 15) != 0 || (reinterpret_cast<uintptr_t>(a.g) & 15) != 0)
     return false;
-  // one workgroup per (sequence, pair of heads) walks the whole pass chunk by chunk: with few of them
-  // (one sequence in prefill: 12 at the 0.5B shape, 20 at the 3B shape) the position-by-position kernel,
-  // which splits every head over several workgroups and stages on wavefronts of its own, is faster
-  // (measured: 12.1 against 15.2 ms, 164 against 184 ms; 16 sequences: 277 against 220 ms)
-  if ((d.Hm / 2) * a.B < 128 && !(d.flags & HH_KF_SSM_MATMUL)) return false;
+  SsdSeg seg{nullptr, nullptr, 0, 1};
+  if ((d.Hm / 2) * a.B < 128 && !(d.flags & HH_KF_SSM_MATMUL)) {
+    seg = ssd_segments(d, a.B, a.T);
+    if (seg.n < 2 || a.seg_scratch == nullptr) return false;
+    seg.states = a.seg_scratch;
+    seg.decay = a.seg_scratch + (size_t)a.B * seg.n * d.Hm * d.P * d.N;
+  }
   switch (d.N) {
-    case 64: *err = ssd_launch<64>(d, a, s); return true;
-    case 128: *err = ssd_launch<128>(d, a, s); return true;
-    case 256: *err = ssd_launch<256>(d, a, s); return true;
+    case 64: *err = ssd_launch<64>(d, a, seg, s); return true;
+    case 128: *err = ssd_launch<128>(d, a, seg, s); return true;
+    case 256: *err = ssd_launch<256>(d, a, seg, s); return true;
   }
   return false;
 }

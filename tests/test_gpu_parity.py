@@ -388,3 +388,21 @@ def test_prefill_scan_matmul_form(B, dtype, d_state, chunk):
     seq = _ctx(B, wts, 4, 400, 3, 10, kv_page_tokens=32, prefill_chunk=chunk, kernel_flags=B.HH_KF_SSM_SEQUENTIAL)
     w2 = run_lockstep(seq, wts, prompts, lens, 10, 3, engine="pass", chunk=64)
     assert w["tokens"] == w2["tokens"]
+
+
+@pytest.mark.parametrize("dtype,d_state,heads,chunk", [(W.BF16, 64, 2, 96), (W.F32, 128, 2, 130), (W.BF16, 128, 32, 352),
+                                                       (W.F32, 256, 26, 200), (W.BF16, 64, 2, 95)])
+def test_prefill_scan_segments(B, dtype, d_state, heads, chunk):
+    """Long passes over few sequences take the scan in segments: one chunk of 32 positions per segment (2 heads) and
+    several (26 and 32 heads x 4 sequences), the shortest pass that takes the form (96 positions; 95 keeps the
+    position-by-position kernel), passes that end inside a segment, sequences that end in the first, in a middle and in
+    the last one or need no further pass.  Compared with the float64 oracle like the other forms, within the tolerance
+    of the storage type; guard bytes behind every workspace region are checked."""
+    cfg = W.scaled_config("seg", n_layers=2, d_model=64, vocab=160, m_heads=heads, m_head_dim=64, d_state=d_state,
+                          n_q_heads=2, n_kv_heads=1, head_dim=32, d_ff=96, w_dtype=dtype)
+    wts = W.make_lively_weights(cfg, 61)
+    lens = [chunk + 101, 17, chunk - 40, 97]
+    prompts = W.make_prompts(cfg.vocab, 4, lens, 23)
+    ctx = _ctx(B, wts, 4, chunk + 160, 3, 8, kv_page_tokens=32, prefill_chunk=chunk, kernel_flags=B.HH_KF_CANARIES)
+    run_lockstep(ctx, wts, prompts, lens, 8, 3, engine="pass", chunk=64, report=_say(f"seg-{dtype}-N{d_state}-H{heads}-T{chunk}"))
+    assert ctx.hh_check_canaries() == 0
