@@ -333,9 +333,11 @@ static bool skinny_plan_k(const GemvArgs& g, int K, SkinnyPlan& p) {
 }
 
 // Number of K windows (1, 2, 4 or 8) the product is computed in, 0 if it does not fit this kernel.
-// Windows are used when the staged activations of a whole row do not fit in LDS, and when the
-// product has too few weight tiles to occupy the chip (N small, K long): the windows run side
-// by side as gridDim.y and a reduction kernel adds them.
+// The whole row where its staged activations fit LDS, however few weight tiles there are: side-by-side windows (gridDim.y)
+// fill the chip but need the reduction launch behind them, which costs more than they gain (5 sequences at the 0.5B shape,
+// 64 tiles: two rounds 15.24 -> 14.55 ms; 8 sequences 1.4 % per round, 12 sequences 0.5 %).  Where the row does not fit
+// (12 to 16 rows of the longer products), as many windows as occupy the chip: there the 64 workgroups of a narrow product
+// would be bound by what a compute unit can take in (16 sequences: 20.76 against 20.45 ms).
 static int skinny_windows(const GemvArgs& g, SkinnyPlan& p) {
   constexpr int min_blocks = 192;
   const int tiles = (g.seg[0].n_rows + 15) / 16;
@@ -349,7 +351,7 @@ static int skinny_windows(const GemvArgs& g, SkinnyPlan& p) {
     if (!skinny_plan_k(g, g.K / w, q)) continue;
     q.windows = w;
     p = q; best = w;
-    if (tiles >= 128 || tiles * w >= min_blocks) break;   // half the chip by tiles alone: no split
+    if (w == 1 || tiles * w >= min_blocks) break;   // the whole row fits: no split
   }
   return best;
 }
