@@ -68,9 +68,9 @@ __device__ __forceinline__ float xor_add(float v) {
 //
 // FUSE (verification: at most 16 new positions, one row chunk): the keys and values of the new
 // positions are not in the cache yet.  The cached keys (positions < pos0) are visible to every
-// row; one wavefront of the launch builds the operands of the new positions from the projection
-// buffer (rotating and rounding k, rounding v), appends them to the cache and scores them as
-// one more step with the causal mask.  Otherwise the cache already holds them (prefill).
+// row; the workgroups of the last key slice take the new positions from the projection buffer (rotating
+// and rounding k, rounding v), append them to the cache and score them as one more step with the
+// causal mask.  Otherwise the cache already holds them (prefill).
 //
 // NW wavefronts per workgroup split the keys of its slice and meet in LDS.
 template <int RT, int KS, bool FUSE, int NW>
@@ -84,7 +84,11 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
   __shared__ int s_last;
   int* pg = reinterpret_cast<int*>(smem_raw);                                  // [NW][64] page numbers of a wavefront's steps
   uint16_t* qT = reinterpret_cast<uint16_t*>(smem_raw + NT * 4);               // [R][QS]
-  float* mrg = reinterpret_cast<float*>(smem_raw + NT * 4 + (size_t)R * QS * 2);   // merge scratch
+  // FUSE: the new keys [16][KNS] and, transposed, the new values [Dhp][VNS] (rows of 16-byte groups, padded against bank conflicts)
+  constexpr int KNS = Dhp + 8, VNS = 24, NEWS = FUSE ? 16 * KNS + Dhp * VNS : 0;
+  uint16_t* kN = qT + R * QS;
+  uint16_t* vN = kN + 16 * KNS;
+  float* mrg = reinterpret_cast<float*>(smem_raw + NT * 4 + (size_t)(R * QS + NEWS) * 2);   // merge scratch
   float* mrg_o = mrg;                                                          // [NW-1][Dhp][kMergeLd]
   float* mrg_ml = mrg + (NW - 1) * Dhp * kMergeLd;                             // [NW-1][16][2]
 
@@ -107,12 +111,15 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
   const uint16_t* kp = static_cast<const uint16_t*>(a.kpool);
   const uint16_t* vp = static_cast<const uint16_t*>(a.vpool);
   const float* xrow = a.qkv + (size_t)b * a.T * d.ldzx;
+  const bool al4 = (d.ldzx & 3) == 0 && (reinterpret_cast<uintptr_t>(xrow) & 15) == 0;   // 16-byte aligned rows (dq, Dh are multiples of 8)
 
   // key steps of this workgroup and of this wavefront
   const int steps = (nk + kStepKeys - 1) / kStepKeys;
   const int sps = (steps + S - 1) / S;
   const int sb = sp * sps, se = min(steps, sb + sps);
-  const int per = (max(se - sb, 0) + NW - 1) / NW;
+  // (the last wavefront of the last slice scores the new positions: one step less for it)
+  const int extra = FUSE && sp == S - 1 ? 1 : 0;
+  const int per = (max(se - sb, 0) + extra + NW - 1) / NW;
   const int ws = sb + wave * per, we = min(se, ws + per);
 
   // Operand loads of one step.  A step's 32 keys lie in one page (the page size is a multiple of
@@ -162,117 +169,139 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
   if (ws < we) load_step(ws, kA, kB, vT);
   TR(1);
 
-  // ---- the new positions (FUSE): one wavefront of the launch builds their operands from the
-  // projection buffer and appends them to the cache, before the queries are staged (it only
-  // needs the queries to score them)
-  const bool new_wave = FUSE && sp == S - 1 && wave == NW - 1 && nk_all > pos0;
-  Frag nA[KS], nB[KS], nV[NDB];
-  if (new_wave) {
-    const float2* rope = reinterpret_cast<const float2*>(a.rope);
-    const bool al4 = (d.ldzx & 3) == 0 && (reinterpret_cast<uintptr_t>(xrow) & 15) == 0;   // 16-byte aligned rows (dq, Dh are multiples of 8)
-    uint16_t* kpw = static_cast<uint16_t*>(a.kpool);
-    uint16_t* vpw = static_cast<uint16_t*>(a.vpool);
-    auto load8 = [&](const float* src, float(&o)[8]) {
-      if (al4) {
-        const float4 x = *reinterpret_cast<const float4*>(src), y = *reinterpret_cast<const float4*>(src + 4);
-        o[0] = x.x; o[1] = x.y; o[2] = x.z; o[3] = x.w; o[4] = y.x; o[5] = y.y; o[6] = y.z; o[7] = y.w;
-      } else {
+  // ---- the new positions (FUSE), in the workgroups of the last slice: all threads rotate and round the new keys and
+  // values, append them to the cache and leave them in LDS, from where the last wavefront takes them as the operands of
+  // one more step.  (Built by that wavefront alone, from 64 and more loads of its own, they were the longest chain of a
+  // short launch.  Launch after a pass over 600 MB, before and after: 24 sequences x 1 position over 777 keys of head
+  // dimension 128 23.4 -> 20.9 us, 64 x 9 over 400 keys 29.7 -> 25.0; one sequence x 3 over 512 keys of dimension 64
+  // 11.9 -> 9.1, 16 x 5 over 2048 keys in 8 slices 12.6 -> 10.6.)
+  // Items of 4 dimensions: nt * half / 4 pairs of key dimensions, then nt * Dh / 4 groups of a value.
+  const bool has_new = FUSE && sp == S - 1 && nk_all > pos0;
+  const bool new_wave = has_new && wave == NW - 1;
+  const int k_items = has_new ? nt * (half >> 2) : 0, kv_items = has_new ? k_items + nt * (Dh >> 2) : 0;
+  auto load4 = [&](const float* src) -> float4 {
+    return al4 ? *reinterpret_cast<const float4*>(src) : make_float4(src[0], src[1], src[2], src[3]);
+  };
+  struct NewItem { float4 x0, x1, c0, c1; int page; };
+  auto new_load = [&](int it) -> NewItem {
+    NewItem v;
+    v.x0 = v.x1 = v.c0 = v.c1 = make_float4(0.f, 0.f, 0.f, 0.f);
+    v.page = 0;
+    if (it >= kv_items) return v;
+    const bool key = it < k_items;
+    const int per = key ? half >> 2 : Dh >> 2, i0 = key ? it : it - k_items, j = i0 / per, i = 4 * (i0 - j * per);
+    v.page = pt_row[(pos0 + j) >> pshift];
+    const float* src = xrow + (size_t)j * d.ldzx + d.dq + (key ? 0 : d.dkv) + (size_t)kvh * Dh + i;
+    v.x0 = load4(src);
+    if (key) {
+      v.x1 = load4(src + half);
+      const float4* c = reinterpret_cast<const float4*>(a.rope + ((size_t)(pos0 + j) * half + i) * 2);
+      v.c0 = c[0]; v.c1 = c[1];
+    }
+    return v;
+  };
+  auto new_store = [&](int it, const NewItem& v) {
+    if (it >= kv_items) return;
+    const bool key = it < k_items;
+    const int per = key ? half >> 2 : Dh >> 2, i0 = key ? it : it - k_items, j = i0 / per, i = 4 * (i0 - j * per);
+    const int in = (pos0 + j) & pmask;
+    auto pack = [](float p, float q) { return (uint32_t)f32_to_bf16_rne(p) | ((uint32_t)f32_to_bf16_rne(q) << 16); };
+    if (key) {
+      const uint2 lo = make_uint2(pack(v.x0.x * v.c0.x - v.x1.x * v.c0.y, v.x0.y * v.c0.z - v.x1.y * v.c0.w),
+                                  pack(v.x0.z * v.c1.x - v.x1.z * v.c1.y, v.x0.w * v.c1.z - v.x1.w * v.c1.w));
+      const uint2 hi = make_uint2(pack(v.x1.x * v.c0.x + v.x0.x * v.c0.y, v.x1.y * v.c0.z + v.x0.y * v.c0.w),
+                                  pack(v.x1.z * v.c1.x + v.x0.z * v.c1.y, v.x1.w * v.c1.z + v.x0.w * v.c1.w));
+      uint16_t* dst = static_cast<uint16_t*>(a.kpool) + (((size_t)v.page * d.Hkv + kvh) * d.page_tokens + in) * Dh + i;
+      *reinterpret_cast<uint2*>(dst) = lo;
+      *reinterpret_cast<uint2*>(dst + half) = hi;
+      *reinterpret_cast<uint2*>(kN + j * KNS + i) = lo;
+      *reinterpret_cast<uint2*>(kN + j * KNS + half + i) = hi;
+    } else {
+      const float x[4] = {v.x0.x, v.x0.y, v.x0.z, v.x0.w};
+      uint16_t* dst = static_cast<uint16_t*>(a.vpool) + (((size_t)v.page * d.Hkv + kvh) * Dh + i) * d.page_tokens + in;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) o[i] = src[i];
-      }
-    };
-    // values of the new positions first (their loads overlap the rotation of the keys below)
-    float vraw[NDB][8];
-    size_t vat[8];
-    {
-      const float* vbase = xrow + d.dq + d.dkv + (size_t)kvh * Dh;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int jc = min(8 * g + i, nt - 1), pos = pos0 + jc;
-        vat[i] = ((size_t)pt_row[pos >> pshift] * d.Hkv + kvh) * Dh * d.page_tokens + (pos & pmask);
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) vraw[db][i] = vbase[(size_t)jc * d.ldzx + min(db * 16 + n, Dh - 1)];
+      for (int q = 0; q < 4; ++q) {
+        const uint16_t h = f32_to_bf16_rne(x[q]);
+        dst[(size_t)q * d.page_tokens] = h;
+        vN[(i + q) * VNS + j] = h;
       }
     }
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      const int j = 8 * (n >> 2) + (n & 3) + 4 * blk;            // new position of this lane's key row
-      const bool live = j < nt;
-      const int jc = min(j, nt - 1);
-      const float* kr = xrow + (size_t)jc * d.ldzx + d.dq + (size_t)kvh * Dh;
-      const size_t kat = (((size_t)pt_row[(pos0 + jc) >> pshift] * d.Hkv + kvh) * d.page_tokens + ((pos0 + jc) & pmask)) * Dh;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int d0 = ks * 32 + 8 * g;
-        Frag f;
-        f.u = make_uint4(0, 0, 0, 0);
-        if (d0 < Dh && (blk == 0 || nt > 4)) {                   // the second block only holds positions 4..7, 12..15
-          const bool low = d0 < half;                            // an 8-dim group lies in one half (Dh % 16 == 0 here)
-          float x[8], xp[8];
-          load8(kr + d0, x);
-          load8(kr + (low ? d0 + half : d0 - half), xp);
-          const float2* cs = rope + (size_t)(pos0 + jc) * half + (low ? d0 : d0 - half);
-          uint32_t h[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const float2 c = cs[i];
-            const float r = low ? x[i] * c.x - xp[i] * c.y : x[i] * c.x + xp[i] * c.y;
-            h[i] = live ? f32_to_bf16_rne(r) : 0u;
-          }
-          f.u = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-          if (live) *reinterpret_cast<uint4*>(kpw + kat + d0) = f.u;
-        }
-        if (blk == 0) nA[ks] = f; else nB[ks] = f;
-      }
-    }
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) {
-      const int dim = db * 16 + n;
-      uint32_t h[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        h[i] = 0u;
-        if (8 * g + i < nt && dim < Dh) {
-          h[i] = f32_to_bf16_rne(vraw[db][i]);
-          vpw[vat[i] + (size_t)dim * d.page_tokens] = (uint16_t)h[i];
-        }
-      }
-      nV[db].u = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-    }
-  }
+  };
+  // the first two items of a thread travel while the queries are staged
+  NewItem new0, new1;
+  if (FUSE && has_new) { new0 = new_load(tid); new1 = new_load(tid + NT); }
 
   // ---- query rows: rotate to their positions, scale, split into 3 bf16 terms, stage in LDS
   {
     const float scale = 1.4426950408889634f / sqrtf((float)Dh);   // scores in base-2 units: softmax through 2^x
     const float2* rope = reinterpret_cast<const float2*>(a.rope);
-    // (the wavefront that builds the new positions' operands takes no part in the staging)
-    const int stagers = FUSE && sp == S - 1 && nk_all > pos0 ? NT - 64 : NT;
-    // four items per thread and pass, their loads issued together
-    for (int it0 = tid; it0 < R * half && tid < stagers; it0 += 4 * stagers) {
-      float x0[4], x1[4];
-      float2 c[4];
+    constexpr int stagers = NT;
+    if (al4 && (half & 3) == 0) {
+      // items of 4 dimension pairs, four per thread and pass, their loads issued together: up to 768 items (32 rows of
+      // head dimension 128 are 512) take one round trip to memory
+      const int h4 = half >> 2, items = R * h4;
+      for (int it0 = tid; it0 < items && tid < stagers; it0 += 4 * stagers) {
+        float4 x0[4], x1[4], c0[4], c1[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int it = it0 + u * stagers, r = it / half, i = it - r * half, rr = row0 + r;
-        x0[u] = 0.f; x1[u] = 0.f; c[u] = make_float2(0.f, 0.f);
-        if (it < R * half && rr < row_lim) {
-          const int j = rr / G;
-          const float* q = xrow + (size_t)j * d.ldzx + (size_t)(kvh * G + rr % G) * Dh;
-          c[u] = rope[(size_t)(pos0 + j) * half + i];
-          x0[u] = q[i]; x1[u] = q[i + half];
+        for (int u = 0; u < 4; ++u) {
+          const int it = it0 + u * stagers, r = it / h4, i = 4 * (it - r * h4), rr = row0 + r;
+          x0[u] = x1[u] = c0[u] = c1[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (it < items && rr < row_lim) {
+            const int j = rr / G;
+            const float* q = xrow + (size_t)j * d.ldzx + (size_t)(kvh * G + rr % G) * Dh + i;
+            const float4* c = reinterpret_cast<const float4*>(rope + (size_t)(pos0 + j) * half + i);
+            c0[u] = c[0]; c1[u] = c[1];
+            x0[u] = *reinterpret_cast<const float4*>(q); x1[u] = *reinterpret_cast<const float4*>(q + half);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int it = it0 + u * stagers, r = it / h4, i = 4 * (it - r * h4);
+          if (it >= items) break;
+          const float lo[4] = {(x0[u].x * c0[u].x - x1[u].x * c0[u].y) * scale, (x0[u].y * c0[u].z - x1[u].y * c0[u].w) * scale,
+                               (x0[u].z * c1[u].x - x1[u].z * c1[u].y) * scale, (x0[u].w * c1[u].z - x1[u].w * c1[u].w) * scale};
+          const float hi[4] = {(x1[u].x * c0[u].x + x0[u].x * c0[u].y) * scale, (x1[u].y * c0[u].z + x0[u].y * c0[u].w) * scale,
+                               (x1[u].z * c1[u].x + x0[u].z * c1[u].y) * scale, (x1[u].w * c1[u].z + x0[u].w * c1[u].w) * scale};
+          uint16_t* row = qT + (size_t)r * QS + i;
+          uint2 t[3];
+          split3_bf16_pair(lo[0], lo[1], t[0].x, t[1].x, t[2].x);
+          split3_bf16_pair(lo[2], lo[3], t[0].y, t[1].y, t[2].y);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(row + k * Dhp) = t[k];
+          split3_bf16_pair(hi[0], hi[1], t[0].x, t[1].x, t[2].x);
+          split3_bf16_pair(hi[2], hi[3], t[0].y, t[1].y, t[2].y);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) *reinterpret_cast<uint2*>(row + k * Dhp + half) = t[k];
         }
       }
+    } else {
+      // four items per thread and pass, their loads issued together
+      for (int it0 = tid; it0 < R * half && tid < stagers; it0 += 4 * stagers) {
+        float x0[4], x1[4];
+        float2 c[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int it = it0 + u * stagers, r = it / half, i = it - r * half;
-        if (it >= R * half) break;
-        const float lo = (x0[u] * c[u].x - x1[u] * c[u].y) * scale, hi = (x1[u] * c[u].x + x0[u] * c[u].y) * scale;
-        uint32_t l0, l1, l2, h0, h1, h2;
-        split3(lo, l0, l1, l2);
-        split3(hi, h0, h1, h2);
-        uint16_t* row = qT + (size_t)r * QS;
-        row[i] = (uint16_t)l0; row[Dhp + i] = (uint16_t)l1; row[2 * Dhp + i] = (uint16_t)l2;
-        row[i + half] = (uint16_t)h0; row[Dhp + i + half] = (uint16_t)h1; row[2 * Dhp + i + half] = (uint16_t)h2;
+        for (int u = 0; u < 4; ++u) {
+          const int it = it0 + u * stagers, r = it / half, i = it - r * half, rr = row0 + r;
+          x0[u] = 0.f; x1[u] = 0.f; c[u] = make_float2(0.f, 0.f);
+          if (it < R * half && rr < row_lim) {
+            const int j = rr / G;
+            const float* q = xrow + (size_t)j * d.ldzx + (size_t)(kvh * G + rr % G) * Dh;
+            c[u] = rope[(size_t)(pos0 + j) * half + i];
+            x0[u] = q[i]; x1[u] = q[i + half];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int it = it0 + u * stagers, r = it / half, i = it - r * half;
+          if (it >= R * half) break;
+          const float lo = (x0[u] * c[u].x - x1[u] * c[u].y) * scale, hi = (x1[u] * c[u].x + x0[u] * c[u].y) * scale;
+          uint32_t l0, l1, l2, h0, h1, h2;
+          split3(lo, l0, l1, l2);
+          split3(hi, h0, h1, h2);
+          uint16_t* row = qT + (size_t)r * QS;
+          row[i] = (uint16_t)l0; row[Dhp + i] = (uint16_t)l1; row[2 * Dhp + i] = (uint16_t)l2;
+          row[i + half] = (uint16_t)h0; row[Dhp + i + half] = (uint16_t)h1; row[2 * Dhp + i + half] = (uint16_t)h2;
+        }
       }
     }
     if (Dh < Dhp) {
@@ -282,6 +311,13 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
         qT[(size_t)r * QS + term * Dhp + Dh + i] = 0;
       }
     }
+  }
+  if (FUSE && has_new) {
+    new_store(tid, new0);
+    new_store(tid + NT, new1);
+    for (int it = tid + 2 * NT; it < kv_items; it += NT) new_store(it, new_load(it));
+    // values of positions that do not exist meet zero probabilities: they must not be NaN
+    for (int it = tid; it < Dh * (16 - nt); it += NT) vN[(it / (16 - nt)) * VNS + nt + it % (16 - nt)] = 0;
   }
   __syncthreads();
   TR(2);
@@ -378,7 +414,19 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
   };
 
   // ---- the new positions (FUSE): scored as one more step by the wavefront that built their operands
-  if (new_wave) {
+  if (FUSE && new_wave) {
+    Frag nA[KS], nB[KS], nV[NDB];
+    const uint4 zero = make_uint4(0, 0, 0, 0);
+    const int j0 = 8 * (n >> 2) + (n & 3);                       // new positions of this lane's key rows: j0 and j0 + 4
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int d0 = ks * 32 + 8 * g;
+      nA[ks].u = d0 < Dh && j0 < nt ? *reinterpret_cast<const uint4*>(kN + j0 * KNS + d0) : zero;
+      nB[ks].u = d0 < Dh && j0 + 4 < nt ? *reinterpret_cast<const uint4*>(kN + (j0 + 4) * KNS + d0) : zero;
+    }
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+      nV[db].u = db * 16 + n < Dh && g < 2 ? *reinterpret_cast<const uint4*>(vN + (db * 16 + n) * VNS + 8 * g) : zero;
     int limn[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -523,12 +571,17 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
     float L = 0.f;
     for (int s0 = 0; s0 < S; s0 += 16) {                // slice order: deterministic; 16 loads in flight
       float4 pv[16];
+      if (it == tid && s0 == 0) {   // (copied by value: a choice between the two places would keep the array in scratch memory)
 #pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (u < 8 || s0 + 8 < S)
-          pv[u] = (it == tid && s0 == 0 && u < 8)
-                      ? pv0[u & 7]
-                      : *reinterpret_cast<const float4*>(a.part_o + (rid * S + min(s0 + u, S - 1)) * Dh + 4 * c4);
+        for (int u = 0; u < 8; ++u) pv[u] = pv0[u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) pv[u] = *reinterpret_cast<const float4*>(a.part_o + (rid * S + min(s0 + u, S - 1)) * Dh + 4 * c4);
+      }
+      if (s0 + 8 < S) {
+#pragma unroll
+        for (int u = 8; u < 16; ++u) pv[u] = *reinterpret_cast<const float4*>(a.part_o + (rid * S + min(s0 + u, S - 1)) * Dh + 4 * c4);
+      }
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         if (s0 + u < S) {
@@ -617,7 +670,8 @@ static hipError_t launch_w(const Dims& d, const AttnArgs& a, int row_chunks, hip
   size_t scratch = (size_t)((NW - 1) * Dhp * kMergeLd + (NW - 1) * 16 * 2) * sizeof(float);
   const size_t gm = (size_t)RT * 16 * a.n_splits * sizeof(float2);
   if (gm > scratch) scratch = gm;
-  const size_t lds = (size_t)NW * 64 * 4 + (size_t)RT * 16 * QS * 2 + scratch;
+  constexpr int news = FUSE ? 16 * (Dhp + 8) + Dhp * 24 : 0;
+  const size_t lds = (size_t)NW * 64 * 4 + (size_t)(RT * 16 * QS + news) * 2 + scratch;
   static size_t lds_enabled = 48 * 1024;
   if (lds > lds_enabled) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_mfma_kernel<RT, KS, FUSE, NW>),

@@ -492,7 +492,7 @@ hh_status run_graphed(hh_ctx* x, long long key, hipStream_t s, F enqueue) {
 int pick_splits(const hh_cfg& c, const Dims& d, int B, int T, int len_upper) {
   const int cap = c.attn_max_splits > 0 ? c.attn_max_splits : 16;
   const int target = c.attn_target_blocks > 0 ? c.attn_target_blocks : 256;   // one workgroup per compute unit: measured best at every workload
-  const int single = c.attn_single_slice_steps == 0 ? 28 : c.attn_single_slice_steps;   // -1: never a single slice by this rule
+  const int single = c.attn_single_slice_steps == 0 ? (d.Dh > 64 ? 12 : 28) : c.attn_single_slice_steps;   // -1: never a single slice by this rule
   int s;
   if (attention_uses_mfma(d)) {
     const int blocks = attention_mfma_row_chunks(d, T) * d.Hkv * B;
@@ -500,7 +500,9 @@ int pick_splits(const hh_cfg& c, const Dims& d, int B, int T, int len_upper) {
     s = (target + blocks - 1) / blocks;
     if (s > (steps + 3) / 4) s = (steps + 3) / 4;
     // short caches: the ticket and the merge across workgroups (about 4 us) cost more than the
-    // few extra steps per wavefront of a single slice
+    // few extra steps per wavefront of a single slice.  A step costs a wavefront about 1 us at head dimension 64 and 1.75 us
+    // at 128 (twice the keys and values through one compute unit): 24 sequences of 400 to 777 keys at the 3B shape take
+    // 22.5 us per layer with one slice of 25 steps, 14.4 + 4.6 us with six and the merge kernel
     if (steps <= single) s = 1;
   } else {
     const int G = d.Hq / d.Hkv;

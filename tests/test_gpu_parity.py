@@ -406,3 +406,20 @@ def test_prefill_scan_segments(B, dtype, d_state, heads, chunk):
     ctx = _ctx(B, wts, 4, chunk + 160, 3, 8, kv_page_tokens=32, prefill_chunk=chunk, kernel_flags=B.HH_KF_CANARIES)
     run_lockstep(ctx, wts, prompts, lens, 8, 3, engine="pass", chunk=64, report=_say(f"seg-{dtype}-N{d_state}-H{heads}-T{chunk}"))
     assert ctx.hh_check_canaries() == 0
+
+
+@pytest.mark.parametrize("head_dim,n_q,n_kv,k,n", [(80, 4, 2, 15, 500), (128, 5, 1, 0, 777), (48, 4, 4, 8, 130),
+                                                   (128, 10, 2, 8, 420), (16, 2, 1, 4, 33), (200, 2, 2, 7, 400)])
+def test_new_positions_in_the_attention_kernel(B, head_dim, n_q, n_kv, k, n):
+    """The verification attention rotates, rounds and appends the new keys and values with all threads of the last
+    slice and scores them from LDS: one to sixteen new positions (every fill of the two 8-position operand groups), head
+    dimensions that fill the 32-wide operands (128), leave half of the last one empty (80, 48, 16) or keep the separate
+    append (200: not a multiple of 16), positions that cross a page, one key slice and - at head dimension 128 from 13 key
+    steps on - several, ragged prompts."""
+    cfg = _thin("thin-new", head_dim, n_q, n_kv)
+    wts = W.make_lively_weights(cfg, 47)
+    lens = [n, n - 13, n // 2 + 1]
+    prompts = W.make_prompts(cfg.vocab, 3, lens, 31)
+    ctx = _ctx(B, wts, 3, n + 2 * k + 60, k, 2 * k + 12, kv_page_tokens=32, prefill_chunk=128, kernel_flags=B.HH_KF_CANARIES)
+    run_lockstep(ctx, wts, prompts, lens, 2 * k + 12, k, engine="pass", chunk=64, report=_say(f"new-Dh{head_dim}-k{k}"))
+    assert ctx.hh_check_canaries() == 0
