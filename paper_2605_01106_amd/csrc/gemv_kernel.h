@@ -123,38 +123,57 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const GemvArgs a, co
   };
   load_unit(row_group(0));   // in flight while the activations are staged
 
-  // ---- prologue: stage x[k] * norm_w[k] (float4 at a time) and the sums of squares.  The
-  // loads of all MT rows of a column group are issued together (one memory round trip, not MT).
+  // ---- prologue: stage x[k] * norm_w[k] (float4 at a time) and the sums of squares.  A thread owns up to KU column
+  // groups; the loads of U of them, all MT rows, are issued together (one memory round trip for the whole row with one
+  // activation row, where a loop over the groups took KU of them, up to 8).
   const bool normed = a.norm_w != nullptr;
   {
+    constexpr int KU = NCW * KS / 2;                              // ceil(Kpad / 4 / threads)
+    constexpr int U = MT == 1 ? KU : (KU < 2 ? KU : 2);
     float ss[MT];
 #pragma unroll
     for (int m = 0; m < MT; ++m) ss[m] = 0.f;
     const float4* n4 = reinterpret_cast<const float4*>(a.norm_w);
-    for (int k4 = tid; k4 < (Kpad >> 2); k4 += kGemvThreads) {
-      const bool in_k = k4 < (K >> 2);
-      const int k4c = min(k4, (K >> 2) - 1);
-      float4 v[MT];
-      float4 nw = make_float4(1.f, 1.f, 1.f, 1.f);
-      if (normed) nw = n4[k4c];
 #pragma unroll
-      for (int m = 0; m < MT; ++m) {
-        const size_t ro = (size_t)(m0 + min(m, mt - 1)) * a.ldx;
-        v[m] = reinterpret_cast<const float4*>(a.X + ro)[k4c];
-        if (a.X2 != nullptr) {
-          const float4 w2 = reinterpret_cast<const float4*>(a.X2 + ro)[k4c];
-          v[m].x += w2.x; v[m].y += w2.y; v[m].z += w2.z; v[m].w += w2.w;
+    for (int u0 = 0; u0 < KU; u0 += U) {
+      float4 v[U][MT], v2[U][MT], nw[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k4c = min((u0 + u) * kGemvThreads + tid, (K >> 2) - 1);
+        nw[u] = make_float4(1.f, 1.f, 1.f, 1.f);
+        if (normed) nw[u] = n4[k4c];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const size_t ro = (size_t)(m0 + min(m, mt - 1)) * a.ldx;
+          v[u][m] = reinterpret_cast<const float4*>(a.X + ro)[k4c];
         }
       }
+      if (a.X2 != nullptr) {
 #pragma unroll
-      for (int m = 0; m < MT; ++m) {
-        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (in_k && m < mt) {
-          o = v[m];
-          ss[m] += o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w;
-          o.x *= nw.x; o.y *= nw.y; o.z *= nw.z; o.w *= nw.w;
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int m = 0; m < MT; ++m)
+            v2[u][m] = reinterpret_cast<const float4*>(a.X2 + (size_t)(m0 + min(m, mt - 1)) * a.ldx)[min((u0 + u) * kGemvThreads + tid, (K >> 2) - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int m = 0; m < MT; ++m) { v[u][m].x += v2[u][m].x; v[u][m].y += v2[u][m].y; v[u][m].z += v2[u][m].z; v[u][m].w += v2[u][m].w; }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k4 = (u0 + u) * kGemvThreads + tid;
+        if (k4 >= (Kpad >> 2)) continue;
+        const bool in_k = k4 < (K >> 2);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (in_k && m < mt) {
+            o = v[u][m];
+            ss[m] += o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w;
+            o.x *= nw[u].x; o.y *= nw[u].y; o.z *= nw[u].z; o.w *= nw[u].w;
+          }
+          xs4[(size_t)m * (Kpad >> 2) + xs_slot4(k4)] = o;
         }
-        xs4[(size_t)m * (Kpad >> 2) + xs_slot4(k4)] = o;
       }
     }
     if (normed) {
