@@ -73,6 +73,9 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
   // after the multiplication instead of before it
   constexpr bool DB = !(NF == 2 && KSTEPS > 5);
   constexpr int SL = KSTEPS * 32 + 8;                       // staged columns per wavefront (+ pad)
+  // staging items (row, 4 columns) a lane has in flight: up to 4 for up to 8 rows, up to 8 above (16 rows x 4 steps are one
+  // round trip instead of two: 16 sequences at the 0.5B shape, two rounds 20.39 -> 19.93 ms; 8 for few rows repeats loads)
+  constexpr int SU = ONCE ? (KSTEPS < 4 ? KSTEPS : 4) : (KSTEPS < 4 ? 2 * KSTEPS : 8);
   constexpr int SL4 = KSTEPS * 8;                           // float4 groups per row of a slice
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -108,12 +111,12 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
   {
     const bool normed = a.norm_w != nullptr;
     const int items = M * SL4;
-    float4 v[4], nw[4];
-    int mi[4], ci[4];
-    bool ok[4];
+    float4 v[SU], nw[SU];
+    int mi[SU], ci[SU];
+    bool ok[SU];
     auto issue = [&](int it0) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < SU; ++u) {
         const int it = it0 + u * 64 + lane;
         mi[u] = min(it / SL4, M - 1); ci[u] = it % SL4;
         const int col = kb + 4 * ci[u];
@@ -129,7 +132,7 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
     };
     auto process = [&](int it0) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < SU; ++u) {
         if (it0 + u * 64 + lane < items) {
           if (!ok[u]) v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
           ssb[mi[u] * SL4 + ci[u]] = v[u].x * v[u].x + v[u].y * v[u].y + v[u].z * v[u].z + v[u].w * v[u].w;
@@ -147,7 +150,7 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
     load_round(0, wf[0]);   // the weights of the first tile stream in while the activations are staged
     TR(1);
     process(0);
-    for (int it0 = 256; it0 < items; it0 += 256) { issue(it0); process(it0); }
+    for (int it0 = SU * 64; it0 < items; it0 += SU * 64) { issue(it0); process(it0); }
     if (normed) {
       // lane (g, n) adds the squares of row n over the groups c = g, g+4, ...; then across g
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
