@@ -33,7 +33,7 @@ union LFrag {
 
 constexpr int kLdsWaves = 8;                  // 4 along the weight rows x 2 along the activation rows
 constexpr int kLdsA = 16;                     // weight fragments per workgroup and step
-// MTW = activation row tiles per wavefront (6, or 1..3 for passes of at most 96 rows): the
+// MTW = activation row tiles per wavefront (1..3 for passes of at most 96 rows, else 2..6): the
 // workgroup covers 2 MTW row tiles, 6 MTW plane fragments per step
 constexpr int lds_row_tiles(int mtw) { return 2 * mtw; }
 constexpr int lds_frags(int mtw) { return kLdsA + 6 * mtw; }

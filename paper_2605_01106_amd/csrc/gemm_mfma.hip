@@ -457,6 +457,8 @@ static hipError_t lds_launch(const LdsGemmArgs& a, int mtw, hipStream_t s) {
     case 1: return lds_launch_m<EPI, 1>(a, s);
     case 2: return lds_launch_m<EPI, 2>(a, s);
     case 3: return lds_launch_m<EPI, 3>(a, s);
+    case 4: return lds_launch_m<EPI, 4>(a, s);
+    case 5: return lds_launch_m<EPI, 5>(a, s);
     case 6: return lds_launch_m<EPI, 6>(a, s);
   }
   return hipErrorInvalidValue;
@@ -481,18 +483,22 @@ static hipError_t gemm_dispatch_m(const GemmArgs& a, int mtw, int units, hipStre
 }
 
 // Row tiles per wavefront (workgroup = 256 weight rows x 32 MTW activation rows) and K split of the
-// LDS-staged kernel, by a cost model in microseconds: a workgroup step takes the longer of its MFMAs
-// (384 MTW cycles per SIMD) and its copies ((16 + 6 MTW) KB at 28 bytes per cycle and compute unit);
-// the workgroups run in rounds of one per compute unit; a K split adds the reduction kernel and
-// ks * M * N floats of partial products written and read again (about 4 TB/s).  Up to 96 rows one
-// workgroup holds all rows; many rows choose between 192-row and 96-row workgroups.
+// LDS-staged kernel, by a cost model in microseconds: a workgroup step takes its MFMAs (384 MTW cycles per
+// SIMD) and about 720 cycles of barrier, first LDS reads and copy issue (measured: 76 % matrix-pipe use with
+// 6 row tiles, 62 % with 3), or its copies ((16 + 6 MTW) KB at 28 bytes per cycle and compute unit) where
+// those are longer; the workgroups run in rounds of one per compute unit; a K split adds the reduction kernel
+// and ks * M * N floats of partial products written and read again (about 4 TB/s).  Up to 96 rows one
+// workgroup holds all rows; many rows choose among 64 to 192 rows, so that the last round is not mostly empty:
+// 512 rows of the gate/up product at the 3B shape are 162 workgroups of 192 rows (120 us) or 216 of 128 (88 us).
+// Prefill of 4096 tokens of one sequence through four 3B blocks 15.0 -> 13.4 ms, 509 tokens at the 0.5B shape
+// 9.3 -> 8.5 ms (against a choice of 96 and 192 rows only).
 static void lds_plan(int m_tiles, int steps, int n_blocks, int nf, int M, int N, int& mtw, int& ks) {
   mtw = 0; ks = 1;
   double best = 1e30;
-  const int mtw_lo = m_tiles > 6 ? 3 : (m_tiles + 1) / 2, mtw_hi = m_tiles > 6 ? 6 : (m_tiles + 1) / 2;
-  for (int cand = mtw_lo; cand <= mtw_hi; cand += 3) {
+  const int mtw_lo = m_tiles > 6 ? 2 : (m_tiles + 1) / 2, mtw_hi = m_tiles > 6 ? 6 : (m_tiles + 1) / 2;
+  for (int cand = mtw_lo; cand <= mtw_hi; ++cand) {
     const int m_blocks = (m_tiles + lds_row_tiles(cand) - 1) / lds_row_tiles(cand);
-    const double mfma = 384.0 * cand, copy = (16.0 + 6.0 * cand) * 1024.0 / 28.0;
+    const double mfma = 384.0 * cand + 720.0, copy = (16.0 + 6.0 * cand) * 1024.0 / 28.0;
     const double step_us = (mfma > copy ? mfma : copy) / 2400.0;
     const int min_steps = m_tiles > 6 ? 8 : 3;
     for (int k = 1; k <= 32; ++k) {

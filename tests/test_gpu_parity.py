@@ -423,3 +423,17 @@ def test_new_positions_in_the_attention_kernel(B, head_dim, n_q, n_kv, k, n):
     ctx = _ctx(B, wts, 3, n + 2 * k + 60, k, 2 * k + 12, kv_page_tokens=32, prefill_chunk=128, kernel_flags=B.HH_KF_CANARIES)
     run_lockstep(ctx, wts, prompts, lens, 2 * k + 12, k, engine="pass", chunk=64, report=_say(f"new-Dh{head_dim}-k{k}"))
     assert ctx.hh_check_canaries() == 0
+
+
+@pytest.mark.parametrize("rows,d_ff", [(97, 96), (128, 4096), (170, 1024), (330, 2080), (512, 6912)])
+def test_many_row_products_by_row_block(B, rows, d_ff):
+    """The many-row products choose 64 to 192 activation rows per workgroup and a K split by a cost model: prefill passes
+    of 97 to 512 rows (row counts that leave the last block of 64, 96, 128, 160 or 192 rows nearly empty) against widths
+    that take one and several rounds of workgroups, with and without a K split and the hand-over of the SwiGLU result."""
+    cfg = W.scaled_config("rows", n_layers=1, d_model=256, vocab=300, m_heads=4, m_head_dim=64, d_state=64,
+                          n_q_heads=4, n_kv_heads=2, head_dim=64, d_ff=d_ff, w_dtype=W.BF16)
+    wts = W.make_lively_weights(cfg, 5)
+    lens = [rows]
+    prompts = W.make_prompts(cfg.vocab, 1, lens, 9)
+    ctx = _ctx(B, wts, 1, rows + 40, 2, 6, prefill_chunk=rows)
+    run_lockstep(ctx, wts, prompts, lens, 6, 2, engine="pass", chunk=64, report=_say(f"rows-{rows}-{d_ff}"))
