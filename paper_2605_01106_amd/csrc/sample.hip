@@ -112,24 +112,66 @@ __device__ void row_stats(const float* __restrict__ row, int V, float inv_t, flo
   m_out = m; s_out = s;
 }
 
+// ---- rows held in registers.  A row of up to 65536 entries that starts on a 16-byte boundary and whose length is a
+// multiple of 4 is read once, with all loads of a thread in flight together, where the loops above and below read it two
+// or three times, a dependent load per pass of a loop.  Same sums in the same order, so the same bits.  Draw from 64 rows
+// of 32768 entries 16.4 -> 12.2 us, of 65536 28.4 -> 21.0; acceptance of 64 sequences at k = 8 over 32768 entries 70 -> 59 us,
+// over 65536 130 -> 115 (the statistics 87 -> 80 us for 285 MB; the draw with the residual keeps the loops there: 64
+// registers of masses spill behind the two exponentials per entry, 121 us).
+constexpr int kRegGroups = 16;   // groups of 4 entries per thread at most: 64 registers, one workgroup of 16 wavefronts per compute unit
+__host__ __device__ constexpr int reg_vocab(int groups) { return groups * kDrawThreads * 4; }
+
+// groups first, first + step, ... of a row (past its end: its last group, to be ignored)
+template <int G>
+__device__ __forceinline__ void load_groups(const float* __restrict__ row, int V, int first, int step, float4 (&l)[G]) {
+#pragma unroll
+  for (int i = 0; i < G; ++i) l[i] = *reinterpret_cast<const float4*>(row + min(first + i * step, V - 4));
+}
+
+// row_stats for such a row
+template <int G>
+__device__ void row_stats_regs(const float* __restrict__ row, int V, float inv_t, float* red, float& m_out, float& s_out) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = kDrawWaves, j0 = threadIdx.x * 4;
+  float4 l[G];
+  load_groups(row, V, j0, kDrawThreads * 4, l);
+  float m = kNoLogit;
+#pragma unroll
+  for (int i = 0; i < G; ++i) m = fmaxf(fmaxf(m, fmaxf(l[i].x, l[i].y)), fmaxf(l[i].z, l[i].w));
+  m = wave_max(m);
+  if (lane == 0) red[w] = m;
+  __syncthreads();
+  m = red[0];
+  for (int i = 1; i < nw; ++i) m = fmaxf(m, red[i]);
+  __syncthreads();
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < G; ++i) {
+    if (j0 + i * kDrawThreads * 4 < V)
+      s += (expf((l[i].x - m) * inv_t) + expf((l[i].y - m) * inv_t)) + (expf((l[i].z - m) * inv_t) + expf((l[i].w - m) * inv_t));
+  }
+  s = wave_sum(s);
+  if (lane == 0) red[w] = s;
+  __syncthreads();
+  s = 0.f;
+  for (int i = 0; i < nw; ++i) s += red[i];
+  m_out = m; s_out = s;
+}
+
 // Inverse-CDF draw by a workgroup of kDrawThreads threads.  val(jj, end, v) fills v[0..3] with the
 // masses (>= 0) of indices jj .. jj+3, zero past `end`.
 // Wavefront w owns the contiguous segment [w * seg, (w + 1) * seg); the segment sums give the
 // segment that holds u * total, and that wavefront alone scans its segment in index order.
 // red: kDrawWaves floats, res: one int (both in LDS).  Every thread returns the drawn index, or -1
 // when no entry has mass.
-template <typename F>
-__device__ int block_draw(F val, int V, float u, float* red, int* res) {
+// draw_walk: the part behind the segment sums (acc: this thread's share of its wavefront's segment); prepare() is called
+// by the whole wavefront that walks, before its first val.
+__device__ __forceinline__ int segment_size(int V) { return ((V + kDrawWaves * 256 - 1) / (kDrawWaves * 256)) * 256; }
+
+template <typename P, typename F>
+__device__ int draw_walk(float acc, P prepare, F val, int V, float u, float* red, int* res) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int seg = ((V + kDrawWaves * 256 - 1) / (kDrawWaves * 256)) * 256;
+  const int seg = segment_size(V);
   const int j0 = min(V, w * seg), j1 = min(V, j0 + seg);
-  float acc = 0.f;
-#pragma unroll 4
-  for (int j = j0 + lane * 4; j < j1; j += 256) {
-    float v[4];
-    val(j, j1, v);
-    acc += (v[0] + v[1]) + (v[2] + v[3]);
-  }
   acc = wave_sum(acc);
   if (lane == 0) red[w] = acc;
   __syncthreads();
@@ -156,6 +198,7 @@ __device__ int block_draw(F val, int V, float u, float* red, int* res) {
     }
   }
   if (w == ws) {
+    prepare();
     int result = -1;
     int last_mass = -1;        // last index with mass seen so far (the answer if rounding hides the crossing)
     float cw = carry;
@@ -213,7 +256,61 @@ __device__ int block_draw(F val, int V, float u, float* red, int* res) {
   return out;
 }
 
-// One row per workgroup: token drawn from softmax(row / T).
+template <typename F>
+__device__ int block_draw(F val, int V, float u, float* red, int* res) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int seg = segment_size(V);
+  const int j0 = min(V, w * seg), j1 = min(V, j0 + seg);
+  float acc = 0.f;
+#pragma unroll 4
+  for (int j = j0 + lane * 4; j < j1; j += 256) {
+    float v[4];
+    val(j, j1, v);
+    acc += (v[0] + v[1]) + (v[2] + v[3]);
+  }
+  return draw_walk(acc, [] {}, val, V, u, red, res);
+}
+
+// The same for masses in registers: mass[i] holds entries j0 + 256 i + 4 lane .. + 3 of the wavefront's segment, zero past
+// its end (V <= reg_vocab(G): the segment has at most G blocks of 256).  The wavefront that walks its segment puts
+// its masses in LDS first (walk: 256 * G floats) and scans them from there.
+template <int G>
+__device__ int block_draw_regs(const float4 (&mass)[G], int V, float u, float* walk, float* red, int* res) {
+  const int lane = threadIdx.x & 63;
+  const int j0 = min(V, (int)(threadIdx.x >> 6) * segment_size(V));
+  float acc = 0.f;
+#pragma unroll
+  for (int i = 0; i < G; ++i) acc += (mass[i].x + mass[i].y) + (mass[i].z + mass[i].w);   // (adding a zero past the end keeps the bits)
+  return draw_walk(
+      acc,
+      [&] {
+#pragma unroll
+        for (int i = 0; i < G; ++i) *reinterpret_cast<float4*>(walk + i * 256 + 4 * lane) = mass[i];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      },
+      [&](int jj, int, float (&v)[4]) {
+        const float4 t = *reinterpret_cast<const float4*>(walk + (jj - j0));
+        v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+      },
+      V, u, red, res);
+}
+
+// masses exp((l - m) / T) of the wavefront's segment from its logits, in place
+template <int G>
+__device__ __forceinline__ void softmax_masses(float4 (&l)[G], int V, float m, float inv_t) {
+  const int seg = segment_size(V), j0 = min(V, (int)(threadIdx.x >> 6) * seg), j1 = min(V, j0 + seg), lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < G; ++i) {
+    const bool on = j0 + i * 256 + 4 * lane < j1;
+    l[i] = on ? make_float4(expf((l[i].x - m) * inv_t), expf((l[i].y - m) * inv_t), expf((l[i].z - m) * inv_t), expf((l[i].w - m) * inv_t))
+              : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+}
+
+// One row per workgroup: token drawn from softmax(row / T).  G > 0: the row in registers (see above), G = 0: any row.
+template <int G>
 __global__ __launch_bounds__(kDrawThreads) void sample_rows_kernel(const float* __restrict__ logits, size_t row_stride, int V,
                                                                     const SamplingParams* __restrict__ prm_dev,
                                                                     const SamplingParams prm_val,
@@ -222,26 +319,46 @@ __global__ __launch_bounds__(kDrawThreads) void sample_rows_kernel(const float* 
                                                                     int out_off) {
   __shared__ float red[kDrawWaves];
   __shared__ int res;
+  __shared__ __align__(16) float walk[G > 0 ? 256 * G : 4];
   const int b = blockIdx.x;
   const float* row = logits + static_cast<size_t>(b) * row_stride;
   const SamplingParams prm = prm_dev ? *prm_dev : prm_val;
   const float inv_t = prm.inv_t;
-  const bool vec = row_is_vec(row);
-  const float m = row_max(row, V, red);
   const int idx = (idx_base ? idx_base[b] : 0) + idx_off;
-  const float u = uniform24(prm.seed, b, idx, purpose);
-  const int tok = block_draw(
-      [&](int jj, int end, float (&v)[4]) {
-        float l[4];
-        load_group(row, jj, end, vec, l);
-        for (int e = 0; e < 4; ++e) v[e] = expf((l[e] - m) * inv_t);
-      },
-      V, u, red, &res);
+  int tok;
+  if constexpr (G > 0) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    float4 l[G];
+    load_groups(row, V, min(V, w * segment_size(V)) + 4 * lane, 256, l);   // (entries past the segment belong to the row: they may count in the maximum)
+    float m = kNoLogit;
+#pragma unroll
+    for (int i = 0; i < G; ++i) m = fmaxf(fmaxf(m, fmaxf(l[i].x, l[i].y)), fmaxf(l[i].z, l[i].w));
+    m = wave_max(m);
+    if (lane == 0) red[w] = m;
+    __syncthreads();
+    m = red[0];
+    for (int i = 1; i < kDrawWaves; ++i) m = fmaxf(m, red[i]);
+    __syncthreads();
+    softmax_masses(l, V, m, inv_t);
+    tok = block_draw_regs(l, V, uniform24(prm.seed, b, idx, purpose), walk, red, &res);
+  } else {
+    const bool vec = row_is_vec(row);
+    const float m = row_max(row, V, red);
+    const float u = uniform24(prm.seed, b, idx, purpose);
+    tok = block_draw(
+        [&](int jj, int end, float (&v)[4]) {
+          float l[4];
+          load_group(row, jj, end, vec, l);
+          for (int e = 0; e < 4; ++e) v[e] = expf((l[e] - m) * inv_t);
+        },
+        V, u, red, &res);
+  }
   if (threadIdx.x == 0) out[static_cast<size_t>(b) * out_stride + out_off] = tok;
 }
 
 // (max, sum) of the k draft rows and the k + 1 verification rows of every sequence:
 // stats[b][r][2], r < kmax: draft row r; r >= kmax: verification row r - kmax.
+template <int G>
 __global__ __launch_bounds__(kDrawThreads) void softmax_stats_kernel(const float* __restrict__ logits_d,
                                                             const float* __restrict__ logits_v, int V, int k, int kmax,
                                                             const SamplingParams* __restrict__ prm_dev,
@@ -253,7 +370,9 @@ __global__ __launch_bounds__(kDrawThreads) void softmax_stats_kernel(const float
   if (r < k) { row = logits_d + (static_cast<size_t>(b) * kmax + r) * V; slot = r; }
   else { row = logits_v + (static_cast<size_t>(b) * (k + 1) + (r - k)) * V; slot = kmax + (r - k); }
   float m, s;
-  row_stats(row, V, prm_dev ? prm_dev->inv_t : prm_val.inv_t, red, m, s);
+  const float inv_t = prm_dev ? prm_dev->inv_t : prm_val.inv_t;
+  if constexpr (G > 0) row_stats_regs<G>(row, V, inv_t, red, m, s);
+  else row_stats(row, V, inv_t, red, m, s);
   if (threadIdx.x == 0) {
     float* st = stats + (static_cast<size_t>(b) * (2 * kmax + 1) + slot) * 2;
     st[0] = m; st[1] = s;
@@ -261,6 +380,7 @@ __global__ __launch_bounds__(kDrawThreads) void softmax_stats_kernel(const float
 }
 
 // The round's acceptance for one sequence per workgroup (Eq. 6) and its targets row.
+template <int G>
 __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float* __restrict__ logits_d,
                                                                      const float* __restrict__ logits_v, int V, int k,
                                                                      int kmax, const SamplingParams* __restrict__ prm_dev,
@@ -272,6 +392,7 @@ __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float*
   __shared__ float red[kDrawWaves];
   __shared__ int res;
   __shared__ int n_sh;
+  __shared__ __align__(16) float walk[G > 0 ? 256 * G : 4];
   const int b = blockIdx.x;
   const SamplingParams prm = prm_dev ? *prm_dev : prm_val;
   const float inv_t = prm.inv_t;
@@ -281,17 +402,24 @@ __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float*
   const float* st = stats + static_cast<size_t>(b) * (2 * kmax + 1) * 2;
   const float* rows_d = logits_d + static_cast<size_t>(b) * kmax * V;
   const float* rows_v = logits_v + static_cast<size_t>(b) * (k + 1) * V;
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {   // a lane per test, 64 drafts at a time: the first that fails ends the kept prefix
     int n = k;
-    for (int i = 0; i < k; ++i) {
-      const int di = d[i];
-      if (di < 0 || di >= V) { n = i; break; }   // not a token: rejected, never used as an index
-      const float ps = prob(rows_d[static_cast<size_t>(i) * V + di], st[2 * i], inv_t, 1.0f / st[2 * i + 1]);
-      const float ph = prob(rows_v[static_cast<size_t>(i) * V + di], st[2 * (kmax + i)], inv_t, 1.0f / st[2 * (kmax + i) + 1]);
-      const float u = uniform24(seed, b, base + i, 1);
-      if (!(u < ph / ps)) { n = i; break; }      // kept with probability min(1, P_H / P_S)
+    for (int i0 = 0; i0 < k && n == k; i0 += 64) {
+      const int i = i0 + (int)threadIdx.x;
+      bool kept = true;
+      if (i < k) {
+        const int di = d[i];
+        kept = di >= 0 && di < V;                // not a token: rejected, never used as an index
+        if (kept) {
+          const float ps = prob(rows_d[static_cast<size_t>(i) * V + di], st[2 * i], inv_t, 1.0f / st[2 * i + 1]);
+          const float ph = prob(rows_v[static_cast<size_t>(i) * V + di], st[2 * (kmax + i)], inv_t, 1.0f / st[2 * (kmax + i) + 1]);
+          kept = uniform24(seed, b, base + i, 1) < ph / ps;   // kept with probability min(1, P_H / P_S)
+        }
+      }
+      const unsigned long long fails = __ballot(!kept);
+      if (fails != 0ull) n = i0 + __ffsll(fails) - 1;
     }
-    n_sh = n;
+    if (threadIdx.x == 0) n_sh = n;
   }
   __syncthreads();
   const int n = n_sh;
@@ -299,9 +427,34 @@ __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float*
   const float* lh = rows_v + static_cast<size_t>(n) * V;
   const float mh = st[2 * (kmax + n)], rsh = 1.0f / st[2 * (kmax + n) + 1];
   int tok;
-  if (n < k) {
-    const float* ls = rows_d + static_cast<size_t>(n) * V;
-    const float ms = st[2 * n], rss = 1.0f / st[2 * n + 1];
+  const float* ls = rows_d + static_cast<size_t>(n < k ? n : 0) * V;
+  const float ms = n < k ? st[2 * n] : 0.f, rss = n < k ? 1.0f / st[2 * n + 1] : 0.f;
+  if constexpr (G > 0) {
+    const int lane = threadIdx.x & 63, seg = segment_size(V), j0 = min(V, (int)(threadIdx.x >> 6) * seg), j1 = min(V, j0 + seg);
+    float4 l[G];
+    load_groups(lh, V, j0 + 4 * lane, 256, l);
+    if (n < k) {
+      constexpr int GB = G < 4 ? G : 4;          // draft groups in flight (registers: 64 hold the row)
+#pragma unroll
+      for (int g0 = 0; g0 < G; g0 += GB) {
+        float4 c[GB];
+        load_groups(ls, V, j0 + g0 * 256 + 4 * lane, 256, c);
+#pragma unroll
+        for (int q = 0; q < GB; ++q) {
+          const float4 a = l[g0 + q], e = c[q];
+          const bool on = j0 + (g0 + q) * 256 + 4 * lane < j1;
+          l[g0 + q] = on ? make_float4(residual_mass(prob(a.x, mh, inv_t, rsh), prob(e.x, ms, inv_t, rss)),
+                                       residual_mass(prob(a.y, mh, inv_t, rsh), prob(e.y, ms, inv_t, rss)),
+                                       residual_mass(prob(a.z, mh, inv_t, rsh), prob(e.z, ms, inv_t, rss)),
+                                       residual_mass(prob(a.w, mh, inv_t, rsh), prob(e.w, ms, inv_t, rss)))
+                         : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+      }
+    } else {
+      softmax_masses(l, V, mh, inv_t);
+    }
+    tok = block_draw_regs(l, V, u, walk, red, &res);
+  } else if (n < k) {
     const bool vec = row_is_vec(lh) && row_is_vec(ls);
     tok = block_draw(
         [&](int jj, int end, float (&v)[4]) {
@@ -311,20 +464,6 @@ __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float*
           for (int e = 0; e < 4; ++e) v[e] = residual_mass(prob(a[e], mh, inv_t, rsh), prob(c[e], ms, inv_t, rss));
         },
         V, u, red, &res);
-    if (tok < 0) {
-      // The residual has no mass (the two distributions agree to rounding; in exact arithmetic a
-      // rejection implies mass elsewhere): the token is drawn from P_H with the same uniform, and
-      // should that be the rejected draft itself, its successor in index order is taken, so that
-      // the targets row still encodes n.
-      tok = block_draw(
-          [&](int jj, int end, float (&v)[4]) {
-            float l[4];
-            load_group(lh, jj, end, row_is_vec(lh), l);
-            for (int e = 0; e < 4; ++e) v[e] = expf((l[e] - mh) * inv_t);
-          },
-          V, u, red, &res);
-      if (tok == d[n]) tok = tok + 1 < V ? tok + 1 : 0;
-    }
   } else {
     const bool vec = row_is_vec(lh);
     tok = block_draw(
@@ -335,17 +474,50 @@ __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float*
         },
         V, u, red, &res);
   }
+  if (n < k && tok < 0) {
+    // The residual has no mass (the two distributions agree to rounding; in exact arithmetic a
+    // rejection implies mass elsewhere): the token is drawn from P_H with the same uniform, and
+    // should that be the rejected draft itself, its successor in index order is taken, so that
+    // the targets row still encodes n.
+    tok = block_draw(
+        [&](int jj, int end, float (&v)[4]) {
+          float l[4];
+          load_group(lh, jj, end, row_is_vec(lh), l);
+          for (int e = 0; e < 4; ++e) v[e] = expf((l[e] - mh) * inv_t);
+        },
+        V, u, red, &res);
+    if (tok == d[n]) tok = tok + 1 < V ? tok + 1 : 0;
+  }
   int* g = targets + static_cast<size_t>(b) * (kmax + 1);
   for (int i = threadIdx.x; i <= k; i += blockDim.x) g[i] = i < n ? d[i] : (i == n ? tok : -1);
 }
 
 }  // namespace
 
+// register groups per thread for rows of V entries with this alignment: 0 = the kernels for any row
+static int reg_groups(const void* p, const void* q, size_t stride, int V) {
+  if (V % 4 != 0 || stride % 4 != 0 || ((reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(q)) & 15) != 0) return 0;
+  for (int g = 2; g <= kRegGroups; g *= 2)
+    if (V <= reg_vocab(g)) return g;
+  return 0;
+}
+#define HH_REG_GROUPS(g_, CALL) \
+  switch (g_) {                 \
+    case 2: CALL(2); break;     \
+    case 4: CALL(4); break;     \
+    case 8: CALL(8); break;     \
+    case 16: CALL(16); break;   \
+    default: CALL(0); break;    \
+  }
+
 hipError_t launch_sample_rows(const float* logits, size_t row_stride, int V, int B, const SamplingParams* prm,
                               SamplingParams prm_val, const int* idx_base, int idx_off, int purpose, int* out,
                               int out_stride, int out_off, hipStream_t s) {
-  hipLaunchKernelGGL(sample_rows_kernel, dim3(B), dim3(kDrawThreads), 0, s, logits, row_stride, V, prm, prm_val, idx_base,
-                     idx_off, purpose, out, out_stride, out_off);
+#define HH_CALL(G)                                                                                                             \
+  hipLaunchKernelGGL((sample_rows_kernel<G>), dim3(B), dim3(kDrawThreads), 0, s, logits, row_stride, V, prm, prm_val, idx_base, \
+                     idx_off, purpose, out, out_stride, out_off)
+  HH_REG_GROUPS(reg_groups(logits, nullptr, row_stride, V), HH_CALL)
+#undef HH_CALL
   return hipGetLastError();
 }
 
@@ -379,12 +551,19 @@ hipError_t static_accept_scratch(float** ptr, size_t* n_floats) {
 hipError_t launch_spec_targets(const float* logits_d, const float* logits_v, int V, int B, int k, int kmax,
                                const SamplingParams* prm, SamplingParams prm_val, float* stats, const int* drafts,
                                const int* committed, int* targets, hipStream_t s) {
-  hipLaunchKernelGGL(softmax_stats_kernel, dim3(2 * k + 1, B), dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, prm,
-                     prm_val, stats);
+  const int groups = reg_groups(logits_d, logits_v, V, V);
+#define HH_CALL(G)                                                                                                               \
+  hipLaunchKernelGGL((softmax_stats_kernel<G>), dim3(2 * k + 1, B), dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, prm, \
+                     prm_val, stats)
+  HH_REG_GROUPS(groups, HH_CALL)
+#undef HH_CALL
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(spec_targets_kernel, dim3(B), dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, prm, prm_val,
-                     stats, drafts, committed, targets);
+#define HH_CALL(G)                                                                                                          \
+  hipLaunchKernelGGL((spec_targets_kernel<(G) <= 8 ? (G) : 0>), dim3(B), dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, prm, prm_val, \
+                     stats, drafts, committed, targets)
+  HH_REG_GROUPS(groups, HH_CALL)
+#undef HH_CALL
   return hipGetLastError();
 }
 

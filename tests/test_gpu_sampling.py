@@ -147,3 +147,35 @@ def test_residual_without_mass_draws_from_p_h(B):
                 assert g[b][n] == tok, (seed, b, g[b], tok)
                 checked += 1
     assert checked > 30
+
+
+@pytest.mark.parametrize("vocab", [4, 1024, 8192, 8196, 16388, 32768, 65536, 65540])
+def test_rows_in_registers_equal_rows_in_memory(vocab):
+    """Rows whose length is a multiple of 4 and that start on 16 bytes are held in registers (up to 65536 entries, the
+    draw of the acceptance up to 32768); rows that start elsewhere take the kernels that read memory again.  The sums
+    are the same in the same order, so the tokens are equal, also with masked (-inf), lowest and equal entries, and where
+    every draft is kept, the first is rejected, or a draft is no token."""
+    import torch
+    from paper_2605_01106_amd import binding as B
+    batch, k, t, seed = 5, 3, 0.6, 77
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    verify = torch.randn((batch, k + 1, vocab), generator=g, device="cuda") * 3
+    draft = verify[:, :k] + torch.randn((batch, k, vocab), generator=g, device="cuda") * 0.5
+    verify[0, :, : vocab // 2] = -float("inf")
+    verify[1, :, 1:] = torch.finfo(torch.float32).min
+    verify[2] = 0.25
+    draft[3] = verify[3, :k]
+    drafts = draft.argmax(-1).to(torch.int32).contiguous()
+    drafts[4, 1] = vocab
+    positions = torch.arange(batch, device="cuda", dtype=torch.int32) * 9
+
+    def shifted(x):   # the same values, contiguous, starting 4 bytes behind a 16-byte boundary
+        buf = torch.empty(x.numel() + 1, device="cuda", dtype=torch.float32)
+        buf[1:] = x.reshape(-1)
+        return buf[1:].view(x.shape)
+
+    rows = verify[:, 0].contiguous()
+    assert torch.equal(B.hh_draw_tokens(rows, t, seed, positions=positions),
+                       B.hh_draw_tokens(shifted(rows), t, seed, positions=positions))
+    assert torch.equal(B.hh_accept_tokens(draft.contiguous(), verify, drafts, positions, t, seed),
+                       B.hh_accept_tokens(shifted(draft), shifted(verify), drafts, positions, t, seed))
