@@ -66,7 +66,7 @@ struct hh_ctx {
   std::vector<size_t> canaries;   // offsets of the guard bytes behind every workspace region (HH_KF_CANARIES)
   bool draft_has_full = false;
   // device int state
-  int *kv_len, *committed, *last_n, *pending, *n_acc, *skip, *adv, *drafts, *targets, *tok, *pos0, *out_tok,
+  int *kv_len, *committed, *last_n, *pending, *n_acc, *skip, *adv, *drafts, *targets, *pos0, *out_tok,
       *page_table, *plan_ntok, *plan_last, *first_tok;
   unsigned long long* best;
   unsigned long long* acc_stats;   // accepted / tested drafts since the last prefill
@@ -191,7 +191,7 @@ size_t carve(hh_ctx* x, char* base) {
   x->first_tok = c.take<int>(B);
   x->drafts = c.take<int>(B * (d.Kmax > 0 ? d.Kmax : 1));
   x->targets = c.take<int>(B * (d.Kmax + 1));
-  x->tok = c.take<int>(Mmax); x->pos0 = c.take<int>(B);
+  x->pos0 = c.take<int>(B);
   x->out_tok = c.take<int>(B * d.Gmax);
   x->page_table = c.take<int>(B * d.pages_per_seq);
   const int chunk = prefill_chunk_of(x->cfg);
@@ -422,36 +422,51 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
   return HH_OK;
 }
 
-// final norm + LM head + argmax of M rows of X; row m = b*T + j -> out[b*out_stride + out_off + j]
-hh_status run_head(hh_ctx* x, const float* X, int M, int T, float* logits, int ld_logits, int* out, int out_stride,
-                   int out_off, hipStream_t s) {
+// arguments of a pass's first launch (which also clears the argmax keys that a many-row LM head of the pass raises)
+PassArgs pass_args(const hh_ctx* x, int mode, int T, int step) {
   const Dims& d = x->d;
+  PassArgs p{};
+  p.embed = x->embed; p.bf16 = d.bf16; p.D = d.D; p.V = d.V; p.h = x->h;
+  p.pending = x->pending; p.drafts = x->drafts; p.kv_len = x->kv_len; p.pos0 = x->pos0;
+  p.kmax = d.Kmax; p.T = T; p.mode = mode; p.step = step; p.clear = x->best;
+  return p;
+}
+
+// final norm + LM head + argmax of M rows of X; row m = b*T + j -> out[b*out_stride + out_off + j].
+// At temperature > 0 the caller draws from the logits and the argmax is not taken.
+// next: the draft step that the argmax's last launch also begins, or nullptr.
+hh_status run_head(hh_ctx* x, const float* X, int M, int T, float* logits, int ld_logits, int* out, int out_stride,
+                   int out_off, const PassArgs* next, hipStream_t s) {
+  const Dims& d = x->d;
+  const bool greedy = !(x->temperature > 0.f);
+  PassArgs begin{}, keyed{};
+  if (next != nullptr) { begin = *next; begin.clear = nullptr; next = &begin; }   // (partials of several workgroups: nothing to clear)
   GemvArgs a{};
   a.X = X; a.ldx = d.D; a.M = M; a.K = d.D; a.norm_w = static_cast<const float*>(x->final_norm); a.eps = d.eps;
   a.epi = EPI_STORE; a.bf16 = d.bf16; a.flags = d.flags; a.best = x->best;
   // greedy rounds of a context created with keep_logits = 0 only need the argmax of every row
-  a.no_store = !x->cfg.keep_logits && !(x->temperature > 0.f);
+  a.no_store = !x->cfg.keep_logits && greedy;
   a.seg[0] = {x->lm_head, nullptr, x->p_lm_head, nullptr, logits, d.V, ld_logits}; a.n_seg = 1;
   GemvArgs sk;
   if (skinny_args(a, sk)) {
     int nb = 0;
     HH_LAUNCH(HH_K_LM_HEAD, launch_skinny_mfma(sk, x->gemm_partial, &nb, s));
-    HH_HIP(launch_argmax_finish(x->best, nb, M, out, out_stride, out_off, T, s));
+    if (greedy) HH_HIP(launch_argmax_finish(x->best, nb, M, out, out_stride, out_off, T, next, s));
     return HH_OK;
   }
   if (a.bf16 && M >= kMfmaMinRows) {
     // many-row kernels: every row's argmax key is raised with atomic maxima in the epilogue (the first
-    // M entries of the partials buffer, cleared here), so the logits need not be written or re-read
+    // M entries of the partials buffer, cleared by the pass's first launch), so the logits need not be written or re-read
     a.best = nullptr; a.row_best = x->best;
-    HH_HIP(launch_fill_i32(reinterpret_cast<int*>(x->best), 0, (size_t)2 * M, s));
+    if (next != nullptr) { keyed = *next; keyed.clear = x->best; next = &keyed; }
     if (mid_mfma_fits(a)) HH_LAUNCH(HH_K_LM_HEAD, launch_mid_mfma(a, x->gemm_partial, s));
     else HH_LAUNCH(HH_K_LM_HEAD, launch_gemm_mfma(a, x->planes, x->gemm_partial, s));
-    HH_HIP(launch_argmax_finish(x->best, 1, M, out, out_stride, out_off, T, s));
+    if (greedy) HH_HIP(launch_argmax_finish(x->best, 1, M, out, out_stride, out_off, T, next, s));
     return HH_OK;
   }
   int nblk = 0;
   HH_LAUNCH(HH_K_LM_HEAD, launch_gemv(a, &nblk, s));
-  HH_HIP(launch_argmax_finish(x->best, nblk, M, out, out_stride, out_off, T, s));
+  if (greedy) HH_HIP(launch_argmax_finish(x->best, nblk, M, out, out_stride, out_off, T, next, s));
   return HH_OK;
 }
 
@@ -524,8 +539,7 @@ int pick_splits(const hh_cfg& c, const Dims& d, int B, int T, int len_upper) {
 hh_status ms_consume(hh_ctx* x, int B, int first, int last, hipStream_t s) {
   const Dims& d = x->d;
   for (int i = first; i <= last; ++i) {
-    HH_HIP(launch_gather_tokens(x->pending, x->drafts, d.Kmax, B, 1, 0, i, x->tok, x->kv_len, x->pos0, s));
-    HH_HIP(launch_embed(d, x->embed, x->tok, B, x->h, s));
+    HH_HIP(launch_begin_pass(pass_args(x, PASS_DRAFT, 1, i), B, s));
     const hh_status st = run_layers(x, x->layers_ms_host, false, nullptr, B, 1, nullptr, i == 0 ? 0 : 1, i == last ? 0 : 2, 1, false, s);
     if (st != HH_OK) return st;
   }
@@ -732,13 +746,14 @@ hh_status hh_prefill(hh_ctx* x, const int32_t* tokens, int32_t row_stride, const
   for (int p = 0; p < n_pass; ++p) {
     const int T = maxlen - p * chunk < chunk ? maxlen - p * chunk : chunk;
     const int* nt = x->plan_ntok + (size_t)p * B;
-    HH_HIP(launch_gather_prompt(tokens, row_stride, p * chunk, nt, B, T, x->tok, x->kv_len, x->pos0, s));
-    HH_HIP(launch_embed(d, x->embed, x->tok, B * T, x->h, s));
+    PassArgs begin = pass_args(x, PASS_PROMPT, T, 0);
+    begin.prompt = tokens; begin.row_stride = row_stride; begin.off = p * chunk; begin.n_tok = nt;
+    HH_HIP(launch_begin_pass(begin, B, s));
     hh_status st = HH_OK;
     if (x->strict) {   // M_S over the same positions first, into its own state and ring (Eq. 4 at every prefix position)
       st = run_layers(x, x->layers_ms_host, false, nullptr, B, T, nt, p == 0 ? 2 : 0, 1, 1, true, s);
       if (st != HH_OK) return st;
-      HH_HIP(launch_embed(d, x->embed, x->tok, B * T, x->h, s));
+      HH_HIP(launch_begin_pass(begin, B, s));
     }
     st = run_layers(x, x->layers_host, true, nullptr, B, T, nt, p == 0 ? 2 : 0, 1, 1, true, s);
     if (st != HH_OK) return st;
@@ -751,7 +766,7 @@ hh_status hh_prefill(hh_ctx* x, const int32_t* tokens, int32_t row_stride, const
       fflush(stderr);
     }
   }
-  hh_status st = run_head(x, x->lasth, B, 1, x->logits_p, d.V, x->first_tok, 1, 0, s);
+  hh_status st = run_head(x, x->lasth, B, 1, x->logits_p, d.V, x->first_tok, 1, 0, nullptr, s);
   if (st != HH_OK) return st;
   if (x->temperature > 0.f)
     HH_HIP(launch_sample_rows(x->logits_p, d.V, d.V, B, x->sampling, SamplingParams{}, nullptr, 0, 2, x->first_tok, 1, 0, s));
@@ -850,13 +865,14 @@ hh_status hh_draft(hh_ctx* x, int32_t k, void* stream) {
   const int splits = x->draft_has_full ? pick_splits(x->cfg, d, B, 1, x->len_upper) : 1;
   auto enqueue = [&]() -> hh_status {
     for (int i = 0; i < k; ++i) {
-      HH_HIP(launch_gather_tokens(x->pending, x->drafts, d.Kmax, B, 1, 0, i, x->tok, x->kv_len, x->pos0, s));
-      HH_HIP(launch_embed(d, x->embed, x->tok, B, x->h, s));
+      // (a greedy step's argmax has begun the step behind it)
+      if (i == 0 || stochastic) HH_HIP(launch_begin_pass(pass_args(x, PASS_DRAFT, 1, i), B, s));
       // the scratch state after the last step is never read (unless M_S goes on to consume d_k): not written
       const int state_out = (i == k - 1 && !x->strict) ? 0 : 2;
       hh_status st = run_layers(x, table, false, modes, B, 1, nullptr, i == 0 ? 0 : 1, state_out, splits, false, s);
       if (st != HH_OK) return st;
-      st = run_head(x, x->h, B, 1, x->logits_d + (size_t)i * d.V, d.Kmax * d.V, x->drafts, d.Kmax, i, s);
+      const PassArgs next = pass_args(x, PASS_DRAFT, 1, i + 1);
+      st = run_head(x, x->h, B, 1, x->logits_d + (size_t)i * d.V, d.Kmax * d.V, x->drafts, d.Kmax, i, i + 1 < k ? &next : nullptr, s);
       if (st != HH_OK) return st;
       if (stochastic)
         HH_HIP(launch_sample_rows(x->logits_d + (size_t)i * d.V, (size_t)d.Kmax * d.V, d.V, B, x->sampling, SamplingParams{},
@@ -954,11 +970,10 @@ hh_status hh_verify(hh_ctx* x, void* stream) {
   x->prof_phase = HH_PHASE_VERIFY;
   const int splits = pick_splits(x->cfg, d, B, T, x->len_upper);
   auto enqueue = [&]() -> hh_status {
-    HH_HIP(launch_gather_tokens(x->pending, x->drafts, d.Kmax, B, T, 1, 0, x->tok, x->kv_len, x->pos0, s));
-    HH_HIP(launch_embed(d, x->embed, x->tok, B * T, x->h, s));
+    HH_HIP(launch_begin_pass(pass_args(x, PASS_VERIFY, T, 0), B, s));
     hh_status st = run_layers(x, x->layers_host, true, nullptr, B, T, nullptr, 0, 0, splits, false, s);
     if (st != HH_OK) return st;
-    st = run_head(x, x->h, B * T, T, x->logits_v, d.V, x->targets, d.Kmax + 1, 0, s);
+    st = run_head(x, x->h, B * T, T, x->logits_v, d.V, x->targets, d.Kmax + 1, 0, nullptr, s);
     if (st != HH_OK) return st;
     if (stochastic)
       HH_HIP(launch_spec_targets(x->logits_d, x->logits_v, d.V, B, x->k, d.Kmax, x->sampling, SamplingParams{}, x->softmax_stats, x->drafts,
@@ -1180,8 +1195,7 @@ hh_status hh_time_kind(hh_ctx* x, int32_t phase, int32_t kind, int32_t k, int32_
   HH_HIP(hipEventCreate(&e0));
   HH_HIP(hipEventCreate(&e1));
   // positions and tokens of an ordinary pass, so that every kernel sees valid inputs
-  HH_HIP(launch_gather_tokens(x->pending, x->drafts, d.Kmax, B, T, full ? 1 : 0, 0, x->tok, x->kv_len, x->pos0, s));
-  HH_HIP(launch_embed(d, x->embed, x->tok, B * T, x->h, s));
+  HH_HIP(launch_begin_pass(pass_args(x, full ? PASS_VERIFY : PASS_DRAFT, T, 0), B, s));
   const bool prof = x->prof_on;
   x->prof_on = true;            // serial launches on one stream (no side stream), but no event pairs:
   const size_t cap = x->prof_ev.size();
@@ -1197,7 +1211,7 @@ hh_status hh_time_kind(hh_ctx* x, int32_t phase, int32_t kind, int32_t k, int32_
     for (int r = 0; r < reps && st == HH_OK; ++r) {
       if (kind == HH_K_LM_HEAD) {
         st = run_head(x, x->h, B * T, T, full ? x->logits_v : x->logits_d, full ? d.V : d.Kmax * d.V,
-                      full ? x->targets : x->drafts, full ? d.Kmax + 1 : d.Kmax, 0, s);
+                      full ? x->targets : x->drafts, full ? d.Kmax + 1 : d.Kmax, 0, nullptr, s);
         n += 1;
       } else {
         st = run_layers(x, x->layers_host, full, nullptr, B, T, nullptr, 0, full ? 0 : 2, pick_splits(x->cfg, d, B, T, x->len_upper), false, s);

@@ -130,12 +130,19 @@ bool attention_mfma_fuses_append(const Dims& d, int T);
 hipError_t launch_attention_mfma(const Dims& d, const AttnArgs& a, hipStream_t s);
 
 // ---- small kernels
-hipError_t launch_embed(const Dims& d, const void* embed, const int* tok, int M, float* h, hipStream_t s);
-// tokens of one draft step: step 0 reads pending[b], step i reads drafts[b][i-1]
-hipError_t launch_gather_tokens(const int* pending, const int* drafts, int kmax, int B, int T, int mode,
-                                int step, int* tok, const int* kv_len, int* pos0, hipStream_t s);
+// first launch of a pass: tokens, embedding, positions, cleared argmax keys (see begin_pass_kernel)
+enum { PASS_DRAFT = 0, PASS_VERIFY = 1, PASS_PROMPT = 2 };
+struct PassArgs {
+  const void* embed; int bf16, D, V;
+  float* h;                                    // [B*T][D]
+  const int *pending, *drafts, *prompt, *n_tok, *kv_len;
+  int* pos0;
+  int kmax, T, mode, step, row_stride, off;
+  unsigned long long* clear;                   // [B*T] keys to clear, or nullptr
+};
+hipError_t launch_begin_pass(const PassArgs& a, int B, hipStream_t s);
 hipError_t launch_argmax_finish(const unsigned long long* best, int n_part, int M, int* out, int out_stride,
-                                int out_off, int T, hipStream_t s);
+                                int out_off, int T, const PassArgs* next, hipStream_t s);
 struct CommitArgs {
   const int* drafts; const int* targets; const int* forced;  // [B][kmax], [B][kmax+1], [B] or nullptr
   int *committed, *last_n, *pending, *out_tok, *n_acc, *skip, *adv;
@@ -144,8 +151,6 @@ struct CommitArgs {
 };
 hipError_t launch_accept(const CommitArgs& a, hipStream_t s);
 hipError_t launch_advance(int* kv_len, const int* n, int B, hipStream_t s);
-hipError_t launch_gather_prompt(const int* prompt, int row_stride, int off, const int* n_tok, int B, int T, int* tok,
-                                const int* kv_len, int* pos0, hipStream_t s);
 hipError_t launch_prefill_tail(const float* h, int T, int D, const int* n_tok, const int* is_last, float* lasth,
                                int* kv_len, int B, hipStream_t s);
 hipError_t launch_prefill_finish(const int* first_tok, int* pending, int* out_tok, int out_stride, int* committed,

@@ -6,68 +6,57 @@
 
 namespace hh {
 
-// h[m][:] = E[tok[m]][:]
-__global__ void embed_kernel(const void* embed, int bf16, const int* tok, int D, int V, float* h) {
-  const int m = blockIdx.x;
-  const size_t src = (size_t)min(max(tok[m], 0), V - 1) * D;   // an id that is no token reads a valid row, never out of bounds
-  for (int k = threadIdx.x; k < D; k += blockDim.x) {
-    float v;
-    if (bf16) v = __uint_as_float((uint32_t) static_cast<const uint16_t*>(embed)[src + k] << 16);
-    else v = static_cast<const float*>(embed)[src + k];
-    h[(size_t)m * D + k] = v;
+// A row of the embedding as float32, by a whole workgroup (D % 8 == 0; an id that is no token reads a valid row, never
+// out of bounds).
+__device__ __forceinline__ void embed_row(const void* embed, int bf16, int tok, int D, int V, float* h) {
+  const size_t src = (size_t)min(max(tok, 0), V - 1) * D;
+  if ((reinterpret_cast<uintptr_t>(embed) & 15) != 0) {   // (the caller's matrix: no alignment is asked of it)
+    for (int k = threadIdx.x; k < D; k += blockDim.x)
+      h[k] = bf16 ? __uint_as_float((uint32_t) static_cast<const uint16_t*>(embed)[src + k] << 16) : static_cast<const float*>(embed)[src + k];
+    return;
   }
-}
-
-hipError_t launch_embed(const Dims& d, const void* embed, const int* tok, int M, float* h, hipStream_t s) {
-  hipLaunchKernelGGL(embed_kernel, dim3(M), dim3(256), 0, s, embed, d.bf16, tok, d.D, d.V, h);
-  return hipGetLastError();
-}
-
-// mode 0: draft step `step`: tok[b] = step == 0 ? pending[b] : drafts[b][step-1]; pos0[b] = kv_len[b] + step
-// mode 1: verification:      tok[b*T + 0] = pending[b], tok[b*T + j] = drafts[b][j-1]; pos0[b] = kv_len[b]
-__global__ void gather_tokens_kernel(const int* pending, const int* drafts, int kmax, int B, int T, int mode, int step,
-                                     int* tok, const int* kv_len, int* pos0) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (mode == 0) {
-    if (i < B) {
-      tok[i] = step == 0 ? pending[i] : drafts[i * kmax + step - 1];
-      pos0[i] = kv_len[i] + step;
+  for (int k = threadIdx.x * 4; k < D; k += blockDim.x * 4) {
+    float4 v;
+    if (bf16) {
+      const uint2 u = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(embed) + src + k);
+      v = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                      __uint_as_float(u.y & 0xffff0000u));
+    } else {
+      v = *reinterpret_cast<const float4*>(static_cast<const float*>(embed) + src + k);
     }
-  } else if (i < B * T) {
-    const int b = i / T, j = i % T;
-    tok[i] = j == 0 ? pending[b] : drafts[b * kmax + j - 1];
-    if (j == 0) pos0[b] = kv_len[b];
+    *reinterpret_cast<float4*>(h + k) = v;
   }
 }
 
-hipError_t launch_gather_tokens(const int* pending, const int* drafts, int kmax, int B, int T, int mode, int step,
-                                int* tok, const int* kv_len, int* pos0, hipStream_t s) {
-  const int n = mode == 0 ? B : B * T;
-  hipLaunchKernelGGL(gather_tokens_kernel, dim3((n + 255) / 256), dim3(256), 0, s, pending, drafts, kmax, B, T, mode,
-                     step, tok, kv_len, pos0);
+// Start of a pass, one workgroup per row m = b*T + j: the row's token, its embedding into h[m], the position of the
+// sequence's first row, and a cleared argmax key of the row (the many-row LM heads raise them with atomic maxima).
+//   PASS_DRAFT   draft step `step`: pending[b] at step 0, else drafts[b][step-1]; position kv_len[b] + step
+//   PASS_VERIFY  pending[b], drafts[b][j-1]; position kv_len[b]
+//   PASS_PROMPT  prompt[b][off + j] for j < n_tok[b] (token 0 beyond); position kv_len[b]
+__global__ __launch_bounds__(256) void begin_pass_kernel(const PassArgs a) {
+  const int m = blockIdx.x, b = m / a.T, j = m - b * a.T;
+  int tok;
+  if (a.mode == PASS_DRAFT) tok = a.step == 0 ? a.pending[b] : a.drafts[b * a.kmax + a.step - 1];
+  else if (a.mode == PASS_VERIFY) tok = j == 0 ? a.pending[b] : a.drafts[b * a.kmax + j - 1];
+  else tok = j < a.n_tok[b] ? a.prompt[(size_t)b * a.row_stride + a.off + j] : 0;
+  if (threadIdx.x == 0) {
+    if (j == 0) a.pos0[b] = a.kv_len[b] + (a.mode == PASS_DRAFT ? a.step : 0);
+    if (a.clear != nullptr) a.clear[m] = 0ull;
+  }
+  embed_row(a.embed, a.bf16, tok, a.D, a.V, a.h + (size_t)m * a.D);
+}
+
+hipError_t launch_begin_pass(const PassArgs& a, int B, hipStream_t s) {
+  if (B * a.T <= 0) return hipSuccess;
+  hipLaunchKernelGGL(begin_pass_kernel, dim3(B * a.T), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-// Prefill pass: tok[b*T + j] = prompt[b][off + j] for j < n_tok[b] (0 beyond); pos0[b] = kv_len[b]
-__global__ void gather_prompt_kernel(const int* prompt, int row_stride, int off, const int* n_tok, int B, int T,
-                                     int* tok, const int* kv_len, int* pos0) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * T) return;
-  const int b = i / T, j = i % T;
-  tok[i] = j < n_tok[b] ? prompt[(size_t)b * row_stride + off + j] : 0;
-  if (j == 0) pos0[b] = kv_len[b];
-}
-
-hipError_t launch_gather_prompt(const int* prompt, int row_stride, int off, const int* n_tok, int B, int T, int* tok,
-                                const int* kv_len, int* pos0, hipStream_t s) {
-  hipLaunchKernelGGL(gather_prompt_kernel, dim3((B * T + 255) / 256), dim3(256), 0, s, prompt, row_stride, off, n_tok,
-                     B, T, tok, kv_len, pos0);
-  return hipGetLastError();
-}
-
-// Reduce the per-workgroup argmax partials of the LM head: row m = b*T + j -> out[b*out_stride + out_off + j]
-__global__ void argmax_finish_kernel(const unsigned long long* best, int n_part, int M, int* out, int out_stride,
-                                     int out_off, int T) {
+// Reduce the per-workgroup argmax partials of the LM head: row m = b*T + j -> out[b*out_stride + out_off + j].
+// next.h != nullptr (draft steps, T = 1): the workgroup also begins the next step of its sequence with the token it has
+// just found (position kv_len[b] + next.step, embedding, cleared key), which saves that step's first launch.
+__global__ __launch_bounds__(256) void argmax_finish_kernel(const unsigned long long* best, int n_part, int M, int* out, int out_stride,
+                                                            int out_off, int T, const PassArgs next) {
   const int m = blockIdx.x;
   unsigned long long v = 0ull;
   for (int i = threadIdx.x; i < n_part; i += blockDim.x) v = max(v, best[(size_t)m * n_part + i]);
@@ -76,16 +65,24 @@ __global__ void argmax_finish_kernel(const unsigned long long* best, int n_part,
   __shared__ unsigned long long w[4];
   if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = v;
   __syncthreads();
+  v = max(max(w[0], w[1]), max(w[2], w[3]));
+  const int tok = (int)(0xFFFFFFFFu - (uint32_t)(v & 0xFFFFFFFFull));
   if (threadIdx.x == 0) {
-    for (int i = 1; i < (int)(blockDim.x >> 6); ++i) v = max(v, w[i]);
     const int b = m / T, j = m % T;
-    out[(size_t)b * out_stride + out_off + j] = (int)(0xFFFFFFFFu - (uint32_t)(v & 0xFFFFFFFFull));
+    out[(size_t)b * out_stride + out_off + j] = tok;
   }
+  if (next.h == nullptr) return;
+  if (threadIdx.x == 0) {
+    next.pos0[m] = next.kv_len[m] + next.step;
+    if (next.clear != nullptr) next.clear[m] = 0ull;      // (n_part = 1 then: the key this workgroup alone has read)
+  }
+  embed_row(next.embed, next.bf16, tok, next.D, next.V, next.h + (size_t)m * next.D);
 }
 
 hipError_t launch_argmax_finish(const unsigned long long* best, int n_part, int M, int* out, int out_stride,
-                                int out_off, int T, hipStream_t s) {
-  hipLaunchKernelGGL(argmax_finish_kernel, dim3(M), dim3(256), 0, s, best, n_part, M, out, out_stride, out_off, T);
+                                int out_off, int T, const PassArgs* next, hipStream_t s) {
+  hipLaunchKernelGGL(argmax_finish_kernel, dim3(M), dim3(256), 0, s, best, n_part, M, out, out_stride, out_off, T,
+                     next != nullptr ? *next : PassArgs{});
   return hipGetLastError();
 }
 
