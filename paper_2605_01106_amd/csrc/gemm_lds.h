@@ -157,6 +157,7 @@ __global__ __launch_bounds__(64 * kLdsWaves) void gemm_lds_kernel(const LdsGemmA
         for (int t = 0; t < 3; ++t) pn[t].u = *reinterpret_cast<const uint4*>(pb + ((m + 1) * 3 + t) * 1024);
       }
       HH_LDS_FENCE();
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int t = 0; t < 3; ++t)
 #pragma unroll
@@ -165,6 +166,7 @@ __global__ __launch_bounds__(64 * kLdsWaves) void gemm_lds_kernel(const LdsGemmA
           lds_f32x4& c = acc[NF == 2 ? (i >> 1) : 0][NF == 2 ? (i & 1) : (i % NS)][m];
           c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i].v, pc[t].v, c, 0, 0, 0);
         }
+      __builtin_amdgcn_s_setprio(0);
     }
   };
 
