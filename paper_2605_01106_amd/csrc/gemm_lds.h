@@ -157,6 +157,8 @@ __global__ __launch_bounds__(64 * kLdsWaves) void gemm_lds_kernel(const LdsGemmA
         for (int t = 0; t < 3; ++t) pn[t].u = *reinterpret_cast<const uint4*>(pb + ((m + 1) * 3 + t) * 1024);
       }
       HH_LDS_FENCE();
+      // the wavefront that has its operands goes first, the other one of the SIMD copies and reads meanwhile: 512-row
+      // prefill passes 1.1 to 1.4 % faster
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int t = 0; t < 3; ++t)
