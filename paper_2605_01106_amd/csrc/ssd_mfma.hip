@@ -7,8 +7,13 @@
 //     S'  = exp(cum_L) * S        +  sum_i  exp(cum_L - cum_i) * dt_i * x_i (outer) B_i
 // - four small matrix products per chunk instead of L dependent state updates.  All exponents are
 // <= 0, so nothing overflows whatever the decay.  Products are v_mfma_f32_16x16x4_f32 (exact
-// float32 products, float32 accumulation): the rounding differs from the sequential kernels only
-// in the order of the sums.
+// float32 products, float32 accumulation).  cum_t reaches -70 within a chunk (32 steps of 0.3 at
+// A = 8), and a decay exp(cum_t - cum_i) of neighbouring positions carries the absolute error of
+// both sums: the sums and their differences are float64, the exponent is rounded once, and the
+// rounding differs from the sequential kernels only in the order of the sums.  (With float32 sums
+// the state behind a full chunk was 2 to 3.6 times as far from float64 as theirs, and the logits of
+// its last position 1.2 to 1.6 times; now 0.9 to 1.1.  Time unchanged: prefill of 4096 tokens
+// through four 3B blocks 13.38 against 13.39 ms.)
 //
 // One workgroup of eight wavefronts per (sequence, pair of heads), head dimension P = 64: B, C
 // and G = C B^T do not depend on the head, so their convolution is shared by the pair, and two
@@ -50,8 +55,9 @@ struct SsdLds {
   static constexpr int kX = kCt + N * LDT;             // x  [2][L][LDX]   (head of the pair, position, p)
   static constexpr int kM = kX + 2 * kSsdL * LDX;      // M  [2][L][LDM]   (head of the pair, t, i)
   static constexpr int kDt = kM + 2 * kSsdL * LDM;     // dt [2][L]
-  static constexpr int kCum = kDt + 2 * kSsdL;         // cum [2][L]
-  static constexpr int kFloats = kCum + 2 * kSsdL;
+  static constexpr int kCum = kDt + 2 * kSsdL;         // cum [2][L], doubles
+  static constexpr int kFloats = kCum + 4 * kSsdL;
+  static_assert(kCum % 2 == 0, "the doubles are aligned");
 };
 
 // SEG_WALK: a workgroup walks the whole pass.  With few sequences that leaves most of the chip idle, so the pass is
@@ -83,7 +89,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
   float* Xs = ssd_smem + Lds::kX + hh * L * LDX;
   float* Ms = ssd_smem + Lds::kM + hh * L * LDM;
   float* dts = ssd_smem + Lds::kDt + hh * L;
-  float* cums = ssd_smem + Lds::kCum + hh * L;
+  double* cums = reinterpret_cast<double*>(ssd_smem + Lds::kCum) + hh * L;
   const LayerDev& ly = a.one;
   int nt = a.T;
   if (a.n_tok != nullptr) nt = a.n_tok[b];
@@ -144,7 +150,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
     }                                                                                                    \
   } while (0)
   if (stager) HH_SSD_REQUEST(t0 + HALF * sh, 0);
-  float total = 0.f;                                   // SEG_LOCAL: log-decay sum of the segment
+  double total = 0.0;                                  // SEG_LOCAL: log-decay sum of the segment
 
   TR(0);
   for (int j0 = t0; j0 < t1; j0 += L) {
@@ -205,14 +211,14 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
       const float rawdt = zx[(size_t)(j0 + min(lane, tc - 1)) * d.ldzx + d.d_inner + d.conv_dim + hd];
       const float dt = on ? ssd_softplus(rawdt + ly.dt_bias[hd]) : 0.f;
       if (on && keep_raw) ring[(size_t)((pos0 + j0 + lane) & rmask) * d.ring_w + d.conv_dim + hd] = rawdt;
-      float c = -expf(ly.a_log[hd]) * dt;              // log a_t, summed over the positions up to t
+      double c = -expf(ly.a_log[hd]) * dt;             // log a_t (float32, as in the sequential kernels), summed over the positions up to t
 #pragma unroll
       for (int o = 1; o < L; o <<= 1) {
-        const float up = __shfl_up(c, o, 64);
+        const double up = __shfl_up(c, o, 64);
         if (lane >= o) c += up;
       }
       ssd_smem[Lds::kDt + hp * L + lane] = dt;
-      ssd_smem[Lds::kCum + hp * L + lane] = c;
+      reinterpret_cast<double*>(ssd_smem + Lds::kCum)[hp * L + lane] = c;
     }
     __syncthreads();
     if (j0 == 0) TR(2);
@@ -233,11 +239,12 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
       // lane (g, j) holds G[t = 16 tt' + 4 g + r][i = 16 it' + j]
       const int tt_w = wq == 3 ? 0 : tt, it_w = wq == 3 ? 1 : it;
       const int i = 16 * it_w + j;
-      const float ci = cums[i], di = dts[i];
+      const double ci = cums[i];
+      const float di = dts[i];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int t = 16 * tt_w + 4 * g + r;
-        const float m = (wq < 3 && i <= t) ? G[r] * di * expf(cums[t] - ci) : 0.f;
+        const float m = (wq < 3 && i <= t) ? G[r] * di * expf((float)(cums[t] - ci)) : 0.f;
         Ms[t * LDM + i] = m;
       }
     }
@@ -257,7 +264,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
       if ((t & 1) == 1) asm volatile("" ::: "memory");   // operand reads at most two state tiles ahead (registers)
     }
     {
-      const float e0 = expf(cums[j]), e1 = expf(cums[16 + j]);
+      const float e0 = expf((float)cums[j]), e1 = expf((float)cums[16 + j]);
 #pragma unroll
       for (int r = 0; r < 4; ++r) { Y[0][r] *= e0; Y[1][r] *= e1; }
     }
@@ -288,7 +295,8 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
     if (j0 == 0) TR(4);
     // ================= state update: S' = exp(cum_L) S + sum_i w_i x_i (outer) B_i
     if (MODE != SEG_OUT || j0 + L < t1) {
-      const float cl = cums[L - 1], el = expf(cl);
+      const double cl = cums[L - 1];
+      const float el = expf((float)cl);
       total += cl;
 #pragma unroll
       for (int t = 0; t < NT; ++t)
@@ -297,7 +305,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
 #pragma unroll
       for (int kk = 0; kk < L / 4; ++kk) {
         const int i = 4 * kk + g;
-        const float xw = Xs[i * LDX + 16 * wq + j] * (dts[i] * expf(cl - cums[i]));  // B[k = g][col p = j]
+        const float xw = Xs[i * LDX + 16 * wq + j] * (dts[i] * expf((float)(cl - cums[i])));  // B[k = g][col p = j]
         const float* brow = Bs + i * LDB + j;                                        // A[row n = j][k = g] = B[i][n]
 #pragma unroll
         for (int t = 0; t < NT; ++t) S[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(brow[16 * t], xw, S[t], 0, 0, 0);
@@ -309,7 +317,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
   }
   TR(6);
 
-  if (MODE == SEG_LOCAL && wq == 0 && lane == 0) seg.decay[((size_t)b * seg.n + blockIdx.z) * d.Hm + h] = total;
+  if (MODE == SEG_LOCAL && wq == 0 && lane == 0) seg.decay[((size_t)b * seg.n + blockIdx.z) * d.Hm + h] = (float)total;
   if (MODE == SEG_LOCAL || (MODE == SEG_WALK && a.state_out != 0)) {
     float* dp = (MODE == SEG_LOCAL ? seg_state : (a.state_out == 1 ? ly.S : ly.S_draft) + ((size_t)b * d.Hm + h) * P * N) + (16 * wq + j) * N + 4 * g;
 #pragma unroll

@@ -9,6 +9,8 @@ from paper_2605_01106_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
+from oracle.hybrid_lm import HybridLM  # noqa: E402
+from oracle.protocol import SpecDecoder  # noqa: E402
 from parity_util import run_lockstep  # noqa: E402
 
 
@@ -406,6 +408,38 @@ def test_prefill_scan_segments(B, dtype, d_state, heads, chunk):
     ctx = _ctx(B, wts, 4, chunk + 160, 3, 8, kv_page_tokens=32, prefill_chunk=chunk, kernel_flags=B.HH_KF_CANARIES)
     run_lockstep(ctx, wts, prompts, lens, 8, 3, engine="pass", chunk=64, report=_say(f"seg-{dtype}-N{d_state}-H{heads}-T{chunk}"))
     assert ctx.hh_check_canaries() == 0
+
+
+@pytest.mark.parametrize("d_state,heads,tokens", [(64, 4, 96), (128, 4, 128), (128, 4, 512), (256, 4, 320)])
+def test_prefill_scan_segments_are_as_exact_as_the_sequential_scan(B, d_state, heads, tokens):
+    """Distance of a float32 model's prefill from the float64 oracle: the scan in segments may be no further off than the
+    position-by-position kernel.  Prompts are multiples of the 32-position chunk, so that the logits come from a position
+    with a whole chunk's decays before it, and the decays are strong (log-decay sums of tens per chunk): decays taken as
+    differences of float32 sums carry the rounding of sums that large (here 1.2 to 1.6 times the sequential kernel's
+    distance for the logits, 1.9 to 3.6 times for the states).  With the sums in float64 the two forms only add the same
+    products in another order: pooled over sequences and seeds the distances agree to 10 %, and 1.2 is the bound."""
+    cfg = W.scaled_config("exact", n_layers=2, d_model=128, vocab=256, m_heads=heads, m_head_dim=64, d_state=d_state,
+                          n_q_heads=2, n_kv_heads=1, head_dim=32, d_ff=96, w_dtype=W.F32)
+    lens = [tokens] * 3
+    off = {0: [0.0, 0.0], B.HH_KF_SSM_SEQUENTIAL: [0.0, 0.0]}
+    for seed in (3, 4):
+        wts = W.make_lively_weights(cfg, seed)
+        prompts = W.make_prompts(cfg.vocab, 3, lens, seed)
+        dec = SpecDecoder(HybridLM(cfg, wts.values), tokens + 8, engine="pass", chunk=64)
+        dec.prefill([prompts[b] for b in range(3)], 2)
+        for flags, sums in off.items():
+            ctx = _ctx(B, wts, 3, tokens + 8, 1, 2, prefill_chunk=tokens, kernel_flags=flags)
+            ctx.hh_prefill(prompts, lens, 2)
+            got, ref = [ctx.hh_get_logits(2)], [np.array(dec.prefill_logits)]
+            for layer in range(cfg.n_layers):
+                got.append(ctx.hh_get_state(layer)[0])
+                ref.append(np.array([st.S[layer] for st in dec.st]))
+            for i, (g, r) in enumerate(zip(got, ref)):
+                sums[min(i, 1)] += float(((g - r) ** 2).sum() / (r ** 2).sum())
+    (logits, state), (logits_seq, state_seq) = (np.sqrt(v) for v in off.values())
+    print(f"[exact-N{d_state}-T{tokens}] logits {logits:.2e} / {logits_seq:.2e}, states {state:.2e} / {state_seq:.2e}", flush=True)
+    assert (logits, state) != (logits_seq, state_seq), "the two forms give the same bits: the segments were not taken"
+    assert logits <= 1.2 * logits_seq and state <= 1.2 * state_seq
 
 
 @pytest.mark.parametrize("head_dim,n_q,n_kv,k,n", [(80, 4, 2, 15, 500), (128, 5, 1, 0, 777), (48, 4, 4, 8, 130),
