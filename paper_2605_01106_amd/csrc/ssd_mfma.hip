@@ -211,7 +211,11 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
       const float rawdt = zx[(size_t)(j0 + min(lane, tc - 1)) * d.ldzx + d.d_inner + d.conv_dim + hd];
       const float dt = on ? ssd_softplus(rawdt + ly.dt_bias[hd]) : 0.f;
       if (on && keep_raw) ring[(size_t)((pos0 + j0 + lane) & rmask) * d.ring_w + d.conv_dim + hd] = rawdt;
-      double c = -expf(ly.a_log[hd]) * dt;             // log a_t (float32, as in the sequential kernels), summed over the positions up to t
+      float la = on ? -expf(ly.a_log[hd]) * dt : 0.f;  // log a_t, float32 as in the sequential kernels
+      // a decay below exp(-200) is zero in float32, and so is every product that holds it; bounded, its sums stay finite
+      // (a rate of infinity would make their differences NaN) and keep the bits of the positions around it
+      la = la < -200.f ? -200.f : la;
+      double c = la;                                   // summed over the positions up to t
 #pragma unroll
       for (int o = 1; o < L; o <<= 1) {
         const double up = __shfl_up(c, o, 64);

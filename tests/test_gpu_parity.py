@@ -442,6 +442,22 @@ def test_prefill_scan_segments_are_as_exact_as_the_sequential_scan(B, d_state, h
     assert logits <= 1.2 * logits_seq and state <= 1.2 * state_seq
 
 
+@pytest.mark.parametrize("form", ["segments", "walk", "sequential"])
+def test_prefill_scan_with_decays_of_zero(B, form):
+    """Decay rates beyond what float32 holds (exp(a_log) = inf: the state never outlives a step) and rates of 1e5, next to
+    an ordinary head: every form of the prefill scan gives the oracle's finite results."""
+    cfg = W.scaled_config("rates", n_layers=2, d_model=64, vocab=160, m_heads=4, m_head_dim=64, d_state=64,
+                          n_q_heads=2, n_kv_heads=1, head_dim=32, d_ff=96, w_dtype=W.F32)
+    wts = W.make_lively_weights(cfg, 12)
+    for layer in range(cfg.n_layers):
+        wts.put_vector(f"L{layer}.a_log", np.array([100.0, 12.0, 0.3, 95.0], np.float32))
+    lens = [133, 60]
+    prompts = W.make_prompts(cfg.vocab, 2, lens, 8)
+    flags = {"segments": 0, "walk": B.HH_KF_SSM_MATMUL, "sequential": B.HH_KF_SSM_SEQUENTIAL}[form]
+    ctx = _ctx(B, wts, 2, 160, 2, 8, prefill_chunk=128, kernel_flags=flags)
+    run_lockstep(ctx, wts, prompts, lens, 8, 2, engine="step", report=_say(f"rates-{form}"))
+
+
 @pytest.mark.parametrize("head_dim,n_q,n_kv,k,n", [(80, 4, 2, 15, 500), (128, 5, 1, 0, 777), (48, 4, 4, 8, 130),
                                                    (128, 10, 2, 8, 420), (16, 2, 1, 4, 33), (200, 2, 2, 7, 400)])
 def test_new_positions_in_the_attention_kernel(B, head_dim, n_q, n_kv, k, n):
