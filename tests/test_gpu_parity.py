@@ -379,24 +379,28 @@ def test_prefill_scan_matmul_form(B, dtype, d_state, chunk):
     a dropped intra-chunk term or a wrong carried state moves the logits.  The state after prefill,
     the conv window, the logits and every later round are compared with the sequential float64 oracle;
     the same run with the position-by-position kernel (HH_KF_SSM_SEQUENTIAL) gives the same tokens."""
-    cfg = W.scaled_config("ssd", n_layers=2, d_model=64, vocab=160, m_heads=2, m_head_dim=64, d_state=d_state,
+    cfg = W.scaled_config("ssd", n_layers=2, d_model=64, vocab=160, m_heads=4, m_head_dim=64, d_state=d_state,
                           n_q_heads=2, n_kv_heads=1, head_dim=32, d_ff=96, w_dtype=dtype)
     wts = W.make_lively_weights(cfg, 61)
     lens = [333, 17, 290, 97]
     prompts = W.make_prompts(cfg.vocab, 4, lens, 23)
-    # (the library takes the matmul form by itself from 128 workgroups on; HH_KF_SSM_MATMUL forces it for these 4 x 1)
+    # (the library takes the matmul form by itself from 128 workgroups on; HH_KF_SSM_MATMUL forces it for these 4 x 2.  Rows
+    # of the ring must be multiples of 16 bytes: head counts that are no multiple of 4 keep the sequential kernel)
     ctx = _ctx(B, wts, 4, 400, 3, 10, kv_page_tokens=32, prefill_chunk=chunk, kernel_flags=B.HH_KF_SSM_MATMUL)
     w = run_lockstep(ctx, wts, prompts, lens, 10, 3, engine="pass", chunk=64, report=_say(f"ssd-{dtype}-N{d_state}-T{chunk}"))
     seq = _ctx(B, wts, 4, 400, 3, 10, kv_page_tokens=32, prefill_chunk=chunk, kernel_flags=B.HH_KF_SSM_SEQUENTIAL)
     w2 = run_lockstep(seq, wts, prompts, lens, 10, 3, engine="pass", chunk=64)
     assert w["tokens"] == w2["tokens"]
+    for c in (ctx, seq):
+        c.hh_prefill(prompts, lens, 10)
+    assert not np.array_equal(ctx.hh_get_state(0)[0], seq.hh_get_state(0)[0]), "same bits: the matmul form was not taken"
 
 
-@pytest.mark.parametrize("dtype,d_state,heads,chunk", [(W.BF16, 64, 2, 96), (W.F32, 128, 2, 130), (W.BF16, 128, 32, 352),
-                                                       (W.F32, 256, 26, 200), (W.BF16, 64, 2, 95)])
+@pytest.mark.parametrize("dtype,d_state,heads,chunk", [(W.BF16, 64, 4, 96), (W.F32, 128, 4, 130), (W.BF16, 128, 32, 352),
+                                                       (W.F32, 256, 28, 200), (W.BF16, 64, 4, 95)])
 def test_prefill_scan_segments(B, dtype, d_state, heads, chunk):
-    """Long passes over few sequences take the scan in segments: one chunk of 32 positions per segment (2 heads) and
-    several (26 and 32 heads x 4 sequences), the shortest pass that takes the form (96 positions; 95 keeps the
+    """Long passes over few sequences take the scan in segments: one chunk of 32 positions per segment (4 heads) and
+    several (28 and 32 heads x 4 sequences), the shortest pass that takes the form (96 positions; 95 keeps the
     position-by-position kernel), passes that end inside a segment, sequences that end in the first, in a middle and in
     the last one or need no further pass.  Compared with the float64 oracle like the other forms, within the tolerance
     of the storage type; guard bytes behind every workspace region are checked."""
@@ -408,6 +412,11 @@ def test_prefill_scan_segments(B, dtype, d_state, heads, chunk):
     ctx = _ctx(B, wts, 4, chunk + 160, 3, 8, kv_page_tokens=32, prefill_chunk=chunk, kernel_flags=B.HH_KF_CANARIES)
     run_lockstep(ctx, wts, prompts, lens, 8, 3, engine="pass", chunk=64, report=_say(f"seg-{dtype}-N{d_state}-H{heads}-T{chunk}"))
     assert ctx.hh_check_canaries() == 0
+    seq = _ctx(B, wts, 4, chunk + 160, 3, 8, kv_page_tokens=32, prefill_chunk=chunk, kernel_flags=B.HH_KF_SSM_SEQUENTIAL)
+    for c in (ctx, seq):
+        c.hh_prefill(prompts, lens, 8)
+    same = np.array_equal(ctx.hh_get_state(0)[0], seq.hh_get_state(0)[0])
+    assert same == (chunk < 96), "the segments serve passes of 96 positions and more, and only those"
 
 
 @pytest.mark.parametrize("d_state,heads,tokens", [(64, 4, 96), (128, 4, 128), (128, 4, 512), (256, 4, 320)])
