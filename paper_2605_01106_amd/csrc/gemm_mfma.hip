@@ -513,6 +513,12 @@ static void lds_plan(int m_tiles, int steps, int n_blocks, int nf, int M, int N,
   }
 }
 
+// The plan that a product of more than 96 rows gets, for the tests that have to reach every kernel shape (host arithmetic).
+extern "C" __attribute__((visibility("default"))) void hh_many_row_plan(int rows, int K, int N, int swiglu, int* row_tiles, int* k_splits) {
+  const int steps = (K + 31) / 32, tiles = (N + 15) / 16, nf = swiglu ? 2 : 1;
+  lds_plan((rows + 15) / 16, steps, (tiles + kLdsA / nf - 1) / (kLdsA / nf), nf, rows, N, *row_tiles, *k_splits);
+}
+
 static bool lds_path(const GemvArgs& g, int m_tiles) { return (m_tiles > 6 || (g.flags & HH_KF_ROWS_LDS)) && gemm_terms(g.M) == 3; }
 
 bool gemm_hands_over_planes(const GemvArgs& g) {

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 from oracle.hybrid_lm import HybridLM  # noqa: E402
 from oracle.protocol import SpecDecoder  # noqa: E402
-from parity_util import run_lockstep  # noqa: E402
+from parity_util import assert_close, run_lockstep, tolerances  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -484,15 +484,54 @@ def test_new_positions_in_the_attention_kernel(B, head_dim, n_q, n_kv, k, n):
     assert ctx.hh_check_canaries() == 0
 
 
-@pytest.mark.parametrize("rows,d_ff", [(97, 96), (128, 4096), (170, 1024), (330, 2080), (512, 6912)])
-def test_many_row_products_by_row_block(B, rows, d_ff):
+# (sequences, tokens, d_model, d_ff) of two-layer models and the plan (row tiles per wavefront, K splits) that each product
+# of a prefill pass over all their rows gets: the input projection (in) and the attention's output (o) store, the
+# state-space output (out) and the down projection add, gate/up (up) is the SwiGLU product
+MANY_ROWS = [
+    ((1, 97, 256, 96), {"in": (2, 1), "o": (2, 1), "out": (2, 1), "up": (2, 1), "down": (2, 1)}),
+    ((1, 129, 512, 520), {"in": (2, 2), "o": (2, 1), "out": (2, 1), "up": (2, 2), "down": (2, 2)}),
+    ((1, 400, 128, 5120), {"in": (2, 1), "o": (2, 1), "out": (2, 1), "up": (3, 1), "down": (2, 20)}),
+    ((1, 400, 128, 6912), {"in": (2, 1), "o": (2, 1), "out": (2, 1), "up": (4, 1), "down": (2, 27)}),
+    ((2, 801, 128, 2560), {"in": (2, 1), "o": (2, 1), "out": (2, 1), "up": (5, 1), "down": (2, 9)}),
+    ((3, 897, 128, 4104), {"in": (2, 1), "o": (2, 1), "out": (2, 1), "up": (6, 1), "down": (3, 8)}),
+    ((3, 897, 2560, 96), {"in": (3, 2), "o": (4, 1), "out": (4, 1), "up": (2, 5), "down": (4, 1)}),
+    ((4, 801, 2560, 96), {"in": (5, 3), "o": (5, 1), "out": (5, 1), "up": (2, 5), "down": (5, 1)}),
+    ((4, 1009, 2560, 96), {"in": (2, 1), "o": (6, 1), "out": (6, 1), "up": (2, 4), "down": (6, 1)}),
+]
+
+
+def _many_rows_model(d_model, d_ff):
+    # two layers: the keys, values and state of the second one depend on every row of every product of the first
+    return W.scaled_config("rows", n_layers=2, d_model=d_model, vocab=300, m_heads=4, m_head_dim=64, d_state=64,
+                           n_q_heads=2, n_kv_heads=1, head_dim=32, d_ff=d_ff, w_dtype=W.BF16)
+
+
+@pytest.mark.parametrize("shape,plans", MANY_ROWS)
+def test_many_row_products_by_row_block(B, shape, plans):
     """The many-row products choose 64 to 192 activation rows per workgroup and a K split by a cost model: prefill passes
-    of 97 to 512 rows (row counts that leave the last block of 64, 96, 128, 160 or 192 rows nearly empty) against widths
-    that take one and several rounds of workgroups, with and without a K split and the hand-over of the SwiGLU result."""
-    cfg = W.scaled_config("rows", n_layers=1, d_model=256, vocab=300, m_heads=4, m_head_dim=64, d_state=64,
-                          n_q_heads=4, n_kv_heads=2, head_dim=64, d_ff=d_ff, w_dtype=W.BF16)
+    of 97 to 4036 rows that reach every block height for the store, the residual add and SwiGLU, with a last block that is
+    nearly empty, with and without a K split, with the SwiGLU result handed to the down projection and (d_ff no multiple of
+    32, or a K split) without.  tests/test_many_row_plan.py checks that the plans are these and that they cover the
+    kernel's shapes.  The second layer's keys and values attest every row of every product of the first one.  They may be
+    off by their own 16-bit rounding (2^-9) and by a first-layer key that took the neighbouring 16-bit value: that moves a
+    score by 2^-8 q k / sqrt(32), up to 0.03 where |q| and |k| are 6 (1.5 by design, four times that at the tail), and the
+    attention's part of a row by as much - 3 % of the row's norm.  A row that misses a product or one of its K splits is
+    off by 10 % and more."""
+    sequences, tokens, d_model, d_ff = shape
+    cfg = _many_rows_model(d_model, d_ff)
     wts = W.make_lively_weights(cfg, 5)
-    lens = [rows]
-    prompts = W.make_prompts(cfg.vocab, 1, lens, 9)
-    ctx = _ctx(B, wts, 1, rows + 40, 2, 6, prefill_chunk=rows)
-    run_lockstep(ctx, wts, prompts, lens, 6, 2, engine="pass", chunk=64, report=_say(f"rows-{rows}-{d_ff}"))
+    lens = [tokens] * sequences
+    prompts = W.make_prompts(cfg.vocab, sequences, lens, 9)
+    dec = SpecDecoder(HybridLM(cfg, wts.values), tokens + 8, engine="pass", chunk=64)
+    dec.prefill([prompts[b] for b in range(sequences)], 2)
+    ctx = _ctx(B, wts, sequences, tokens + 8, 1, 2, prefill_chunk=tokens, kernel_flags=B.HH_KF_CANARIES)
+    ctx.hh_prefill(prompts, lens, 2)
+    assert_close("logits", ctx.hh_get_logits(2), np.array(dec.prefill_logits), *tolerances(cfg.w_dtype))
+    worst = 0.0
+    for layer in range(cfg.n_layers):
+        for b in range(sequences):
+            for got, ref in zip(ctx.hh_get_kv(layer, b, tokens), (dec.st[b].K[layer][:tokens], dec.st[b].V[layer][:tokens])):
+                off = np.linalg.norm((got - ref).reshape(tokens, -1), axis=1) / np.linalg.norm(ref.reshape(tokens, -1), axis=1)
+                worst = max(worst, float(off.max()))
+    print(f"[rows-{shape}] worst key or value row off by {worst:.2e}", flush=True)
+    assert worst < 0.03 and ctx.hh_check_canaries() == 0
