@@ -485,8 +485,8 @@ static hipError_t gemm_dispatch_m(const GemmArgs& a, int mtw, int units, hipStre
 // Row tiles per wavefront (workgroup = 256 weight rows x 32 MTW activation rows) and K split of the
 // LDS-staged kernel, by a cost model in microseconds: a workgroup step takes its MFMAs (384 MTW cycles per
 // SIMD) and about 720 cycles of barrier, first LDS reads and copy issue (measured: 76 % matrix-pipe use with
-// 6 row tiles, 62 % with 3), or its copies ((16 + 6 MTW) KB at 28 bytes per cycle and compute unit) where
-// those are longer; the workgroups run in rounds of one per compute unit; a K split adds the reduction kernel
+// 6 row tiles, 62 % with 3; its copies, (16 + 6 MTW) KB at 28 bytes per cycle and compute unit, are shorter at
+// every MTW); the workgroups run in rounds of one per compute unit; a K split adds the reduction kernel
 // and ks * M * N floats of partial products written and read again (about 4 TB/s).  Up to 96 rows one
 // workgroup holds all rows; many rows choose among 64 to 192 rows, so that the last round is not mostly empty:
 // 512 rows of the gate/up product at the 3B shape are 162 workgroups of 192 rows (120 us) or 216 of 128 (88 us).
@@ -498,8 +498,7 @@ static void lds_plan(int m_tiles, int steps, int n_blocks, int nf, int M, int N,
   const int mtw_lo = m_tiles > 6 ? 2 : (m_tiles + 1) / 2, mtw_hi = m_tiles > 6 ? 6 : (m_tiles + 1) / 2;
   for (int cand = mtw_lo; cand <= mtw_hi; ++cand) {
     const int m_blocks = (m_tiles + lds_row_tiles(cand) - 1) / lds_row_tiles(cand);
-    const double mfma = 384.0 * cand + 720.0, copy = (16.0 + 6.0 * cand) * 1024.0 / 28.0;
-    const double step_us = (mfma > copy ? mfma : copy) / 2400.0;
+    const double step_us = (384.0 * cand + 720.0) / 2400.0;
     const int min_steps = m_tiles > 6 ? 8 : 3;
     for (int k = 1; k <= 32; ++k) {
       if (k > 1 && (steps / k < min_steps || (size_t)k * nf * M * N > gemm_partial_elems())) break;
