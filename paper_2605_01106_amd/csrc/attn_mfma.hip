@@ -235,16 +235,15 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
   {
     const float scale = 1.4426950408889634f / sqrtf((float)Dh);   // scores in base-2 units: softmax through 2^x
     const float2* rope = reinterpret_cast<const float2*>(a.rope);
-    constexpr int stagers = NT;
     if (al4 && (half & 3) == 0) {
-      // items of 4 dimension pairs, four per thread and pass, their loads issued together: up to 768 items (32 rows of
-      // head dimension 128 are 512) take one round trip to memory
+      // items of 4 dimension pairs, four per thread and pass, their loads issued together: up to 4 NT items (1024 with four
+      // wavefronts; 32 rows of head dimension 128 are 512) take one round trip to memory
       const int h4 = half >> 2, items = R * h4;
-      for (int it0 = tid; it0 < items && tid < stagers; it0 += 4 * stagers) {
+      for (int it0 = tid; it0 < items; it0 += 4 * NT) {
         float4 x0[4], x1[4], c0[4], c1[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int it = it0 + u * stagers, r = it / h4, i = 4 * (it - r * h4), rr = row0 + r;
+          const int it = it0 + u * NT, r = it / h4, i = 4 * (it - r * h4), rr = row0 + r;
           x0[u] = x1[u] = c0[u] = c1[u] = make_float4(0.f, 0.f, 0.f, 0.f);
           if (it < items && rr < row_lim) {
             const int j = rr / G;
@@ -256,7 +255,7 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int it = it0 + u * stagers, r = it / h4, i = 4 * (it - r * h4);
+          const int it = it0 + u * NT, r = it / h4, i = 4 * (it - r * h4);
           if (it >= items) break;
           const float lo[4] = {(x0[u].x * c0[u].x - x1[u].x * c0[u].y) * scale, (x0[u].y * c0[u].z - x1[u].y * c0[u].w) * scale,
                                (x0[u].z * c1[u].x - x1[u].z * c1[u].y) * scale, (x0[u].w * c1[u].z - x1[u].w * c1[u].w) * scale};
@@ -276,12 +275,12 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
       }
     } else {
       // four items per thread and pass, their loads issued together
-      for (int it0 = tid; it0 < R * half && tid < stagers; it0 += 4 * stagers) {
+      for (int it0 = tid; it0 < R * half; it0 += 4 * NT) {
         float x0[4], x1[4];
         float2 c[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int it = it0 + u * stagers, r = it / half, i = it - r * half, rr = row0 + r;
+          const int it = it0 + u * NT, r = it / half, i = it - r * half, rr = row0 + r;
           x0[u] = 0.f; x1[u] = 0.f; c[u] = make_float2(0.f, 0.f);
           if (it < R * half && rr < row_lim) {
             const int j = rr / G;
@@ -292,7 +291,7 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int it = it0 + u * stagers, r = it / half, i = it - r * half;
+          const int it = it0 + u * NT, r = it / half, i = it - r * half;
           if (it >= R * half) break;
           const float lo = (x0[u] * c[u].x - x1[u] * c[u].y) * scale, hi = (x1[u] * c[u].x + x0[u] * c[u].y) * scale;
           uint32_t l0, l1, l2, h0, h1, h2;
@@ -306,7 +305,7 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
     }
     if (Dh < Dhp) {
       const int padw = Dhp - Dh;
-      for (int it = tid; it < R * padw * 3 && tid < stagers; it += stagers) {
+      for (int it = tid; it < R * padw * 3; it += NT) {
         const int r = it / (padw * 3), rem = it - r * padw * 3, term = rem / padw, i = rem - term * padw;
         qT[(size_t)r * QS + term * Dhp + Dh + i] = 0;
       }
@@ -413,7 +412,7 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
     }
   };
 
-  // ---- the new positions (FUSE): scored as one more step by the wavefront that built their operands
+  // ---- the new positions (FUSE): scored as one more step by the last wavefront
   if (FUSE && new_wave) {
     Frag nA[KS], nB[KS], nV[NDB];
     const uint4 zero = make_uint4(0, 0, 0, 0);

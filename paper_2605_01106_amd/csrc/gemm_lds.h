@@ -8,10 +8,10 @@
 // read back with one 16-byte LDS read per lane, without bank conflicts and without any transpose.
 //
 // A workgroup of eight wavefronts owns 16 weight fragments (16 strips of 16 weight rows, or 8
-// gate/up strip pairs) x 12 row tiles (256 x 192 outputs) and a range of K.  Per step of 32
-// columns it brings 16 + 36 fragments (52 KB) into LDS once; wavefront (wn, wm) multiplies its
-// 4 weight fragments with its 6 row tiles (72 MFMAs per step, 96 accumulator registers).  A
-// compute unit takes in well under 30 bytes per cycle this way (the register-tiled kernel, where
+// gate/up strip pairs) x 2 MTW row tiles (at most 12: 256 x 192 outputs) and a range of K.  Per step
+// of 32 columns it brings 16 + 6 MTW fragments (at most 52 KB) into LDS once; wavefront (wn, wm)
+// multiplies its 4 weight fragments with its MTW row tiles (12 MTW MFMAs per step, 16 MTW accumulator
+// registers).  With 12 row tiles a compute unit takes in well under 30 bytes per cycle this way (the register-tiled kernel, where
 // every wavefront loads its own operands, asks for 85 and is bound by exactly that).  The copies
 // are LDS-direct loads (global_load_lds_dwordx4: lane l's 16 bytes land at the wavefront's LDS
 // base + 16 l, no registers in between) into three to six stages of LDS (what fits 160 KB): the

@@ -6,8 +6,8 @@
 //   * a wavefront owns R output rows and up to 2048 of their columns and issues all of its
 //     16-byte weight loads at once, BEFORE it touches the activations; rows longer than
 //     that are split between the wavefronts of a workgroup and added through LDS;
-//   * many small workgroups (up to 8 wavefronts resident per SIMD) rather than deep software
-//     pipelines: measured on MI355X this streams at 5.4-5.8 TB/s;
+//   * many small workgroups (2 to 8 wavefronts resident per SIMD, fewer the longer the rows, whose
+//     activations are requested in one go) rather than deep software pipelines: measured on MI355X this streams at 5.4-5.8 TB/s;
 //   * the activation rows are staged once per workgroup in LDS in float32 and never rounded:
 //     a bf16 weight times a float32 activation, accumulated in float32;
 //   * RMSNorm is fused as a prologue in one pass: LDS holds x[k] * w[k], and the scalar

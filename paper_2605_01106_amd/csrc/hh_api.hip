@@ -1194,7 +1194,8 @@ hh_status hh_time_kind(hh_ctx* x, int32_t phase, int32_t kind, int32_t k, int32_
   hipEvent_t e0, e1;
   HH_HIP(hipEventCreate(&e0));
   HH_HIP(hipEventCreate(&e1));
-  // positions and tokens of an ordinary pass, so that every kernel sees valid inputs
+  // positions and tokens of an ordinary pass, so that every kernel sees valid inputs (the argmax keys are cleared here, once:
+  // every repetition of a many-row LM head raises them to the same values)
   HH_HIP(launch_begin_pass(pass_args(x, full ? PASS_VERIFY : PASS_DRAFT, T, 0), B, s));
   const bool prof = x->prof_on;
   x->prof_on = true;            // serial launches on one stream (no side stream), but no event pairs:

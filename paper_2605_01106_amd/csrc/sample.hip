@@ -115,9 +115,9 @@ __device__ void row_stats(const float* __restrict__ row, int V, float inv_t, flo
 // ---- rows held in registers.  A row of up to 65536 entries that starts on a 16-byte boundary and whose length is a
 // multiple of 4 is read once, with all loads of a thread in flight together, where the loops above and below read it two
 // or three times, a dependent load per pass of a loop.  Same sums in the same order, so the same bits.  Draw from 64 rows
-// of 32768 entries 16.4 -> 12.2 us, of 65536 28.4 -> 21.0; acceptance of 64 sequences at k = 8 over 32768 entries 70 -> 59 us,
-// over 65536 130 -> 115 (the statistics 87 -> 80 us for 285 MB; the draw with the residual keeps the loops there: 64
-// registers of masses spill behind the two exponentials per entry, 121 us).
+// of 1000 entries 5.7 -> 5.0 us, of 4096 6.4 -> 5.5, of 32768 16.4 -> 12.2, of 65536 28.4 -> 21.0; acceptance of 64 sequences
+// at k = 8 over 4096 entries 21 -> 14 us, over 32768 70 -> 59, over 65536 130 -> 115 (the statistics 87 -> 80 us for 285 MB;
+// the draw with the residual keeps the loops there: 64 registers of masses spill behind the two exponentials per entry, 121 us).
 constexpr int kRegGroups = 16;   // groups of 4 entries per thread at most: 64 registers, one workgroup of 16 wavefronts per compute unit
 __host__ __device__ constexpr int reg_vocab(int groups) { return groups * kDrawThreads * 4; }
 

@@ -106,7 +106,7 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
     }
   };
   // ---- stage this wavefront's slice of the activations: norm weight, 3-term split, squares.
-  // Items (row, group of 4 columns) are spread over the lanes, 4 loads in flight per lane; the
+  // Items (row, group of 4 columns) are spread over the lanes, SU loads in flight per lane; the
   // first batch is requested before the weights so that it does not wait behind them.
   {
     const bool normed = a.norm_w != nullptr;

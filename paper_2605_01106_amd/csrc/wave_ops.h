@@ -8,8 +8,12 @@ namespace hh {
 
 // 16 bytes of a matrix that one workgroup of a launch reads, once: a streaming load, so that the weights of a pass (0.9 GB
 // and more) do not push out of the caches what the next small launches start with - activations, launch arguments, code.
-// Decode passes of one sequence, two rounds: 0.5B shape, k = 2, 7.18 -> 6.69 ms; 3B shape, k = 4, 10.08 -> 9.59 ms.  Not for
-// float32 weights: models of that size stay in the cache from pass to pass (2 % slower).
+// Decode passes of one sequence, two rounds: 0.5B shape, k = 2, 7.18 -> 6.69 ms; 3B shape, k = 4, 10.08 -> 9.59 ms.  Models
+// that would fit the 256 MB cache gain as well (one sequence, 1 to 12 blocks of the 0.5B shape, k = 2: 2.5 to 7 %; one and two
+// blocks of the 3B shape, k = 4: 2 and 6 %; four sequences: -1 to 1 %), so the rule looks at the type alone.  It loses where
+// drafts of less than the cache alternate with a verification that loads plainly (two blocks of the 3B shape, the second one
+// left out of the draft, k = 8: 2910 against 2838 us with one sequence, 3631 against 3567 with four).  Not for float32
+// weights: models of that size stay in the cache from pass to pass (2 % slower).
 __device__ __forceinline__ uint4 load_once16(const void* p) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   const u32x4 v = __builtin_nontemporal_load(static_cast<const u32x4*>(p));
