@@ -227,15 +227,23 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
       }
     }
   };
-  // the first two items of a thread travel while the queries are staged
+  // the first items of a thread travel while the queries are staged: two, or one where 16 positions have no more (head
+  // dimensions up to 32: 192 items; a second one is 17 registers and a division for nothing)
+  constexpr bool two_items = KS > 1;
   NewItem new0, new1;
-  if (FUSE && has_new) { new0 = new_load(tid); new1 = new_load(tid + NT); }
+  if (FUSE && has_new) {
+    new0 = new_load(tid);
+    if (two_items) new1 = new_load(tid + NT);
+  }
 
   // ---- query rows: rotate to their positions, scale, split into 3 bf16 terms, stage in LDS
   {
     const float scale = 1.4426950408889634f / sqrtf((float)Dh);   // scores in base-2 units: softmax through 2^x
     const float2* rope = reinterpret_cast<const float2*>(a.rope);
-    if (al4 && (half & 3) == 0) {
+    // (up to head dimension 32 the single elements below keep more threads busy, in one round trip as well: with these two
+    // rules the launch is back at its time before the items of 4, e.g. 64 sequences x 1 position over 1000 keys of head
+    // dimension 32 12.5 -> 11.3 us, 16 x 3 over 300 keys of head dimension 16 8.8 -> 7.8; runs differ by up to 5 %)
+    if (KS > 1 && al4 && (half & 3) == 0) {
       // items of 4 dimension pairs, four per thread and pass, their loads issued together: up to 4 NT items (1024 with four
       // wavefronts; 32 rows of head dimension 128 are 512) take one round trip to memory
       const int h4 = half >> 2, items = R * h4;
@@ -313,8 +321,10 @@ __global__ __launch_bounds__(64 * NW) void attn_mfma_kernel(const Dims d, const 
   }
   if (FUSE && has_new) {
     new_store(tid, new0);
-    new_store(tid + NT, new1);
-    for (int it = tid + 2 * NT; it < kv_items; it += NT) new_store(it, new_load(it));
+    if (two_items) {
+      new_store(tid + NT, new1);
+      for (int it = tid + 2 * NT; it < kv_items; it += NT) new_store(it, new_load(it));
+    }
     // values of positions that do not exist meet zero probabilities: they must not be NaN
     for (int it = tid; it < Dh * (16 - nt); it += NT) vN[(it / (16 - nt)) * VNS + nt + it % (16 - nt)] = 0;
   }

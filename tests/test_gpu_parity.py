@@ -467,20 +467,22 @@ def test_prefill_scan_with_decays_of_zero(B, form):
     run_lockstep(ctx, wts, prompts, lens, 8, 2, engine="step", report=_say(f"rates-{form}"))
 
 
-@pytest.mark.parametrize("head_dim,n_q,n_kv,k,n", [(80, 4, 2, 15, 500), (128, 5, 1, 0, 777), (48, 4, 4, 8, 130),
+@pytest.mark.parametrize("head_dim,n_q,n_kv,k,n", [(80, 4, 2, 15, 500), (128, 5, 1, 0, 777), (48, 4, 4, 8, 130), (32, 4, 2, 15, 300),
                                                    (128, 10, 2, 8, 420), (16, 2, 1, 4, 33), (200, 2, 2, 7, 400)])
 def test_new_positions_in_the_attention_kernel(B, head_dim, n_q, n_kv, k, n):
     """The verification attention rotates, rounds and appends the new keys and values with all threads of the last
-    slice and scores them from LDS: one to sixteen new positions (every fill of the two 8-position operand groups), head
-    dimensions that fill the 32-wide operands (128), leave half of the last one empty (80, 48, 16) or keep the separate
-    append (200: not a multiple of 16), positions that cross a page, one key slice and - at head dimension 128 from 13 key
-    steps on - several, ragged prompts."""
+    slice and scores them from LDS: one to sixteen new positions (draft lengths from k = 15 down to 0, round by round: every
+    fill of the two 8-position operand groups), head dimensions that fill the 32-wide operands (128, 32: one item per
+    thread there), leave half of the last one empty (80, 48, 16) or keep the separate append (200: not a multiple of 16),
+    positions that cross a page, one key slice and - at head dimension 128 from 13 key steps on - several, ragged prompts."""
     cfg = _thin("thin-new", head_dim, n_q, n_kv)
     wts = W.make_lively_weights(cfg, 47)
     lens = [n, n - 13, n // 2 + 1]
     prompts = W.make_prompts(cfg.vocab, 3, lens, 31)
     ctx = _ctx(B, wts, 3, n + 2 * k + 60, k, 2 * k + 12, kv_page_tokens=32, prefill_chunk=128, kernel_flags=B.HH_KF_CANARIES)
-    run_lockstep(ctx, wts, prompts, lens, 2 * k + 12, k, engine="pass", chunk=64, report=_say(f"new-Dh{head_dim}-k{k}"))
+    worst = run_lockstep(ctx, wts, prompts, lens, 2 * k + 12, list(range(k, -1, -1)) if k == 15 else k, engine="pass", chunk=64,
+                         report=_say(f"new-Dh{head_dim}-k{k}"))
+    assert k < 15 or worst["rounds"] >= 16
     assert ctx.hh_check_canaries() == 0
 
 
