@@ -104,10 +104,12 @@ __global__ void accept_kernel(const CommitArgs a) {
     while (n < a.k && d[n] == g[n]) ++n;
   }
   int c = a.committed[b];
-  int* out = a.out_tok + (size_t)b * a.out_stride;
+  int* row = a.out_tok + (size_t)b * a.out_stride;    // the committed count, then the tokens
+  int* out = row + 1;
   for (int i = 0; i < n && c < a.G; ++i) out[c++] = d[i];
   if (c < a.G) out[c++] = g[n];
   a.committed[b] = c;
+  row[0] = c;
   a.pending[b] = g[n];
   a.last_n[b] = n;
   a.n_acc[b] = n;
@@ -153,13 +155,14 @@ hipError_t launch_prefill_tail(const float* h, int T, int D, const int* n_tok, c
   return hipGetLastError();
 }
 
-// First generated token: pending, first entry of the output, committed = 1
+// First generated token: pending, first entry of the output (behind its count), committed = 1
 __global__ void prefill_finish_kernel(const int* first_tok, int* pending, int* out_tok, int out_stride, int* committed,
                                       int* last_n, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
   pending[b] = first_tok[b];
-  out_tok[(size_t)b * out_stride] = first_tok[b];
+  out_tok[(size_t)b * out_stride] = 1;
+  out_tok[(size_t)b * out_stride + 1] = first_tok[b];
   committed[b] = 1;
   last_n[b] = 0;
 }

@@ -167,3 +167,23 @@ def test_nothing_is_written_outside_the_workspace(B, strict):
     plain = B.Context(wts, 5, 160, 4, 30)
     with pytest.raises(B.HHError):
         plain.hh_check_canaries()
+
+
+def test_read_backs_below_the_capacities(B):
+    """One copy brings both arrays of a round (and the three of the lengths, and a sequence's count with its tokens), laid out
+    for the capacities of the context: batch, draft length and budget below them, against the oracle, round by round, and a
+    token buffer shorter than what was committed."""
+    import ctypes as C
+
+    from parity_util import run_lockstep
+    cfg, wts = _model()
+    lens = [21, 9]
+    prompts = W.make_prompts(cfg.vocab, 2, lens, 4)
+    ctx = B.Context(wts, 5, 128, 6, 40, prefill_chunk=32)
+    w = run_lockstep(ctx, wts, prompts, lens, 11, [2, 0, 6, 3], engine="pass")
+    assert w["rounds"] >= 2
+    for b in range(2):
+        for cap in (0, 1, 5, 11, 64):
+            out, n = (C.c_int32 * 64)(*[-7] * 64), C.c_int32(-1)
+            assert B.lib.hh_get_tokens(ctx.ctx, b, out, cap, C.byref(n), None) == B.HH_OK
+            assert n.value == min(cap, 11) and list(out[:n.value]) == w["tokens"][b][:cap] and set(out[n.value:]) <= {-7}
