@@ -371,6 +371,11 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
       HH_HIP(hipEventRecord(x->fork_ev[l], s));
       HH_HIP(hipStreamWaitEvent(sa, x->fork_ev[l], 0));
     }
+    SsmArgs scan{};   // conv + selective scan -> y * silu(z)
+    scan.layers = nullptr; scan.one = w; scan.layer0 = 0; scan.n_layers_z = 1;
+    scan.zx = x->zx; scan.g = x->g; scan.pos0 = x->pos0; scan.n_tok = n_tok; scan.T = T; scan.B = B;
+    scan.state_in = state_in; scan.state_out = state_out; scan.write_ring = 1; scan.seg_scratch = x->seg_scratch;
+    bool scanned = false;
     if (full) {
       AttnArgs a{};
       a.kpool = w.kpool; a.vpool = w.vpool; a.qkv = x->qkv; a.o = x->o; a.pos0 = x->pos0; a.n_tok = n_tok;
@@ -385,17 +390,15 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
         HH_HIP(product(x, b, sa, true));
         HH_HIP(hipEventRecord(x->join_ev[l], sa));
       } else {
-        HH_LAUNCH(HH_K_ATTN, launch_attention(d, a, s));
+        // (timed kind by kind the branches are launched one by one)
+        hipError_t e = hipSuccess;
+        scanned = !x->prof_on && launch_branches(d, a, scan, s, &e);
+        HH_HIP(e);
+        if (!scanned) HH_LAUNCH(HH_K_ATTN, launch_attention(d, a, s));
         HH_LAUNCH(HH_K_O_PROJ, product(x, b, s));
       }
     }
-    {  // conv + selective scan -> y * silu(z)
-      SsmArgs a{};
-      a.layers = nullptr; a.one = w; a.layer0 = 0; a.n_layers_z = 1;
-      a.zx = x->zx; a.g = x->g; a.pos0 = x->pos0; a.n_tok = n_tok; a.T = T; a.B = B;
-      a.state_in = state_in; a.state_out = state_out; a.write_ring = 1; a.seg_scratch = x->seg_scratch;
-      HH_LAUNCH(HH_K_SSM, launch_ssm(d, a, s));
-    }
+    if (!scanned) HH_LAUNCH(HH_K_SSM, launch_ssm(d, scan, s));
     {  // h += W_out * gated_norm(g)
       GemvArgs a{};
       a.X = x->g; a.ldx = d.d_inner; a.M = M; a.K = d.d_inner; a.norm_w = w.gnorm; a.eps = d.eps; a.epi = EPI_ADD; a.bf16 = d.bf16; a.flags = d.flags;
@@ -512,7 +515,10 @@ hh_status run_graphed(hh_ctx* x, long long key, hipStream_t s, F enqueue) {
 int pick_splits(const hh_cfg& c, const Dims& d, int B, int T, int len_upper) {
   const int cap = c.attn_max_splits > 0 ? c.attn_max_splits : 16;
   const int target = c.attn_target_blocks > 0 ? c.attn_target_blocks : 256;   // one workgroup per compute unit: measured best at every workload
-  const int single = c.attn_single_slice_steps == 0 ? (d.Dh > 64 ? 12 : 28) : c.attn_single_slice_steps;   // -1: never a single slice by this rule
+  // (beside a scan of several rounds of workgroups in the same launch the longer wavefronts of a single slice cost nothing:
+  // 24 sequences of up to 777 keys, four greedy steps 1913 -> 1853 us; 16 of 400 keys 2525 -> 2502)
+  const bool hidden = c.overlap_mode != 3 && branches_fit(d, B, T) && branches_scan_blocks(d, B, T) >= 1024;
+  const int single = c.attn_single_slice_steps == 0 ? (d.Dh > 64 && !hidden ? 12 : 28) : c.attn_single_slice_steps;   // -1: never a single slice by this rule
   int s;
   if (attention_uses_mfma(d)) {
     const int blocks = attention_mfma_row_chunks(d, T) * d.Hkv * B;

@@ -106,6 +106,11 @@ struct SsmArgs {
   float* seg_scratch;        // ssd_segment_elems() floats for the segmented form of long passes over few sequences (nullptr: not available)
 };
 hipError_t launch_ssm(const Dims& d, const SsmArgs& a, hipStream_t s);
+// the kernel for up to 9 positions on aligned shapes: whether it takes the pass, its position count (1, 3, 5, 9), and
+// whether 16 lanes share a row (else 8)
+bool ssm_small_fits(const Dims& d, const SsmArgs& a);
+int ssm_small_tmax(int T);
+bool ssm_small_wide(const Dims& d, const SsmArgs& a);
 // matmul-form kernel for passes with many positions (ssd_mfma.hip); true if it took the pass
 size_t ssd_segment_elems(const Dims& d);
 bool launch_ssd_mfma(const Dims& d, const SsmArgs& a, hipStream_t s, hipError_t* err);
@@ -128,6 +133,16 @@ int attention_mfma_row_chunks(const Dims& d, int T);
 bool attention_mfma_fuses_append(const Dims& d, int T);
 // bf16 cache, new keys already appended: the matrix-core kernel alone
 hipError_t launch_attention_mfma(const Dims& d, const AttnArgs& a, hipStream_t s);
+bool attention_mfma_accepts(const Dims& d, const AttnArgs& a);
+int attention_mfma_row_tiles(const Dims& d, int T);
+bool attention_mfma_two_kernels(const Dims& d, const AttnArgs& a);
+hipError_t launch_attention_merge(const Dims& d, const AttnArgs& a, hipStream_t s);
+
+// ---- both branches of a block in one launch (branches.hip): attention and scan of a pass of few positions.  True if it took
+// them (*err: its status); false: nothing was launched.
+bool branches_fit(const Dims& d, int B, int T);
+int branches_scan_blocks(const Dims& d, int B, int T);   // workgroups of the scan there
+bool launch_branches(const Dims& d, const AttnArgs& at, const SsmArgs& ss, hipStream_t s, hipError_t* err);
 
 // ---- small kernels
 // first launch of a pass: tokens, embedding, positions, cleared argmax keys (see begin_pass_kernel)

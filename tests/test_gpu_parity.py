@@ -486,6 +486,43 @@ def test_new_positions_in_the_attention_kernel(B, head_dim, n_q, n_kv, k, n):
     assert ctx.hh_check_canaries() == 0
 
 
+@pytest.mark.parametrize("head_dim,n_q,n_kv,d_state,heads,batch,k", [
+    (64, 4, 2, 128, 4, 1, 2), (128, 5, 1, 256, 4, 2, 4), (64, 4, 1, 128, 32, 4, 0), (96, 5, 1, 256, 32, 4, 8),
+    (48, 4, 2, 256, 4, 3, 8), (128, 6, 2, 128, 4, 3, 1), (64, 5, 1, 256, 4, 2, 8)])
+def test_both_branches_in_one_launch(B, head_dim, n_q, n_kv, d_state, heads, batch, k):
+    """A pass of few positions runs attention and scan in one launch: against the oracle, and bit for bit against the two
+    kernels on streams of their own, for one to nine positions, one to three row tiles, both operand widths, both lane counts
+    per state row (16, and 8 with 32 heads and four sequences), one and several key slices, a page boundary crossed."""
+    cfg = W.scaled_config("pair", n_layers=2, d_model=64, vocab=160, m_heads=heads, m_head_dim=64, d_state=d_state,
+                          n_q_heads=n_q, n_kv_heads=n_kv, head_dim=head_dim, d_ff=96, w_dtype=W.BF16)
+    wts = W.make_lively_weights(cfg, 23)
+    lens = [150 - 31 * b for b in range(batch)]
+    prompts = W.make_prompts(cfg.vocab, batch, lens, 19)
+    ks = [k, max(k - 1, 0), max(k - 3, 0)]
+    G = 12
+    run_lockstep(_ctx(B, wts, batch, 256, k, G, kernel_flags=B.HH_KF_CANARIES), wts, prompts, lens, G, ks, engine="pass",
+                 chunk=64, report=_say(f"pair-{head_dim}-{d_state}-k{k}"))
+    for splits in (1, 3):
+        seen = []
+        for overlap_mode in (1, 3):
+            ctx = _ctx(B, wts, batch, 256, k, G, overlap_mode=overlap_mode, attn_max_splits=splits, attn_single_slice_steps=-1,
+                       kernel_flags=B.HH_KF_CANARIES)
+            ctx.hh_prefill(prompts, lens, G)
+            got = []
+            for kk in ks:
+                ctx.hh_draft(kk)
+                ctx.hh_verify()
+                got.append(ctx.hh_get_logits(1))
+                ctx.hh_commit()
+            for layer in range(cfg.n_layers):
+                got += list(ctx.hh_get_state(layer))
+                for b in range(batch):
+                    got += list(ctx.hh_get_kv(layer, b, ctx.hh_get_lengths()[0][b]))
+            assert ctx.hh_check_canaries() == 0
+            seen.append([a.tobytes() for a in got])
+        assert seen[0] == seen[1]
+
+
 # (sequences, tokens, d_model, d_ff) of two-layer models and the plan (row tiles per wavefront, K splits) that each product
 # of a prefill pass over all their rows gets: the input projection (in) and the attention's output (o) store, the
 # state-space output (out) and the down projection add, gate/up (up) is the SwiGLU product
