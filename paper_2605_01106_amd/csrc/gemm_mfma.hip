@@ -319,8 +319,8 @@ __global__ __launch_bounds__(256, 2) void gemm_tiled_kernel(const GemmArgs a) {
 // workgroup stays in one row.  Splits that do not exist are not loaded, and both matrices of a SwiGLU product are one round
 // trip: per pass of 16 sequences at the 0.5B shape (13 reductions per layer and round) 19.93 -> 19.5 ms.
 // ARGMAX (EPI_STORE): it raises the row's argmax key by one atomic maximum.
-template <int EPI, bool VEC, bool ARGMAX = false>
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmArgs a) {
+template <int EPI, bool VEC, bool ARGMAX>
+__device__ __forceinline__ void gemm_reduce_body(const GemmArgs& a) {
   constexpr int NF = EPI == EPI_SWIGLU ? 2 : 1;
   constexpr int W = VEC ? 4 : 1;
   const size_t total = (size_t)a.M * a.N;
@@ -413,6 +413,18 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmArgs a) {
       if (best != 0ull) atomicMax(a.row_best + blockIdx.y, best);
     }
   }
+}
+
+template <int EPI, bool VEC, bool ARGMAX = false>
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmArgs a) {
+  gemm_reduce_body<EPI, VEC, ARGMAX>(a);
+}
+
+// the reductions of two products of the same shape in one launch: blockIdx.z = 0 adds a onto its output, 1 stores b
+template <bool VEC>
+__global__ __launch_bounds__(256) void gemm_reduce_pair_kernel(const GemmArgs a, const GemmArgs b) {
+  if (blockIdx.z == 0) gemm_reduce_body<EPI_ADD, VEC, false>(a);
+  else gemm_reduce_body<EPI_STORE, VEC, false>(b);
 }
 
 template <int EPI>
@@ -645,6 +657,23 @@ hipError_t launch_gemm_reduce(int epi, float* partial, int ksplit, int M, int N,
     case EPI_SWIGLU: return reduce_launch<EPI_SWIGLU>(a, s);
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemm_reduce_pair(const ReduceJob& ja, const ReduceJob& jb, int M, int N, hipStream_t s) {
+  GemmArgs g[2]{};
+  const ReduceJob* jobs[2] = {&ja, &jb};
+  for (int i = 0; i < 2; ++i) {
+    const ReduceJob& j = *jobs[i];
+    if (j.ssq != nullptr && M > j.ssq_ld) return hipErrorInvalidValue;
+    g[i].partial = j.partial; g[i].ksplit = j.ksplit; g[i].M = M; g[i].N = N; g[i].Y = j.Y; g[i].ldy = j.ldy; g[i].R2 = j.R2;
+    g[i].ssq = j.ssq; g[i].ssq_ld = j.ssq_ld; g[i].rnorm_k = j.rnorm_k; g[i].eps = j.eps; g[i].store = 1;
+  }
+  const bool vec = N % 4 == 0 && ja.ldy % 4 == 0 && jb.ldy % 4 == 0;
+  const int per = vec ? 1024 : 256;
+  const dim3 grid((N + per - 1) / per, M < 65535 ? M : 65535, 2);
+  if (vec) hipLaunchKernelGGL((gemm_reduce_pair_kernel<true>), grid, dim3(256), 0, s, g[0], g[1]);
+  else hipLaunchKernelGGL((gemm_reduce_pair_kernel<false>), grid, dim3(256), 0, s, g[0], g[1]);
+  return hipGetLastError();
 }
 
 }  // namespace hh

@@ -26,6 +26,30 @@ static constexpr size_t kLdsBudget = 150 * 1024;
 
 int gemv_max_blocks() { return kMaxBlocks; }
 
+// rows of a launch: `left` rows, or fewer where their activations do not fit in LDS
+static int row_tile(int K, int left) {
+  const int Kpad = (K + 511) & ~511;
+  int mt_cap = 8;
+  while (mt_cap > 1 && (size_t)mt_cap * Kpad * 4 + 4096 > kLdsBudget) --mt_cap;
+  mt_cap = mt_cap >= 8 ? 8 : mt_cap >= 5 ? 5 : mt_cap >= 3 ? 3 : 1;
+  const int mt = left > 5 ? 8 : left > 3 ? 5 : left > 1 ? 3 : 1;
+  return mt > mt_cap ? mt_cap : mt;
+}
+
+static void set_blocks(const GemvArgs& a, GemvPlan& p) {
+  const int rgb = kGemvWaves / p.KS, nrg = a.seg[0].n_rows / p.R;
+  // several row groups per workgroup, so that staging the activations (MT * K floats per
+  // workgroup, from L2) stays small next to the weights it meets
+  constexpr int target = 1024;
+  const int per = (nrg + rgb - 1) / rgb;
+  p.iters = (per + target - 1) / target;
+  if (p.iters < 1) p.iters = 1;
+  if (p.iters > 64) p.iters = 64;
+  p.blocks = (nrg + rgb * p.iters - 1) / (rgb * p.iters);
+  const int pn = (a.epi == EPI_SWIGLU ? 2 : 1) * p.R * p.MT;
+  p.lds = ((size_t)p.MT * ((a.K + 511) & ~511) + kGemvWaves * p.MT + 2 * kGemvWaves * pn + 4) * sizeof(float);
+}
+
 static bool make_plan(const GemvArgs& a, int MT, GemvPlan& p) {
   const int N = a.seg[0].n_rows;
   const int Kpad = (a.K + 511) & ~511;
@@ -46,35 +70,30 @@ static bool make_plan(const GemvArgs& a, int MT, GemvPlan& p) {
   // R must divide N; use fewer rows per wavefront while that is needed to cover the CUs
   constexpr int min_blocks = 256;
   while (p.R > 1 && (N % p.R || N / p.R / rgb < min_blocks)) p.R >>= 1;
-  const int nrg = N / p.R;
-  // several row groups per workgroup, so that staging the activations (MT * K floats per
-  // workgroup, from L2) stays small next to the weights it meets
-  constexpr int tb1 = 1024, tbm = 1024;
-  const int per = (nrg + rgb - 1) / rgb;
-  const int target = MT == 1 ? tb1 : tbm;
-  p.iters = (per + target - 1) / target;
-  if (p.iters < 1) p.iters = 1;
-  if (p.iters > 64) p.iters = 64;
-  p.blocks = (nrg + rgb * p.iters - 1) / (rgb * p.iters);
-  if (p.blocks > kMaxBlocks) return false;
-  const int pn = (a.epi == EPI_SWIGLU ? 2 : 1) * p.R * MT;
-  p.lds = ((size_t)MT * Kpad + kGemvWaves * MT + 2 * kGemvWaves * pn + 4) * sizeof(float);
-  return true;
+  set_blocks(a, p);
+  return p.blocks <= kMaxBlocks;
+}
+
+// The plan of a pair: b takes the split of a (the longer rows); wavefronts behind the end of b's rows re-read its last columns
+// and meet zero activations.
+bool gemv_pair_plan(const GemvArgs& a, const GemvArgs& b, GemvPlan& pa, GemvPlan& pb) {
+  if (a.epi != EPI_ADD || b.epi != EPI_STORE || a.M != b.M || a.M < 1 || a.bf16 != b.bf16 || a.n_seg != 1 || b.n_seg != 1 ||
+      a.best != nullptr || b.best != nullptr || b.K > a.K || a.K % 8 != 0 || b.K % 8 != 0 || b.K < 8 || a.ldx % 4 != 0 || b.ldx % 4 != 0 ||
+      a.seg[0].n_rows <= 0 || b.seg[0].n_rows <= 0)
+    return false;
+  const int mt = row_tile(a.K, a.M);
+  if (a.M > mt || !make_plan(a, mt, pa) || b.seg[0].n_rows % pa.R != 0) return false;
+  pb = pa;
+  set_blocks(b, pb);
+  return pa.blocks + pb.blocks <= kMaxBlocks;
 }
 
 hipError_t launch_gemv(const GemvArgs& a, int* n_blocks_out, hipStream_t s) {
   if (a.K % 8 != 0 || a.K < 8 || a.ldx % 4 != 0 || a.n_seg != 1) return hipErrorInvalidValue;
   if (a.seg[0].n_rows <= 0 || a.M <= 0) return hipSuccess;
-  const int Kpad = (a.K + 511) & ~511;
-  // largest row tile whose activations fit in LDS
-  int mt_cap = 8;
-  while (mt_cap > 1 && (size_t)mt_cap * Kpad * 4 + 4096 > kLdsBudget) --mt_cap;
-  mt_cap = mt_cap >= 8 ? 8 : mt_cap >= 5 ? 5 : mt_cap >= 3 ? 3 : 1;
   int mt_first = 0;
   for (int m0 = 0; m0 < a.M;) {
-    const int left = a.M - m0;
-    int mt = left > 5 ? 8 : left > 3 ? 5 : left > 1 ? 3 : 1;
-    if (mt > mt_cap) mt = mt_cap;
+    int mt = row_tile(a.K, a.M - m0);
     // the argmax partials of all row tiles share one layout: keep one launch shape
     if (a.best != nullptr) { if (mt_first == 0) mt_first = mt; mt = mt_first; }
     GemvPlan p;

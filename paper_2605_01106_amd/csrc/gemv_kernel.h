@@ -73,13 +73,13 @@ __device__ __forceinline__ int xs_slot4(int k4) {       // k4 = k / 4 -> float4 
 // unconditionally (columns past K read a clamped, valid address and meet zero activations);
 // the first unit is issued before the activations are staged.  Latency is hidden by the other
 // resident wavefronts and by the loads of a wavefront itself, not by software pipelining.
+// bid of nblk workgroups; smem: GemvPlan::lds bytes of LDS.
 template <int BF16, int MT, int R, int NCW, int KS, int EPI>
-__global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const GemvArgs a, const int m0, const int iters) {
+__device__ __forceinline__ void gemv_body(const GemvArgs& a, const int m0, const int iters, const int bid, const int nblk, float* smem) {
   constexpr int NW = EPI == EPI_SWIGLU ? 2 * R : R;   // weight rows held per wavefront
   constexpr int RGB = kGemvWaves / KS;                // row groups per workgroup per iteration
   constexpr int NOUT = R * MT;                        // outputs per row group
   constexpr int PN = EPI == EPI_SWIGLU ? 2 * NOUT : NOUT;
-  extern __shared__ __align__(16) float smem[];
   const int K = a.K;
   const int Kpad = (K + 511) & ~511;
   const int nch = Kpad >> 9;
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const GemvArgs a, co
 
   W8<BF16> w[NW][NCW];
   float resid = 0.f;
-  auto row_group = [&](int it) { return (blockIdx.x * iters + it) * RGB + slot; };
+  auto row_group = [&](int it) { return (bid * iters + it) * RGB + slot; };
   auto load_unit = [&](int rg) {
     const int n = min(rg, nrg - 1) * R;
 #pragma unroll
@@ -269,9 +269,24 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const GemvArgs a, co
       unsigned long long b = 0ull;
       for (int i = 0; i < kGemvWaves; ++i)
         for (int r = 0; r < R; ++r) b = max(b, bw[i * NOUT + r * MT + tid]);
-      a.best[(size_t)(m0 + tid) * gridDim.x + blockIdx.x] = b;
+      a.best[(size_t)(m0 + tid) * nblk + bid] = b;
     }
   }
+}
+
+template <int BF16, int MT, int R, int NCW, int KS, int EPI>
+__global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const GemvArgs a, const int m0, const int iters) {
+  extern __shared__ __align__(16) float smem[];
+  gemv_body<BF16, MT, R, NCW, KS, EPI>(a, m0, iters, blockIdx.x, gridDim.x, smem);
+}
+
+// Two independent products of the same rows and the same split in one launch: the first na workgroups add a onto its output,
+// the others store b.
+template <int BF16, int MT, int R, int NCW, int KS>
+__global__ __launch_bounds__(kGemvThreads) void gemv_pair_kernel(const GemvArgs a, const GemvArgs b, const int iters_a, const int iters_b, const int na) {
+  extern __shared__ __align__(16) float smem[];
+  if ((int)blockIdx.x < na) gemv_body<BF16, MT, R, NCW, KS, EPI_ADD>(a, 0, iters_a, blockIdx.x, na, smem);
+  else gemv_body<BF16, MT, R, NCW, KS, EPI_STORE>(b, 0, iters_b, blockIdx.x - na, gridDim.x - na, smem);
 }
 
 // shape of one launch, chosen on the host
@@ -320,6 +335,7 @@ hipError_t gemv_dispatch(const GemvArgs& a, int m0, const GemvPlan& p, hipStream
   return hipErrorInvalidValue;
 }
 
+bool gemv_pair_plan(const GemvArgs& a, const GemvArgs& b, GemvPlan& pa, GemvPlan& pb);
 hipError_t gemv_dispatch_store(const GemvArgs& a, int m0, const GemvPlan& p, hipStream_t s);
 hipError_t gemv_dispatch_add(const GemvArgs& a, int m0, const GemvPlan& p, hipStream_t s);
 hipError_t gemv_dispatch_swiglu(const GemvArgs& a, int m0, const GemvPlan& p, hipStream_t s);

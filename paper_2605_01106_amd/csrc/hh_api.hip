@@ -324,6 +324,28 @@ hipError_t product(hh_ctx* x, const GemvArgs& a, hipStream_t s, bool side = fals
   return launch_gemv(a, nullptr, s);
 }
 
+// Two independent products in one launch where both take the same kernel: true if launched (*err: its status).  The output
+// projections of the two branches: a launch of its own (and a reduction from 17 rows on) is 4 to 9 us, mostly the launch and one
+// round trip to memory, which the other product's workgroups hide.  One sequence at the 0.5B shape, two rounds 6030 -> 5790 us;
+// 16 sequences 18.86 -> 18.39 ms, 5 with sampling 13.58 -> 13.16; 3B shape, 24 sequences, four greedy steps 1815 -> 1739 us.
+bool product_pair(hh_ctx* x, const GemvArgs& a, const GemvArgs& b, hipStream_t s, hipError_t* err) {
+  GemvArgs sa, sb;
+  const bool ska = skinny_args(a, sa), skb = skinny_args(b, sb);
+  if (ska && skb) {
+    if (!skinny_pair_fits(sa, sb)) return false;
+    *err = launch_skinny_pair(sa, sb, s);
+    return true;
+  }
+  if (ska || skb) return false;
+  if (mid_pair_fits(a, b)) {
+    *err = launch_mid_pair(a, b, x->gemm_partial, x->gemm_partial_side, s);
+    return true;
+  }
+  if (mid_mfma_fits(a) || mid_mfma_fits(b) || (a.bf16 && a.M >= kMfmaMinRows) || !gemv_pair_fits(a, b)) return false;
+  *err = launch_gemv_pair(a, b, s);
+  return true;
+}
+
 // Whether a full pass runs its attention branch on the side stream beside the SSM branch.
 // Prefill passes do (both branches are long there).  A verification pass does not unless asked:
 // what can overlap is the shorter branch (scan + out projection: 130 us of 900 us per layer at the 3B
@@ -376,13 +398,14 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
     scan.zx = x->zx; scan.g = x->g; scan.pos0 = x->pos0; scan.n_tok = n_tok; scan.T = T; scan.B = B;
     scan.state_in = state_in; scan.state_out = state_out; scan.write_ring = 1; scan.seg_scratch = x->seg_scratch;
     bool scanned = false;
+    GemvArgs o_proj{};
     if (full) {
       AttnArgs a{};
       a.kpool = w.kpool; a.vpool = w.vpool; a.qkv = x->qkv; a.o = x->o; a.pos0 = x->pos0; a.n_tok = n_tok;
       a.page_table = x->page_table; a.rope = x->rope; a.part_o = x->part_o; a.part_ml = x->part_ml;
       a.counters = x->attn_counters;
       a.T = T; a.B = B; a.n_splits = n_splits;
-      GemvArgs b{};
+      GemvArgs& b = o_proj;
       b.X = x->o; b.ldx = d.dq; b.M = M; b.K = d.dq; b.norm_w = nullptr; b.epi = EPI_STORE; b.bf16 = d.bf16; b.flags = d.flags;
       b.seg[0] = {w.w_o, nullptr, w.p_o, nullptr, x->ho, d.D, d.D}; b.n_seg = 1;
       if (overlap) {
@@ -390,20 +413,25 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
         HH_HIP(product(x, b, sa, true));
         HH_HIP(hipEventRecord(x->join_ev[l], sa));
       } else {
-        // (timed kind by kind the branches are launched one by one)
+        // (timed kind by kind, the branches and their output projections are launched one by one)
         hipError_t e = hipSuccess;
         scanned = !x->prof_on && launch_branches(d, a, scan, s, &e);
         HH_HIP(e);
         if (!scanned) HH_LAUNCH(HH_K_ATTN, launch_attention(d, a, s));
-        HH_LAUNCH(HH_K_O_PROJ, product(x, b, s));
       }
     }
     if (!scanned) HH_LAUNCH(HH_K_SSM, launch_ssm(d, scan, s));
-    {  // h += W_out * gated_norm(g)
+    {  // h += W_out * gated_norm(g), and W_o * o -> ho
       GemvArgs a{};
       a.X = x->g; a.ldx = d.d_inner; a.M = M; a.K = d.d_inner; a.norm_w = w.gnorm; a.eps = d.eps; a.epi = EPI_ADD; a.bf16 = d.bf16; a.flags = d.flags;
       a.seg[0] = {w.w_out, nullptr, w.p_out, nullptr, x->h, d.D, d.D}; a.n_seg = 1;
-      HH_LAUNCH(HH_K_OUT_PROJ, product(x, a, s));
+      hipError_t e = hipSuccess;
+      const bool paired = full && !overlap && !x->prof_on && product_pair(x, a, o_proj, s, &e);
+      HH_HIP(e);
+      if (!paired) {
+        if (full && !overlap) HH_LAUNCH(HH_K_O_PROJ, product(x, o_proj, s));
+        HH_LAUNCH(HH_K_OUT_PROJ, product(x, a, s));
+      }
     }
     if (overlap) HH_HIP(hipStreamWaitEvent(s, x->join_ev[l], 0));
     {  // SwiGLU MLP on r = rmsnorm(h + ho); h += ho + W_d(...)   (ho: full mode only)

@@ -81,6 +81,17 @@ hipError_t launch_gemm_reduce(int epi, float* partial, int ksplit, int M, int N,
 bool mid_mfma_fits(const GemvArgs& a);
 hipError_t launch_mid_mfma(const GemvArgs& a, float* partial, hipStream_t s);
 
+// ---- two independent products of the same rows in one launch (and one reduction): a adds onto its output, b (no longer rows
+// than a) stores.  b is split as a is, so that its sums may be grouped otherwise than in a launch of its own.
+struct ReduceJob { float* partial; int ksplit; float* Y; int ldy; const float* R2; const float* ssq; int ssq_ld; float rnorm_k, eps; };
+hipError_t launch_gemm_reduce_pair(const ReduceJob& a, const ReduceJob& b, int M, int N, hipStream_t s);
+bool gemv_pair_fits(const GemvArgs& a, const GemvArgs& b);
+hipError_t launch_gemv_pair(const GemvArgs& a, const GemvArgs& b, hipStream_t s);
+bool skinny_pair_fits(const GemvArgs& a, const GemvArgs& b);   // (packed weights in seg[0].W, as launch_skinny_mfma)
+hipError_t launch_skinny_pair(const GemvArgs& a, const GemvArgs& b, hipStream_t s);
+bool mid_pair_fits(const GemvArgs& a, const GemvArgs& b);
+hipError_t launch_mid_pair(const GemvArgs& a, const GemvArgs& b, float* partial_a, float* partial_b, hipStream_t s);
+
 // ---- the same product on the matrix cores (bf16 weights, more than a few activation rows)
 size_t gemm_planes_elems(int M, int K);   // bf16 elements of scratch for the split activations
 size_t gemm_partial_elems();              // float elements of scratch for split-K partial products

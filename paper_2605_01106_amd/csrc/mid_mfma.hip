@@ -62,8 +62,9 @@ struct MidArgs {
 // workgroup per compute unit: 104 KB of LDS at 64 rows) or 4 x 2 (half the columns and half the window:
 // 55 KB of LDS and half the registers, so that two workgroups share a compute unit and one's loads,
 // staging and barriers hide behind the other's MFMAs).
+// Workgroup (bx, by); smem_raw: MidPlan::lds bytes of LDS.
 template <int NF, int MT, int NW, int KSW>
-__global__ __launch_bounds__(64 * NW) void mid_loop_kernel(const MidArgs a) {
+__device__ __forceinline__ void mid_loop_body(const MidArgs& a, const int bx, const int by, unsigned char* smem_raw) {
   constexpr int KW = KSW * 32, SL = KW + mid_pad(MT, KW);
   constexpr int ROWS = MT * 16;
   constexpr int GPR = KW / 4;                    // float4 column groups per staged row: 32 or 16 lanes
@@ -72,15 +73,14 @@ __global__ __launch_bounds__(64 * NW) void mid_loop_kernel(const MidArgs a) {
   constexpr int NP = ROWS / PASS;
   static_assert(PASS == 16 && (KSW == 4 || KSW == 2), "a staging pass is one row tile");
   constexpr size_t BUF = (size_t)kMidTerms * ROWS * SL;   // bf16 elements per LDS buffer
-  extern __shared__ __align__(16) unsigned char smem_raw[];
   uint16_t* xs = reinterpret_cast<uint16_t*>(smem_raw);     // [2][kMidTerms][ROWS][SL]
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, n = lane & 15;
   const int M = a.M, K = a.K, N = a.N;
   const int n_tiles = (N + 15) >> 4, KST = (K + 31) >> 5;
   const int n_win = (K + KW - 1) / KW;
-  const int win0 = blockIdx.y * a.wpb, win1 = min(n_win, win0 + a.wpb);   // win0 < n_win by construction
-  const int unit = blockIdx.x * NW + wave;
+  const int win0 = by * a.wpb, win1 = min(n_win, win0 + a.wpb);   // win0 < n_win by construction
+  const int unit = bx * NW + wave;
   int tile[2];
   const uint16_t* wrow[2];
 #pragma unroll
@@ -207,31 +207,32 @@ __global__ __launch_bounds__(64 * NW) void mid_loop_kernel(const MidArgs a) {
   if (win + 1 < win1) window(win + 1, w1, w0);
   TR(3);
   // sums of squares of the rows this wavefront staged (GPR lanes per row), for the norm scale
-  if (a.ssq != nullptr && blockIdx.x == 0) {
+  if (a.ssq != nullptr && bx == 0) {
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
       float t = row16_sum(sq[u]);                                   // every row of 16 lanes holds its total
       if (GPR == 32) t += __shfl_xor(t, 16, 64);                    // a staged row spans two rows of lanes
       const int r = u * PASS + wave * RPW + rsub;
-      if (cgi == 0 && r < M) a.ssq[(size_t)blockIdx.y * a.ssq_ld + r] = t;
+      if (cgi == 0 && r < M) a.ssq[(size_t)by * a.ssq_ld + r] = t;
     }
   }
   // lane (g, n) holds Y[activation row mt*16 + n][weight rows tile*16 + 4g .. + 3]
   TR(4);
   if (unit >= a.units) return;
+  const bool vec = (N & 3) == 0;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if (tile[i] >= n_tiles) continue;
     const int f = NF == 2 ? i : 0;
-    float* pb = a.partial + ((size_t)(blockIdx.y * NF + f) * M) * N;
+    float* pb = a.partial + ((size_t)(by * NF + f) * M) * N;
     const int c0 = tile[i] * 16 + 4 * g;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const int m = mt * 16 + n;
       if (m >= M) continue;
       float* y = pb + (size_t)m * N + c0;
-      if (c0 + 3 < N && (N & 3) == 0) {
-        *reinterpret_cast<float4*>(y) = make_float4(acc[i][mt][0], acc[i][mt][1], acc[i][mt][2], acc[i][mt][3]);
+      if (vec) {                                    // (N % 4 == 0: four columns are inside or outside)
+        if (c0 < N) *reinterpret_cast<float4*>(y) = make_float4(acc[i][mt][0], acc[i][mt][1], acc[i][mt][2], acc[i][mt][3]);
       } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -242,6 +243,20 @@ __global__ __launch_bounds__(64 * NW) void mid_loop_kernel(const MidArgs a) {
   TR(5);
 }
 
+template <int NF, int MT, int NW, int KSW>
+__global__ __launch_bounds__(64 * NW) void mid_loop_kernel(const MidArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  mid_loop_body<NF, MT, NW, KSW>(a, blockIdx.x, blockIdx.y, smem_raw);
+}
+
+// Two independent products of the same rows in one launch: the first na workgroups (ax of them per K chunk) a's, the others b's.
+template <int MT, int NW, int KSW>
+__global__ __launch_bounds__(64 * NW) void mid_pair_kernel(const MidArgs a, const MidArgs b, const int na, const int ax, const int bx) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int i = blockIdx.x, j = i - na;
+  if (i < na) mid_loop_body<1, MT, NW, KSW>(a, i % ax, i / ax, smem_raw);
+  else mid_loop_body<1, MT, NW, KSW>(b, j % bx, j / bx, smem_raw);
+}
 
 struct MidPlan { int mt, windows, units, blocks, wpb, small; size_t lds, partial_elems; };   // windows: K chunks = partial products
 
@@ -328,6 +343,54 @@ static hipError_t mid_dispatch(const MidArgs& a, const MidPlan& p, hipStream_t s
   return hipErrorInvalidValue;
 }
 
+static MidArgs mid_kernel_args(const GemvArgs& g, const MidPlan& p, float* partial) {
+  const int N = g.seg[0].n_rows, nf = g.epi == EPI_SWIGLU ? 2 : 1;
+  MidArgs a{};
+  a.X = g.X; a.ldx = g.ldx; a.M = g.M; a.K = g.K; a.X2 = g.X2; a.norm_w = g.norm_w;
+  a.W = static_cast<const uint16_t*>(g.seg[0].P); a.W2 = static_cast<const uint16_t*>(g.seg[0].P2);
+  a.N = N; a.kst_row = (g.K + 31) / 32; a.partial = partial; a.units = p.units; a.wpb = p.wpb;
+  a.ssq_ld = 96;
+  a.ssq = g.norm_w != nullptr ? partial + (size_t)p.windows * nf * g.M * N : nullptr;
+  return a;
+}
+
+bool mid_pair_fits(const GemvArgs& a, const GemvArgs& b) {
+  MidPlan p;
+  return a.epi == EPI_ADD && b.epi == EPI_STORE && a.M == b.M && a.row_best == nullptr && b.row_best == nullptr && mid_mfma_fits(a) &&
+         mid_mfma_fits(b) && mid_plan(a, p) && p.small && a.seg[0].n_rows > 0 && a.seg[0].n_rows == b.seg[0].n_rows;
+}
+
+template <int MT>
+static hipError_t mid_pair_launch(const MidArgs& a, const MidArgs& b, const MidPlan& pa, const MidPlan& pb, hipStream_t s) {
+  auto kern = mid_pair_kernel<MT, 4, 2>;
+  static size_t lds_enabled = 48 * 1024;
+  if (pa.lds > lds_enabled) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pa.lds);
+    if (e != hipSuccess) return e;
+    lds_enabled = pa.lds;
+  }
+  hipLaunchKernelGGL(kern, dim3(pa.blocks * pa.windows + pb.blocks * pb.windows), dim3(256), pa.lds, s, a, b, pa.blocks * pa.windows, pa.blocks, pb.blocks);
+  return hipGetLastError();
+}
+
+hipError_t launch_mid_pair(const GemvArgs& a, const GemvArgs& b, float* partial_a, float* partial_b, hipStream_t s) {
+  MidPlan pa, pb;
+  if (!mid_pair_fits(a, b) || !mid_plan(a, pa) || !mid_plan(b, pb) || partial_a == nullptr || partial_b == nullptr || partial_a == partial_b)
+    return hipErrorInvalidValue;
+  const MidArgs ka = mid_kernel_args(a, pa, partial_a), kb = mid_kernel_args(b, pb, partial_b);
+  hipError_t e = hipErrorInvalidValue;
+  switch (pa.mt) {
+    case 2: e = mid_pair_launch<2>(ka, kb, pa, pb, s); break;
+    case 3: e = mid_pair_launch<3>(ka, kb, pa, pb, s); break;
+    case 4: e = mid_pair_launch<4>(ka, kb, pa, pb, s); break;
+    case 5: e = mid_pair_launch<5>(ka, kb, pa, pb, s); break;
+  }
+  if (e != hipSuccess) return e;
+  const ReduceJob ja{partial_a, pa.windows, a.seg[0].Y, a.seg[0].ldy, a.R2, ka.ssq, ka.ssq_ld, 1.0f / (float)a.K, a.eps};
+  const ReduceJob jb{partial_b, pb.windows, b.seg[0].Y, b.seg[0].ldy, nullptr, kb.ssq, kb.ssq_ld, 1.0f / (float)b.K, b.eps};
+  return launch_gemm_reduce_pair(ja, jb, a.M, a.seg[0].n_rows, s);
+}
+
 // `partial`: scratch of gemm_partial_elems() floats
 hipError_t launch_mid_mfma(const GemvArgs& g, float* partial, hipStream_t s) {
   MidPlan p;
@@ -335,12 +398,7 @@ hipError_t launch_mid_mfma(const GemvArgs& g, float* partial, hipStream_t s) {
   const int N = g.seg[0].n_rows;
   if (N <= 0) return hipSuccess;
   const int nf = g.epi == EPI_SWIGLU ? 2 : 1;
-  MidArgs a{};
-  a.X = g.X; a.ldx = g.ldx; a.M = g.M; a.K = g.K; a.X2 = g.X2; a.norm_w = g.norm_w;
-  a.W = static_cast<const uint16_t*>(g.seg[0].P); a.W2 = static_cast<const uint16_t*>(g.seg[0].P2);
-  a.N = N; a.kst_row = (g.K + 31) / 32; a.partial = partial; a.units = p.units; a.wpb = p.wpb;
-  a.ssq_ld = 96;
-  a.ssq = g.norm_w != nullptr ? partial + (size_t)p.windows * nf * g.M * N : nullptr;
+  const MidArgs a = mid_kernel_args(g, p, partial);
   hipError_t e = nf == 2 ? mid_dispatch<2>(a, p, s) : mid_dispatch<1>(a, p, s);
   if (e != hipSuccess) return e;
   return launch_gemm_reduce(g.epi, partial, p.windows, g.M, N, g.seg[0].Y, g.seg[0].ldy, g.R2, a.ssq, a.ssq_ld,

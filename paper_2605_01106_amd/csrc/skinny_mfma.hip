@@ -66,8 +66,9 @@ struct SkinnyArgs {
 // ONCE: streaming weight loads (see load_once16), for up to kOnceRows rows: 5 rows at the 0.5B shape 1.9 % faster per pass,
 // 16 rows 0.25 % slower (a choice inside the kernel instead of two kernels costs 1 to 2.6 %).
 static constexpr int kOnceRows = 8;
+// Workgroup (bx, by) of nbx columns of workgroups; smem_raw: SkinnyPlan::lds bytes of LDS.
 template <int EPI, int NWAVES, int KSTEPS, bool ONCE>
-__global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyArgs a) {
+__device__ __forceinline__ void skinny_body(const SkinnyArgs& a, const int bx, const int by, const int nbx, unsigned char* smem_raw) {
   constexpr int NF = EPI == EPI_SWIGLU ? 2 : 1;
   // two weight matrices and long slices: one set of fragments, the next round is requested
   // after the multiplication instead of before it
@@ -77,12 +78,11 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
   // round trip instead of two: 16 sequences at the 0.5B shape, two rounds 20.39 -> 19.93 ms; 8 for few rows repeats loads)
   constexpr int SU = ONCE ? (KSTEPS < 4 ? KSTEPS : 4) : (KSTEPS < 4 ? 2 * KSTEPS : 8);
   constexpr int SL4 = KSTEPS * 8;                           // float4 groups per row of a slice
-  extern __shared__ __align__(16) unsigned char smem_raw[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, n = lane & 15;
   const int K = a.K, M = a.M, N = a.N;
-  const int k0 = a.k0 + (int)blockIdx.y * K;                // first column of this workgroup's window
-  float* const Yw = a.Y + (size_t)blockIdx.y * a.ywin;
+  const int k0 = a.k0 + by * K;                // first column of this workgroup's window
+  float* const Yw = a.Y + (size_t)by * a.ywin;
   const int kb = wave * KSTEPS * 32;                        // first column of this wavefront's slice
   uint16_t* xs = reinterpret_cast<uint16_t*>(smem_raw) + (size_t)wave * 3 * M * SL;          // [3][M][SL]
   float* red = reinterpret_cast<float*>(smem_raw + (size_t)NWAVES * 3 * M * SL * 2);         // [NWAVES][16]
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
   TR(0);
   SFrag wf[DB ? 2 : 1][NF][KSTEPS];
   auto load_round = [&](int rd, SFrag(&w)[NF][KSTEPS]) {
-    const int tile = min(blockIdx.x + rd * (int)gridDim.x, n_tiles - 1);
+    const int tile = min(bx + rd * nbx, n_tiles - 1);
 #pragma unroll
     for (int s = 0; s < KSTEPS; ++s) {
       // steps past the end of the row (last wavefronts only) re-read the last step and meet zero activations
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
 #pragma unroll
     for (int w = 0; w < NWAVES; ++w) tot += red[w * 16 + n];
     if (a.ssq == nullptr) rstd = 1.0f / sqrtf(tot * a.rnorm_k + a.eps);
-    else if (blockIdx.x == 0 && wave == 0 && g == 0) a.ssq[blockIdx.y * 16 + n] = tot;   // the reduction kernel scales
+    else if (bx == 0 && wave == 0 && g == 0) a.ssq[by * 16 + n] = tot;   // the reduction kernel scales
   }
   // this lane's activation fragments; lanes n >= M hold copies of a valid row (their columns of
   // the product are never stored)
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
   unsigned long long best = 0ull;
   auto round = [&](int rd, SFrag(&w)[NF][KSTEPS], SFrag(&wnext)[NF][KSTEPS]) {
     if (DB && rd + 1 < a.rounds) load_round(rd + 1, wnext);
-    const int tile = blockIdx.x + rd * (int)gridDim.x;
+    const int tile = bx + rd * nbx;
     const int fin = rd % NWAVES;                 // the wavefront that finishes this tile
     // residual of the tile: requested now, needed after the reduction
     float4 old = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -269,10 +269,24 @@ __global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyAr
       unsigned long long b = 0ull;
 #pragma unroll
       for (int w = 0; w < NWAVES; ++w) b = max(b, bestb[w * 16 + tid]);
-      a.best[(size_t)tid * gridDim.x + blockIdx.x] = b;
+      a.best[(size_t)tid * nbx + bx] = b;
     }
   }
   TR(5);
+}
+
+template <int EPI, int NWAVES, int KSTEPS, bool ONCE>
+__global__ __launch_bounds__(64 * NWAVES) void skinny_mfma_kernel(const SkinnyArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  skinny_body<EPI, NWAVES, KSTEPS, ONCE>(a, blockIdx.x, blockIdx.y, gridDim.x, smem_raw);
+}
+
+// Two independent products of the same rows in one launch: the first na workgroups add a onto its output, the others store b.
+template <int NWAVES, int KSTEPS, bool ONCE>
+__global__ __launch_bounds__(64 * NWAVES) void skinny_pair_kernel(const SkinnyArgs a, const SkinnyArgs b, const int na) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  if ((int)blockIdx.x < na) skinny_body<EPI_ADD, NWAVES, KSTEPS, ONCE>(a, blockIdx.x, 0, na, smem_raw);
+  else skinny_body<EPI_STORE, NWAVES, KSTEPS, ONCE>(b, blockIdx.x - na, 0, gridDim.x - na, smem_raw);
 }
 
 // Weight layout of the matrix-core kernels: tiles of 16 rows x 32 columns stored in operand
@@ -412,6 +426,71 @@ bool skinny_mfma_fits(const GemvArgs& g) {
          skinny_windows(g, p) > 0;
 }
 
+static SkinnyArgs skinny_kernel_args(const GemvArgs& g, const SkinnyPlan& p) {
+  SkinnyArgs a{};
+  a.X = g.X; a.X2 = g.X2; a.R2 = g.R2; a.ldx = g.ldx; a.M = g.M; a.norm_w = g.norm_w; a.eps = g.eps;
+  a.W = static_cast<const uint16_t*>(g.seg[0].W); a.W2 = static_cast<const uint16_t*>(g.seg[0].W2);
+  a.Y = g.seg[0].Y; a.ldy = g.seg[0].ldy; a.N = g.seg[0].n_rows; a.best = g.best;
+  a.rounds = p.rounds; a.kst_row = (g.K + 31) / 32; a.rnorm_k = 1.0f / (float)g.K;
+  a.K = g.K; a.k0 = 0;
+  return a;
+}
+
+// The plan of a pair: both products in one launch each (no K windows), b with the wavefronts and steps of a (the longer rows);
+// wavefronts behind the end of b's rows re-read its last step and meet zero activations.
+static bool skinny_pair_plan(const GemvArgs& a, const GemvArgs& b, SkinnyPlan& pa, SkinnyPlan& pb) {
+  if (a.epi != EPI_ADD || b.epi != EPI_STORE || a.M != b.M || a.best != nullptr || b.best != nullptr || b.K > a.K ||
+      !skinny_mfma_fits(a) || !skinny_mfma_fits(b) || skinny_windows(a, pa) != 1)
+    return false;
+  const int tiles = (b.seg[0].n_rows + 15) / 16;
+  pb = pa;
+  pb.rounds = (tiles + 767) / 768;
+  pb.blocks = (tiles + pb.rounds - 1) / pb.rounds;
+  return true;
+}
+template <int NWAVES, int KSTEPS, bool ONCE>
+static hipError_t skinny_pair_launch(const GemvArgs& a, const GemvArgs& b, const SkinnyPlan& pa, const SkinnyPlan& pb, hipStream_t s) {
+  auto kern = skinny_pair_kernel<NWAVES, KSTEPS, ONCE>;
+  static size_t lds_enabled = 48 * 1024;
+  if (pa.lds > lds_enabled) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pa.lds);
+    if (e != hipSuccess) return e;
+    lds_enabled = pa.lds;
+  }
+  hipLaunchKernelGGL(kern, dim3(pa.blocks + pb.blocks), dim3(64 * NWAVES), pa.lds, s, skinny_kernel_args(a, pa), skinny_kernel_args(b, pb), pa.blocks);
+  return hipGetLastError();
+}
+template <int NWAVES, int KSTEPS>
+static hipError_t skinny_pair_rows(const GemvArgs& a, const GemvArgs& b, const SkinnyPlan& pa, const SkinnyPlan& pb, hipStream_t s) {
+  return a.M <= kOnceRows ? skinny_pair_launch<NWAVES, KSTEPS, true>(a, b, pa, pb, s) : skinny_pair_launch<NWAVES, KSTEPS, false>(a, b, pa, pb, s);
+}
+
+bool skinny_pair_fits(const GemvArgs& a, const GemvArgs& b) {
+  SkinnyPlan pa, pb;
+  return skinny_pair_plan(a, b, pa, pb);
+}
+
+hipError_t launch_skinny_pair(const GemvArgs& a, const GemvArgs& b, hipStream_t s) {
+  SkinnyPlan pa, pb;
+  if (!skinny_pair_plan(a, b, pa, pb)) return hipErrorInvalidValue;
+  switch (pa.nwaves * 16 + pa.ksteps) {
+    case 0x81: return skinny_pair_rows<8, 1>(a, b, pa, pb, s);
+    case 0x82: return skinny_pair_rows<8, 2>(a, b, pa, pb, s);
+    case 0x83: return skinny_pair_rows<8, 3>(a, b, pa, pb, s);
+    case 0x84: return skinny_pair_rows<8, 4>(a, b, pa, pb, s);
+    case 0x85: return skinny_pair_rows<8, 5>(a, b, pa, pb, s);
+    case 0x86: return skinny_pair_rows<8, 6>(a, b, pa, pb, s);
+    case 0x88: return skinny_pair_rows<8, 8>(a, b, pa, pb, s);
+    case 0x104: return skinny_pair_rows<16, 4>(a, b, pa, pb, s);
+    case 0x105: return skinny_pair_rows<16, 5>(a, b, pa, pb, s);
+    case 0x106: return skinny_pair_rows<16, 6>(a, b, pa, pb, s);
+    case 0x108: return skinny_pair_rows<16, 8>(a, b, pa, pb, s);
+    case 0x10a: return skinny_pair_rows<16, 10>(a, b, pa, pb, s);
+    case 0x10e: return skinny_pair_rows<16, 14>(a, b, pa, pb, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 // `partial`: scratch of gemm_partial_elems() floats, used when the product is computed in K windows
 hipError_t launch_skinny_mfma(const GemvArgs& g, float* partial, int* n_blocks_out, hipStream_t s) {
   SkinnyPlan p;
@@ -419,12 +498,8 @@ hipError_t launch_skinny_mfma(const GemvArgs& g, float* partial, int* n_blocks_o
   const int windows = skinny_windows(g, p);
   if (g.seg[0].n_rows <= 0) return hipSuccess;
   if (windows > 1 && partial == nullptr) return hipErrorInvalidValue;
-  SkinnyArgs a{};
-  a.X = g.X; a.X2 = g.X2; a.R2 = g.R2; a.ldx = g.ldx; a.M = g.M; a.norm_w = g.norm_w; a.eps = g.eps;
-  a.W = static_cast<const uint16_t*>(g.seg[0].W); a.W2 = static_cast<const uint16_t*>(g.seg[0].W2);
-  a.Y = g.seg[0].Y; a.ldy = g.seg[0].ldy; a.N = g.seg[0].n_rows; a.best = g.best;
-  a.rounds = p.rounds; a.kst_row = (g.K + 31) / 32; a.rnorm_k = 1.0f / (float)g.K;
-  a.K = g.K / windows; a.k0 = 0;
+  SkinnyArgs a = skinny_kernel_args(g, p);
+  a.K = g.K / windows;
   if (n_blocks_out) *n_blocks_out = p.blocks;
   int epi = g.epi;
   const size_t total = (size_t)g.M * a.N;

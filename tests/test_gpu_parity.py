@@ -487,16 +487,17 @@ def test_new_positions_in_the_attention_kernel(B, head_dim, n_q, n_kv, k, n):
 
 
 @pytest.mark.parametrize("head_dim,n_q,n_kv,d_state,heads,batch,k", [
-    (64, 4, 2, 128, 4, 1, 2), (128, 5, 1, 256, 4, 2, 4), (64, 4, 1, 128, 32, 4, 0), (96, 5, 1, 256, 32, 4, 8),
-    (48, 4, 2, 256, 4, 3, 8), (128, 6, 2, 128, 4, 3, 1), (64, 5, 1, 256, 4, 2, 8)])
+    (64, 6, 2, 128, 4, 1, 2), (128, 5, 1, 256, 4, 2, 4), (64, 16, 4, 128, 8, 16, 0), (96, 10, 2, 256, 8, 16, 8),
+    (48, 8, 4, 256, 4, 3, 8), (128, 6, 2, 128, 4, 3, 1), (64, 5, 1, 256, 4, 2, 8)])
 def test_both_branches_in_one_launch(B, head_dim, n_q, n_kv, d_state, heads, batch, k):
     """A pass of few positions runs attention and scan in one launch: against the oracle, and bit for bit against the two
     kernels on streams of their own, for one to nine positions, one to three row tiles, both operand widths, both lane counts
-    per state row (16, and 8 with 32 heads and four sequences), one and several key slices, a page boundary crossed."""
+    per state row (16, and 8 with 16 sequences), one and several key slices, a page boundary crossed.  (The attention is wider
+    than the state space, so that the output projections stay two launches on both sides: a pair may split its sums otherwise.)"""
     cfg = W.scaled_config("pair", n_layers=2, d_model=64, vocab=160, m_heads=heads, m_head_dim=64, d_state=d_state,
                           n_q_heads=n_q, n_kv_heads=n_kv, head_dim=head_dim, d_ff=96, w_dtype=W.BF16)
     wts = W.make_lively_weights(cfg, 23)
-    lens = [150 - 31 * b for b in range(batch)]
+    lens = [max(150 - 31 * b, 30 + b) for b in range(batch)]
     prompts = W.make_prompts(cfg.vocab, batch, lens, 19)
     ks = [k, max(k - 1, 0), max(k - 3, 0)]
     G = 12
@@ -521,6 +522,26 @@ def test_both_branches_in_one_launch(B, head_dim, n_q, n_kv, d_state, heads, bat
             assert ctx.hh_check_canaries() == 0
             seen.append([a.tobytes() for a in got])
         assert seen[0] == seen[1]
+
+
+@pytest.mark.parametrize("dtype,d_model,head_dim,n_q,m_heads,batch,ks", [
+    (W.F32, 72, 24, 6, 5, 1, [2, 0]), (W.F32, 72, 40, 3, 5, 4, [0, 1]), (W.F32, 64, 64, 4, 8, 1, [5, 8]),     # 1, 3, 5, 8 rows and more
+    (W.BF16, 1096, 64, 4, 24, 1, [2, 1, 0]), (W.BF16, 200, 32, 2, 66, 3, [0]),                  # 1..3 rows
+    (W.BF16, 264, 64, 4, 24, 2, [1, 3, 6]), (W.BF16, 200, 48, 4, 44, 4, [2, 0]),                             # 4..16 rows
+    (W.BF16, 264, 64, 4, 24, 5, [4, 7]), (W.BF16, 200, 48, 4, 36, 9, [1, 5, 8])])                           # 17..80 rows and more
+def test_both_output_projections_in_one_launch(B, dtype, d_model, head_dim, n_q, m_heads, batch, ks):
+    """The output projections of the two branches are one launch where both take the same kernel: every kernel family, rows of
+    the attention's projection that end inside the split of the longer state-space rows (1 to 4 wavefronts of it have nothing
+    to do), weight rows that leave the last tile or row group partly empty, row counts on both sides of every family's limits."""
+    cfg = W.scaled_config("outs", n_layers=2, d_model=d_model, vocab=160, m_heads=m_heads, m_head_dim=32, d_state=32,
+                          n_q_heads=n_q, n_kv_heads=1, head_dim=head_dim, d_ff=96, w_dtype=dtype)
+    assert cfg.d_q <= cfg.d_inner
+    wts = W.make_lively_weights(cfg, 29)
+    lens = [34 - 3 * b for b in range(batch)]
+    prompts = W.make_prompts(cfg.vocab, batch, lens, 21)
+    ctx = _ctx(B, wts, batch, 128, max(ks), 14, overlap_mode=1, kernel_flags=B.HH_KF_CANARIES)
+    run_lockstep(ctx, wts, prompts, lens, 14, ks, engine="pass", report=_say(f"outs-{dtype}-{d_model}-b{batch}"))
+    assert ctx.hh_check_canaries() == 0
 
 
 # (sequences, tokens, d_model, d_ff) of two-layer models and the plan (row tiles per wavefront, K splits) that each product
