@@ -14,6 +14,7 @@
 #include <mutex>
 
 #include "hh_internal.h"
+#include "wave_ops.h"
 
 namespace hh {
 namespace {
@@ -33,13 +34,27 @@ __device__ __forceinline__ float uniform24(uint64_t seed, int b, int idx, int pu
   return static_cast<float>(splitmix64_at(seed, c) >> 40) * 0x1p-24f;
 }
 
+// Over the 64 lanes, left in every lane, in the order lane ^ 32, 16, 8, 4, 2, 1, on the vector unit (a shuffle through LDS is
+// a round trip of its own): the row swaps give both halves, and a rotation by 8 or 4 inside a row of 16 is lane ^ 8 or 4 once the
+// lanes ^ 8 agree.
+template <typename F>
+__device__ __forceinline__ float wave_combine(float v, F f) {
+  const uint32_t x = __float_as_uint(v);
+  const auto s32 = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  v = f(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
+  const uint32_t y = __float_as_uint(v);
+  const auto s16 = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+  v = f(__uint_as_float(s16[0]), __uint_as_float(s16[1]));
+  v = f(v, dpp_move<0x128>(v));   // row_ror:8
+  v = f(v, dpp_move<0x124>(v));   // row_ror:4
+  v = f(v, dpp_move<0x4E>(v));    // quad_perm [2,3,0,1]
+  return f(v, dpp_move<0xB1>(v)); // quad_perm [1,0,3,2]
+}
 __device__ __forceinline__ float wave_max(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
+  return wave_combine(v, [](float p, float q) { return fmaxf(p, q); });
 }
 __device__ __forceinline__ float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  return wave_combine(v, [](float p, float q) { return p + q; });
 }
 
 // softmax(l / T) entry from the row's maximum m and 1 / sum: the one expression every kernel here uses,
@@ -115,9 +130,11 @@ __device__ void row_stats(const float* __restrict__ row, int V, float inv_t, flo
 // ---- rows held in registers.  A row of up to 65536 entries that starts on a 16-byte boundary and whose length is a
 // multiple of 4 is read once, with all loads of a thread in flight together, where the loops above and below read it two
 // or three times, a dependent load per pass of a loop.  Same sums in the same order, so the same bits.  Draw from 64 rows
-// of 1000 entries 5.7 -> 5.0 us, of 4096 6.4 -> 5.5, of 32768 16.4 -> 12.2, of 65536 28.4 -> 21.0; acceptance of 64 sequences
-// at k = 8 over 4096 entries 21 -> 14 us, over 32768 70 -> 59, over 65536 130 -> 115 (the statistics 87 -> 80 us for 285 MB;
-// the draw with the residual keeps the loops there: 64 registers of masses spill behind the two exponentials per entry, 121 us).
+// of 1000 entries 5.7 -> 5.0 us, of 4096 6.4 -> 5.5, of 32768 16.4 -> 10.5, of 65536 28.4 -> 15.0; acceptance of 64 sequences
+// at k = 8 over 4096 entries 21 -> 14 us, over 32768 70 -> 43 (statistics of two rows on a compute unit at a time: at most 64
+// registers), over 65536 130 -> 107: the statistics 78 us for 285 MB, 3.7 TB/s (a plain sum of 2 GiB reads 4.0), then 23 us on
+// one compute unit per sequence, two rows of 256 KB and 131072 exponentials each.  The draw with the residual keeps sums
+// only there: 64 registers of masses spill behind the two exponentials per entry.
 constexpr int kRegGroups = 16;   // groups of 4 entries per thread at most: 64 registers, one workgroup of 16 wavefronts per compute unit
 __host__ __device__ constexpr int reg_vocab(int groups) { return groups * kDrawThreads * 4; }
 
@@ -128,12 +145,10 @@ __device__ __forceinline__ void load_groups(const float* __restrict__ row, int V
   for (int i = 0; i < G; ++i) l[i] = *reinterpret_cast<const float4*>(row + min(first + i * step, V - 4));
 }
 
-// row_stats for such a row
+// row_stats for such a row, which is in l.  next: the row to leave in l behind it, or nullptr.
 template <int G>
-__device__ void row_stats_regs(const float* __restrict__ row, int V, float inv_t, float* red, float& m_out, float& s_out) {
+__device__ void row_stats_regs(float4 (&l)[G], const float* __restrict__ next, int V, float inv_t, float* red, float& m_out, float& s_out) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = kDrawWaves, j0 = threadIdx.x * 4;
-  float4 l[G];
-  load_groups(row, V, j0, kDrawThreads * 4, l);
   float m = kNoLogit;
 #pragma unroll
   for (int i = 0; i < G; ++i) m = fmaxf(fmaxf(m, fmaxf(l[i].x, l[i].y)), fmaxf(l[i].z, l[i].w));
@@ -144,27 +159,92 @@ __device__ void row_stats_regs(const float* __restrict__ row, int V, float inv_t
   for (int i = 1; i < nw; ++i) m = fmaxf(m, red[i]);
   __syncthreads();
   float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < G; ++i) {
+  auto add = [&](const float4& t, int i) {
     if (j0 + i * kDrawThreads * 4 < V)
-      s += (expf((l[i].x - m) * inv_t) + expf((l[i].y - m) * inv_t)) + (expf((l[i].z - m) * inv_t) + expf((l[i].w - m) * inv_t));
+      s += (expf((t.x - m) * inv_t) + expf((t.y - m) * inv_t)) + (expf((t.z - m) * inv_t) + expf((t.w - m) * inv_t));
+  };
+  if (next != nullptr) {
+    // a group is requested into the registers of the one that has just been added: the next row travels behind this one's
+    // exponentials
+    int jn = j0;
+    asm volatile("" : "+v"(jn));                 // (not 16 addresses kept from row to row)
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      add(l[i], i);
+      l[i] = *reinterpret_cast<const float4*>(next + min(jn + i * kDrawThreads * 4, V - 4));
+      __builtin_amdgcn_sched_barrier(0);         // (all requested first, the next row would need registers of its own)
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < G; ++i) add(l[i], i);
   }
   s = wave_sum(s);
   if (lane == 0) red[w] = s;
   __syncthreads();
   s = 0.f;
   for (int i = 0; i < nw; ++i) s += red[i];
+  __syncthreads();
   m_out = m; s_out = s;
+}
+
+// A block of 256 entries in a wavefront: the lane's four masses, the running sum up to and with them, the last index with mass
+// among them (-1: none).
+struct WalkBlock { int jj, last; float v[4], incl; };
+template <typename F>
+__device__ __forceinline__ WalkBlock walk_block(int jj, int end, F val) {
+  const int lane = threadIdx.x & 63;
+  WalkBlock k;
+  k.jj = jj; k.last = -1;
+  val(jj, end, k.v);
+  float t = 0.f;
+  for (int e = 0; e < 4; ++e) {
+    t += k.v[e];
+    if (k.v[e] > 0.f) k.last = jj + e;
+  }
+  k.incl = t;
+  for (int o = 1; o < 64; o <<= 1) {
+    const float up = __shfl_up(k.incl, o);
+    if (lane >= o) k.incl += up;
+  }
+  return k;
+}
+// The index drawn from a block that some lane's running sum says holds it (hit: those lanes; carry: the mass before the block;
+// prev_mass: the last index with mass before it), by the whole wavefront.
+__device__ __forceinline__ int pick_in_block(const WalkBlock& k, unsigned long long hit, float carry, float target, int prev_mass, int end) {
+  const int lane = threadIdx.x & 63;
+  float excl = __shfl_up(k.incl, 1);
+  if (lane == 0) excl = 0.f;
+  const int fl = __ffsll(hit) - 1;
+  int r = -1;
+  if (lane == fl) {
+    float c2 = carry + excl;
+    for (int e = 0; e < 4; ++e) {
+      c2 += k.v[e];
+      if (r < 0 && k.v[e] > 0.f && c2 > target) r = k.jj + e;
+    }
+    if (r < 0) r = k.last;
+  }
+  r = __shfl(r, fl);
+  if (r < 0) {   // the lane's own walk fell short by rounding and it holds no mass: nearest mass before it
+    int prev = lane < fl ? k.last : -1;
+    for (int o = 32; o > 0; o >>= 1) prev = max(prev, __shfl_xor(prev, o));
+    r = prev >= 0 ? prev : prev_mass;
+    if (r < 0) r = min(k.jj, end - 1);
+    r = __shfl(r, fl);
+  }
+  return r;
 }
 
 // Inverse-CDF draw by a workgroup of kDrawThreads threads.  val(jj, end, v) fills v[0..3] with the
 // masses (>= 0) of indices jj .. jj+3, zero past `end`.
 // Wavefront w owns the contiguous segment [w * seg, (w + 1) * seg); the segment sums give the
-// segment that holds u * total, and that wavefront alone scans its segment in index order.
+// segment that holds u * total, which is scanned in index order in blocks of 256 entries, a block per wavefront (one
+// wavefront alone walked up to 16 blocks, a round trip and a scan each: draw from 64 rows of 32768 entries 12.0 -> 10.5 us,
+// of 65536 20.9 -> 15.0; acceptance over 65536 entries, 8 sequences, k = 1, 42 -> 34).
 // red: kDrawWaves floats, res: one int (both in LDS).  Every thread returns the drawn index, or -1
 // when no entry has mass.
 // draw_walk: the part behind the segment sums (acc: this thread's share of its wavefront's segment); prepare() is called
-// by the whole wavefront that walks, before its first val.
+// by the wavefront that owns the segment, before the first val.
 __device__ __forceinline__ int segment_size(int V) { return ((V + kDrawWaves * 256 - 1) / (kDrawWaves * 256)) * 256; }
 
 template <typename P, typename F>
@@ -197,63 +277,73 @@ __device__ int draw_walk(float acc, P prepare, F val, int V, float u, float* red
       c += red[i];
     }
   }
-  if (w == ws) {
-    prepare();
-    int result = -1;
-    int last_mass = -1;        // last index with mass seen so far (the answer if rounding hides the crossing)
-    float cw = carry;
-    for (int j = j0; j < j1 && result < 0; j += 256) {
-      const int jj = j + lane * 4;
-      float v[4];
-      val(jj, j1, v);
-      float t = 0.f;
-      int lm = -1;
-      for (int e = 0; e < 4; ++e) {
-        t += v[e];
-        if (v[e] > 0.f) lm = jj + e;
-      }
-      float incl = t;
-      for (int o = 1; o < 64; o <<= 1) {
-        const float up = __shfl_up(incl, o);
-        if (lane >= o) incl += up;
-      }
-      float excl = __shfl_up(incl, 1);
-      if (lane == 0) excl = 0.f;
-      const unsigned long long hit = __ballot(cw + incl > target);
-      if (hit != 0ull) {
-        const int fl = __ffsll(hit) - 1;
-        int r = -1;
-        if (lane == fl) {
-          float c2 = cw + excl;
-          for (int e = 0; e < 4; ++e) {
-            c2 += v[e];
-            if (r < 0 && v[e] > 0.f && c2 > target) r = jj + e;
-          }
-          if (r < 0) r = lm;
+  const int s0 = min(V, ws * seg), s1 = min(V, s0 + seg), n_blk = (s1 - s0 + 255) >> 8;
+  int last_mass = -1;        // last index with mass before the block in hand (the answer if rounding hides the crossing)
+  if (n_blk <= 2) {          // (rows of up to 8192 entries: the owner alone, without the two barriers per round below)
+    if (w == ws) {
+      prepare();
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      int result = -1;
+      for (int q = 0; q < n_blk && result < 0; ++q) {
+        const WalkBlock k = walk_block(s0 + q * 256 + lane * 4, s1, val);
+        const unsigned long long hit = __ballot(carry + k.incl > target);
+        if (hit != 0ull) {
+          result = pick_in_block(k, hit, carry, target, last_mass, s1);
+        } else {
+          carry += __shfl(k.incl, 63);
+          const unsigned long long massy = __ballot(k.last >= 0);
+          if (massy != 0ull) last_mass = __shfl(k.last, 63 - __clzll(massy));
         }
-        r = __shfl(r, fl);
-        if (r < 0) {   // the lane's own walk fell short by rounding and it holds no mass: nearest mass before it
-          int prev = lane < fl ? lm : -1;
-          for (int o = 32; o > 0; o >>= 1) prev = max(prev, __shfl_xor(prev, o));
-          r = prev >= 0 ? prev : last_mass;
-          if (r < 0) r = min(jj, j1 - 1);
-          r = __shfl(r, fl);
-        }
-        result = r;
-      } else {
-        cw += __shfl(incl, 63);
-        int blk = lm;
-        for (int o = 32; o > 0; o >>= 1) blk = max(blk, __shfl_xor(blk, o));
-        if (blk >= 0) last_mass = blk;
       }
+      if (result < 0) result = last_mass >= 0 ? last_mass : max(s1 - 1, 0);
+      if (lane == 0) *res = result;
     }
-    if (result < 0) result = last_mass >= 0 ? last_mass : max(j1 - 1, 0);
-    if (lane == 0) *res = result;
+    __syncthreads();
+    const int out = *res;
+    __syncthreads();
+    return out;
   }
+  if (w == ws) prepare();
+  __shared__ float blk_sum[kDrawWaves];      // of the blocks of a round: mass,
+  __shared__ int blk_last[kDrawWaves];       // last index with mass (-1: none),
+  __shared__ int blk_hit[kDrawWaves];        // whether u * total lies in the block
   __syncthreads();
-  const int out = *res;
-  __syncthreads();
-  return out;
+  int first = -1;
+  for (int b0 = 0; b0 < n_blk && first < 0; b0 += kDrawWaves) {
+    WalkBlock k{};
+    k.last = -1;
+    if (b0 + w < n_blk) k = walk_block(s0 + (b0 + w) * 256 + lane * 4, s1, val);      // (uniform over the wavefront)
+    const unsigned long long massy = __ballot(k.last >= 0);
+    if (lane == 63) blk_sum[w] = k.incl;
+    if (lane == (massy != 0ull ? 63 - __clzll(massy) : 0)) blk_last[w] = k.last;
+    __syncthreads();
+    // lane i of every wavefront holds block i's values; the sums are added in block order
+    const float bs = lane < kDrawWaves ? blk_sum[lane] : 0.f;
+    const int bl = lane < kDrawWaves ? blk_last[lane] : -1;
+    float cw = carry;                        // mass before this wavefront's block
+#pragma unroll
+    for (int i = 0; i < kDrawWaves; ++i) {
+      if (i == w) cw = carry;
+      carry += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bs), i));   // (blocks past the segment's end hold nothing)
+    }
+    const unsigned long long hit = __ballot(cw + k.incl > target);
+    if (lane == 0) blk_hit[w] = hit != 0ull && b0 + w < n_blk;
+    __syncthreads();
+    const unsigned long long hits = __ballot(lane < kDrawWaves && blk_hit[lane] != 0);
+    if (hits != 0ull) first = __ffsll(hits) - 1;
+    const unsigned long long with_mass = __ballot(bl >= 0), before = with_mass & ((1ull << w) - 1);
+    const int prev_mass = before != 0ull ? __shfl(bl, 63 - __clzll(before)) : last_mass;
+    if (with_mass != 0ull) last_mass = __shfl(bl, 63 - __clzll(with_mass));
+    if (first == w) {
+      const int r = pick_in_block(k, hit, cw, target, prev_mass, s1);
+      if (lane == 0) *res = r;
+    }
+    __syncthreads();
+  }
+  // (every thread has read the same flags, so that they agree on the branch and on last_mass)
+  return first >= 0 ? *res : last_mass >= 0 ? last_mass : max(s1 - 1, 0);
 }
 
 template <typename F>
@@ -272,12 +362,12 @@ __device__ int block_draw(F val, int V, float u, float* red, int* res) {
 }
 
 // The same for masses in registers: mass[i] holds entries j0 + 256 i + 4 lane .. + 3 of the wavefront's segment, zero past
-// its end (V <= reg_vocab(G): the segment has at most G blocks of 256).  The wavefront that walks its segment puts
-// its masses in LDS first (walk: 256 * G floats) and scans them from there.
+// its end (V <= reg_vocab(G): the segment has at most G blocks of 256).  The wavefront whose segment is scanned puts
+// its masses in LDS first (walk: 256 * G floats).
 template <int G>
 __device__ int block_draw_regs(const float4 (&mass)[G], int V, float u, float* walk, float* red, int* res) {
   const int lane = threadIdx.x & 63;
-  const int j0 = min(V, (int)(threadIdx.x >> 6) * segment_size(V));
+  const int seg = segment_size(V);
   float acc = 0.f;
 #pragma unroll
   for (int i = 0; i < G; ++i) acc += (mass[i].x + mass[i].y) + (mass[i].z + mass[i].w);   // (adding a zero past the end keeps the bits)
@@ -286,12 +376,9 @@ __device__ int block_draw_regs(const float4 (&mass)[G], int V, float u, float* w
       [&] {
 #pragma unroll
         for (int i = 0; i < G; ++i) *reinterpret_cast<float4*>(walk + i * 256 + 4 * lane) = mass[i];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       },
-      [&](int jj, int, float (&v)[4]) {
-        const float4 t = *reinterpret_cast<const float4*>(walk + (jj - j0));
+      [&](int jj, int, float (&v)[4]) {      // (the segment starts at a multiple of its size)
+        const float4 t = *reinterpret_cast<const float4*>(walk + jj % seg);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
       },
       V, u, red, res);
@@ -358,24 +445,46 @@ __global__ __launch_bounds__(kDrawThreads) void sample_rows_kernel(const float* 
 
 // (max, sum) of the k draft rows and the k + 1 verification rows of every sequence:
 // stats[b][r][2], r < kmax: draft row r; r >= kmax: verification row r - kmax.
+// grid: x = rows of a sequence, y = sequences; or (G = kRegGroups) workgroups that take the rows blockIdx.x, blockIdx.x +
+// gridDim.x, ... of all sequences.
 template <int G>
 __global__ __launch_bounds__(kDrawThreads) void softmax_stats_kernel(const float* __restrict__ logits_d,
-                                                            const float* __restrict__ logits_v, int V, int k, int kmax,
+                                                            const float* __restrict__ logits_v, int V, int k, int kmax, int rows,
                                                             const SamplingParams* __restrict__ prm_dev,
                                                             const SamplingParams prm_val, float* __restrict__ stats) {
   __shared__ float red[kDrawWaves];
-  const int r = blockIdx.x, b = blockIdx.y;
-  const float* row;
-  int slot;
-  if (r < k) { row = logits_d + (static_cast<size_t>(b) * kmax + r) * V; slot = r; }
-  else { row = logits_v + (static_cast<size_t>(b) * (k + 1) + (r - k)) * V; slot = kmax + (r - k); }
-  float m, s;
   const float inv_t = prm_dev ? prm_dev->inv_t : prm_val.inv_t;
-  if constexpr (G > 0) row_stats_regs<G>(row, V, inv_t, red, m, s);
-  else row_stats(row, V, inv_t, red, m, s);
-  if (threadIdx.x == 0) {
-    float* st = stats + (static_cast<size_t>(b) * (2 * kmax + 1) + slot) * 2;
+  auto row_at = [&](int b, int r) -> const float* {
+    return r < k ? logits_d + (static_cast<size_t>(b) * kmax + r) * V : logits_v + (static_cast<size_t>(b) * (k + 1) + (r - k)) * V;
+  };
+  auto store = [&](int b, int r, float m, float s) {
+    if (threadIdx.x != 0) return;
+    float* st = stats + (static_cast<size_t>(b) * (2 * kmax + 1) + (r < k ? r : kmax + (r - k))) * 2;
     st[0] = m; st[1] = s;
+  };
+  float m, s;
+  if constexpr (G == kRegGroups) {
+    const int per = 2 * k + 1;
+    int i = blockIdx.x, b = i / per, r = i - b * per;
+    float4 l[G];
+    load_groups(row_at(b, r), V, threadIdx.x * 4, kDrawThreads * 4, l);
+    while (true) {
+      const int i1 = i + gridDim.x, b1 = i1 / per, r1 = i1 - b1 * per;
+      row_stats_regs<G>(l, i1 < rows ? row_at(b1, r1) : nullptr, V, inv_t, red, m, s);
+      store(b, r, m, s);
+      if (i1 >= rows) break;
+      i = i1; b = b1; r = r1;
+    }
+  } else {
+    const float* row = row_at(blockIdx.y, blockIdx.x);
+    if constexpr (G > 0) {
+      float4 l[G];
+      load_groups(row, V, threadIdx.x * 4, kDrawThreads * 4, l);
+      row_stats_regs<G>(l, nullptr, V, inv_t, red, m, s);
+    } else {
+      row_stats(row, V, inv_t, red, m, s);
+    }
+    store(blockIdx.y, blockIdx.x, m, s);
   }
 }
 
@@ -392,7 +501,7 @@ __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float*
   __shared__ float red[kDrawWaves];
   __shared__ int res;
   __shared__ int n_sh;
-  __shared__ __align__(16) float walk[G > 0 ? 256 * G : 4];
+  __shared__ __align__(16) float walk[G > 0 && G <= 8 ? 256 * G : 4];
   const int b = blockIdx.x;
   const SamplingParams prm = prm_dev ? *prm_dev : prm_val;
   const float inv_t = prm.inv_t;
@@ -429,7 +538,59 @@ __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float*
   int tok;
   const float* ls = rows_d + static_cast<size_t>(n < k ? n : 0) * V;
   const float ms = n < k ? st[2 * n] : 0.f, rss = n < k ? 1.0f / st[2 * n + 1] : 0.f;
-  if constexpr (G > 0) {
+  auto residual = [&](const float4& a, const float4& e) {
+    return make_float4(residual_mass(prob(a.x, mh, inv_t, rsh), prob(e.x, ms, inv_t, rss)), residual_mass(prob(a.y, mh, inv_t, rsh), prob(e.y, ms, inv_t, rss)),
+                       residual_mass(prob(a.z, mh, inv_t, rsh), prob(e.z, ms, inv_t, rss)), residual_mass(prob(a.w, mh, inv_t, rsh), prob(e.w, ms, inv_t, rss)));
+  };
+  if constexpr (G > 8) {
+    // Rows that would fill the registers: only the sums are kept, over chunks of 4 blocks of the segment with the next chunk
+    // requested ahead of the exponentials of this one; the blocks of the segment that is scanned are read again.
+    constexpr int CB = 4, NC = G / CB;
+    const int lane = threadIdx.x & 63, seg = segment_size(V), j0 = min(V, (int)(threadIdx.x >> 6) * seg), j1 = min(V, j0 + seg);
+    float acc = 0.f;
+    auto add = [&](const float4& v, int i) {
+      if (j0 + i * 256 + 4 * lane < j1) acc += (v.x + v.y) + (v.z + v.w);
+    };
+    auto one = [&](const float4& a) {
+      return make_float4(expf((a.x - mh) * inv_t), expf((a.y - mh) * inv_t), expf((a.z - mh) * inv_t), expf((a.w - mh) * inv_t));
+    };
+    float4 a[2][CB], e[2][CB];
+    if (n < k) {
+      load_groups(lh, V, j0 + 4 * lane, 256, a[0]);
+      load_groups(ls, V, j0 + 4 * lane, 256, e[0]);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (c + 1 < NC) {
+          load_groups(lh, V, j0 + (c + 1) * CB * 256 + 4 * lane, 256, a[(c + 1) & 1]);
+          load_groups(ls, V, j0 + (c + 1) * CB * 256 + 4 * lane, 256, e[(c + 1) & 1]);
+        }
+#pragma unroll
+        for (int q = 0; q < CB; ++q) add(residual(a[c & 1][q], e[c & 1][q]), c * CB + q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      load_groups(lh, V, j0 + 4 * lane, 256, a[0]);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (c + 1 < NC) load_groups(lh, V, j0 + (c + 1) * CB * 256 + 4 * lane, 256, a[(c + 1) & 1]);
+#pragma unroll
+        for (int q = 0; q < CB; ++q) add(one(a[c & 1][q]), c * CB + q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    tok = draw_walk(
+        acc, [] {},
+        [&](int jj, int end, float(&v)[4]) {
+          const int at = min(jj, V - 4);
+          const float4 x = *reinterpret_cast<const float4*>(lh + at);
+          float4 t;
+          if (n < k) t = residual(x, *reinterpret_cast<const float4*>(ls + at));
+          else t = one(x);
+          const bool on = jj < end;              // (a group of 4 is inside the segment or outside)
+          v[0] = on ? t.x : 0.f; v[1] = on ? t.y : 0.f; v[2] = on ? t.z : 0.f; v[3] = on ? t.w : 0.f;
+        },
+        V, u, red, &res);
+  } else if constexpr (G > 0) {
     const int lane = threadIdx.x & 63, seg = segment_size(V), j0 = min(V, (int)(threadIdx.x >> 6) * seg), j1 = min(V, j0 + seg);
     float4 l[G];
     load_groups(lh, V, j0 + 4 * lane, 256, l);
@@ -443,10 +604,7 @@ __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float*
         for (int q = 0; q < GB; ++q) {
           const float4 a = l[g0 + q], e = c[q];
           const bool on = j0 + (g0 + q) * 256 + 4 * lane < j1;
-          l[g0 + q] = on ? make_float4(residual_mass(prob(a.x, mh, inv_t, rsh), prob(e.x, ms, inv_t, rss)),
-                                       residual_mass(prob(a.y, mh, inv_t, rsh), prob(e.y, ms, inv_t, rss)),
-                                       residual_mass(prob(a.z, mh, inv_t, rsh), prob(e.z, ms, inv_t, rss)),
-                                       residual_mass(prob(a.w, mh, inv_t, rsh), prob(e.w, ms, inv_t, rss)))
+          l[g0 + q] = on ? residual(a, e)
                          : make_float4(0.f, 0.f, 0.f, 0.f);
         }
       }
@@ -552,15 +710,20 @@ hipError_t launch_spec_targets(const float* logits_d, const float* logits_v, int
                                const SamplingParams* prm, SamplingParams prm_val, float* stats, const int* drafts,
                                const int* committed, int* targets, hipStream_t s) {
   const int groups = reg_groups(logits_d, logits_v, V, V);
+  // Rows that fill the registers leave a compute unit one workgroup: as many of them as compute units, each with several rows,
+  // the next one requested behind the exponentials of this one.  Shorter rows share compute units, a workgroup each.
+  const long rows = (long)B * (2 * k + 1);
+  if (rows > 0x7fffffffL) return hipErrorInvalidValue;
+  const dim3 stat_blocks = groups == kRegGroups ? dim3((unsigned)(rows < 256 ? rows : 256)) : dim3(2 * k + 1, B);
 #define HH_CALL(G)                                                                                                               \
-  hipLaunchKernelGGL((softmax_stats_kernel<G>), dim3(2 * k + 1, B), dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, prm, \
+  hipLaunchKernelGGL((softmax_stats_kernel<G>), stat_blocks, dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, (int)rows, prm, \
                      prm_val, stats)
   HH_REG_GROUPS(groups, HH_CALL)
 #undef HH_CALL
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 #define HH_CALL(G)                                                                                                          \
-  hipLaunchKernelGGL((spec_targets_kernel<(G) <= 8 ? (G) : 0>), dim3(B), dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, prm, prm_val, \
+  hipLaunchKernelGGL((spec_targets_kernel<G>), dim3(B), dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, prm, prm_val, \
                      stats, drafts, committed, targets)
   HH_REG_GROUPS(groups, HH_CALL)
 #undef HH_CALL

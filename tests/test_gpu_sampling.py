@@ -179,3 +179,41 @@ def test_rows_in_registers_equal_rows_in_memory(vocab):
                        B.hh_draw_tokens(shifted(rows), t, seed, positions=positions))
     assert torch.equal(B.hh_accept_tokens(draft.contiguous(), verify, drafts, positions, t, seed),
                        B.hh_accept_tokens(shifted(draft), shifted(verify), drafts, positions, t, seed))
+
+
+@pytest.mark.parametrize("vocab", [32772, 65536])
+def test_statistics_of_more_rows_than_workgroups(vocab):
+    """Rows that fill the registers: 256 workgroups take all rows in turn, the next one requested behind the sums of this one
+    (41 sequences, k = 3: 287 rows, 31 workgroups with a second one), against the kernels that read memory again."""
+    import torch
+    from paper_2605_01106_amd import binding as B
+    batch, k, t, seed = 41, 3, 0.7, 5
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    verify = torch.randn((batch, k + 1, vocab), generator=g, device="cuda") * 3
+    draft = verify[:, :k] + torch.randn((batch, k, vocab), generator=g, device="cuda") * 0.7
+    drafts = draft.argmax(-1).to(torch.int32).contiguous()
+    positions = torch.arange(batch, device="cuda", dtype=torch.int32) * 5
+    buf = torch.empty(verify.numel() + 1, device="cuda", dtype=torch.float32)
+    buf[1:] = verify.reshape(-1)
+    assert torch.equal(B.hh_accept_tokens(draft.contiguous(), verify, drafts, positions, t, seed),
+                       B.hh_accept_tokens(draft.contiguous(), buf[1:].view(verify.shape), drafts, positions, t, seed))
+
+
+@pytest.mark.parametrize("vocab", [7, 1000, 8192, 8196, 20000, 32768, 65536, 65539, 150000])
+def test_draws_at_block_and_segment_edges(B, vocab):
+    """A row with one entry of mass returns it and a row with two equal ones the one its uniform selects, wherever they lie:
+    first and last entry of the row, of a 256-entry block, of a wavefront's segment, with everything between them empty; up to
+    two blocks per segment, up to 16 and more than 16 (two rounds of blocks)."""
+    import torch
+    seg = (vocab + 4095) // 4096 * 256
+    edges = sorted({p for p in (0, 1, 255, 256, 511, 512, seg - 1, seg, 2 * seg - 1, 2 * seg, 15 * seg - 1, 15 * seg, vocab - 2, vocab - 1,
+                                seg // 2, vocab // 2 + 3) if 0 <= p < vocab})
+    rows = [(p, p) for p in edges] + list(zip(edges[:-1], edges[1:])) + [(edges[0], edges[-1])]
+    logits = torch.full((len(rows), vocab), -1e30, device="cuda")
+    for r, (i, j) in enumerate(rows):
+        logits[r, i] = 1.5
+        logits[r, j] = 1.5
+    for seed in (3, 4, 5):
+        got = B.hh_draw_tokens(logits, 1.0, seed).tolist()
+        want = [i if S.uniform(seed, r, 0, 2) < 0.5 else j for r, (i, j) in enumerate(rows)]
+        assert got == want
