@@ -82,7 +82,8 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
   const int* pt_row = a.page_table + (size_t)b * d.pages_per_seq;
   const float scale = 1.0f / sqrtf((float)Dh);
   const float2* rope = reinterpret_cast<const float2*>(a.rope);
-  const float* xrow = a.qkv + (size_t)b * a.T * d.ldzx;   // q | k | v of this sequence's positions
+  const size_t rows0 = first_row(a.row0, b, a.T);
+  const float* xrow = a.qkv + rows0 * d.ldzx;   // q | k | v of this sequence's positions
   const size_t esz = BF16 ? 2 : 4;
   const char* kbytes = static_cast<const char*>(a.kpool);
   const char* vbytes = static_cast<const char*>(a.vpool);
@@ -305,8 +306,8 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
 #pragma unroll
     for (int r = 0; r < kRowsPerWave; ++r) {
       const int rg = row0 + wave * kRowsPerWave + r;
-      if (rg >= n_rows) continue;
-      const size_t mrow = (size_t)b * a.T + rj[r];
+      if (rg >= (a.row0 != nullptr ? row_lim : n_rows)) continue;   // (packed rows: what follows is the next sequence's)
+      const size_t mrow = rows0 + rj[r];
       const float inv = (rok[r] && lrun[r] > 0.f) ? 1.0f / lrun[r] : 0.f;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
@@ -434,7 +435,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const Dims d, const Attn
   if (j >= nt) return;
   const int pos = a.pos0[b] + j;
   const int Dh = d.Dh, half = Dh >> 1;
-  const float* krow = a.qkv + (size_t)m * d.ldzx + d.dq;
+  const float* krow = a.qkv + (first_row(a.row0, b, a.T) + j) * d.ldzx + d.dq;
   const float* vrow = krow + d.dkv;
   const int* pt_row = a.page_table + (size_t)b * d.pages_per_seq;
   const float2* cs = reinterpret_cast<const float2*>(a.rope) + (size_t)pos * half;
@@ -472,7 +473,7 @@ __global__ __launch_bounds__(256) void kv_append8_kernel(const Dims d, const Att
   if (nt <= 0 || p_first >= pos0 + nt) return;
   const int Dh = d.Dh, half = Dh >> 1;
   const int* pt_row = a.page_table + (size_t)b * d.pages_per_seq;
-  const float* rows = a.qkv + (size_t)b * a.T * d.ldzx + d.dq;   // row j: k | v of position pos0 + j
+  const float* rows = a.qkv + first_row(a.row0, b, a.T) * d.ldzx + d.dq;   // row j: k | v of position pos0 + j
   const bool whole = p_first >= pos0 && p_first + 8 <= pos0 + nt;
   uint16_t* vpool = static_cast<uint16_t*>(a.vpool);
   for (int it = threadIdx.x; it < d.Hkv * Dh; it += 256) {
@@ -511,7 +512,7 @@ bool attention_uses_mfma(const Dims& d) {
 }
 
 hipError_t launch_attention(const Dims& d, const AttnArgs& a, hipStream_t s) {
-  if (d.Dh > kMaxDh || d.Dh % 8 != 0 || a.n_splits > 64 || a.n_splits < 1 || a.T < 1 || a.B < 1) return hipErrorInvalidValue;
+  if (d.Dh > kMaxDh || d.Dh % 8 != 0 || a.n_splits > 64 || a.n_splits < 1 || a.T < 1 || a.B < 1 || (a.row0 != nullptr && a.n_splits != 1)) return hipErrorInvalidValue;
   if (attention_uses_mfma(d)) {
     if (!attention_mfma_fuses_append(d, a.T)) {
       if (a.T >= 16 && d.page_tokens % 8 == 0) {

@@ -99,6 +99,7 @@ __device__ __forceinline__ void attn_mfma_body(const Dims& d, const AttnArgs& a,
   const int n_rows = a.T * G;
   const int row_lim = min(n_rows, nt * G);     // row = position j * G + query head of the group; valid while j < nt
   const int row0 = chunk * R;
+  if (a.row0 != nullptr && row0 >= row_lim) return;   // packed rows: no row of this chunk exists (the whole workgroup leaves)
   const int jmax = row0 < row_lim ? (min(row_lim, row0 + R) - 1) / G : -1;
   const int nk_all = jmax < 0 ? 0 : pos0 + jmax + 1;      // keys 0 .. nk_all-1 are visible to some row of this chunk
   const int nk = FUSE ? min(nk_all, pos0) : nk_all;       // ... of which the cache holds 0 .. nk-1
@@ -106,7 +107,8 @@ __device__ __forceinline__ void attn_mfma_body(const Dims& d, const AttnArgs& a,
   const int pshift = 31 - __clz(d.page_tokens), pmask = d.page_tokens - 1;
   const uint16_t* kp = static_cast<const uint16_t*>(a.kpool);
   const uint16_t* vp = static_cast<const uint16_t*>(a.vpool);
-  const float* xrow = a.qkv + (size_t)b * a.T * d.ldzx;
+  const size_t rows0 = first_row(a.row0, b, a.T);
+  const float* xrow = a.qkv + rows0 * d.ldzx;
   const bool al4 = (d.ldzx & 3) == 0 && (reinterpret_cast<uintptr_t>(xrow) & 15) == 0;   // 16-byte aligned rows (dq, Dh are multiples of 8)
 
   // key steps of this workgroup and of this wavefront
@@ -501,11 +503,11 @@ __device__ __forceinline__ void attn_mfma_body(const Dims& d, const AttnArgs& a,
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       const int rr = row0 + rt * 16 + n;
-      if (rr >= n_rows) continue;
+      if (rr >= (a.row0 != nullptr ? row_lim : n_rows)) continue;   // (packed rows: what follows is the next sequence's)
       const int j = rr / G, hq = kvh * G + rr % G;
       if (S == 1) {
         const float inv = (rr < row_lim && lrun[rt] > 0.f) ? 1.0f / lrun[rt] : 0.f;
-        float* orow = a.o + ((size_t)b * a.T + j) * d.dq + (size_t)hq * Dh;
+        float* orow = a.o + (rows0 + j) * d.dq + (size_t)hq * Dh;
 #pragma unroll
         for (int db = 0; db < NDB; ++db) {
           const int dim = db * 16 + 4 * g;

@@ -67,7 +67,7 @@ struct hh_ctx {
   bool draft_has_full = false;
   // device int state
   int *kv_len, *committed, *last_n, *pending, *n_acc, *skip, *adv, *drafts, *targets, *pos0, *out_tok,
-      *page_table, *plan_ntok, *plan_last, *first_tok;
+      *page_table, *prefill_plan, *first_tok;
   unsigned long long* best;
   unsigned long long* acc_stats;   // accepted / tested drafts since the last prefill
   SamplingParams* sampling;   // temperature and seed read by the drawing kernels
@@ -201,8 +201,7 @@ size_t carve(hh_ctx* x, char* base) {
   x->page_table = c.take<int>(B * d.pages_per_seq);
   const int chunk = prefill_chunk_of(x->cfg);
   x->max_passes = (d.max_seq + chunk - 1) / chunk;
-  x->plan_ntok = c.take<int>((size_t)x->max_passes * B);
-  x->plan_last = c.take<int>((size_t)x->max_passes * B);
+  x->prefill_plan = c.take<int>(3 * (size_t)x->max_passes * B);
   x->best = c.take<unsigned long long>(Mv * gemv_max_blocks());
   x->acc_stats = c.take<unsigned long long>(2);
   x->sampling = c.take<SamplingParams>(1);
@@ -361,15 +360,19 @@ bool branch_overlap(const hh_ctx* x, int B, int T, bool prefill) {
   return prefill;
 }
 
-// ---- one pass of the block stack over M = B*T rows.  all_full: M_H (both branches of every
+// Rows of a prefill pass over prompts of unequal length: only the positions that exist, sequence behind sequence.
+struct PackedRows { const int* row0; int rows; };   // row0[b]: first row of sequence b (device memory)
+
+// ---- one pass of the block stack over M = B*T rows (packed != nullptr: over packed->rows).  all_full: M_H (both branches of every
 // block, Eq. 2); otherwise M_S (Eq. 4), or, with `modes` (one HH_DRAFT_* per layer), the draft
 // model in which a layer keeps both branches, only its SSM branch, or is passed over whole
 // (identity on the residual stream, Eq. 5 applied to the block).  table: the layers with the
 // recurrent state and ring this pass works on.
 hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_full, const int* modes, int B, int T,
-                     const int* n_tok, int state_in, int state_out, int n_splits, bool prefill, hipStream_t s) {
+                     const int* n_tok, const PackedRows* packed, int state_in, int state_out, int n_splits, bool prefill, hipStream_t s) {
   const Dims& d = x->d;
-  const int M = B * T;
+  const int M = packed != nullptr ? packed->rows : B * T;
+  const int* row0 = packed != nullptr ? packed->row0 : nullptr;
   for (int l = 0; l < d.L; ++l) {
     const int mode = all_full ? HH_DRAFT_FULL : (modes ? modes[l] : HH_DRAFT_SSM);
     if (mode == HH_DRAFT_SKIP) continue;
@@ -395,13 +398,13 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
     }
     SsmArgs scan{};   // conv + selective scan -> y * silu(z)
     scan.layers = nullptr; scan.one = w; scan.layer0 = 0; scan.n_layers_z = 1;
-    scan.zx = x->zx; scan.g = x->g; scan.pos0 = x->pos0; scan.n_tok = n_tok; scan.T = T; scan.B = B;
+    scan.zx = x->zx; scan.g = x->g; scan.pos0 = x->pos0; scan.n_tok = n_tok; scan.row0 = row0; scan.T = T; scan.B = B;
     scan.state_in = state_in; scan.state_out = state_out; scan.write_ring = 1; scan.seg_scratch = x->seg_scratch;
     bool scanned = false;
     GemvArgs o_proj{};
     if (full) {
       AttnArgs a{};
-      a.kpool = w.kpool; a.vpool = w.vpool; a.qkv = x->qkv; a.o = x->o; a.pos0 = x->pos0; a.n_tok = n_tok;
+      a.kpool = w.kpool; a.vpool = w.vpool; a.qkv = x->qkv; a.o = x->o; a.pos0 = x->pos0; a.n_tok = n_tok; a.row0 = row0;
       a.page_table = x->page_table; a.rope = x->rope; a.part_o = x->part_o; a.part_ml = x->part_ml;
       a.counters = x->attn_counters;
       a.T = T; a.B = B; a.n_splits = n_splits;
@@ -579,7 +582,7 @@ hh_status ms_consume(hh_ctx* x, int B, int first, int last, hipStream_t s) {
   const Dims& d = x->d;
   for (int i = first; i <= last; ++i) {
     HH_HIP(launch_begin_pass(pass_args(x, PASS_DRAFT, 1, i), B, s));
-    const hh_status st = run_layers(x, x->layers_ms_host, false, nullptr, B, 1, nullptr, i == 0 ? 0 : 1, i == last ? 0 : 2, 1, false, s);
+    const hh_status st = run_layers(x, x->layers_ms_host, false, nullptr, B, 1, nullptr, nullptr, i == 0 ? 0 : 1, i == last ? 0 : 2, 1, false, s);
     if (st != HH_OK) return st;
   }
   return HH_OK;
@@ -767,36 +770,45 @@ hh_status hh_prefill(hh_ctx* x, const int32_t* tokens, int32_t row_stride, const
         if (got[b] < need[b]) x->h_page_table[(size_t)b * d.pages_per_seq + got[b]++] = next++;
     if (next > d.n_pages) return fail(x, HH_ECAPACITY, "hh_prefill: KV page pool exhausted");
   }
-  x->h_plan.assign((size_t)2 * n_pass * B, 0);
+  x->h_plan.assign((size_t)3 * n_pass * B, 0);   // per pass: positions, whether they are the last ones, first row
+  std::vector<int> pass_rows(n_pass, 0);
   for (int p = 0; p < n_pass; ++p)
     for (int b = 0; b < B; ++b) {
       int nt = lens[b] - p * chunk;
       nt = nt < 0 ? 0 : (nt > chunk ? chunk : nt);
       x->h_plan[(size_t)p * B + b] = nt;
       x->h_plan[(size_t)(n_pass + p) * B + b] = (nt > 0 && lens[b] <= (p + 1) * chunk) ? 1 : 0;
+      x->h_plan[(size_t)(2 * n_pass + p) * B + b] = pass_rows[p];
+      pass_rows[p] += nt;
     }
   HH_HIP(hipMemcpyAsync(x->page_table, x->h_page_table.data(), x->h_page_table.size() * sizeof(int), hipMemcpyHostToDevice, s));
-  HH_HIP(hipMemcpyAsync(x->plan_ntok, x->h_plan.data(), (size_t)n_pass * B * sizeof(int), hipMemcpyHostToDevice, s));
-  HH_HIP(hipMemcpyAsync(x->plan_last, x->h_plan.data() + (size_t)n_pass * B, (size_t)n_pass * B * sizeof(int), hipMemcpyHostToDevice, s));
+  HH_HIP(hipMemcpyAsync(x->prefill_plan, x->h_plan.data(), x->h_plan.size() * sizeof(int), hipMemcpyHostToDevice, s));
   HH_HIP(launch_fill_i32(x->kv_len, 0, B, s));
   HH_HIP(launch_fill_i32(x->committed, 0, B, s));
   HH_HIP(launch_fill_i32(reinterpret_cast<int*>(x->acc_stats), 0, 4, s));
 
   for (int p = 0; p < n_pass; ++p) {
     const int T = maxlen - p * chunk < chunk ? maxlen - p * chunk : chunk;
-    const int* nt = x->plan_ntok + (size_t)p * B;
+    const int* nt = x->prefill_plan + (size_t)p * B;
+    const int* is_last = nt + (size_t)n_pass * B;
+    // Prompts of unequal length: a pass computes the rows of the positions that exist and no others (of 64 prompts of 224 to
+    // 448 tokens a quarter of batch x positions lies behind a prompt's end).  Passes of up to 16 positions keep batch x
+    // positions rows: the kernels for few positions index them so, and there is little to leave out.
+    const PackedRows rows{is_last + (size_t)n_pass * B, pass_rows[p]};
+    const PackedRows* packed = T > 16 && rows.rows < B * T ? &rows : nullptr;
     PassArgs begin = pass_args(x, PASS_PROMPT, T, 0);
     begin.prompt = tokens; begin.row_stride = row_stride; begin.off = p * chunk; begin.n_tok = nt;
+    begin.row0 = packed != nullptr ? packed->row0 : nullptr;
     HH_HIP(launch_begin_pass(begin, B, s));
     hh_status st = HH_OK;
     if (x->strict) {   // M_S over the same positions first, into its own state and ring (Eq. 4 at every prefix position)
-      st = run_layers(x, x->layers_ms_host, false, nullptr, B, T, nt, p == 0 ? 2 : 0, 1, 1, true, s);
+      st = run_layers(x, x->layers_ms_host, false, nullptr, B, T, nt, packed, p == 0 ? 2 : 0, 1, 1, true, s);
       if (st != HH_OK) return st;
       HH_HIP(launch_begin_pass(begin, B, s));
     }
-    st = run_layers(x, x->layers_host, true, nullptr, B, T, nt, p == 0 ? 2 : 0, 1, 1, true, s);
+    st = run_layers(x, x->layers_host, true, nullptr, B, T, nt, packed, p == 0 ? 2 : 0, 1, 1, true, s);
     if (st != HH_OK) return st;
-    HH_HIP(launch_prefill_tail(x->h, T, d.D, nt, x->plan_last + (size_t)p * B, x->lasth, x->kv_len, B, s));
+    HH_HIP(launch_prefill_tail(x->h, T, d.D, nt, begin.row0, is_last, x->lasth, x->kv_len, B, s));
     // cfg.prefill_progress = n: wait for every n-th pass and report it (long prompts; otherwise the call only enqueues)
     const int progress = x->cfg.prefill_progress;
     if (progress > 0 && (p + 1) % progress == 0) {
@@ -908,7 +920,7 @@ hh_status hh_draft(hh_ctx* x, int32_t k, void* stream) {
       if (i == 0 || stochastic) HH_HIP(launch_begin_pass(pass_args(x, PASS_DRAFT, 1, i), B, s));
       // the scratch state after the last step is never read (unless M_S goes on to consume d_k): not written
       const int state_out = (i == k - 1 && !x->strict) ? 0 : 2;
-      hh_status st = run_layers(x, table, false, modes, B, 1, nullptr, i == 0 ? 0 : 1, state_out, splits, false, s);
+      hh_status st = run_layers(x, table, false, modes, B, 1, nullptr, nullptr, i == 0 ? 0 : 1, state_out, splits, false, s);
       if (st != HH_OK) return st;
       const PassArgs next = pass_args(x, PASS_DRAFT, 1, i + 1);
       st = run_head(x, x->h, B, 1, x->logits_d + (size_t)i * d.V, d.Kmax * d.V, x->drafts, d.Kmax, i, i + 1 < k ? &next : nullptr, s);
@@ -1010,7 +1022,7 @@ hh_status hh_verify(hh_ctx* x, void* stream) {
   const int splits = pick_splits(x->cfg, d, B, T, x->len_upper);
   auto enqueue = [&]() -> hh_status {
     HH_HIP(launch_begin_pass(pass_args(x, PASS_VERIFY, T, 0), B, s));
-    hh_status st = run_layers(x, x->layers_host, true, nullptr, B, T, nullptr, 0, 0, splits, false, s);
+    hh_status st = run_layers(x, x->layers_host, true, nullptr, B, T, nullptr, nullptr, 0, 0, splits, false, s);
     if (st != HH_OK) return st;
     st = run_head(x, x->h, B * T, T, x->logits_v, d.V, x->targets, d.Kmax + 1, 0, nullptr, s);
     if (st != HH_OK) return st;
@@ -1261,7 +1273,7 @@ hh_status hh_time_kind(hh_ctx* x, int32_t phase, int32_t kind, int32_t k, int32_
                       full ? x->targets : x->drafts, full ? d.Kmax + 1 : d.Kmax, 0, nullptr, s);
         n += 1;
       } else {
-        st = run_layers(x, x->layers_host, full, nullptr, B, T, nullptr, 0, full ? 0 : 2, pick_splits(x->cfg, d, B, T, x->len_upper), false, s);
+        st = run_layers(x, x->layers_host, full, nullptr, B, T, nullptr, nullptr, 0, full ? 0 : 2, pick_splits(x->cfg, d, B, T, x->len_upper), false, s);
         n += d.L;
       }
     }

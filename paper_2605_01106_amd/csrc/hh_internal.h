@@ -109,6 +109,7 @@ struct SsmArgs {
   float* g;            // [B*T][d_inner]  y * silu(z)  (nullptr: no output)
   const int* pos0;     // [B] position of the first token of this pass
   const int* n_tok;    // [B] valid positions (<= T); nullptr: T for all
+  const int* row0;     // [B] first row of each sequence in zx and g; nullptr: b * T (passes of more than 16 positions only)
   const int* n_acc;    // [B] rebuild mode: positions = n_acc[b] + 1
   const int* skip;     // [B] nonzero: leave this sequence untouched (may be nullptr)
   int T, B;
@@ -132,6 +133,7 @@ struct AttnArgs {
   const float* qkv;       // [B*T][ldzx] (offset to the q column): raw q | k | v of this pass
   float* o;               // [B*T][dq]
   const int* pos0; const int* n_tok; const int* page_table;  // [B], [B], [B][pages_per_seq]
+  const int* row0;        // [B] first row of each sequence in qkv and o; nullptr: b * T (one key slice only)
   const float* rope;      // [max_seq][Dh/2][2] (cos, sin)
   float* part_o; float* part_ml;  // split scratch: [B*T*Hq][S][Dh], [B*T*Hq][S][2]
   int* counters;          // [B][Hkv][row chunks], zero between launches: tickets of the key slices
@@ -155,6 +157,11 @@ bool branches_fit(const Dims& d, int B, int T);
 int branches_scan_blocks(const Dims& d, int B, int T);   // workgroups of the scan there
 bool launch_branches(const Dims& d, const AttnArgs& at, const SsmArgs& ss, hipStream_t s, hipError_t* err);
 
+// First row of sequence b in the buffers of a pass: b * T, or, in a prefill pass over prompts of unequal length, where the rows
+// of the sequences before it end (only positions that exist have a row; then row0[b] + T <= (b + 1) * T, so that a read of up to T
+// rows stays in the buffer, but a write past the valid positions would hit the next sequence).
+__device__ __forceinline__ size_t first_row(const int* row0, int b, int T) { return row0 != nullptr ? (size_t)row0[b] : (size_t)b * T; }
+
 // ---- small kernels
 // first launch of a pass: tokens, embedding, positions, cleared argmax keys (see begin_pass_kernel)
 enum { PASS_DRAFT = 0, PASS_VERIFY = 1, PASS_PROMPT = 2 };
@@ -164,6 +171,7 @@ struct PassArgs {
   const int *pending, *drafts, *prompt, *n_tok, *kv_len;
   int* pos0;
   int kmax, T, mode, step, row_stride, off;
+  const int* row0;                             // PASS_PROMPT: [B] first row of each sequence in h, its n_tok rows alone; nullptr: b * T
   unsigned long long* clear;                   // [B*T] keys to clear, or nullptr
 };
 hipError_t launch_begin_pass(const PassArgs& a, int B, hipStream_t s);
@@ -177,7 +185,7 @@ struct CommitArgs {
 };
 hipError_t launch_accept(const CommitArgs& a, hipStream_t s);
 hipError_t launch_advance(int* kv_len, const int* n, int B, hipStream_t s);
-hipError_t launch_prefill_tail(const float* h, int T, int D, const int* n_tok, const int* is_last, float* lasth,
+hipError_t launch_prefill_tail(const float* h, int T, int D, const int* n_tok, const int* row0, const int* is_last, float* lasth,
                                int* kv_len, int B, hipStream_t s);
 hipError_t launch_prefill_finish(const int* first_tok, int* pending, int* out_tok, int out_stride, int* committed,
                                  int* last_n, int B, hipStream_t s);

@@ -32,7 +32,7 @@ __device__ __forceinline__ void embed_row(const void* embed, int bf16, int tok, 
 // sequence's first row, and a cleared argmax key of the row (the many-row LM heads raise them with atomic maxima).
 //   PASS_DRAFT   draft step `step`: pending[b] at step 0, else drafts[b][step-1]; position kv_len[b] + step
 //   PASS_VERIFY  pending[b], drafts[b][j-1]; position kv_len[b]
-//   PASS_PROMPT  prompt[b][off + j] for j < n_tok[b] (token 0 beyond); position kv_len[b]
+//   PASS_PROMPT  prompt[b][off + j] for j < n_tok[b] (token 0 beyond, or no row at all: row0); position kv_len[b]
 __global__ __launch_bounds__(256) void begin_pass_kernel(const PassArgs a) {
   const int m = blockIdx.x, b = m / a.T, j = m - b * a.T;
   int tok;
@@ -43,7 +43,8 @@ __global__ __launch_bounds__(256) void begin_pass_kernel(const PassArgs a) {
     if (j == 0) a.pos0[b] = a.kv_len[b] + (a.mode == PASS_DRAFT ? a.step : 0);
     if (a.clear != nullptr) a.clear[m] = 0ull;
   }
-  embed_row(a.embed, a.bf16, tok, a.D, a.V, a.h + (size_t)m * a.D);
+  if (a.row0 != nullptr && j >= a.n_tok[b]) return;
+  embed_row(a.embed, a.bf16, tok, a.D, a.V, a.h + (first_row(a.row0, b, a.T) + j) * a.D);
 }
 
 hipError_t launch_begin_pass(const PassArgs& a, int B, hipStream_t s) {
@@ -138,20 +139,20 @@ hipError_t launch_advance(int* kv_len, const int* n, int B, hipStream_t s) {
 
 // After a prefill pass: keep the stream of each sequence's last prompt position (input of the
 // LM head) and advance the cache length by the positions consumed.
-__global__ void prefill_tail_kernel(const float* h, int T, int D, const int* n_tok, const int* is_last, float* lasth,
+__global__ void prefill_tail_kernel(const float* h, int T, int D, const int* n_tok, const int* row0, const int* is_last, float* lasth,
                                     int* kv_len) {
   const int b = blockIdx.x;
   const int nt = n_tok[b];
   if (nt > 0 && is_last[b]) {
-    const float* src = h + ((size_t)b * T + nt - 1) * D;
+    const float* src = h + (first_row(row0, b, T) + nt - 1) * D;
     for (int k = threadIdx.x; k < D; k += blockDim.x) lasth[(size_t)b * D + k] = src[k];
   }
   if (threadIdx.x == 0) kv_len[b] += nt;
 }
 
-hipError_t launch_prefill_tail(const float* h, int T, int D, const int* n_tok, const int* is_last, float* lasth,
+hipError_t launch_prefill_tail(const float* h, int T, int D, const int* n_tok, const int* row0, const int* is_last, float* lasth,
                                int* kv_len, int B, hipStream_t s) {
-  hipLaunchKernelGGL(prefill_tail_kernel, dim3(B), dim3(256), 0, s, h, T, D, n_tok, is_last, lasth, kv_len);
+  hipLaunchKernelGGL(prefill_tail_kernel, dim3(B), dim3(256), 0, s, h, T, D, n_tok, row0, is_last, lasth, kv_len);
   return hipGetLastError();
 }
 

@@ -101,7 +101,8 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
   const int pos0 = a.pos0[b];
   const int rmask = d.ring_slots - 1;
   float* ring = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
-  const float* zx = a.zx + (size_t)b * a.T * d.ldzx;
+  const size_t rows0 = first_row(a.row0, b, a.T);
+  const float* zx = a.zx + rows0 * d.ldzx;
 
   // ---- state slice of this wavefront, transposed: acc[tile][r] = S[16 wq + j][16 tile + 4 g + r]
   ssd_f32x4 S[NT];
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
     for (int tt = 0; tt < 2; ++tt) {
       const int t = 16 * tt + j;
       if (t < tc) {
-        const size_t m = (size_t)b * a.T + j0 + t;
+        const size_t m = rows0 + j0 + t;
         const int p = 16 * wq + 4 * g;
         const float4 xv = *reinterpret_cast<const float4*>(Xs + t * LDX + p);
         const float4 z = *reinterpret_cast<const float4*>(a.zx + m * d.ldzx + h * P + p);

@@ -51,7 +51,8 @@ __global__ __launch_bounds__(kRows * kSub) void ssm_kernel(const Dims d, const S
   const bool prow = p < d.P;
   const int rmask = d.ring_slots - 1;
   const float* ring = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
-  const float* zx = a.zx != nullptr ? a.zx + (size_t)b * a.T * d.ldzx : nullptr;
+  const size_t rows0 = first_row(a.row0, b, a.T);
+  const float* zx = a.zx != nullptr ? a.zx + rows0 * d.ldzx : nullptr;
 
   // raw (pre-conv) input of channel c (c < conv_dim: xBC, else dt of head c - conv_dim) at position pos
   // (one unconditional load from a selected address, so that independent loads overlap)
@@ -148,7 +149,7 @@ __global__ __launch_bounds__(kRows * kSub) void ssm_kernel(const Dims d, const S
       part += dpp_move<0x4E>(part);    // lane ^ 2
       part += dpp_move<0x141>(part);   // the other quad of the 8 lanes that share a row
       if (a.g != nullptr && sub == 0 && prow) {
-        const size_t m = (size_t)b * a.T + j0 + jj;
+        const size_t m = rows0 + j0 + jj;
         const float z = a.zx[m * d.ldzx + h * d.P + p];
         a.g[m * d.d_inner + h * d.P + p] = (part + dskip * xv) * silu_f(z);
       }
@@ -219,7 +220,8 @@ __global__ __launch_bounds__(kRows * kSub + (PIPE ? chunk_stage_threads<NV, kRow
   const bool prow = worker && p < d.P;
   const int rmask = d.ring_slots - 1;
   float* ring = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
-  const float* zx = a.zx != nullptr ? a.zx + (size_t)b * a.T * d.ldzx : nullptr;
+  const size_t rows0 = first_row(a.row0, b, a.T);
+  const float* zx = a.zx != nullptr ? a.zx + rows0 * d.ldzx : nullptr;
   // row of raw inputs (xBC | dt) of position pos (positions < 0 read slot 0 and count as 0)
   auto raw_row = [&](int pos) -> const float* {
     return (zx != nullptr && pos >= pos0) ? zx + (size_t)(pos - pos0) * d.ldzx + d.d_inner
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(kRows * kSub + (PIPE ? chunk_stage_threads<NV, kRow
       part += dpp_move<0x4E>(part);    // lane ^ 2
       part += dpp_move<0x141>(part);   // the other quad of the 8 lanes that share a row
       if (a.g != nullptr && sub == 0 && prow)
-        a.g[((size_t)b * a.T + j0 + jj) * d.d_inner + h * d.P + p] = (part + dskip * xv) * silu_f(zs[buf][jj][row]);
+        a.g[(rows0 + j0 + jj) * d.d_inner + h * d.P + p] = (part + dskip * xv) * silu_f(zs[buf][jj][row]);
     }
   };
 

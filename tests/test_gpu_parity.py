@@ -56,6 +56,25 @@ def test_lively_ragged_batch(B, dtype):
     run_lockstep(ctx, wts, prompts, lens, 24, 3, engine="pass", report=_say(f"lively-{dtype}"))
 
 
+@pytest.mark.parametrize("dtype,heads,p,d_state,head_dim,page,chunk,overlap,lens", [
+    (W.F32, 4, 12, 32, 32, 32, 32, 0, [97, 5, 64, 33, 1]),         # sequences that end with, within and before a pass; last pass of one position
+    (W.BF16, 4, 64, 64, 32, 32, 40, 1, [80, 17, 41, 80, 3]),       # matmul-form scan, both branches on one stream
+    (W.BF16, 3, 40, 16, 24, 16, 17, 0, [17, 34, 20, 9]),           # odd sizes, scalar attention and scan, the shortest packed pass
+    (W.BF16, 4, 64, 128, 64, 64, 320, 0, [300, 40, 200, 96]),      # segmented scan, several row chunks of the attention
+    (W.BF16, 4, 16, 64, 64, 32, 18, 2, [18, 1, 2, 36, 20, 35, 3])])   # last pass of 18 positions, three of seven sequences left
+def test_packed_rows_of_ragged_prompts(B, dtype, heads, p, d_state, head_dim, page, chunk, overlap, lens):
+    """Prefill passes over prompts of unequal length compute only the rows that exist, sequence behind sequence: states,
+    caches, windows and logits of every sequence against the oracle, whatever its neighbours' lengths."""
+    cfg = W.scaled_config("packed", n_layers=2, d_model=72, vocab=180, m_heads=heads, m_head_dim=p, d_state=d_state,
+                          n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=104, w_dtype=dtype)
+    wts = W.make_lively_weights(cfg, 29)
+    prompts = W.make_prompts(cfg.vocab, len(lens), lens, 8)
+    ctx = _ctx(B, wts, len(lens), max(lens) + 40, 2, 8, kv_page_tokens=page, prefill_chunk=chunk, overlap_mode=overlap,
+               kernel_flags=B.HH_KF_CANARIES)
+    run_lockstep(ctx, wts, prompts, lens, 8, 2, engine="pass", report=_say(f"packed-{chunk}"))
+    assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
+
+
 @pytest.mark.parametrize("k", [0, 1, 5])
 def test_draft_lengths_and_plain_greedy(B, k):
     cfg = W.scaled_config("klen", n_layers=2, d_model=64, vocab=128, m_heads=2, m_head_dim=32, d_state=32,
