@@ -427,7 +427,7 @@ static hipError_t launch_ssm_small_t(const Dims& d, const SsmArgs& a, int tmax, 
 }
 
 bool ssm_small_fits(const Dims& d, const SsmArgs& a) {
-  return !(d.flags & HH_KF_SSM_GENERAL) && a.T <= 9 && d.Hm % 4 == 0 && d.P % 4 == 0 && d.N % 32 == 0 && d.ldzx % 4 == 0 && d.d_inner % 4 == 0;
+  return !(d.flags & HH_KF_SSM_GENERAL) && a.T <= 9 && d.Hm % 4 == 0 && d.P % 4 == 0 && (d.N % 32 == 0 || d.N == 16) && d.ldzx % 4 == 0 && d.d_inner % 4 == 0;
 }
 int ssm_small_tmax(int T) { return T <= 1 ? 1 : T <= 3 ? 3 : T <= 5 ? 5 : 9; }
 bool ssm_small_wide(const Dims& d, const SsmArgs& a) {   // 16 lanes per row: twice the wavefronts
@@ -440,6 +440,9 @@ static bool launch_ssm_small(const Dims& d, const SsmArgs& a, hipStream_t s, hip
   if (!ssm_small_fits(d, a)) return false;
   const int tmax = ssm_small_tmax(a.T);
   const bool wide = ssm_small_wide(d, a);
+  // state size 16: 4 lanes share a row (the position-by-position kernel, with its chunk of 16 positions staged in several
+  // round trips, took 5.6 us per launch at the tiny float32 model)
+  if (d.N == 16) { *err = launch_ssm_small_t<4, 4>(d, a, tmax, s); return true; }
   switch (wide ? d.N / 16 : d.N / 8) {
     case 4: *err = wide ? launch_ssm_small_t<4, 16>(d, a, tmax, s) : launch_ssm_small_t<4, 8>(d, a, tmax, s); return true;
     case 8: *err = wide ? launch_ssm_small_t<8, 16>(d, a, tmax, s) : launch_ssm_small_t<8, 8>(d, a, tmax, s); return true;

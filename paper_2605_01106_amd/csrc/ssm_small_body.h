@@ -261,7 +261,7 @@ __device__ __forceinline__ void ssm_small_body(const Dims& d, const SsmArgs& a, 
       }
       part += dpp_move<0xB1>(part);    // lane ^ 1
       part += dpp_move<0x4E>(part);    // lane ^ 2
-      part += dpp_move<0x141>(part);   // the other quad of 8 lanes
+      if (SUBS >= 8) part += dpp_move<0x141>(part);    // the other quad of 8 lanes
       if (SUBS == 16) part += dpp_move<0x140>(part);   // the other half of 16 lanes
       y[j] = (part + dskip * xv) * gate;
     }

@@ -102,6 +102,20 @@ def test_aligned_shapes_fast_paths(B, k, d_state, dtype):
     run_lockstep(ctx, wts, prompts, lens, 30, k, engine="pass", report=_say(f"aligned-k{k}-N{d_state}-{dtype}"))
 
 
+@pytest.mark.parametrize("k,heads,p,batch,dtype", [(0, 8, 32, 1, W.F32), (2, 4, 20, 3, W.F32), (8, 8, 32, 2, W.BF16), (4, 32, 64, 20, W.F32)])
+def test_state_size_16(B, k, heads, p, batch, dtype):
+    """State size 16 on aligned shapes: 4 lanes per state row in the few-positions scan, a partly filled last workgroup
+    (20 rows of a head), several row groups per wavefront in the rebuild and four wavefronts per workgroup (32 heads x 64)."""
+    cfg = W.scaled_config("state16", n_layers=2, d_model=64, vocab=160, m_heads=heads, m_head_dim=p, d_state=16,
+                          n_q_heads=4, n_kv_heads=2, head_dim=32, d_ff=96, w_dtype=dtype)
+    wts = W.make_lively_weights(cfg, 37)
+    lens = [(7 * b) % 31 + 4 for b in range(batch)]
+    prompts = W.make_prompts(cfg.vocab, batch, lens, 5)
+    ctx = _ctx(B, wts, batch, 96, 8, 12, prefill_chunk=8, kernel_flags=B.HH_KF_CANARIES)
+    run_lockstep(ctx, wts, prompts, lens, 12, k, engine="pass", report=_say(f"state16-k{k}"))
+    assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
+
+
 # ---------------------------------------------------------------------------------------------
 # Long caches on thin models: the key-slice paths of the matrix-core attention that the
 # paper-shaped workloads take at their real prompt lengths (Section 3.3, verification phase: M_H
