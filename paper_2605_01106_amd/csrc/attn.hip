@@ -53,19 +53,22 @@ __device__ __forceinline__ float round_store(float v, int bf16) {
   return bf16 ? __uint_as_float((uint32_t)f32_to_bf16_rne(v) << 16) : v;
 }
 
-// grid: x = row_chunks * n_splits, y = Hkv, z = B.  E = ceil(Dh / 64).
+// grid: x = row_chunks * n_splits, y = Hkv, z = B.  E = ceil(Dh / 64); FULL: Dh = 64 * E, so that every index division is one
+// by a constant and the operand reads of the products are 16 bytes wide.
 //
-// Order of the global loads of a workgroup (each later group needs the one before): position
-// of the sequence -> page numbers, query rows, rotation table, new keys -> cached keys of the
-// first tile.  The cached keys of tile t + 1 are requested before tile t is scored.
-template <int BF16, int E>
+// Bound by its chain of memory round trips, one workgroup having few keys.  Order of the global loads (each later group needs
+// the one before): position of the sequence | page numbers -> rotation table, query rows, new keys | cached keys of the first
+// tile.  Whole tiles are requested whatever their number of cached keys, page numbers first: loads under a condition per
+// item make the compiler wait for each item's page number before it asks for the next.  The first key slice does not even
+// need the position for its first tile.  The cached keys of tile t + 1 are requested before tile t is scored.
+template <int BF16, int E, bool FULL>
 __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const AttnArgs a, const int row_chunks) {
   constexpr int EPI = BF16 ? 8 : 4;          // elements per 16-byte item
   constexpr int NI = BF16 ? 2 * E : 4 * E;   // items of a K (or V) tile per thread
   constexpr int NQ = 2 * E;                  // rotation pairs of the query rows per thread
   extern __shared__ __align__(16) float smem[];
   __shared__ int s_last;
-  const int Dh = d.Dh, G = d.Hq / d.Hkv, half = Dh >> 1;
+  const int Dh = FULL ? 64 * E : d.Dh, G = d.Hq / d.Hkv, half = Dh >> 1;
   const int ldk = Dh + 1;
   float* Ks = smem;                         // [kKeys][Dh+1]
   float* Vs = Ks + kKeys * ldk;             // [kKeys][Dh]
@@ -76,8 +79,6 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
   const int chunk = blockIdx.x % row_chunks, sp = blockIdx.x / row_chunks;
   const int kvh = blockIdx.y, b = blockIdx.z;
   TR(0);
-  const int nt = a.n_tok != nullptr ? a.n_tok[b] : a.T;
-  const int pos0 = a.pos0[b];
   const int n_rows = a.T * G;
   const int* pt_row = a.page_table + (size_t)b * d.pages_per_seq;
   const float scale = 1.0f / sqrtf((float)Dh);
@@ -88,7 +89,37 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
   const char* kbytes = static_cast<const char*>(a.kpool);
   const char* vbytes = static_cast<const char*>(a.vpool);
 
+  // ---- cached keys of a tile: pages -> registers -> LDS as float32.  A K item is 16 bytes of one key row; a V item is 16 bytes
+  // of one dimension (consecutive tokens of a page).  Items without a cached key read their place in the page all the same (a
+  // page number of the table's end where the tile goes past it) and are not used.
+  const int cpk = Dh / EPI;                 // items per key
+  const int n_items = kKeys * cpk;
+  uint4 kreg[NI], vreg[NI];
+  constexpr int TPI = EPI;                   // tokens per V item
+  const int pshift = 31 - __clz(d.page_tokens), pmask = d.page_tokens - 1;   // page sizes are powers of two
+  auto load_tile = [&](int t) {
+    const int key0 = t * kKeys;
+    int kpg[NI], vpg[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int it = tid + 256 * i;
+      kpg[i] = pt_row[min((key0 + min(it / cpk, kKeys - 1)) >> pshift, d.pages_per_seq - 1)];
+      vpg[i] = pt_row[min((key0 + min(it / Dh, kKeys / TPI - 1) * TPI) >> pshift, d.pages_per_seq - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int it = tid + 256 * i;
+      const int kq = it / cpk, c = (it - kq * cpk) * EPI, kpos = key0 + min(kq, kKeys - 1);
+      kreg[i] = *reinterpret_cast<const uint4*>(kbytes + ((((size_t)kpg[i] * d.Hkv + kvh) * d.page_tokens + (kpos & pmask)) * Dh + c) * esz);
+      const int grp = it / Dh, dd = it - grp * Dh, vpos = key0 + min(grp, kKeys / TPI - 1) * TPI;
+      vreg[i] = *reinterpret_cast<const uint4*>(vbytes + ((((size_t)vpg[i] * d.Hkv + kvh) * Dh + dd) * d.page_tokens + (vpos & pmask)) * esz);
+    }
+  };
+  if (sp == 0 && a.T <= 16) load_tile(0);   // (longer passes begin with an empty cache)
+
   // rows of this workgroup: row = position j * G + query head of the group; valid while j < nt
+  const int nt = a.n_tok != nullptr ? a.n_tok[b] : a.T;
+  const int pos0 = a.pos0[b];
   const int row_lim = min(n_rows, nt * G);
   const int row0 = chunk * kRowsPerBlock;
   const int jmax = row0 < row_lim ? (min(row_lim, row0 + kRowsPerBlock) - 1) / G : -1;
@@ -106,25 +137,6 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
   const int tiles = (nk + kKeys - 1) / kKeys;
   const int tps = (tiles + a.n_splits - 1) / a.n_splits;
   const int t_begin = sp * tps, t_end = min(tiles, (sp + 1) * tps);
-  const int cpk = Dh / EPI;                 // items per key
-  const int n_items = kKeys * cpk;
-
-  // ---- cached keys of a tile: pages -> registers -> LDS as float32.  A K item is 16 bytes of
-  // one key row; a V item is 16 bytes of one dimension (consecutive tokens of a page).
-  uint4 kreg[NI], vreg[NI];
-  constexpr int TPI = EPI;                   // tokens per V item
-  auto load_tile = [&](int t) {
-    const int key0 = t * kKeys;
-    const int n_old = min(max(pos0 - key0, 0), kKeys);          // keys of this tile already in the cache
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int it = tid + 256 * i;
-      const int kk = it / cpk, c = (it - kk * cpk) * EPI;
-      if (kk < n_old) kreg[i] = *reinterpret_cast<const uint4*>(kbytes + (k_index(d, pt_row, kvh, key0 + kk) + c) * esz);
-      const int grp = it / Dh, dd = it - grp * Dh;
-      if (grp * TPI < n_old) vreg[i] = *reinterpret_cast<const uint4*>(vbytes + v_index(d, pt_row, kvh, key0 + grp * TPI, dd) * esz);
-    }
-  };
   auto store_tile = [&](int t) {
     const int key0 = t * kKeys;
     const int n_old = min(max(pos0 - key0, 0), kKeys);
@@ -216,7 +228,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
   NewKey nw0;
   const int n_new0 = t_begin < t_end ? new_count(t_begin) * half : 0;   // rotation pairs of new keys in the first tile
   if (tid < n_new0) load_new(t_begin, tid, nw0);
-  if (t_begin < t_end) load_tile(t_begin);
+  if (t_begin < t_end && t_begin * kKeys < pos0 && (sp != 0 || a.T > 16)) load_tile(t_begin);
   TR(1);
   // query rows, rotated to their positions and scaled
 #pragma unroll
@@ -229,6 +241,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
     }
   }
 
+  const bool rows_here = row0 + wave * kRowsPerWave < row_lim;
   float mrun[kRowsPerWave], lrun[kRowsPerWave], acc[kRowsPerWave][E];
 #pragma unroll
   for (int r = 0; r < kRowsPerWave; ++r) {
@@ -251,16 +264,22 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
     store_tile(t);
     __syncthreads();
     TR(3);
-    if (t + 1 < t_end) load_tile(t + 1);
+    if (t + 1 < t_end && (t + 1) * kKeys < pos0) load_tile(t + 1);
+    if (!rows_here) continue;               // none of this wavefront's rows exists
     // scores: lane = key
     float sc[kRowsPerWave];
 #pragma unroll
     for (int r = 0; r < kRowsPerWave; ++r) sc[r] = 0.f;
-#pragma unroll 8
-    for (int dd = 0; dd < Dh; ++dd) {
-      const float kvv = Ks[lane * ldk + dd];
+#pragma unroll 4
+    for (int dd = 0; dd < Dh; dd += 4) {    // (Dh is a multiple of 8)
+      float kvv[4];
 #pragma unroll
-      for (int r = 0; r < kRowsPerWave; ++r) sc[r] = fmaf(qs[(wave * kRowsPerWave + r) * Dh + dd], kvv, sc[r]);
+      for (int u = 0; u < 4; ++u) kvv[u] = Ks[lane * ldk + dd + u];
+#pragma unroll
+      for (int r = 0; r < kRowsPerWave; ++r) {
+        const float4 q = *reinterpret_cast<const float4*>(qs + (wave * kRowsPerWave + r) * Dh + dd);
+        sc[r] = fmaf(q.x, kvv[0], sc[r]); sc[r] = fmaf(q.y, kvv[1], sc[r]); sc[r] = fmaf(q.z, kvv[2], sc[r]); sc[r] = fmaf(q.w, kvv[3], sc[r]);
+      }
     }
     TR(4);
     const int key = key0 + lane;
@@ -287,14 +306,22 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
     TR(5);
     // output: lane = dimension
 #pragma unroll 4
-    for (int kk = 0; kk < kKeys; ++kk) {
+    for (int kk = 0; kk < kKeys; kk += 4) {
+      float4 p[kRowsPerWave];
+#pragma unroll
+      for (int r = 0; r < kRowsPerWave; ++r) p[r] = *reinterpret_cast<const float4*>(ps + (wave * kRowsPerWave + r) * kKeys + kk);
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const int dd = lane + 64 * e;
-        if (dd < Dh) {
-          const float vv = Vs[kk * Dh + dd];
+        if (FULL || dd < Dh) {
+          float vv[4];
 #pragma unroll
-          for (int r = 0; r < kRowsPerWave; ++r) acc[r][e] = fmaf(ps[(wave * kRowsPerWave + r) * kKeys + kk], vv, acc[r][e]);
+          for (int u = 0; u < 4; ++u) vv[u] = Vs[(kk + u) * Dh + dd];
+#pragma unroll
+          for (int r = 0; r < kRowsPerWave; ++r) {
+            acc[r][e] = fmaf(p[r].x, vv[0], acc[r][e]); acc[r][e] = fmaf(p[r].y, vv[1], acc[r][e]);
+            acc[r][e] = fmaf(p[r].z, vv[2], acc[r][e]); acc[r][e] = fmaf(p[r].w, vv[3], acc[r][e]);
+          }
         }
       }
     }
@@ -413,18 +440,24 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
   TR(12);
 }
 
-template <int BF16, int E>
-static hipError_t launch_attention_t(const Dims& d, const AttnArgs& a, int row_chunks, size_t lds, hipStream_t s) {
+template <int BF16, int E, bool FULL>
+static hipError_t launch_attention_f(const Dims& d, const AttnArgs& a, int row_chunks, size_t lds, hipStream_t s) {
   static size_t lds_enabled = 48 * 1024;
   if (lds > lds_enabled) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attention_kernel<BF16, E>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attention_kernel<BF16, E, FULL>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     lds_enabled = lds;
   }
-  hipLaunchKernelGGL((attention_kernel<BF16, E>), dim3(row_chunks * a.n_splits, d.Hkv, a.B), dim3(256), lds, s, d, a,
+  hipLaunchKernelGGL((attention_kernel<BF16, E, FULL>), dim3(row_chunks * a.n_splits, d.Hkv, a.B), dim3(256), lds, s, d, a,
                      row_chunks);
   return hipGetLastError();
+}
+template <int BF16, int E>
+static hipError_t launch_attention_t(const Dims& d, const AttnArgs& a, int row_chunks, size_t lds, hipStream_t s) {
+  // (a bf16 cache comes here only for cross-checks)
+  if (!BF16 && d.Dh == 64 * E) return launch_attention_f<BF16, E, !BF16>(d, a, row_chunks, lds, s);
+  return launch_attention_f<BF16, E, false>(d, a, row_chunks, lds, s);
 }
 
 // Keys and values of the new positions: rotate k, round to the storage type, write to the pages.

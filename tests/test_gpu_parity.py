@@ -116,6 +116,23 @@ def test_state_size_16(B, k, heads, p, batch, dtype):
     assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
 
 
+@pytest.mark.parametrize("head_dim,n_q,page,k,lens,splits", [
+    (64, 4, 16, 2, [30, 63, 64, 65, 130], 0),     # whole head dimensions: tiles that end at, before and behind a tile's last key
+    (128, 2, 64, 8, [190, 12], 1),                # several tiles in one slice, the next requested while one is scored
+    (256, 2, 32, 0, [140, 64, 3], 32),
+    (40, 4, 16, 15, [70, 1, 33], 0)])             # part of a 64-wide head; pages shorter than a tile, the table's end within one
+def test_float32_attention_tiles(B, head_dim, n_q, page, k, lens, splits):
+    """Float32 caches: whole key tiles are requested whatever is cached of them, the first one before the position is known."""
+    cfg = W.scaled_config("f32attn", n_layers=2, d_model=64, vocab=160, m_heads=2, m_head_dim=16, d_state=16,
+                          n_q_heads=n_q, n_kv_heads=2, head_dim=head_dim, d_ff=96, w_dtype=W.F32)
+    wts = W.make_lively_weights(cfg, 41)
+    prompts = W.make_prompts(cfg.vocab, len(lens), lens, 6)
+    ctx = _ctx(B, wts, len(lens), max(lens) + 10 + 2 * k + 2, k, 10, kv_page_tokens=page, prefill_chunk=24, attn_max_splits=splits,
+               kernel_flags=B.HH_KF_CANARIES)
+    run_lockstep(ctx, wts, prompts, lens, 10, k, engine="pass", report=_say(f"f32-attention-{head_dim}"))
+    assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
+
+
 # ---------------------------------------------------------------------------------------------
 # Long caches on thin models: the key-slice paths of the matrix-core attention that the
 # paper-shaped workloads take at their real prompt lengths (Section 3.3, verification phase: M_H
