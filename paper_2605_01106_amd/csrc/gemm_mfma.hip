@@ -118,29 +118,66 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
 // wavefronts per tile of 16 rows.  Thread = (row r = tid % 16, column group tid / 16 of 8 columns), so that a
 // wavefront holds the 16 rows x 32 columns of one step and each of its three stores is one whole fragment:
 // 1 KB contiguous (the row-wise kernel above writes a fragment as 64 separate 16-byte pieces from 16
-// workgroups).  Rows with a norm are read twice, as there: sums of squares first (the four lanes of a row
-// within the wavefront, then the 16 wavefronts through LDS in a fixed order), then the split.
+// workgroups).  Rows with a norm: sums of squares first (the four lanes of a row within the wavefront, then the
+// 16 wavefronts through LDS in a fixed order), then the split.
 // grid: x = row tiles, y = column slices of `slice` columns (a multiple of 512) for passes with few row tiles:
 // every workgroup of a tile then sums the squares of the whole rows (from L2) and splits its slice.
+// HELD > 0: rows with a norm of up to 512 * HELD columns stay in registers between the sum and the split, the norm weights
+// requested with them: one memory round trip instead of three, which is what bounds a launch of few rows.  HELD = 0: rows
+// without a norm, or longer ones, which are read twice.
+__device__ __forceinline__ void split_store8(const float (&v)[8], uint16_t* dst) {
+  uint32_t w0[4], w1[4], w2[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) split3_bf16_pair(v[2 * i], v[2 * i + 1], w0[i], w1[i], w2[i]);
+  *reinterpret_cast<uint4*>(dst) = make_uint4(w0[0], w0[1], w0[2], w0[3]);
+  *reinterpret_cast<uint4*>(dst + 512) = make_uint4(w1[0], w1[1], w1[2], w1[3]);
+  *reinterpret_cast<uint4*>(dst + 1024) = make_uint4(w2[0], w2[1], w2[2], w2[3]);
+}
+// the 8 values of one thread at column k (X + X2)
+__device__ __forceinline__ void split_load8(const float* xr, const float* xr2, int k, float (&v)[8]) {
+  const float4 a0 = *reinterpret_cast<const float4*>(xr + k), a1 = *reinterpret_cast<const float4*>(xr + k + 4);
+  v[0] = a0.x; v[1] = a0.y; v[2] = a0.z; v[3] = a0.w; v[4] = a1.x; v[5] = a1.y; v[6] = a1.z; v[7] = a1.w;
+  if (xr2 != nullptr) {
+    const float4 b0 = *reinterpret_cast<const float4*>(xr2 + k), b1 = *reinterpret_cast<const float4*>(xr2 + k + 4);
+    v[0] += b0.x; v[1] += b0.y; v[2] += b0.z; v[3] += b0.w; v[4] += b1.x; v[5] += b1.y; v[6] += b1.z; v[7] += b1.w;
+  }
+}
+template <int HELD>
 __global__ __launch_bounds__(1024) void split_tiles_kernel(const float* __restrict__ X, const float* __restrict__ X2, int ldx, int M, int K, int Kp,
                                                            const float* __restrict__ norm_w, float eps, uint16_t* __restrict__ planes, int slice) {
+  constexpr int NH = HELD > 0 ? HELD : 1;
   __shared__ float red[16][16];
   const int tid = threadIdx.x, r = tid & 15, kg = tid >> 4, wave = tid >> 6;
   const int m = blockIdx.x * 16 + r;
   const bool row_ok = m < M;
   const float* xr = X + (size_t)min(m, M - 1) * ldx;
   const float* xr2 = X2 != nullptr ? X2 + (size_t)min(m, M - 1) * ldx : nullptr;
-  float rstd = 1.f;
-  if (norm_w != nullptr) {
+  const int KST = Kp >> 5, k_begin = (int)blockIdx.y * slice, k_end = min(Kp, k_begin + slice);
+  // fragment (row tile, step k / 32): element 8 * (16 * ((k % 32) / 8) + r) = 8 * (tid % 64)
+  uint16_t* const dst = planes + (size_t)blockIdx.x * KST * 3 * 512 + (size_t)(tid & 63) * 8;
+  float held[NH][8], nw[NH][8], rstd = 1.f;
+  if (HELD > 0 || norm_w != nullptr) {
     float ss = 0.f;
-    for (int k = kg * 8; k < K; k += 512) {
-      float4 a0 = *reinterpret_cast<const float4*>(xr + k), a1 = *reinterpret_cast<const float4*>(xr + k + 4);
-      if (xr2 != nullptr) {
-        const float4 b0 = *reinterpret_cast<const float4*>(xr2 + k), b1 = *reinterpret_cast<const float4*>(xr2 + k + 4);
-        a0.x += b0.x; a0.y += b0.y; a0.z += b0.z; a0.w += b0.w; a1.x += b1.x; a1.y += b1.y; a1.z += b1.z; a1.w += b1.w;
+    if (HELD > 0) {
+#pragma unroll
+      for (int i = 0; i < NH; ++i) {   // K % 8 == 0: a group is inside or outside
+        split_load8(xr, xr2, min(kg * 8 + 512 * i, K - 8), held[i]);
+        const float4 n0 = *reinterpret_cast<const float4*>(norm_w + min(kg * 8 + 512 * i, K - 8)), n1 = *reinterpret_cast<const float4*>(norm_w + min(kg * 8 + 512 * i, K - 8) + 4);
+        nw[i][0] = n0.x; nw[i][1] = n0.y; nw[i][2] = n0.z; nw[i][3] = n0.w; nw[i][4] = n1.x; nw[i][5] = n1.y; nw[i][6] = n1.z; nw[i][7] = n1.w;
       }
-      ss = fmaf(a0.x, a0.x, ss); ss = fmaf(a0.y, a0.y, ss); ss = fmaf(a0.z, a0.z, ss); ss = fmaf(a0.w, a0.w, ss);
-      ss = fmaf(a1.x, a1.x, ss); ss = fmaf(a1.y, a1.y, ss); ss = fmaf(a1.z, a1.z, ss); ss = fmaf(a1.w, a1.w, ss);
+#pragma unroll
+      for (int i = 0; i < NH; ++i)
+        if (kg * 8 + 512 * i < K) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) ss = fmaf(held[i][e], held[i][e], ss);
+        }
+    } else {
+      for (int k = kg * 8; k < K; k += 512) {
+        float v[8];
+        split_load8(xr, xr2, k, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
+      }
     }
     ss += __shfl_xor(ss, 16, 64);
     ss += __shfl_xor(ss, 32, 64);
@@ -151,34 +188,32 @@ __global__ __launch_bounds__(1024) void split_tiles_kernel(const float* __restri
     for (int w = 0; w < 16; ++w) tot += red[w][r];
     rstd = 1.0f / sqrtf(tot / (float)K + eps);
   }
-  const int KST = Kp >> 5;
-  const int k_end = min(Kp, ((int)blockIdx.y + 1) * slice);
-  for (int k = (int)blockIdx.y * slice + kg * 8; k < k_end; k += 512) {
+  if (HELD > 0) {
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+      const int k = kg * 8 + 512 * i;
+      if (512 * i < k_begin || k >= k_end) continue;
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = row_ok && k < K ? held[i][e] * nw[i][e] * rstd : 0.f;
+      split_store8(v, dst + (size_t)(k >> 5) * 3 * 512);
+    }
+    return;
+  }
+  for (int k = k_begin + kg * 8; k < k_end; k += 512) {
     float v[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = 0.f;
-    if (row_ok && k < K) {                        // K % 8 == 0: a group is inside or outside
-      const float4 a0 = *reinterpret_cast<const float4*>(xr + k), a1 = *reinterpret_cast<const float4*>(xr + k + 4);
-      v[0] = a0.x; v[1] = a0.y; v[2] = a0.z; v[3] = a0.w; v[4] = a1.x; v[5] = a1.y; v[6] = a1.z; v[7] = a1.w;
-      if (xr2 != nullptr) {
-        const float4 b0 = *reinterpret_cast<const float4*>(xr2 + k), b1 = *reinterpret_cast<const float4*>(xr2 + k + 4);
-        v[0] += b0.x; v[1] += b0.y; v[2] += b0.z; v[3] += b0.w; v[4] += b1.x; v[5] += b1.y; v[6] += b1.z; v[7] += b1.w;
-      }
+    if (row_ok && k < K) {
+      split_load8(xr, xr2, k, v);
       if (norm_w != nullptr) {
         const float4 n0 = *reinterpret_cast<const float4*>(norm_w + k), n1 = *reinterpret_cast<const float4*>(norm_w + k + 4);
-        const float nw[8] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
+        const float n[8] = {n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, n1.z, n1.w};
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = v[i] * nw[i] * rstd;
+        for (int i = 0; i < 8; ++i) v[i] = v[i] * n[i] * rstd;
       }
     }
-    uint32_t w0[4], w1[4], w2[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split3_bf16_pair(v[2 * i], v[2 * i + 1], w0[i], w1[i], w2[i]);
-    // fragment (row tile, step k / 32): element 8 * (16 * ((k % 32) / 8) + r) = 8 * (tid % 64)
-    uint16_t* dst = planes + (((size_t)blockIdx.x * KST + (k >> 5)) * 3) * 512 + (size_t)(tid & 63) * 8;
-    *reinterpret_cast<uint4*>(dst) = make_uint4(w0[0], w0[1], w0[2], w0[3]);
-    *reinterpret_cast<uint4*>(dst + 512) = make_uint4(w1[0], w1[1], w1[2], w1[3]);
-    *reinterpret_cast<uint4*>(dst + 1024) = make_uint4(w2[0], w2[1], w2[2], w2[3]);
+    split_store8(v, dst + (size_t)(k >> 5) * 3 * 512);
   }
 }
 
@@ -563,7 +598,10 @@ hipError_t launch_gemm_mfma(const GemvArgs& g, uint16_t* planes, float* partial,
       if (slices > iters) slices = iters;
       const int per = (iters + slices - 1) / slices;
       slices = (iters + per - 1) / per;
-      hipLaunchKernelGGL(split_tiles_kernel, dim3(tiles, slices), dim3(1024), 0, s, g.X, g.X2, g.ldx, M, K, Kp, g.norm_w, g.eps, planes, per * 512);
+      auto kern = split_tiles_kernel<0>;
+      if (g.norm_w != nullptr && iters <= 3) kern = iters == 1 ? split_tiles_kernel<1> : iters == 2 ? split_tiles_kernel<2> : split_tiles_kernel<3>;
+      else if (g.norm_w != nullptr && iters <= 5) kern = split_tiles_kernel<5>;
+      hipLaunchKernelGGL(kern, dim3(tiles, slices), dim3(1024), 0, s, g.X, g.X2, g.ldx, M, K, Kp, g.norm_w, g.eps, planes, per * 512);
     } else if (vec) hipLaunchKernelGGL(split_rows_kernel<true>, dim3(Mp), dim3(256), 0, s, g.X, g.X2, g.ldx, M, K, Mp, Kp, g.norm_w, g.eps, planes, gemm_terms(M));
     else hipLaunchKernelGGL(split_rows_kernel<false>, dim3(Mp), dim3(256), 0, s, g.X, g.X2, g.ldx, M, K, Mp, Kp, g.norm_w, g.eps, planes, gemm_terms(M));
     e = hipGetLastError();
