@@ -148,7 +148,16 @@ hipError_t launch_attention_merge(const Dims& d, const AttnArgs& a, hipStream_t 
 hipError_t launch_attention_mfma(const Dims& d, const AttnArgs& a_in, hipStream_t s) {
   AttnArgs a = a_in;
   if (!attention_mfma_accepts(d, a)) return hipErrorInvalidValue;
-  const int rt = attention_mfma_row_tiles(d, a.T), row_chunks = attention_mfma_row_chunks(d, a.T);
+  int rt = attention_mfma_row_tiles(d, a.T), row_chunks = attention_mfma_row_chunks(d, a.T);
+  if (a.n_splits == 1 && !attention_mfma_fuses_append(d, a.T)) {
+    // A prefill pass of few sequences: the smallest tiles that still run side by side, one workgroup per compute unit (a
+    // workgroup's key steps are a serial chain that shortens with its rows).  One sequence: 509 positions at the 0.5B shape,
+    // 64 workgroups of 4 tiles or 256 of one, prefill 7.53 -> 7.40 ms; 4096 in passes of 512 through four 3B blocks, 80
+    // workgroups of 4 tiles 13.10 ms, 160 of 2 tiles 12.92, 320 of one 13.14.
+    for (int t = 1; t < rt; ++t)
+      if ((long)((a.T * (d.Hq / d.Hkv) + 16 * t - 1) / (16 * t)) * d.Hkv * a.B <= 256) rt = t;
+    row_chunks = (a.T * (d.Hq / d.Hkv) + 16 * rt - 1) / (16 * rt);
+  }
   const int ks = (d.Dh + 31) / 32;
   const bool two_kernels = attention_mfma_two_kernels(d, a);
   if (two_kernels) a.counters = nullptr;
