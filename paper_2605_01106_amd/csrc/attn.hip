@@ -497,7 +497,9 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const Dims d, const Attn
 // The same for a bf16 cache whose pages hold a multiple of 8 tokens, in groups of 8 consecutive positions
 // (aligned to 8, so a group lies in one page): the values of one dimension for the 8 tokens are 16 contiguous
 // bytes of the transposed V page and are written as one store (the kernel above writes them as 8 separate
-// 2-byte stores from 8 workgroups).  Same arithmetic and rounding.  grid: sequence x groups_per_seq.
+// 2-byte stores from 8 workgroups).  Same arithmetic and rounding.  grid: x = sequence x groups_per_seq, y = the items
+// of a group (values of a dimension, then rotation pairs of keys), one per thread: each is a chain of memory round trips,
+// so that loops over them cost a launch of one sequence 9 us (now 5).
 __global__ __launch_bounds__(256) void kv_append8_kernel(const Dims d, const AttnArgs a, int groups_per_seq) {
   const int b = blockIdx.x / groups_per_seq, gl = blockIdx.x - b * groups_per_seq;
   const int nt = min(a.n_tok != nullptr ? a.n_tok[b] : a.T, a.T);
@@ -509,8 +511,12 @@ __global__ __launch_bounds__(256) void kv_append8_kernel(const Dims d, const Att
   const float* rows = a.qkv + first_row(a.row0, b, a.T) * d.ldzx + d.dq;   // row j: k | v of position pos0 + j
   const bool whole = p_first >= pos0 && p_first + 8 <= pos0 + nt;
   uint16_t* vpool = static_cast<uint16_t*>(a.vpool);
-  for (int it = threadIdx.x; it < d.Hkv * Dh; it += 256) {
-    const int kvh = it / Dh, dd = it - kvh * Dh;
+  uint16_t* kpool = static_cast<uint16_t*>(a.kpool);
+  const int per = d.Hkv * half, n_v = d.Hkv * Dh;
+  const int item = blockIdx.y * 256 + threadIdx.x;
+  if (item >= n_v + 8 * per) return;
+  if (item < n_v) {
+    const int it = item, kvh = it / Dh, dd = it - kvh * Dh;
     const size_t at = v_index(d, pt_row, kvh, p_first, dd);
     if (whole) {
       uint32_t h[8];
@@ -523,20 +529,17 @@ __global__ __launch_bounds__(256) void kv_append8_kernel(const Dims d, const Att
         if (j >= 0 && j < nt) vpool[at + u] = f32_to_bf16_rne(rows[(size_t)j * d.ldzx + d.dkv + it]);
       }
     }
+    return;
   }
-  uint16_t* kpool = static_cast<uint16_t*>(a.kpool);
-  const int per = d.Hkv * half;
-  for (int it = threadIdx.x; it < 8 * per; it += 256) {
-    const int u = it / per, rem = it - u * per, kvh = rem / half, i = rem - kvh * half;
-    const int pos = p_first + u, j = pos - pos0;
-    if (j < 0 || j >= nt) continue;
-    const float2 c = reinterpret_cast<const float2*>(a.rope)[(size_t)pos * half + i];
-    const float* krow = rows + (size_t)j * d.ldzx;
-    const float x0 = krow[kvh * Dh + i], x1 = krow[kvh * Dh + i + half];
-    const float lo = x0 * c.x - x1 * c.y, hi = x1 * c.x + x0 * c.y;
-    uint16_t* kp = kpool + k_index(d, pt_row, kvh, pos);
-    kp[i] = f32_to_bf16_rne(lo); kp[i + half] = f32_to_bf16_rne(hi);
-  }
+  const int it = item - n_v, u = it / per, rem = it - u * per, kvh = rem / half, i = rem - kvh * half;
+  const int pos = p_first + u, j = pos - pos0;
+  if (j < 0 || j >= nt) return;
+  const float2 c = reinterpret_cast<const float2*>(a.rope)[(size_t)pos * half + i];
+  const float* krow = rows + (size_t)j * d.ldzx;
+  const float x0 = krow[kvh * Dh + i], x1 = krow[kvh * Dh + i + half];
+  const float lo = x0 * c.x - x1 * c.y, hi = x1 * c.x + x0 * c.y;
+  uint16_t* kp = kpool + k_index(d, pt_row, kvh, pos);
+  kp[i] = f32_to_bf16_rne(lo); kp[i + half] = f32_to_bf16_rne(hi);
 }
 
 // bf16 cache: matrix-core kernel (HH_KF_ATTN_SCALAR selects the float32-FMA kernel instead, for cross-checks)
@@ -550,7 +553,9 @@ hipError_t launch_attention(const Dims& d, const AttnArgs& a, hipStream_t s) {
     if (!attention_mfma_fuses_append(d, a.T)) {
       if (a.T >= 16 && d.page_tokens % 8 == 0) {
         const int groups = (a.T + 7) / 8 + 1;      // 8-aligned groups that T consecutive positions can touch
-        hipLaunchKernelGGL(kv_append8_kernel, dim3(a.B * groups), dim3(256), 0, s, d, a, groups);
+        // an item per thread: each is a chain of page number, inputs and store
+        const int parts = (d.Hkv * d.Dh * 5 + 255) / 256;
+        hipLaunchKernelGGL(kv_append8_kernel, dim3(a.B * groups, parts), dim3(256), 0, s, d, a, groups);
       } else {
         hipLaunchKernelGGL(kv_append_kernel, dim3(a.B * a.T), dim3(256), 0, s, d, a);
       }

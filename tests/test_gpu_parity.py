@@ -610,6 +610,23 @@ MANY_ROWS = [
 ]
 
 
+@pytest.mark.parametrize("d_model,head_dim,n_q,tokens", [
+    (520, 24, 4, 260),      # one full and one almost empty group of 512 columns; 17 steps of 32 columns; 65 row tiles of the attention
+    (1032, 128, 2, 271),    # three groups, held in registers
+    (2048, 256, 2, 256),    # four groups, whole row tiles
+    (2568, 64, 10, 300)])   # six groups: rows are read twice
+def test_prefill_of_few_sequences(B, d_model, head_dim, n_q, tokens):
+    """One prompt in one pass: split of rows of 1 to 6 groups of 512 columns with the norm, short tiles of the attention,
+    products of odd numbers of steps."""
+    cfg = W.scaled_config("fewseq", n_layers=1, d_model=d_model, vocab=160, m_heads=4, m_head_dim=64, d_state=64,
+                          n_q_heads=n_q, n_kv_heads=2, head_dim=head_dim, d_ff=160, w_dtype=W.BF16)
+    wts = W.make_lively_weights(cfg, 43)
+    prompts = W.make_prompts(cfg.vocab, 1, [tokens], 4)
+    ctx = _ctx(B, wts, 1, tokens + 20, 1, 4, prefill_chunk=512, kernel_flags=B.HH_KF_CANARIES)
+    run_lockstep(ctx, wts, prompts, [tokens], 4, 1, engine="pass", report=_say(f"few-{d_model}"))
+    assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
+
+
 def _many_rows_model(d_model, d_ff):
     # two layers: the keys, values and state of the second one depend on every row of every product of the first
     return W.scaled_config("rows", n_layers=2, d_model=d_model, vocab=300, m_heads=4, m_head_dim=64, d_state=64,
