@@ -274,10 +274,11 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a, const int m0, const
   }
 }
 
+// grid: x = tiles of MT rows from m0 on (the workgroups that share weights are neighbours), y = weight rows
 template <int BF16, int MT, int R, int NCW, int KS, int EPI>
 __global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const GemvArgs a, const int m0, const int iters) {
   extern __shared__ __align__(16) float smem[];
-  gemv_body<BF16, MT, R, NCW, KS, EPI>(a, m0, iters, blockIdx.x, gridDim.x, smem);
+  gemv_body<BF16, MT, R, NCW, KS, EPI>(a, m0 + (int)blockIdx.x * MT, iters, blockIdx.y, gridDim.y, smem);
 }
 
 // Two independent products of the same rows and the same split in one launch: the first na workgroups add a onto its output,
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_pair_kernel(const GemvArgs 
 }
 
 // shape of one launch, chosen on the host
-struct GemvPlan { int MT, R, NCW, KS, iters, blocks; size_t lds; };
+struct GemvPlan { int MT, R, NCW, KS, iters, blocks, tiles; size_t lds; };   // tiles: row tiles of MT rows
 
 template <int BF16, int MT, int R, int NCW, int KS, int EPI>
 hipError_t gemv_launch_one(const GemvArgs& a, int m0, const GemvPlan& p, hipStream_t s) {
@@ -302,7 +303,7 @@ hipError_t gemv_launch_one(const GemvArgs& a, int m0, const GemvPlan& p, hipStre
     if (e != hipSuccess) return e;
     lds_enabled = p.lds;
   }
-  hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(kGemvThreads), p.lds, s, a, m0, p.iters);
+  hipLaunchKernelGGL(kern, dim3(p.tiles, p.blocks), dim3(kGemvThreads), p.lds, s, a, m0, p.iters);
   return hipGetLastError();
 }
 

@@ -133,6 +133,20 @@ def test_float32_attention_tiles(B, head_dim, n_q, page, k, lens, splits):
     assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
 
 
+@pytest.mark.parametrize("batch,k,d_ff", [(8, 0, 96), (9, 0, 96), (17, 0, 96), (8, 2, 96), (7, 4, 5008), (11, 2, 8192)])
+def test_float32_rows_in_tiles(B, batch, k, d_ff):
+    """Float32 products of many rows: tiles of 8 rows in one launch, the rest behind them, whole and partly filled last tiles,
+    argmax partials of all tiles; rows of 5008 and 8192 columns, of which 5 and 3 fit the LDS; prefill of 100 and more rows."""
+    cfg = W.scaled_config("f32rows", n_layers=1, d_model=72, vocab=170, m_heads=4, m_head_dim=16, d_state=16,
+                          n_q_heads=4, n_kv_heads=2, head_dim=24, d_ff=d_ff, w_dtype=W.F32)
+    wts = W.make_lively_weights(cfg, 61)
+    lens = [12 + (5 * b) % 7 for b in range(batch)]
+    prompts = W.make_prompts(cfg.vocab, batch, lens, 13)
+    ctx = _ctx(B, wts, batch, 48, k, 5, prefill_chunk=16, kernel_flags=B.HH_KF_CANARIES)
+    run_lockstep(ctx, wts, prompts, lens, 5, k, engine="pass", report=_say(f"f32-rows-{batch * (k + 1)}"))
+    assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
+
+
 # ---------------------------------------------------------------------------------------------
 # Long caches on thin models: the key-slice paths of the matrix-core attention that the
 # paper-shaped workloads take at their real prompt lengths (Section 3.3, verification phase: M_H
