@@ -559,6 +559,20 @@ static void lds_plan(int m_tiles, int steps, int n_blocks, int nf, int M, int N,
   }
 }
 
+// Row tiles per wavefront for a given K split, by the same model: products of fewer rows than their split was chosen for.
+static int lds_tiles(int m_tiles, int steps, int n_blocks, int ks) {
+  int mtw = 0;
+  double best = 1e30;
+  const int ksteps = (steps + ks - 1) / ks;
+  const int lo = m_tiles > 6 ? 2 : (m_tiles + 1) / 2, hi = m_tiles > 6 ? 6 : (m_tiles + 1) / 2;
+  for (int cand = lo; cand <= hi; ++cand) {
+    const long wgs = (long)n_blocks * ((m_tiles + lds_row_tiles(cand) - 1) / lds_row_tiles(cand)) * ks;
+    const double t = (double)((wgs + 255) / 256) * (ksteps + 3) * (384.0 * cand + 720.0);
+    if (t < best) { best = t; mtw = cand; }
+  }
+  return mtw;
+}
+
 // The plan that a product of more than 96 rows gets, for the tests that have to reach every kernel shape (host arithmetic).
 extern "C" __attribute__((visibility("default"))) void hh_many_row_plan(int rows, int K, int N, int swiglu, int* row_tiles, int* k_splits) {
   const int steps = (K + 31) / 32, tiles = (N + 15) / 16, nf = swiglu ? 2 : 1;
@@ -569,8 +583,8 @@ static bool lds_path(const GemvArgs& g, int m_tiles) { return (m_tiles > 6 || (g
 
 bool gemm_hands_over_planes(const GemvArgs& g) {
   if (!g.bf16 || g.n_seg != 1 || g.epi != EPI_SWIGLU || g.seg[0].P == nullptr || g.seg[0].P2 == nullptr || g.K % 8 != 0 || g.K < 8) return false;
-  const int M = g.M, N = g.seg[0].n_rows, m_tiles = (M + 15) / 16, steps = (g.K + 31) / 32, tiles = (N + 15) / 16;
-  if (M <= 0 || N <= 0 || N % 32 != 0 || !lds_path(g, m_tiles)) return false;
+  const int M = plan_rows(g), N = g.seg[0].n_rows, m_tiles = (M + 15) / 16, steps = (g.K + 31) / 32, tiles = (N + 15) / 16;
+  if (g.M <= 0 || N <= 0 || N % 32 != 0 || !lds_path(g, m_tiles)) return false;
   int mtw = 0, ks = 1;
   lds_plan(m_tiles, steps, (tiles + kLdsA / 2 - 1) / (kLdsA / 2), 2, M, N, mtw, ks);
   return ks == 1;
@@ -591,7 +605,7 @@ hipError_t launch_gemm_mfma(const GemvArgs& g, uint16_t* planes, float* partial,
     if (g.norm_w != nullptr || g.X2 != nullptr) return hipErrorInvalidValue;   // the producer wrote the operand as it is multiplied
     planes = const_cast<uint16_t*>(g.planes_in);
   } else {
-    if (vec && M >= 256 && gemm_terms(M) == 3) {
+    if (vec && plan_rows(g) >= 256 && gemm_terms(M) == 3) {
       // tile-wise; column slices so that about 256 workgroups run where the row tiles alone are fewer
       const int tiles = Mp / 16, iters = (Kp + 511) / 512;
       int slices = (256 + tiles - 1) / tiles;
@@ -613,8 +627,8 @@ hipError_t launch_gemm_mfma(const GemvArgs& g, uint16_t* planes, float* partial,
   a.W = static_cast<const uint16_t*>(g.seg[0].P); a.W2 = static_cast<const uint16_t*>(g.seg[0].P2);
   a.Y = g.seg[0].Y; a.ldy = g.seg[0].ldy; a.R2 = g.R2; a.partial = partial; a.M = M; a.N = N; a.K = K;
   a.row_best = g.epi == EPI_STORE ? g.row_best : nullptr; a.store = g.no_store && a.row_best != nullptr ? 0 : 1;
-  const int steps = Kp / 32, tiles = (N + 15) / 16, m_tiles = Mp / 16;
-  if (lds_path(g, m_tiles)) {
+  const int steps = Kp / 32, tiles = (N + 15) / 16, m_tiles = Mp / 16, plan_m = plan_rows(g), plan_tiles = (plan_m + 15) / 16;
+  if (lds_path(g, plan_tiles)) {
     LdsGemmArgs l{};
     l.planes = planes; l.m_tiles = m_tiles; l.KST = steps;
     l.W = a.W; l.W2 = a.W2; l.Y = a.Y; l.ldy = a.ldy; l.R2 = a.R2; l.partial = partial;
@@ -622,7 +636,8 @@ hipError_t launch_gemm_mfma(const GemvArgs& g, uint16_t* planes, float* partial,
     l.n_blocks = (tiles + kLdsA / nf - 1) / (kLdsA / nf);
 
     int mtw = 0, ks = 1;
-    lds_plan(m_tiles, steps, l.n_blocks, nf, M, N, mtw, ks);
+    lds_plan(plan_tiles, steps, l.n_blocks, nf, plan_m, N, mtw, ks);
+    if (m_tiles != plan_tiles) mtw = lds_tiles(m_tiles, steps, l.n_blocks, ks);
     l.m_blocks = (m_tiles + lds_row_tiles(mtw) - 1) / lds_row_tiles(mtw);
     // per-XCD tile ranges where few workgroups share a block of weights (verification: 3 row blocks; measured
     // 63 against 67 us for the down projection of the 3B shape); with the 22 row blocks of a prefill pass the
@@ -657,8 +672,9 @@ hipError_t launch_gemm_mfma(const GemvArgs& g, uint16_t* planes, float* partial,
   // K split: enough units (wavefronts) to cover the chip, at least 4 steps each, partial buffer permitting
   constexpr int unit_target = 2048;
   int ksplit = 1;
-  while (a.strip_groups * a.m_groups * ksplit * 2 <= unit_target && steps / (ksplit * 2) >= 4 &&
-         (size_t)(ksplit * 2) * nf * M * N <= gemm_partial_elems())
+  const int plan_groups = (plan_tiles + mtw_cap - 1) / mtw_cap;
+  while (a.strip_groups * plan_groups * ksplit * 2 <= unit_target && steps / (ksplit * 2) >= 4 &&
+         (size_t)(ksplit * 2) * nf * plan_m * N <= gemm_partial_elems())
     ksplit *= 2;
   a.ksplit = ksplit;
   a.ksteps = (steps + ksplit - 1) / ksplit;

@@ -373,6 +373,7 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
   const Dims& d = x->d;
   const int M = packed != nullptr ? packed->rows : B * T;
   const int* row0 = packed != nullptr ? packed->row0 : nullptr;
+  const int planned = packed != nullptr ? B * T : 0;   // (see GemvArgs::plan_rows)
   for (int l = 0; l < d.L; ++l) {
     const int mode = all_full ? HH_DRAFT_FULL : (modes ? modes[l] : HH_DRAFT_SSM);
     if (mode == HH_DRAFT_SKIP) continue;
@@ -380,7 +381,7 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
     const LayerDev& w = table[l];
     {  // shared input norm, Mamba-2 input projection (+ q, k, v of the attention branch)
       GemvArgs a{};
-      a.X = x->h; a.ldx = d.D; a.M = M; a.K = d.D; a.norm_w = w.norm1; a.eps = d.eps; a.epi = EPI_STORE; a.bf16 = d.bf16; a.flags = d.flags;
+      a.X = x->h; a.ldx = d.D; a.M = M; a.K = d.D; a.norm_w = w.norm1; a.eps = d.eps; a.epi = EPI_STORE; a.bf16 = d.bf16; a.flags = d.flags; a.plan_rows = planned;
       a.seg[0] = {w.w_inqkv, nullptr, w.p_inqkv, nullptr, x->zx, full ? d.ldzx : d.d_in_proj, d.ldzx};
       a.n_seg = 1;
       HH_LAUNCH(HH_K_IN_PROJ, product(x, a, s));
@@ -409,7 +410,7 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
       a.counters = x->attn_counters;
       a.T = T; a.B = B; a.n_splits = n_splits;
       GemvArgs& b = o_proj;
-      b.X = x->o; b.ldx = d.dq; b.M = M; b.K = d.dq; b.norm_w = nullptr; b.epi = EPI_STORE; b.bf16 = d.bf16; b.flags = d.flags;
+      b.X = x->o; b.ldx = d.dq; b.M = M; b.K = d.dq; b.norm_w = nullptr; b.epi = EPI_STORE; b.bf16 = d.bf16; b.flags = d.flags; b.plan_rows = planned;
       b.seg[0] = {w.w_o, nullptr, w.p_o, nullptr, x->ho, d.D, d.D}; b.n_seg = 1;
       if (overlap) {
         HH_HIP(launch_attention(d, a, sa));
@@ -426,7 +427,7 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
     if (!scanned) HH_LAUNCH(HH_K_SSM, launch_ssm(d, scan, s));
     {  // h += W_out * gated_norm(g), and W_o * o -> ho
       GemvArgs a{};
-      a.X = x->g; a.ldx = d.d_inner; a.M = M; a.K = d.d_inner; a.norm_w = w.gnorm; a.eps = d.eps; a.epi = EPI_ADD; a.bf16 = d.bf16; a.flags = d.flags;
+      a.X = x->g; a.ldx = d.d_inner; a.M = M; a.K = d.d_inner; a.norm_w = w.gnorm; a.eps = d.eps; a.epi = EPI_ADD; a.bf16 = d.bf16; a.flags = d.flags; a.plan_rows = planned;
       a.seg[0] = {w.w_out, nullptr, w.p_out, nullptr, x->h, d.D, d.D}; a.n_seg = 1;
       hipError_t e = hipSuccess;
       const bool paired = full && !overlap && !x->prof_on && product_pair(x, a, o_proj, s, &e);
@@ -440,10 +441,10 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
     {  // SwiGLU MLP on r = rmsnorm(h + ho); h += ho + W_d(...)   (ho: full mode only)
       const float* ho = full ? x->ho : nullptr;
       GemvArgs a{};
-      a.X = x->h; a.X2 = ho; a.ldx = d.D; a.M = M; a.K = d.D; a.norm_w = w.norm2; a.eps = d.eps; a.epi = EPI_SWIGLU; a.bf16 = d.bf16; a.flags = d.flags;
+      a.X = x->h; a.X2 = ho; a.ldx = d.D; a.M = M; a.K = d.D; a.norm_w = w.norm2; a.eps = d.eps; a.epi = EPI_SWIGLU; a.bf16 = d.bf16; a.flags = d.flags; a.plan_rows = planned;
       a.seg[0] = {w.w_gate, w.w_up, w.p_gate, w.p_up, x->act, d.F, d.F}; a.n_seg = 1;
       GemvArgs b{};
-      b.X = x->act; b.ldx = d.F; b.M = M; b.K = d.F; b.norm_w = nullptr; b.epi = EPI_ADD; b.bf16 = d.bf16; b.flags = d.flags; b.R2 = ho;
+      b.X = x->act; b.ldx = d.F; b.M = M; b.K = d.F; b.norm_w = nullptr; b.epi = EPI_ADD; b.bf16 = d.bf16; b.flags = d.flags; b.plan_rows = planned; b.R2 = ho;
       b.seg[0] = {w.w_down, nullptr, w.p_down, nullptr, x->h, d.D, d.D}; b.n_seg = 1;
       // many rows: the SwiGLU result goes to the down projection as split bf16 planes, without the float32
       // round trip through `act` and without a split kernel of its own

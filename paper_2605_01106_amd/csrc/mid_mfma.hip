@@ -262,10 +262,11 @@ struct MidPlan { int mt, windows, units, blocks, wpb, small; size_t lds, partial
 
 static bool mid_plan(const GemvArgs& g, MidPlan& p) {
   if (!g.bf16 || g.n_seg != 1 || g.seg[0].P == nullptr || g.best != nullptr) return false;   // (argmax: through g.row_best)
-  if (g.M <= 16 || g.M > 96 || g.K % 8 != 0 || g.K < 32 || g.ldx % 4 != 0) return false;
+  const int rows = plan_rows(g);     // (at least M)
+  if (g.M <= 16 || rows > 96 || g.K % 8 != 0 || g.K < 32 || g.ldx % 4 != 0) return false;
   if (g.epi == EPI_SWIGLU && g.seg[0].P2 == nullptr) return false;
   const int nf = g.epi == EPI_SWIGLU ? 2 : 1, N = g.seg[0].n_rows, tiles = (N + 15) / 16;
-  p.mt = (g.M + 15) / 16;
+  p.mt = (rows + 15) / 16;
   p.units = nf == 2 ? tiles : (tiles + 1) / 2;
   // the small shape (4 wavefronts, windows of 64 columns, two workgroups per compute unit) for up to 80 rows
   // (96 rows: two workgroups' staging buffers no longer fit the LDS)
@@ -286,7 +287,7 @@ static bool mid_plan(const GemvArgs& g, MidPlan& p) {
     // Few long workgroups beat many short ones for the narrow products: out_proj 18.2 -> 14.5 us with 8 chunks of
     // 5 windows instead of 20 of 2, in_proj 19.0 -> 17.4 us with 5 chunks of 8 instead of 10 of 4.  The longest
     // workgroups within 3 % of the cheapest plan win (fewer partial sums).
-    const double tw = 0.305 * p.mt, cc = 0.49 * (g.M / 64.0) * nf * (N / 2560.0);
+    const double tw = 0.305 * p.mt, cc = 0.49 * (rows / 64.0) * nf * (N / 2560.0);
     double t_min = 1e30;
     for (int pass = 0; pass < 2; ++pass) {
       for (int w = 1; w <= n_win; ++w) {
@@ -300,6 +301,7 @@ static bool mid_plan(const GemvArgs& g, MidPlan& p) {
     }
   }
   p.windows = (n_win + p.wpb - 1) / p.wpb;          // K chunks = partial products
+  p.mt = (g.M + 15) / 16;
   p.lds = (size_t)2 * kMidTerms * p.mt * 16 * (kw + mid_pad(p.mt, kw)) * 2;
   p.partial_elems = (size_t)p.windows * nf * g.M * N + (size_t)p.windows * 96;
   return p.lds <= 160 * 1024 && p.partial_elems <= gemm_partial_elems() && p.windows <= 65535;

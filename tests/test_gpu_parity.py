@@ -75,6 +75,33 @@ def test_packed_rows_of_ragged_prompts(B, dtype, heads, p, d_state, head_dim, pa
     assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
 
 
+@pytest.mark.parametrize("d_model,heads,d_ff,chunk,longest,others", [
+    (1032, 16, 1536, 320, 300, [(150, 151, 299, 7), (20, 30, 9, 1), (300, 300, 300, 300)]),   # many rows, K splits of every product
+    (264, 4, 320, 0, 20, [(3, 4, 1, 2), (19, 20, 18, 20), (20, 20, 20, 20)]),              # 100 rows planned, 30 of them there
+    (520, 8, 104, 64, 60, [(10, 11, 12, 13), (59, 60, 1, 30), (60, 60, 60, 60)]),          # 300 planned, 106 there: the split's kernel
+    (520, 8, 320, 24, 42, [(1, 25, 30, 42), (24, 3, 20, 10), (42, 42, 42, 42)])])          # two passes, the second of 90 rows at most
+def test_bits_do_not_depend_on_the_other_prompts_lengths(B, d_model, heads, d_ff, chunk, longest, others):
+    """The longest prompt of a batch gives the same bits whatever the lengths of the others: packing the rows that exist must
+    not move a product to another kernel or K split."""
+    cfg = W.scaled_config("alone", n_layers=2, d_model=d_model, vocab=180, m_heads=heads, m_head_dim=64, d_state=64,
+                          n_q_heads=4, n_kv_heads=2, head_dim=64, d_ff=d_ff, w_dtype=W.BF16)
+    wts = W.make_lively_weights(cfg, 31)
+    first = W.make_prompts(cfg.vocab, 1, [longest], 9)[0]
+    seen = []
+    for lens in others:
+        lens = [longest, *lens]
+        prompts = W.make_prompts(cfg.vocab, len(lens), lens, 17 + lens[1])
+        prompts[0, :longest] = first
+        ctx = _ctx(B, wts, len(lens), longest + 12, 1, 4, prefill_chunk=chunk)
+        ctx.hh_prefill(prompts, lens, 4)
+        got = [ctx.hh_get_logits(2)[0]]
+        for layer in range(cfg.n_layers):
+            got += [a[0] for a in ctx.hh_get_state(layer)] + list(ctx.hh_get_kv(layer, 0, longest))
+        seen.append(got)
+    for other in seen[1:]:
+        assert [np.array_equal(a, b) for a, b in zip(seen[0], other)] == [True] * len(got)
+
+
 @pytest.mark.parametrize("k", [0, 1, 5])
 def test_draft_lengths_and_plain_greedy(B, k):
     cfg = W.scaled_config("klen", n_layers=2, d_model=64, vocab=128, m_heads=2, m_head_dim=32, d_state=32,
