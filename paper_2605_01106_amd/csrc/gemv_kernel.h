@@ -172,7 +172,7 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a, const int m0, const
           float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
           if (in_k && m < mt) {
             o = v[u][m];
-            ss[m] += o.x * o.x + o.y * o.y + o.z * o.z + o.w * o.w;
+            ss[m] += sum_squares4(o);
             o.x *= nw[u].x; o.y *= nw[u].y; o.z *= nw[u].z; o.w *= nw[u].w;
           }
           xs4[(size_t)m * (Kpad >> 2) + xs_slot4(k4)] = o;

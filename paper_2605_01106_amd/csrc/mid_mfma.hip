@@ -129,7 +129,7 @@ __device__ __forceinline__ void mid_loop_body(const MidArgs& a, const int bx, co
     for (int u = 0; u < NP; ++u) {
       const int r = u * PASS + wave * RPW + rsub;
       if (!(okc && r < M)) v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      sq[u] += v[u].x * v[u].x + v[u].y * v[u].y + v[u].z * v[u].z + v[u].w * v[u].w;
+      sq[u] += sum_squares4(v[u]);
       uint32_t a0, a1, a2, b0, b1, b2;
       split3_bf16_pair(v[u].x * nw.x, v[u].y * nw.y, a0, a1, a2);
       split3_bf16_pair(v[u].z * nw.z, v[u].w * nw.w, b0, b1, b2);

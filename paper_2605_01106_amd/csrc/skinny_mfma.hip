@@ -135,7 +135,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, const int bx, c
       for (int u = 0; u < SU; ++u) {
         if (it0 + u * 64 + lane < items) {
           if (!ok[u]) v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-          ssb[mi[u] * SL4 + ci[u]] = v[u].x * v[u].x + v[u].y * v[u].y + v[u].z * v[u].z + v[u].w * v[u].w;
+          ssb[mi[u] * SL4 + ci[u]] = sum_squares4(make_float4(v[u].y, v[u].x, v[u].z, v[u].w));   // (x rounded first)
           uint32_t t0[4], t1[4], t2[4];
           sk_split3(v[u].x * nw[u].x, t0[0], t1[0], t2[0]); sk_split3(v[u].y * nw[u].y, t0[1], t1[1], t2[1]);
           sk_split3(v[u].z * nw[u].z, t0[2], t1[2], t2[2]); sk_split3(v[u].w * nw[u].w, t0[3], t1[3], t2[3]);

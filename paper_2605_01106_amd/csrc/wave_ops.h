@@ -20,6 +20,10 @@ __device__ __forceinline__ uint4 load_once16(const void* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// Sum of four squares in one order wherever it stands (y's square is rounded, the others are added by fused operations).  As a plain expression the compiler picks per use which product it
+// fuses, and rows that a kernel unrolls over were summed in different orders: equal rows of a batch with unequal bits.
+__device__ __forceinline__ float sum_squares4(const float4& v) { return fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.x, v.x, v.y * v.y))); }
+
 // v of lane l combined with the lane that a DPP control selects (row_shr, quad_perm, row_bcast ...)
 template <int CTRL>
 __device__ __forceinline__ float dpp_move(float v) {

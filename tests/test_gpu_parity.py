@@ -102,6 +102,26 @@ def test_bits_do_not_depend_on_the_other_prompts_lengths(B, d_model, heads, d_ff
         assert [np.array_equal(a, b) for a, b in zip(seen[0], other)] == [True] * len(got)
 
 
+@pytest.mark.parametrize("batch,k,flags", [(3, 0, 0), (7, 1, 0), (16, 0, 0), (24, 0, 0), (48, 0, 0), (13, 4, 0), (80, 0, 0), (96, 0, 0),
+                                           (40, 0, "HH_KF_MID_WIDE"), (30, 4, 0)])
+def test_equal_prompts_give_equal_bits(B, batch, k, flags):
+    """Every sequence of a batch of equal prompts gives the same bits: no row of a product is summed in another order than its
+    neighbours (few rows, 4 to 16, 17 to 96 in both shapes, more)."""
+    cfg = W.scaled_config("equal", n_layers=2, d_model=264, vocab=180, m_heads=4, m_head_dim=64, d_state=64,
+                          n_q_heads=4, n_kv_heads=2, head_dim=64, d_ff=320, w_dtype=W.BF16)
+    wts = W.make_lively_weights(cfg, 53)
+    prompts = np.repeat(W.make_prompts(cfg.vocab, 1, [21], 3), batch, axis=0)
+    ctx = _ctx(B, wts, batch, 64, k, 8, kernel_flags=getattr(B, flags) if flags else 0)
+    ctx.hh_prefill(prompts, [21] * batch, 8)
+    ctx.hh_draft(k)
+    got = [ctx.hh_get_logits(2)] + ([ctx.hh_get_logits(0)] if k else [])
+    ctx.hh_verify()
+    got.append(ctx.hh_get_logits(1))
+    ctx.hh_commit()
+    got += [ctx.hh_get_state(layer)[0] for layer in range(cfg.n_layers)]
+    assert [sum(not np.array_equal(a[0], a[b]) for b in range(batch)) for a in got] == [0] * len(got)
+
+
 @pytest.mark.parametrize("k", [0, 1, 5])
 def test_draft_lengths_and_plain_greedy(B, k):
     cfg = W.scaled_config("klen", n_layers=2, d_model=64, vocab=128, m_heads=2, m_head_dim=32, d_state=32,
