@@ -189,13 +189,12 @@ size_t carve(hh_ctx* x, char* base) {
   x->layers_dev = c.take<LayerDev>(d.L);
   const bool strict = x->cfg.draft_state_mode == 1;
   x->layers_ms_dev = strict ? c.take<LayerDev>(d.L) : nullptr;
-  // what one read-back returns lies together, so that it is one copy: a copy of device memory to pageable memory takes 11 to
-  // 13 us whatever its size, and a strided one as much again for every two rows
-  x->kv_len = c.take<int>(3 * B); x->committed = x->kv_len + B; x->last_n = x->kv_len + 2 * B;
+  // what one read-back returns lies together, so that one copy brings it, the padding and guard bytes between the arrays with it
+  x->kv_len = c.take<int>(B); x->committed = c.take<int>(B); x->last_n = c.take<int>(B);
   x->pending = c.take<int>(B); x->n_acc = c.take<int>(B); x->skip = c.take<int>(B); x->adv = c.take<int>(B);
   x->first_tok = c.take<int>(B);
-  x->drafts = c.take<int>(B * (2 * d.Kmax + 1));
-  x->targets = x->drafts + B * d.Kmax;
+  x->drafts = c.take<int>(B * (d.Kmax > 0 ? d.Kmax : 1));
+  x->targets = c.take<int>(B * (d.Kmax + 1));
   x->pos0 = c.take<int>(B);
   x->out_tok = c.take<int>(B * out_stride(d));
   x->page_table = c.take<int>(B * d.pages_per_seq);
@@ -1098,12 +1097,11 @@ hh_status hh_get_lengths(hh_ctx* x, int32_t* kv_len, int32_t* committed, int32_t
   if (x->phase == PH_CREATED) return fail(x, HH_ESTATE, "hh_get_lengths: nothing prefilled");
   hh_status st = sync_stream(x, stream);
   if (st != HH_OK) return st;
-  const size_t n = x->B, stride = x->d.Bmax;
-  std::vector<int> v(3 * stride);
+  const size_t n = x->B;
+  std::vector<int> v(x->last_n - x->kv_len + n);
   HH_HIP(hipMemcpy(v.data(), x->kv_len, v.size() * sizeof(int), hipMemcpyDeviceToHost));
-  if (kv_len) std::copy(v.begin(), v.begin() + n, kv_len);
-  if (committed) std::copy(v.begin() + stride, v.begin() + stride + n, committed);
-  if (last_n) std::copy(v.begin() + 2 * stride, v.begin() + 2 * stride + n, last_n);
+  auto bring = [&](const int* from, int32_t* to) { if (to) std::copy_n(v.begin() + (from - x->kv_len), n, to); };
+  bring(x->kv_len, kv_len); bring(x->committed, committed); bring(x->last_n, last_n);
   return HH_OK;
 }
 
@@ -1151,10 +1149,10 @@ hh_status hh_get_round(hh_ctx* x, int32_t* drafts, int32_t* targets, void* strea
   if (st != HH_OK) return st;
   const Dims& d = x->d;
   // both arrays in one copy, their rows picked out here (as strided copies 871 us for 64 sequences at k = 8, now 14)
-  std::vector<int> v((size_t)d.Bmax * (2 * d.Kmax + 1));
+  std::vector<int> v(x->targets - x->drafts + (size_t)x->B * (d.Kmax + 1));
   HH_HIP(hipMemcpy(v.data(), x->drafts, v.size() * sizeof(int), hipMemcpyDeviceToHost));
   const int* dr = v.data();
-  const int* tg = v.data() + (size_t)d.Bmax * d.Kmax;
+  const int* tg = v.data() + (x->targets - x->drafts);
   for (int b = 0; b < x->B; ++b) {
     if (drafts) std::copy(dr + (size_t)b * d.Kmax, dr + (size_t)b * d.Kmax + x->k, drafts + (size_t)b * x->k);
     if (targets) std::copy(tg + (size_t)b * (d.Kmax + 1), tg + (size_t)b * (d.Kmax + 1) + x->k + 1, targets + (size_t)b * (x->k + 1));

@@ -42,6 +42,23 @@ def test_workspace_sizes(B):
     assert 69e9 < big < 130e9
 
 
+@pytest.mark.parametrize("strict", [0, 1])
+def test_every_array_has_a_guard_of_its_own(B, strict):
+    """HH_KF_CANARIES puts 256 guard bytes behind every array that a kernel writes, so the workspace grows by 256 bytes per
+    array: arrays that lie together for a read-back have theirs as well."""
+    state = ["layer table", "cache lengths", "committed counts", "accepted counts", "pending tokens", "counts of the commit", "skipped",
+             "advances", "first tokens", "drafts", "targets", "positions", "generated tokens", "page table", "prefill plan",
+             "argmax keys", "acceptance sums", "sampling parameters", "row statistics", "attention tickets"]
+    scratch = ["planes", "planes of the side stream", "rotary table", "h", "zx", "g", "o", "ho", "act", "draft logits", "verify logits",
+               "prefill logits", "last rows", "partial outputs", "partial statistics", "export buffer"]
+    layer = ["S", "draft S", "ring", "K", "V", "stacked projections"]
+    cfg = W.scaled_config("guards", n_layers=3, d_model=64, vocab=100, m_heads=2, m_head_dim=24, d_state=16, n_q_heads=2,
+                          n_kv_heads=1, head_dim=32, d_ff=64, w_dtype=W.F32)   # (float32: no packed copies, no planes to hand over)
+    sizes = [B.hh_workspace_bytes(B.make_cfg(cfg, 3, 90, 4, 20, draft_state_mode=strict, kernel_flags=f)) for f in (0, B.HH_KF_CANARIES)]
+    arrays = len(state) + len(scratch) + cfg.n_layers * len(layer) + strict * (1 + 2 * cfg.n_layers)   # (layer table, S and ring of M_S)
+    assert sizes[1] - sizes[0] == 256 * arrays
+
+
 @pytest.mark.parametrize("field,value", [("n_groups", 2), ("d_conv", 3), ("n_kv_heads", 3), ("head_dim", 12),
                                          ("d_state", 24), ("kv_page_tokens", 48), ("w_dtype", 7),
                                          ("d_model", 60), ("max_batch", 0), ("struct_size", 8),
