@@ -187,3 +187,56 @@ def test_read_backs_below_the_capacities(B):
             out, n = (C.c_int32 * 64)(*[-7] * 64), C.c_int32(-1)
             assert B.lib.hh_get_tokens(ctx.ctx, b, out, cap, C.byref(n), None) == B.HH_OK
             assert n.value == min(cap, 11) and list(out[:n.value]) == w["tokens"][b][:cap] and set(out[n.value:]) <= {-7}
+
+
+@pytest.mark.parametrize("max_batch,max_draft", [(3, 6), (1024, 66)])
+def test_read_backs_of_one_array_and_of_large_capacities(B, max_batch, max_draft):
+    """Drafts or targets alone, both, and both where the rows of 1022 absent sequences lie between them (two copies then): the
+    same entries, which are also what the commit appends, and nothing behind them."""
+    import ctypes as C
+    cfg, wts = _model()
+    lens, budget = [9, 5], 14
+    prompts = W.make_prompts(cfg.vocab, 2, lens, 4)
+    ctx = B.Context(wts, max_batch, 30 + 2 * max_draft, max_draft, budget, prefill_chunk=8)
+    ctx.hh_prefill(prompts, lens, budget)
+    tokens = [ctx.hh_get_tokens(b) for b in range(2)]
+    for k in (4, 0, 6, 5):
+        ctx.hh_draft(k)
+        ctx.hh_verify()
+        d, g = ctx.hh_get_round()
+        only_d, only_g = (C.c_int32 * (2 * k + 1))(*[-7] * (2 * k + 1)), (C.c_int32 * (2 * k + 3))(*[-7] * (2 * k + 3))
+        assert B.lib.hh_get_round(ctx.ctx, only_d, None, None) == B.HH_OK and list(only_d) == [*d.ravel(), -7]
+        assert B.lib.hh_get_round(ctx.ctx, None, only_g, None) == B.HH_OK and list(only_g) == [*g.ravel(), -7]
+        assert B.lib.hh_get_round(ctx.ctx, None, None, None) == B.HH_OK
+        ctx.hh_commit()
+        _, committed, last_n = ctx.hh_get_lengths()
+        for b in range(2):
+            if len(tokens[b]) < budget:
+                tokens[b] = (tokens[b] + list(d[b][:last_n[b]]) + [int(g[b][last_n[b]])])[:budget]
+            assert ctx.hh_get_tokens(b) == tokens[b] and committed[b] == len(tokens[b])
+
+
+def test_token_rows_longer_than_the_first_copy(B):
+    """hh_get_tokens brings up to 4095 tokens with the count and the others in a second copy."""
+    import ctypes as C
+    import torch
+    cfg, wts = _model()
+    budget, seen = 4200, [[], []]
+    ctx = B.Context(wts, 2, budget + 30, 4, budget, prefill_chunk=8)
+    ctx.hh_prefill(W.make_prompts(cfg.vocab, 2, [9, 5], 4), [9, 5], budget)
+    for b in range(2):
+        seen[b] += ctx.hh_get_tokens(b)
+    while min(len(t) for t in seen) < budget:
+        ctx.hh_draft(4)
+        ctx.hh_verify()
+        _, g = ctx.hh_get_round()
+        ctx.hh_commit(torch.full((2,), 4, dtype=torch.int32, device="cuda:0"))
+        d = ctx.hh_get_round()[0]
+        for b in range(2):
+            seen[b] = (seen[b] + list(d[b]) + [int(g[b][4])])[:budget]
+    for b in range(2):
+        for cap in (0, 1, 4094, 4095, 4096, budget - 1, budget, budget + 5):
+            out, n = (C.c_int32 * (budget + 6))(*[-7] * (budget + 6)), C.c_int32(-1)
+            assert B.lib.hh_get_tokens(ctx.ctx, b, out, cap, C.byref(n), None) == B.HH_OK
+            want = seen[b][:cap]
+            assert n.value == len(want) and out[:n.value] == want and set(out[n.value:]) == {-7}
