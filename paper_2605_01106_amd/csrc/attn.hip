@@ -61,7 +61,7 @@ __device__ __forceinline__ float round_store(float v, int bf16) {
 // tile.  Whole tiles are requested whatever their number of cached keys, page numbers first: loads under a condition per
 // item make the compiler wait for each item's page number before it asks for the next.  The first key slice does not even
 // need the position for its first tile.  The cached keys of tile t + 1 are requested before tile t is scored.
-template <int BF16, int E, bool FULL>
+template <int BF16, int E, bool FULL, bool WALK>
 __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const AttnArgs a, const int row_chunks) {
   constexpr int EPI = BF16 ? 8 : 4;          // elements per 16-byte item
   constexpr int NI = BF16 ? 2 * E : 4 * E;   // items of a K (or V) tile per thread
@@ -97,22 +97,40 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
   uint4 kreg[NI], vreg[NI];
   constexpr int TPI = EPI;                   // tokens per V item
   const int pshift = 31 - __clz(d.page_tokens), pmask = d.page_tokens - 1;   // page sizes are powers of two
+  // Item i of a thread, number tid + 256 i, as (key, group of its row) and (group of tokens, dimension).  WALK: from the item before
+  // it, and anew for every tile; otherwise by divisions, which the compiler keeps from tile to tile in up to 50 registers.
+  struct Place { int kq, c, grp, dd; };
+  const Place origin{tid / cpk, tid % cpk, tid / Dh, tid % Dh};
+  auto place = [&](int i, Place& p) {
+    if (!WALK) {
+      const int it = tid + 256 * i;
+      p.kq = it / cpk; p.c = it - p.kq * cpk; p.grp = it / Dh; p.dd = it - p.grp * Dh;
+    } else if (i == 0) {
+      p = origin;
+      asm volatile("" : "+v"(p.kq), "+v"(p.c), "+v"(p.grp), "+v"(p.dd));
+    } else {
+      p.c += 256 % cpk; p.kq += 256 / cpk;
+      if (p.c >= cpk) { p.c -= cpk; ++p.kq; }
+      p.dd += 256 % Dh; p.grp += 256 / Dh;
+      if (p.dd >= Dh) { p.dd -= Dh; ++p.grp; }
+    }
+  };
   auto load_tile = [&](int t) {
     const int key0 = t * kKeys;
     int kpg[NI], vpg[NI];
+    Place p;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int it = tid + 256 * i;
-      kpg[i] = pt_row[min((key0 + min(it / cpk, kKeys - 1)) >> pshift, d.pages_per_seq - 1)];
-      vpg[i] = pt_row[min((key0 + min(it / Dh, kKeys / TPI - 1) * TPI) >> pshift, d.pages_per_seq - 1)];
+      place(i, p);
+      kpg[i] = pt_row[min((key0 + min(p.kq, kKeys - 1)) >> pshift, d.pages_per_seq - 1)];
+      vpg[i] = pt_row[min((key0 + min(p.grp, kKeys / TPI - 1) * TPI) >> pshift, d.pages_per_seq - 1)];
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int it = tid + 256 * i;
-      const int kq = it / cpk, c = (it - kq * cpk) * EPI, kpos = key0 + min(kq, kKeys - 1);
-      kreg[i] = *reinterpret_cast<const uint4*>(kbytes + ((((size_t)kpg[i] * d.Hkv + kvh) * d.page_tokens + (kpos & pmask)) * Dh + c) * esz);
-      const int grp = it / Dh, dd = it - grp * Dh, vpos = key0 + min(grp, kKeys / TPI - 1) * TPI;
-      vreg[i] = *reinterpret_cast<const uint4*>(vbytes + ((((size_t)vpg[i] * d.Hkv + kvh) * Dh + dd) * d.page_tokens + (vpos & pmask)) * esz);
+      place(i, p);
+      const int kpos = key0 + min(p.kq, kKeys - 1), vpos = key0 + min(p.grp, kKeys / TPI - 1) * TPI;
+      kreg[i] = *reinterpret_cast<const uint4*>(kbytes + ((((size_t)kpg[i] * d.Hkv + kvh) * d.page_tokens + (kpos & pmask)) * Dh + p.c * EPI) * esz);
+      vreg[i] = *reinterpret_cast<const uint4*>(vbytes + ((((size_t)vpg[i] * d.Hkv + kvh) * Dh + p.dd) * d.page_tokens + (vpos & pmask)) * esz);
     }
   };
   if (sp == 0 && a.T <= 16) load_tile(0);   // (longer passes begin with an empty cache)
@@ -140,32 +158,31 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
   auto store_tile = [&](int t) {
     const int key0 = t * kKeys;
     const int n_old = min(max(pos0 - key0, 0), kKeys);
+    Place p;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int it = tid + 256 * i;
-      if (it >= n_items) continue;
-      const int kk = it / cpk, c = (it - kk * cpk) * EPI;
-      float* kd = Ks + kk * ldk + c;
-      if (kk < n_old) {
+      place(i, p);
+      if (tid + 256 * i >= n_items) continue;
+      float* kd = Ks + p.kq * ldk + p.c * EPI;
+      if (p.kq < n_old) {
         const uint32_t kw[4] = {kreg[i].x, kreg[i].y, kreg[i].z, kreg[i].w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           if (BF16) { kd[2 * e] = __uint_as_float(kw[e] << 16); kd[2 * e + 1] = __uint_as_float(kw[e] & 0xffff0000u); }
           else kd[e] = __uint_as_float(kw[e]);
         }
-      } else if (key0 + kk >= nk) {           // past the last key: zeros (the new keys are staged separately)
+      } else if (key0 + p.kq >= nk) {         // past the last key: zeros (the new keys are staged separately)
 #pragma unroll
         for (int e = 0; e < EPI; ++e) kd[e] = 0.f;
       }
-      const int grp = it / Dh, dd = it - grp * Dh;
       const uint32_t vw[4] = {vreg[i].x, vreg[i].y, vreg[i].z, vreg[i].w};
 #pragma unroll
       for (int e = 0; e < TPI; ++e) {
-        const int vk = grp * TPI + e;
+        const int vk = p.grp * TPI + e;
         float val = 0.f;
         if (vk < n_old) val = BF16 ? ((e & 1) ? __uint_as_float(vw[e >> 1] & 0xffff0000u) : __uint_as_float(vw[e >> 1] << 16))
                                    : __uint_as_float(vw[e & 3]);
-        if (vk < n_old || key0 + vk >= nk) Vs[vk * Dh + dd] = val;
+        if (vk < n_old || key0 + vk >= nk) Vs[vk * Dh + p.dd] = val;
       }
     }
   };
@@ -440,24 +457,33 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
   TR(12);
 }
 
-template <int BF16, int E, bool FULL>
+template <int BF16, int E, bool FULL, bool WALK>
 static hipError_t launch_attention_f(const Dims& d, const AttnArgs& a, int row_chunks, size_t lds, hipStream_t s) {
   static size_t lds_enabled = 48 * 1024;
   if (lds > lds_enabled) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attention_kernel<BF16, E, FULL>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attention_kernel<BF16, E, FULL, WALK>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     lds_enabled = lds;
   }
-  hipLaunchKernelGGL((attention_kernel<BF16, E, FULL>), dim3(row_chunks * a.n_splits, d.Hkv, a.B), dim3(256), lds, s, d, a,
+  hipLaunchKernelGGL((attention_kernel<BF16, E, FULL, WALK>), dim3(row_chunks * a.n_splits, d.Hkv, a.B), dim3(256), lds, s, d, a,
                      row_chunks);
   return hipGetLastError();
 }
 template <int BF16, int E>
 static hipError_t launch_attention_t(const Dims& d, const AttnArgs& a, int row_chunks, size_t lds, hipStream_t s) {
-  // (a bf16 cache comes here only for cross-checks)
-  if (!BF16 && d.Dh == 64 * E) return launch_attention_f<BF16, E, !BF16>(d, a, row_chunks, lds, s);
-  return launch_attention_f<BF16, E, false>(d, a, row_chunks, lds, s);
+  // (a bf16 cache comes here with pages of 16 tokens, and for cross-checks)
+  if (!BF16 && d.Dh == 64 * E) return launch_attention_f<BF16, E, !BF16, false>(d, a, row_chunks, lds, s);
+  // Places of the items walked where the registers they take cost a workgroup per compute unit in launches of many.  Float32,
+  // head dimensions 72 to 120 (256 + 41 registers against 213: one against two), head dimension 96: prefill of 64 x 300 positions
+  // 2570 -> 1480 us, of 256 x 100 1850 -> 996, verification of 64 x 9 positions over 1000 keys 300 -> 189, of one sequence the
+  // same, of 64 x 3 over 300 keys 65.9 -> 67.5.  Head dimensions below 64, bf16 64 as well (203 to 233 registers against 147 to
+  // 159: two against three), prefill: float32, 40, 256 x 100 positions 605 -> 452 us, bf16, 64, 694 -> 530; not verification (64 x 9
+  // positions over 1000 keys, float32 96 against 104 us walked, bf16 104 against 109), nor where no workgroup is gained (bf16,
+  // 128: prefill of 64 x 300 positions 1510 against 1554 us walked; float32, 200: 2503 against 2610).
+  if constexpr (!BF16 && E == 2) return launch_attention_f<BF16, E, false, true>(d, a, row_chunks, lds, s);
+  else if (E == 1 && a.T > 16) return launch_attention_f<BF16, E, false, E == 1>(d, a, row_chunks, lds, s);
+  else return launch_attention_f<BF16, E, false, false>(d, a, row_chunks, lds, s);
 }
 
 // Keys and values of the new positions: rotate k, round to the storage type, write to the pages.

@@ -180,6 +180,21 @@ def test_float32_attention_tiles(B, head_dim, n_q, page, k, lens, splits):
     assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
 
 
+@pytest.mark.parametrize("dtype,head_dim,page", [(W.F32, 8, 16), (W.F32, 56, 32), (W.F32, 72, 16), (W.F32, 96, 64), (W.F32, 120, 256),
+                                                 (W.BF16, 8, 16), (W.BF16, 24, 16), (W.BF16, 64, 16)])
+def test_key_tiles_of_odd_head_dimensions(B, dtype, head_dim, page):
+    """Key tiles whose items do not divide evenly over the threads, place after place, in prefill passes over cached keys (the
+    second and later passes of a prompt) and in verification: float32 caches, and bf16 caches with pages of 16 tokens."""
+    cfg = W.scaled_config("places", n_layers=2, d_model=64, vocab=160, m_heads=2, m_head_dim=16, d_state=16,
+                          n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=96, w_dtype=dtype)
+    wts = W.make_lively_weights(cfg, 47)
+    lens = [150, 64, 21]
+    prompts = W.make_prompts(cfg.vocab, len(lens), lens, 6)
+    ctx = _ctx(B, wts, len(lens), max(lens) + 20, 2, 6, kv_page_tokens=page, prefill_chunk=40, kernel_flags=B.HH_KF_CANARIES)
+    run_lockstep(ctx, wts, prompts, lens, 6, 2, engine="pass", report=_say(f"places-{head_dim}"))
+    assert ctx.hh_check_canaries() == 0, B.hh_last_error(ctx.ctx)
+
+
 @pytest.mark.parametrize("batch,k,d_ff", [(8, 0, 96), (9, 0, 96), (17, 0, 96), (8, 2, 96), (7, 4, 5008), (11, 2, 8192)])
 def test_float32_rows_in_tiles(B, batch, k, d_ff):
     """Float32 products of many rows: tiles of 8 rows in one launch, the rest behind them, whole and partly filled last tiles,
