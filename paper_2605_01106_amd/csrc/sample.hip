@@ -145,10 +145,12 @@ __device__ __forceinline__ void load_groups(const float* __restrict__ row, int V
   for (int i = 0; i < G; ++i) l[i] = *reinterpret_cast<const float4*>(row + min(first + i * step, V - 4));
 }
 
-// row_stats for such a row, which is in l.  next: the row to leave in l behind it, or nullptr.
+// row_stats for such a row
 template <int G>
-__device__ void row_stats_regs(float4 (&l)[G], const float* __restrict__ next, int V, float inv_t, float* red, float& m_out, float& s_out) {
+__device__ void row_stats_regs(const float* __restrict__ row, int V, float inv_t, float* red, float& m_out, float& s_out) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = kDrawWaves, j0 = threadIdx.x * 4;
+  float4 l[G];
+  load_groups(row, V, j0, kDrawThreads * 4, l);
   float m = kNoLogit;
 #pragma unroll
   for (int i = 0; i < G; ++i) m = fmaxf(fmaxf(m, fmaxf(l[i].x, l[i].y)), fmaxf(l[i].z, l[i].w));
@@ -159,31 +161,16 @@ __device__ void row_stats_regs(float4 (&l)[G], const float* __restrict__ next, i
   for (int i = 1; i < nw; ++i) m = fmaxf(m, red[i]);
   __syncthreads();
   float s = 0.f;
-  auto add = [&](const float4& t, int i) {
+#pragma unroll
+  for (int i = 0; i < G; ++i) {
     if (j0 + i * kDrawThreads * 4 < V)
-      s += (expf((t.x - m) * inv_t) + expf((t.y - m) * inv_t)) + (expf((t.z - m) * inv_t) + expf((t.w - m) * inv_t));
-  };
-  if (next != nullptr) {
-    // a group is requested into the registers of the one that has just been added: the next row travels behind this one's
-    // exponentials
-    int jn = j0;
-    asm volatile("" : "+v"(jn));                 // (not 16 addresses kept from row to row)
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-      add(l[i], i);
-      l[i] = *reinterpret_cast<const float4*>(next + min(jn + i * kDrawThreads * 4, V - 4));
-      __builtin_amdgcn_sched_barrier(0);         // (all requested first, the next row would need registers of its own)
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < G; ++i) add(l[i], i);
+      s += (expf((l[i].x - m) * inv_t) + expf((l[i].y - m) * inv_t)) + (expf((l[i].z - m) * inv_t) + expf((l[i].w - m) * inv_t));
   }
   s = wave_sum(s);
   if (lane == 0) red[w] = s;
   __syncthreads();
   s = 0.f;
   for (int i = 0; i < nw; ++i) s += red[i];
-  __syncthreads();
   m_out = m; s_out = s;
 }
 
@@ -445,46 +432,25 @@ __global__ __launch_bounds__(kDrawThreads) void sample_rows_kernel(const float* 
 
 // (max, sum) of the k draft rows and the k + 1 verification rows of every sequence:
 // stats[b][r][2], r < kmax: draft row r; r >= kmax: verification row r - kmax.
-// grid: x = rows of a sequence, y = sequences; or (G = kRegGroups) workgroups that take the rows blockIdx.x, blockIdx.x +
-// gridDim.x, ... of all sequences.
+// grid: x = rows of a sequence, y = sequences
 template <int G>
 __global__ __launch_bounds__(kDrawThreads) void softmax_stats_kernel(const float* __restrict__ logits_d,
-                                                            const float* __restrict__ logits_v, int V, int k, int kmax, int rows,
+                                                            const float* __restrict__ logits_v, int V, int k, int kmax,
                                                             const SamplingParams* __restrict__ prm_dev,
                                                             const SamplingParams prm_val, float* __restrict__ stats) {
   __shared__ float red[kDrawWaves];
-  const float inv_t = prm_dev ? prm_dev->inv_t : prm_val.inv_t;
-  auto row_at = [&](int b, int r) -> const float* {
-    return r < k ? logits_d + (static_cast<size_t>(b) * kmax + r) * V : logits_v + (static_cast<size_t>(b) * (k + 1) + (r - k)) * V;
-  };
-  auto store = [&](int b, int r, float m, float s) {
-    if (threadIdx.x != 0) return;
-    float* st = stats + (static_cast<size_t>(b) * (2 * kmax + 1) + (r < k ? r : kmax + (r - k))) * 2;
-    st[0] = m; st[1] = s;
-  };
+  const int r = blockIdx.x, b = blockIdx.y;
+  const float* row;
+  int slot;
+  if (r < k) { row = logits_d + (static_cast<size_t>(b) * kmax + r) * V; slot = r; }
+  else { row = logits_v + (static_cast<size_t>(b) * (k + 1) + (r - k)) * V; slot = kmax + (r - k); }
   float m, s;
-  if constexpr (G == kRegGroups) {
-    const int per = 2 * k + 1;
-    int i = blockIdx.x, b = i / per, r = i - b * per;
-    float4 l[G];
-    load_groups(row_at(b, r), V, threadIdx.x * 4, kDrawThreads * 4, l);
-    while (true) {
-      const int i1 = i + gridDim.x, b1 = i1 / per, r1 = i1 - b1 * per;
-      row_stats_regs<G>(l, i1 < rows ? row_at(b1, r1) : nullptr, V, inv_t, red, m, s);
-      store(b, r, m, s);
-      if (i1 >= rows) break;
-      i = i1; b = b1; r = r1;
-    }
-  } else {
-    const float* row = row_at(blockIdx.y, blockIdx.x);
-    if constexpr (G > 0) {
-      float4 l[G];
-      load_groups(row, V, threadIdx.x * 4, kDrawThreads * 4, l);
-      row_stats_regs<G>(l, nullptr, V, inv_t, red, m, s);
-    } else {
-      row_stats(row, V, inv_t, red, m, s);
-    }
-    store(blockIdx.y, blockIdx.x, m, s);
+  const float inv_t = prm_dev ? prm_dev->inv_t : prm_val.inv_t;
+  if constexpr (G > 0) row_stats_regs<G>(row, V, inv_t, red, m, s);
+  else row_stats(row, V, inv_t, red, m, s);
+  if (threadIdx.x == 0) {
+    float* st = stats + (static_cast<size_t>(b) * (2 * kmax + 1) + slot) * 2;
+    st[0] = m; st[1] = s;
   }
 }
 
@@ -710,13 +676,8 @@ hipError_t launch_spec_targets(const float* logits_d, const float* logits_v, int
                                const SamplingParams* prm, SamplingParams prm_val, float* stats, const int* drafts,
                                const int* committed, int* targets, hipStream_t s) {
   const int groups = reg_groups(logits_d, logits_v, V, V);
-  // Rows that fill the registers leave a compute unit one workgroup: as many of them as compute units, each with several rows,
-  // the next one requested behind the exponentials of this one.  Shorter rows share compute units, a workgroup each.
-  const long rows = (long)B * (2 * k + 1);
-  if (rows > 0x7fffffffL) return hipErrorInvalidValue;
-  const dim3 stat_blocks = groups == kRegGroups ? dim3((unsigned)(rows < 256 ? rows : 256)) : dim3(2 * k + 1, B);
 #define HH_CALL(G)                                                                                                               \
-  hipLaunchKernelGGL((softmax_stats_kernel<G>), stat_blocks, dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, (int)rows, prm, \
+  hipLaunchKernelGGL((softmax_stats_kernel<G>), dim3(2 * k + 1, B), dim3(kDrawThreads), 0, s, logits_d, logits_v, V, k, kmax, prm, \
                      prm_val, stats)
   HH_REG_GROUPS(groups, HH_CALL)
 #undef HH_CALL
