@@ -521,28 +521,22 @@ __global__ __launch_bounds__(kDrawThreads) void spec_targets_kernel(const float*
       return make_float4(expf((a.x - mh) * inv_t), expf((a.y - mh) * inv_t), expf((a.z - mh) * inv_t), expf((a.w - mh) * inv_t));
     };
     float4 a[2][CB], e[2][CB];
+    auto sum = [&](auto load, auto mass) {
+      load(0);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (c * CB * 256 >= seg) break;          // (the same in every thread: segments of rows just above 32768 entries end in the third chunk)
+        if (c + 1 < NC && (c + 1) * CB * 256 < seg) load(c + 1);
+#pragma unroll
+        for (int q = 0; q < CB; ++q) add(mass(c & 1, q), c * CB + q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
     if (n < k) {
-      load_groups(lh, V, j0 + 4 * lane, 256, a[0]);
-      load_groups(ls, V, j0 + 4 * lane, 256, e[0]);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (c + 1 < NC) {
-          load_groups(lh, V, j0 + (c + 1) * CB * 256 + 4 * lane, 256, a[(c + 1) & 1]);
-          load_groups(ls, V, j0 + (c + 1) * CB * 256 + 4 * lane, 256, e[(c + 1) & 1]);
-        }
-#pragma unroll
-        for (int q = 0; q < CB; ++q) add(residual(a[c & 1][q], e[c & 1][q]), c * CB + q);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      sum([&](int c) { load_groups(lh, V, j0 + c * CB * 256 + 4 * lane, 256, a[c & 1]); load_groups(ls, V, j0 + c * CB * 256 + 4 * lane, 256, e[c & 1]); },
+          [&](int h, int q) { return residual(a[h][q], e[h][q]); });
     } else {
-      load_groups(lh, V, j0 + 4 * lane, 256, a[0]);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (c + 1 < NC) load_groups(lh, V, j0 + (c + 1) * CB * 256 + 4 * lane, 256, a[(c + 1) & 1]);
-#pragma unroll
-        for (int q = 0; q < CB; ++q) add(one(a[c & 1][q]), c * CB + q);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      sum([&](int c) { load_groups(lh, V, j0 + c * CB * 256 + 4 * lane, 256, a[c & 1]); }, [&](int h, int q) { return one(a[h][q]); });
     }
     tok = draw_walk(
         acc, [] {},

@@ -181,10 +181,17 @@ def test_rows_in_registers_equal_rows_in_memory(vocab):
                        B.hh_accept_tokens(shifted(draft), shifted(verify), drafts, positions, t, seed))
 
 
+@pytest.mark.parametrize("vocab", [32772, 36864, 49152, 49156, 61440])
+def test_residual_sums_end_with_the_segment(vocab):
+    """Acceptance of rows above 32768 entries sums the residual in chunks of 1024 entries of a segment, up to its end: segments
+    that end in the third chunk, with it, and in the fourth."""
+    test_rows_in_registers_equal_rows_in_memory(vocab)
+
+
 @pytest.mark.parametrize("vocab", [32772, 65536])
 def test_statistics_of_more_rows_than_workgroups(vocab):
-    """Rows that fill the registers: 256 workgroups take all rows in turn, the next one requested behind the sums of this one
-    (41 sequences, k = 3: 287 rows, 31 workgroups with a second one), against the kernels that read memory again."""
+    """Rows that fill the registers, more of them than compute units (41 sequences, k = 3: 287 rows), against the kernels that
+    read memory again."""
     import torch
     from paper_2605_01106_amd import binding as B
     batch, k, t, seed = 41, 3, 0.7, 5
