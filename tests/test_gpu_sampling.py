@@ -224,3 +224,9 @@ def test_draws_at_block_and_segment_edges(B, vocab):
         got = B.hh_draw_tokens(logits, 1.0, seed).tolist()
         want = [i if S.uniform(seed, r, 0, 2) < 0.5 else j for r, (i, j) in enumerate(rows)]
         assert got == want
+
+
+@pytest.mark.parametrize("vocab", [12284, 16384, 16388])
+def test_draws_on_both_sides_of_the_shared_walk(B, vocab):
+    """Segments of up to four blocks are walked by the wavefront that owns them, longer ones by all."""
+    test_draws_at_block_and_segment_edges(B, vocab)
