@@ -47,6 +47,7 @@ def measured_traffic(workload):
 
 KIND_NAMES = {0: "in_proj", 1: "ssm_scan", 2: "rope_append", 3: "attention", 4: "out_proj", 5: "o_proj",
               6: "mlp_gate_up", 7: "mlp_down", 8: "lm_head"}
+TOGETHER = {9: ("branches", (1, 3)), 10: ("out_projs", (4, 5))}   # launches that do the work of two kinds
 PHASE_NAMES = {0: "prefill", 1: "draft", 2: "verify", 3: "commit"}
 
 
@@ -228,7 +229,8 @@ def main():
         prof = ctx.hh_profile_read()
         ctx.hh_profile(False)
         tot = sum(ms for (ph, _), (_, ms) in prof.items() if ph == 0)
-        prefill_kernels = {KIND_NAMES[kd]: {"launches": c, "total_ms": round(ms, 2), "avg_us": round(ms / c * 1e3, 1),
+        names = {**KIND_NAMES, **{kd: name for kd, (name, _) in TOGETHER.items()}}
+        prefill_kernels = {names[kd]: {"launches": c, "total_ms": round(ms, 2), "avg_us": round(ms / c * 1e3, 1),
                                             "share": round(ms / tot, 3)}
                            for (ph, kd), (c, ms) in sorted(prof.items()) if ph == 0}
 
@@ -331,6 +333,17 @@ def main():
         kernels["commit.ssm_scan"] = {"launches_per_round": 1, "avg_us": round(ms / cnt * 1e3, 3),
                                       "us_per_round": round(ms / cnt * 1e3, 1), "bytes": by,
                                       "gbs": round(by / (ms / cnt * 1e-3) / 1e9, 1), "stream": "launch"}
+    # Launches of the verification pass that do the work of two kinds, timed with the per-launch events as well (launch
+    # overhead included); the rows of their parts above are then kernels launched apart, for comparison, and no part of a round.
+    for kind, (name, parts) in TOGETHER.items():
+        if (2, kind) in prof and not side_branch:
+            cnt, ms = prof[(2, kind)]
+            by = sum(per_kind[(2, part)] for part in parts)
+            kernels[f"verify.{name}"] = {"launches_per_round": cnt // prof_rounds, "avg_us": round(ms / cnt * 1e3, 3),
+                                         "us_per_round": round(ms / prof_rounds * 1e3, 1), "bytes": by,
+                                         "gbs": round(by / (ms / cnt * 1e-3) / 1e9, 1), "stream": "launch"}
+            for part in parts:
+                kernels[f"verify.{KIND_NAMES[part]}"].update(launches_per_round=0, us_per_round=0.0, stream="apart")
     # dominant kernel: the kind of kernel (draft and verification launches together) with the largest
     # share of a round on the launch stream (the in-order critical path; the side-stream kernels
     # overlap it), reported for the phase in which it takes longer

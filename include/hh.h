@@ -304,10 +304,13 @@ HH_API hh_status hh_get_kv(hh_ctx* ctx, int32_t layer, int32_t seq, int32_t n_to
 
 /* ---- optional per-launch timing (for measurement; perturbs throughput, keep it out of timed runs) ----
  * While enabled, every kernel launch of prefill/draft/verify/commit is bracketed by a HIP event
- * pair on the call's stream, tagged  phase * 16 + kind.  Enabling clears earlier records. */
+ * pair on the call's stream, tagged  phase * 16 + kind.  Enabling clears earlier records.  The launches are those of
+ * an ordinary pass (enqueued directly, and with the attention branch on the call's stream): where attention and
+ * scan of a block are one launch it carries HH_K_BRANCHES, where both output projections are, HH_K_OUT_PROJS, and the
+ * kinds of the parts do not occur. */
 enum { HH_PHASE_PREFILL = 0, HH_PHASE_DRAFT = 1, HH_PHASE_VERIFY = 2, HH_PHASE_COMMIT = 3 };
 enum { HH_K_IN_PROJ = 0, HH_K_SSM = 1, HH_K_RESERVED = 2, HH_K_ATTN = 3, HH_K_OUT_PROJ = 4, HH_K_O_PROJ = 5,
-       HH_K_MLP_UP = 6, HH_K_MLP_DOWN = 7, HH_K_LM_HEAD = 8 };
+       HH_K_MLP_UP = 6, HH_K_MLP_DOWN = 7, HH_K_LM_HEAD = 8, HH_K_BRANCHES = 9, HH_K_OUT_PROJS = 10 };
 HH_API hh_status hh_profile(hh_ctx* ctx, int32_t enable);
 /* Synchronises `stream`; launches[tag] and total_ms[tag] (HOST, n_tags entries, tag as above)
  * receive the number of timed launches and their summed duration. */
@@ -317,7 +320,9 @@ HH_API hh_status hh_profile_read(hh_ctx* ctx, int32_t n_tags, int32_t* launches,
  * or verification (HH_PHASE_VERIFY, k+1 positions) passes in which ONLY kernels of `kind` are
  * launched (so consecutive launches read different layers' weights, as in a real pass), between
  * one HIP event pair on `stream`; synchronises.  *total_ms / *launches is the average duration
- * including the launch gap.  Valid between rounds; activations and draft scratch are left
+ * including the launch gap.  kind <= HH_K_LM_HEAD: attention, scan and the output projections are launched apart
+ * also where a pass launches them together, with the key slices of an attention launch of its own (hh_profile
+ * times the launches of the pass).  Valid between rounds; activations and draft scratch are left
  * undefined, committed state is untouched.  HOST outputs. */
 HH_API hh_status hh_time_kind(hh_ctx* ctx, int32_t phase, int32_t kind, int32_t k, int32_t reps, float* total_ms,
                               int32_t* launches, void* stream);

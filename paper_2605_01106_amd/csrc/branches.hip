@@ -89,16 +89,19 @@ bool branches_fit(const Dims& d, int B, int T) {
   return branches_scan_blocks(d, B, T) <= (two_per_cu(rt, ks == 2 ? 2 : 4) ? 2048 : 384);
 }
 
-bool launch_branches(const Dims& d, const AttnArgs& at_in, const SsmArgs& ss, hipStream_t s, hipError_t* err) {
+bool branches_take(const Dims& d, const AttnArgs& at, const SsmArgs& ss) {
+  return branches_fit(d, at.B, at.T) && attention_mfma_accepts(d, at) && ss.n_layers_z == 1 && ss.T == at.T && ss.B == at.B;
+}
+
+hipError_t launch_branches(const Dims& d, const AttnArgs& at_in, const SsmArgs& ss, hipStream_t s) {
   AttnArgs at = at_in;
-  if (!branches_fit(d, at.B, at.T) || !attention_mfma_accepts(d, at) || ss.n_layers_z != 1 || ss.T != at.T || ss.B != at.B) return false;
+  if (!branches_take(d, at, ss)) return hipErrorInvalidValue;
   // (by ticket the last workgroups' fences would wait for all that the scan writes: 24 sequences 1913 -> 2975 us per call)
   const bool two_kernels = attention_mfma_two_kernels(d, at);
   if (two_kernels) at.counters = nullptr;
   const int rt = attention_mfma_row_tiles(d, at.T);
-  *err = d.Dh <= 64 ? launch_state<2>(d, at, ss, rt, s) : launch_state<4>(d, at, ss, rt, s);
-  if (*err == hipSuccess && two_kernels) *err = launch_attention_merge(d, at, s);
-  return true;
+  const hipError_t e = d.Dh <= 64 ? launch_state<2>(d, at, ss, rt, s) : launch_state<4>(d, at, ss, rt, s);
+  return e == hipSuccess && two_kernels ? launch_attention_merge(d, at, s) : e;
 }
 
 }  // namespace hh

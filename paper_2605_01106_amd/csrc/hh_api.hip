@@ -323,26 +323,28 @@ hipError_t product(hh_ctx* x, const GemvArgs& a, hipStream_t s, bool side = fals
   return launch_gemv(a, nullptr, s);
 }
 
-// Two independent products in one launch where both take the same kernel: true if launched (*err: its status).  The output
+// Two independent products in one launch where both take the same kernel.  The output
 // projections of the two branches: a launch of its own (and a reduction from 17 rows on) is 4 to 9 us, mostly the launch and one
 // round trip to memory, which the other product's workgroups hide.  One sequence at the 0.5B shape, two rounds 6030 -> 5790 us;
 // 16 sequences 18.86 -> 18.39 ms, 5 with sampling 13.58 -> 13.16; 3B shape, 24 sequences, four greedy steps 1815 -> 1739 us.
-bool product_pair(hh_ctx* x, const GemvArgs& a, const GemvArgs& b, hipStream_t s, hipError_t* err) {
+enum PairKernel { PAIR_NONE = 0, PAIR_SKINNY, PAIR_MID, PAIR_GEMV };
+PairKernel pair_kernel(const GemvArgs& a, const GemvArgs& b) {
   GemvArgs sa, sb;
   const bool ska = skinny_args(a, sa), skb = skinny_args(b, sb);
-  if (ska && skb) {
-    if (!skinny_pair_fits(sa, sb)) return false;
-    *err = launch_skinny_pair(sa, sb, s);
-    return true;
+  if (ska || skb) return ska && skb && skinny_pair_fits(sa, sb) ? PAIR_SKINNY : PAIR_NONE;
+  if (mid_pair_fits(a, b)) return PAIR_MID;
+  if (mid_mfma_fits(a) || mid_mfma_fits(b) || (a.bf16 && a.M >= kMfmaMinRows)) return PAIR_NONE;
+  return gemv_pair_fits(a, b) ? PAIR_GEMV : PAIR_NONE;
+}
+hipError_t product_pair(hh_ctx* x, PairKernel kernel, const GemvArgs& a, const GemvArgs& b, hipStream_t s) {
+  GemvArgs sa, sb;
+  switch (kernel) {
+    case PAIR_SKINNY: return skinny_args(a, sa) && skinny_args(b, sb) ? launch_skinny_pair(sa, sb, s) : hipErrorInvalidValue;
+    case PAIR_MID: return launch_mid_pair(a, b, x->gemm_partial, x->gemm_partial_side, s);
+    case PAIR_GEMV: return launch_gemv_pair(a, b, s);
+    case PAIR_NONE: break;
   }
-  if (ska || skb) return false;
-  if (mid_pair_fits(a, b)) {
-    *err = launch_mid_pair(a, b, x->gemm_partial, x->gemm_partial_side, s);
-    return true;
-  }
-  if (mid_mfma_fits(a) || mid_mfma_fits(b) || (a.bf16 && a.M >= kMfmaMinRows) || !gemv_pair_fits(a, b)) return false;
-  *err = launch_gemv_pair(a, b, s);
-  return true;
+  return hipErrorInvalidValue;
 }
 
 // Whether a full pass runs its attention branch on the side stream beside the SSM branch.
@@ -401,7 +403,8 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
     scan.layers = nullptr; scan.one = w; scan.layer0 = 0; scan.n_layers_z = 1;
     scan.zx = x->zx; scan.g = x->g; scan.pos0 = x->pos0; scan.n_tok = n_tok; scan.row0 = row0; scan.T = T; scan.B = B;
     scan.state_in = state_in; scan.state_out = state_out; scan.write_ring = 1; scan.seg_scratch = x->seg_scratch;
-    bool scanned = false;
+    // (hh_time_kind times the branches and their output projections one by one)
+    bool together = false;   // attention and scan in one launch
     GemvArgs o_proj{};
     if (full) {
       AttnArgs a{};
@@ -417,22 +420,20 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
         HH_HIP(product(x, b, sa, true));
         HH_HIP(hipEventRecord(x->join_ev[l], sa));
       } else {
-        // (timed kind by kind, the branches and their output projections are launched one by one)
-        hipError_t e = hipSuccess;
-        scanned = !x->prof_on && launch_branches(d, a, scan, s, &e);
-        HH_HIP(e);
-        if (!scanned) HH_LAUNCH(HH_K_ATTN, launch_attention(d, a, s));
+        together = x->only_kind < 0 && branches_take(d, a, scan);
+        if (together) HH_LAUNCH(HH_K_BRANCHES, launch_branches(d, a, scan, s));
+        else HH_LAUNCH(HH_K_ATTN, launch_attention(d, a, s));
       }
     }
-    if (!scanned) HH_LAUNCH(HH_K_SSM, launch_ssm(d, scan, s));
+    if (!together) HH_LAUNCH(HH_K_SSM, launch_ssm(d, scan, s));
     {  // h += W_out * gated_norm(g), and W_o * o -> ho
       GemvArgs a{};
       a.X = x->g; a.ldx = d.d_inner; a.M = M; a.K = d.d_inner; a.norm_w = w.gnorm; a.eps = d.eps; a.epi = EPI_ADD; a.bf16 = d.bf16; a.flags = d.flags; a.plan_rows = planned;
       a.seg[0] = {w.w_out, nullptr, w.p_out, nullptr, x->h, d.D, d.D}; a.n_seg = 1;
-      hipError_t e = hipSuccess;
-      const bool paired = full && !overlap && !x->prof_on && product_pair(x, a, o_proj, s, &e);
-      HH_HIP(e);
-      if (!paired) {
+      const PairKernel pair = full && !overlap && x->only_kind < 0 ? pair_kernel(a, o_proj) : PAIR_NONE;
+      if (pair != PAIR_NONE) {
+        HH_LAUNCH(HH_K_OUT_PROJS, product_pair(x, pair, a, o_proj, s));
+      } else {
         if (full && !overlap) HH_LAUNCH(HH_K_O_PROJ, product(x, o_proj, s));
         HH_LAUNCH(HH_K_OUT_PROJ, product(x, a, s));
       }
@@ -544,12 +545,13 @@ hh_status run_graphed(hh_ctx* x, long long key, hipStream_t s, F enqueue) {
 // cover the chip once (more slices cost more in partial results and their merge than they gain:
 // at 64 sequences x 2 KV heads over 8192-token caches 2 slices take 133 us per layer, 4 slices 151,
 // 8 slices 188), but no slice smaller than the unit of work of the kernel.
-int pick_splits(const hh_cfg& c, const Dims& d, int B, int T, int len_upper) {
+// together: the pass may launch attention and scan together (hh_time_kind does not).
+int pick_splits(const hh_cfg& c, const Dims& d, int B, int T, int len_upper, bool together) {
   const int cap = c.attn_max_splits > 0 ? c.attn_max_splits : 16;
   const int target = c.attn_target_blocks > 0 ? c.attn_target_blocks : 256;   // one workgroup per compute unit: measured best at every workload
   // (beside a scan of several rounds of workgroups in the same launch the longer wavefronts of a single slice cost nothing:
   // 24 sequences of up to 777 keys, four greedy steps 1913 -> 1853 us; 16 of 400 keys 2525 -> 2502)
-  const bool hidden = c.overlap_mode != 3 && branches_fit(d, B, T) && branches_scan_blocks(d, B, T) >= 1024;
+  const bool hidden = together && c.overlap_mode != 3 && branches_fit(d, B, T) && branches_scan_blocks(d, B, T) >= 1024;
   const int single = c.attn_single_slice_steps == 0 ? (d.Dh > 64 && !hidden ? 12 : 28) : c.attn_single_slice_steps;   // -1: never a single slice by this rule
   int s;
   if (attention_uses_mfma(d)) {
@@ -916,7 +918,7 @@ hh_status hh_draft(hh_ctx* x, int32_t k, void* stream) {
   x->prof_phase = HH_PHASE_DRAFT;
   const std::vector<LayerDev>& table = x->strict ? x->layers_ms_host : x->layers_host;
   const int* modes = x->draft_modes.empty() ? nullptr : x->draft_modes.data();
-  const int splits = x->draft_has_full ? pick_splits(x->cfg, d, B, 1, x->len_upper) : 1;
+  const int splits = x->draft_has_full ? pick_splits(x->cfg, d, B, 1, x->len_upper, true) : 1;
   auto enqueue = [&]() -> hh_status {
     for (int i = 0; i < k; ++i) {
       // (a greedy step's argmax has begun the step behind it)
@@ -1022,7 +1024,7 @@ hh_status hh_verify(hh_ctx* x, void* stream) {
   const int B = x->B, T = x->k + 1;
   const bool stochastic = x->temperature > 0.f;
   x->prof_phase = HH_PHASE_VERIFY;
-  const int splits = pick_splits(x->cfg, d, B, T, x->len_upper);
+  const int splits = pick_splits(x->cfg, d, B, T, x->len_upper, true);
   auto enqueue = [&]() -> hh_status {
     HH_HIP(launch_begin_pass(pass_args(x, PASS_VERIFY, T, 0), B, s));
     hh_status st = run_layers(x, x->layers_host, true, nullptr, B, T, nullptr, nullptr, 0, 0, splits, false, s);
@@ -1293,7 +1295,7 @@ hh_status hh_time_kind(hh_ctx* x, int32_t phase, int32_t kind, int32_t k, int32_
                       full ? x->targets : x->drafts, full ? d.Kmax + 1 : d.Kmax, 0, nullptr, s);
         n += 1;
       } else {
-        st = run_layers(x, x->layers_host, full, nullptr, B, T, nullptr, nullptr, 0, full ? 0 : 2, pick_splits(x->cfg, d, B, T, x->len_upper), false, s);
+        st = run_layers(x, x->layers_host, full, nullptr, B, T, nullptr, nullptr, 0, full ? 0 : 2, pick_splits(x->cfg, d, B, T, x->len_upper, false), false, s);
         n += d.L;
       }
     }

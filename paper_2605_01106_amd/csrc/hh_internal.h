@@ -157,11 +157,11 @@ int attention_mfma_row_tiles(const Dims& d, int T);
 bool attention_mfma_two_kernels(const Dims& d, const AttnArgs& a);
 hipError_t launch_attention_merge(const Dims& d, const AttnArgs& a, hipStream_t s);
 
-// ---- both branches of a block in one launch (branches.hip): attention and scan of a pass of few positions.  True if it took
-// them (*err: its status); false: nothing was launched.
+// ---- both branches of a block in one launch (branches.hip): attention and scan of a pass of few positions
 bool branches_fit(const Dims& d, int B, int T);
 int branches_scan_blocks(const Dims& d, int B, int T);   // workgroups of the scan there
-bool launch_branches(const Dims& d, const AttnArgs& at, const SsmArgs& ss, hipStream_t s, hipError_t* err);
+bool branches_take(const Dims& d, const AttnArgs& at, const SsmArgs& ss);   // whether launch_branches accepts the pass
+hipError_t launch_branches(const Dims& d, const AttnArgs& at, const SsmArgs& ss, hipStream_t s);
 
 // First row of sequence b in the buffers of a pass: b * T, or, in a prefill pass over prompts of unequal length, where the rows
 // of the sequences before it end (only positions that exist have a row; then row0[b] + T <= (b + 1) * T, so that a read of up to T

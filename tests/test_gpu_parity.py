@@ -670,6 +670,57 @@ def test_both_output_projections_in_one_launch(B, dtype, d_model, head_dim, n_q,
     assert ctx.hh_check_canaries() == 0
 
 
+def _verification_launches(B, cfg, batch, k, **kw):
+    """{kind of launch: count} of one verification pass of k + 1 positions."""
+    wts = W.make_lively_weights(cfg, 23)
+    lens = [30 + b % 7 for b in range(batch)]
+    ctx = _ctx(B, wts, batch, 96, k, 12, **kw)
+    ctx.hh_prefill(W.make_prompts(cfg.vocab, batch, lens, 19), lens, 12)
+    ctx.hh_draft(k)
+    ctx.hh_profile(True)
+    ctx.hh_verify()
+    seen = ctx.hh_profile_read()
+    ctx.hh_profile(False)
+    return {kind: n for (phase, kind), (n, _) in seen.items() if phase == 2}
+
+
+ATTENTION, SCAN, OUT_PROJ, O_PROJ, BRANCHES, OUT_PROJS = 3, 1, 4, 5, 9, 10
+
+
+@pytest.mark.parametrize("head_dim,n_q,n_kv,d_state,heads,batch,k,together", [
+    # the shapes of test_both_branches_in_one_launch
+    (64, 6, 2, 128, 4, 1, 2, True), (128, 5, 1, 256, 4, 2, 4, True), (64, 16, 4, 128, 8, 16, 0, True), (96, 10, 2, 256, 8, 16, 8, True),
+    (48, 8, 4, 256, 4, 3, 8, True), (128, 6, 2, 128, 4, 3, 1, True), (64, 5, 1, 256, 4, 2, 8, True),
+    # the last and the first behind each limit: workgroups of the scan with one and with two per compute unit, positions, row tiles,
+    # head dimension, state size
+    (128, 5, 1, 256, 8, 24, 4, True), (128, 5, 1, 256, 8, 25, 4, False), (64, 4, 2, 128, 32, 32, 0, True), (64, 4, 2, 128, 32, 33, 0, False),
+    (64, 6, 2, 128, 4, 1, 9, False), (64, 16, 2, 128, 4, 1, 2, False), (64, 2, 2, 128, 4, 1, 5, False), (32, 4, 2, 128, 4, 1, 2, False),
+    (136, 4, 2, 128, 4, 1, 2, False), (64, 6, 2, 64, 4, 1, 2, False)])
+def test_which_passes_launch_both_branches_together(B, head_dim, n_q, n_kv, d_state, heads, batch, k, together):
+    """The pass launches what the comparison of the two forms takes for granted, and apart what lies behind the rule's limits;
+    what is timed are the launches of the pass."""
+    cfg = W.scaled_config("pair", n_layers=2, d_model=64, vocab=160, m_heads=heads, m_head_dim=64, d_state=d_state,
+                          n_q_heads=n_q, n_kv_heads=n_kv, head_dim=head_dim, d_ff=96, w_dtype=W.BF16)
+    seen = _verification_launches(B, cfg, batch, k)
+    assert (seen.get(BRANCHES, 0), seen.get(ATTENTION, 0), seen.get(SCAN, 0)) == ((2, 0, 0) if together else (0, 2, 2))
+
+
+@pytest.mark.parametrize("dtype,d_model,head_dim,n_q,m_heads,batch,ks", [
+    # the shapes of test_both_output_projections_in_one_launch; {k: whether the pass takes one launch}
+    (W.F32, 72, 24, 6, 5, 1, {2: True, 0: True}), (W.F32, 72, 40, 3, 5, 4, {0: True, 1: True}), (W.F32, 64, 64, 4, 8, 1, {5: True, 7: True, 8: False}),
+    (W.BF16, 1096, 64, 4, 24, 1, {2: True, 1: True, 0: True}), (W.BF16, 200, 32, 2, 66, 3, {0: True}),
+    (W.BF16, 264, 64, 4, 24, 2, {1: True, 3: True, 6: True}), (W.BF16, 200, 48, 4, 44, 4, {2: True, 0: True}),
+    (W.BF16, 264, 64, 4, 24, 5, {4: True, 7: True}), (W.BF16, 200, 48, 4, 36, 9, {1: True, 5: True, 8: False}),
+    # attention rows longer than the state-space ones: apart up to 16 rows
+    (W.BF16, 264, 64, 8, 4, 2, {0: False, 3: False, 8: True})])
+def test_which_passes_launch_both_output_projections_together(B, dtype, d_model, head_dim, n_q, m_heads, batch, ks):
+    cfg = W.scaled_config("outs", n_layers=2, d_model=d_model, vocab=160, m_heads=m_heads, m_head_dim=32, d_state=32,
+                          n_q_heads=n_q, n_kv_heads=1, head_dim=head_dim, d_ff=96, w_dtype=dtype)
+    for k, together in ks.items():
+        seen = _verification_launches(B, cfg, batch, k, overlap_mode=1)
+        assert (seen.get(OUT_PROJS, 0), seen.get(OUT_PROJ, 0), seen.get(O_PROJ, 0)) == ((2, 0, 0) if together else (0, 2, 2)), k
+
+
 # (sequences, tokens, d_model, d_ff) of two-layer models and the plan (row tiles per wavefront, K splits) that each product
 # of a prefill pass over all their rows gets: the input projection (in) and the attention's output (o) store, the
 # state-space output (out) and the down projection add, gate/up (up) is the SwiGLU product
