@@ -146,6 +146,7 @@ template <int HELD>
 __global__ __launch_bounds__(1024) void split_tiles_kernel(const float* __restrict__ X, const float* __restrict__ X2, int ldx, int M, int K, int Kp,
                                                            const float* __restrict__ norm_w, float eps, uint16_t* __restrict__ planes, int slice) {
   constexpr int NH = HELD > 0 ? HELD : 1;
+  constexpr bool HELD_NORM = HELD <= 3;
   __shared__ float red[16][16];
   const int tid = threadIdx.x, r = tid & 15, kg = tid >> 4, wave = tid >> 6;
   const int m = blockIdx.x * 16 + r;
@@ -162,8 +163,7 @@ __global__ __launch_bounds__(1024) void split_tiles_kernel(const float* __restri
 #pragma unroll
       for (int i = 0; i < NH; ++i) {   // K % 8 == 0: a group is inside or outside
         split_load8(xr, xr2, min(kg * 8 + 512 * i, K - 8), held[i]);
-        const float4 n0 = *reinterpret_cast<const float4*>(norm_w + min(kg * 8 + 512 * i, K - 8)), n1 = *reinterpret_cast<const float4*>(norm_w + min(kg * 8 + 512 * i, K - 8) + 4);
-        nw[i][0] = n0.x; nw[i][1] = n0.y; nw[i][2] = n0.z; nw[i][3] = n0.w; nw[i][4] = n1.x; nw[i][5] = n1.y; nw[i][6] = n1.z; nw[i][7] = n1.w;
+        if (HELD_NORM) split_load8(norm_w, nullptr, min(kg * 8 + 512 * i, K - 8), nw[i]);
       }
 #pragma unroll
       for (int i = 0; i < NH; ++i)
@@ -193,6 +193,7 @@ __global__ __launch_bounds__(1024) void split_tiles_kernel(const float* __restri
     for (int i = 0; i < NH; ++i) {
       const int k = kg * 8 + 512 * i;
       if (512 * i < k_begin || k >= k_end) continue;
+      if (!HELD_NORM) split_load8(norm_w, nullptr, min(k, K - 8), nw[i]);
       float v[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = row_ok && k < K ? held[i][e] * nw[i][e] * rstd : 0.f;
