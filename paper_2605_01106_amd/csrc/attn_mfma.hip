@@ -149,11 +149,14 @@ hipError_t launch_attention_mfma(const Dims& d, const AttnArgs& a_in, hipStream_
   AttnArgs a = a_in;
   if (!attention_mfma_accepts(d, a)) return hipErrorInvalidValue;
   int rt = attention_mfma_row_tiles(d, a.T), row_chunks = attention_mfma_row_chunks(d, a.T);
-  if (a.n_splits == 1 && !attention_mfma_fuses_append(d, a.T)) {
+  if (a.n_splits == 1 && !attention_mfma_fuses_append(d, a.T) && (a.keys > 1024 || (long)row_chunks * d.Hkv * a.B <= 64)) {
     // A prefill pass of few sequences: the smallest tiles that still run side by side, one workgroup per compute unit (a
     // workgroup's key steps are a serial chain that shortens with its rows).  One sequence: 509 positions at the 0.5B shape,
     // 64 workgroups of 4 tiles or 256 of one, prefill 7.53 -> 7.40 ms; 4096 in passes of 512 through four 3B blocks, 80
-    // workgroups of 4 tiles 13.10 ms, 160 of 2 tiles 12.92, 320 of one 13.14.
+    // workgroups of 4 tiles 13.10 ms, 160 of 2 tiles 12.92, 320 of one 13.14.  Up to 1024 keys only where the launch would leave
+    // three quarters of the chip idle: otherwise the scan beside it is the longer branch, and loses the compute units that the
+    // attention spreads over (512 positions, 4 tiles against 2: two sequences at the 0.5B shape 1505 against 1532 us, one at the
+    // 3B shape 787 against 800; two sequences of 6144 positions 19.65 against 19.03 ms).
     for (int t = 1; t < rt; ++t)
       if ((long)((a.T * (d.Hq / d.Hkv) + 16 * t - 1) / (16 * t)) * d.Hkv * a.B <= 256) rt = t;
     row_chunks = (a.T * (d.Hq / d.Hkv) + 16 * rt - 1) / (16 * rt);

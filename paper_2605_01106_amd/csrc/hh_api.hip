@@ -86,6 +86,7 @@ struct hh_ctx {
   int phase = PH_CREATED;
   int B = 0, G = 0, k = 0;
   int len_upper = 0;
+  int prefill_keys = 0;   // most keys of the prefill pass that is being enqueued
   std::vector<int> h_page_table, h_plan;
   std::vector<int> read_back;   // what hh_get_lengths and hh_get_round bring in one copy (sized in hh_create: those calls allocate nothing)
   std::string err;
@@ -411,7 +412,7 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
       a.kpool = w.kpool; a.vpool = w.vpool; a.qkv = x->qkv; a.o = x->o; a.pos0 = x->pos0; a.n_tok = n_tok; a.row0 = row0;
       a.page_table = x->page_table; a.rope = x->rope; a.part_o = x->part_o; a.part_ml = x->part_ml;
       a.counters = x->attn_counters;
-      a.T = T; a.B = B; a.n_splits = n_splits;
+      a.T = T; a.B = B; a.n_splits = n_splits; a.keys = prefill ? x->prefill_keys : x->len_upper + T;
       GemvArgs& b = o_proj;
       b.X = x->o; b.ldx = d.dq; b.M = M; b.K = d.dq; b.norm_w = nullptr; b.epi = EPI_STORE; b.bf16 = d.bf16; b.flags = d.flags; b.plan_rows = planned;
       b.seg[0] = {w.w_o, nullptr, w.p_o, nullptr, x->ho, d.D, d.D}; b.n_seg = 1;
@@ -794,6 +795,7 @@ hh_status hh_prefill(hh_ctx* x, const int32_t* tokens, int32_t row_stride, const
 
   for (int p = 0; p < n_pass; ++p) {
     const int T = maxlen - p * chunk < chunk ? maxlen - p * chunk : chunk;
+    x->prefill_keys = p * chunk + T;
     const int* nt = x->prefill_plan + (size_t)p * B;
     const int* is_last = nt + (size_t)n_pass * B;
     // Prompts of unequal length: a pass computes the rows of the positions that exist and no others (of 64 prompts of 224 to

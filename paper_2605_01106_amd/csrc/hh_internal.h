@@ -144,6 +144,7 @@ struct AttnArgs {
   float* part_o; float* part_ml;  // split scratch: [B*T*Hq][S][Dh], [B*T*Hq][S][2]
   int* counters;          // [B][Hkv][row chunks], zero between launches: tickets of the key slices
   int T, B, n_splits;
+  int keys;               // most keys that a sequence of the pass attends over (as far as the host knows)
 };
 int attention_row_chunks(const Dims& d, int T);
 hipError_t launch_attention(const Dims& d, const AttnArgs& a, hipStream_t s);
