@@ -155,7 +155,7 @@ def main():
     ap.add_argument("--prefill-profile", action="store_true",
                     help="after the timed prefill, run it once more with per-launch events (serial, no branch overlap) and "
                          "report the time per kind of kernel under prefill_kernels")
-    ap.add_argument("--attn-target-blocks", type=int, default=0, help="hh_cfg.attn_target_blocks (0: the library's 512)")
+    ap.add_argument("--attn-target-blocks", type=int, default=0, help="hh_cfg.attn_target_blocks (0: the library's 256)")
     ap.add_argument("--attn-max-splits", type=int, default=0, help="hh_cfg.attn_max_splits (0: the library's 16)")
     ap.add_argument("--overlap-mode", type=int, default=0, help="hh_cfg.overlap_mode (0 automatic, 1 never, 2 prefill only, 3 always)")
     ap.add_argument("--k", type=int, default=None, help="draft length (default: the workload's)")

@@ -105,7 +105,9 @@ typedef struct hh_cfg {
   int32_t attn_target_blocks;           /* key slices are chosen so that an attention launch has about this many workgroups
                                            (sequences x KV heads x row chunks x slices): 64..8192; 0 = 256 */
   int32_t attn_single_slice_steps;      /* matrix-core attention: caches of at most this many 32-key steps use one slice;
-                                           0 = 28 (12 for head dimensions above 64), -1 = split from the first step on */
+                                           0 = 28 (12 for head dimensions above 64, but 28 there too where attention and scan
+                                           are one launch with at least 1024 workgroups of the scan: batches of large states),
+                                           -1 = split from the first step on */
   int32_t kernel_flags;                 /* HH_KF_* bits: kernel selection for cross-checks, all 0 by default */
   int32_t prefill_progress;             /* n > 0: hh_prefill waits for every n-th pass and reports it on stderr */
   int32_t draft_state_mode;             /* recurrent state the draft model M_S runs on (Eq. 4, Section 3.3 draft phase):

@@ -1,7 +1,7 @@
 // Attention branch of the hybrid block for multi-position passes (verification, prefill):
 // the float32-FMA kernel (float32 KV cache; any head dimension that is a multiple of 8), the
 // append of new keys and values to the paged cache, and the dispatch between this kernel and
-// the matrix-core kernel used for a bf16 cache.
+// the matrix-core kernel used for a bf16 cache with pages of 32 tokens and more (with pages of 16 it takes this one as well).
 //
 // One kernel per layer: rotary embedding of q and k, append of k and v to the paged KV cache
 // (rounded to the storage type), causal grouped-query attention of the T new positions over
@@ -133,7 +133,8 @@ __global__ __launch_bounds__(256) void attention_kernel(const Dims d, const Attn
       vreg[i] = *reinterpret_cast<const uint4*>(vbytes + ((((size_t)vpg[i] * d.Hkv + kvh) * Dh + p.dd) * d.page_tokens + (vpos & pmask)) * esz);
     }
   };
-  if (sp == 0 && a.T <= 16) load_tile(0);   // (longer passes begin with an empty cache)
+  // (Longer passes ask for it below, once the position says that something is cached: of a prompt's first pass nothing is.)
+  if (sp == 0 && a.T <= 16) load_tile(0);
 
   // rows of this workgroup: row = position j * G + query head of the group; valid while j < nt
   const int nt = a.n_tok != nullptr ? a.n_tok[b] : a.T;

@@ -131,10 +131,11 @@ __device__ void row_stats(const float* __restrict__ row, int V, float inv_t, flo
 // multiple of 4 is read once, with all loads of a thread in flight together, where the loops above and below read it two
 // or three times, a dependent load per pass of a loop.  Same sums in the same order, so the same bits.  Draw from 64 rows
 // of 1000 entries 5.7 -> 5.0 us, of 4096 6.4 -> 5.5, of 32768 16.4 -> 10.5, of 65536 28.4 -> 15.0; acceptance of 64 sequences
-// at k = 8 over 4096 entries 21 -> 14 us, over 32768 70 -> 43 (statistics of two rows on a compute unit at a time: at most 64
-// registers), over 65536 130 -> 107: the statistics 78 us for 285 MB, 3.7 TB/s (a plain sum of 2 GiB reads 4.0), then 23 us on
-// one compute unit per sequence, two rows of 256 KB and 131072 exponentials each.  The draw with the residual keeps sums
-// only there: 64 registers of masses spill behind the two exponentials per entry.
+// at k = 8 over 4096 entries 21 -> 14 us, over 32768 70 -> 40 (statistics of two rows on a compute unit at a time: at most 64
+// registers), over 65536 130 -> 96: the statistics 74 us for 285 MB, 3.8 TB/s (a plain sum of 2 GiB reads 4.0; the next row
+// requested behind the exponentials of this one takes 74 as well, with 17 registers spilled, and its scratch memory makes the
+// call 7 us longer), then 22 us on one compute unit per sequence, two rows of 256 KB and 131072 exponentials each.  The draw with
+// the residual keeps sums only there: 64 registers of masses spill behind the two exponentials per entry.
 constexpr int kRegGroups = 16;   // groups of 4 entries per thread at most: 64 registers, one workgroup of 16 wavefronts per compute unit
 __host__ __device__ constexpr int reg_vocab(int groups) { return groups * kDrawThreads * 4; }
 
@@ -238,7 +239,6 @@ template <typename P, typename F>
 __device__ int draw_walk(float acc, P prepare, F val, int V, float u, float* red, int* res) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int seg = segment_size(V);
-  const int j0 = min(V, w * seg), j1 = min(V, j0 + seg);
   acc = wave_sum(acc);
   if (lane == 0) red[w] = acc;
   __syncthreads();

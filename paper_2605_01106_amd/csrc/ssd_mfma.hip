@@ -397,8 +397,9 @@ static hipError_t ssd_launch(const Dims& d, const SsmArgs& a, const SsdSeg& seg,
 
 // When the segmented form is taken.  Fewer than 128 workgroups (sequence, pair of heads) leave half the chip idle in a
 // walk, and the position-by-position kernel that served them is a serial chain of 0.36 us (0.5B shape) or 0.59 us (3B
-// shape) per position.  As many segments as give kSegWorkgroups workgroups (two per compute unit; one at state size 256,
-// where the staged chunk takes 101 KB of LDS), at least one chunk each.  One sequence, pass of 512 positions: 0.5B shape
+// shape) per position.  As many segments as give kSegWorkgroups workgroups (half of them at state size 256), at least one chunk
+// each.  One workgroup of 8 wavefronts is resident per compute unit at a time (146 to 253 registers; two would need 128, and at
+// state size 256 the staged chunk takes 101 KB of LDS as well), so that 512 of them are up to two rounds: what was measured.  One sequence, pass of 512 positions: 0.5B shape
 // 186 -> 43 us (16.0 + 7.8 + 19.6), 3B shape 300 -> 90 us (31.5 + 10.4 + 48.2); prefill of 509 tokens at the 0.5B shape
 // 13.8 -> 8.7 ms, of 4096 tokens through four 3B blocks 20.8 -> 15.0 ms, 8 sequences of 512 at 12 0.5B blocks 11.2 -> 9.7.
 // The local pass repeats the staging and the state products, so at state size 256 fewer than three segments give nothing
