@@ -82,7 +82,7 @@ int branches_scan_blocks(const Dims& d, int B, int T) {
 // 5120 2843 -> 2860; one per compute unit, 320 workgroups 6230 -> 6078, but 640 8650 -> 8780.
 // The kernels that exist are those of the shapes that were measured, not all that could gain: state sizes 128 and 256, head
 // dimensions 33 to 128, and the row tiles that 3 to 5 query heads per KV head give (one tile up to three positions, one or two up
-// to five, two or three up to nine).  Others, as 8 query heads per KV head at three positions or 2 at nine, launch the branches apart.
+// to five, two or three up to nine).  Others, as 8 query heads per KV head at three positions or 1 at nine, launch the branches apart.
 bool branches_fit(const Dims& d, int B, int T) {
   const SsmArgs ss = one_layer(B, T);
   if (!attention_uses_mfma(d) || !attention_mfma_fuses_append(d, T) || !ssm_small_fits(d, ss) || (d.N != 128 && d.N != 256)) return false;
