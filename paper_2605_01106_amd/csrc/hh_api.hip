@@ -1083,28 +1083,26 @@ static hh_status sync_stream(hh_ctx* x, void* stream) {
   return HH_OK;
 }
 
-// A copy of device memory to the caller's (pageable) memory takes 13 us up to 16 KB, 22 where the context works on the NULL stream;
-// as a strided copy of a single row it takes 11, but from 16 KB on the plain one is faster (9.5 us; 19.5 at 256 KB).
-static hipError_t copy_out(void* dst, const void* src, size_t bytes) {
-  if (bytes <= 16384) return hipMemcpy2D(dst, bytes, src, bytes, bytes, 1, hipMemcpyDeviceToHost);
-  return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+// Device memory to the caller's (pageable) memory, behind all work of the stream and done when it returns: 12 us up to 16 KB, 9
+// to 19 from there to 256 KB, where hipStreamSynchronize and hipMemcpy take 13, or 22 on the NULL stream.  (hipMemcpy2D of a
+// single row takes 11, but under rocprofv3 it returns without having copied anything.)
+static hipError_t copy_out(void* dst, const void* src, size_t bytes, void* stream) {
+  return hipMemcpyWithStream(dst, src, bytes, hipMemcpyDeviceToHost, static_cast<hipStream_t>(stream));
 }
 
 hh_status hh_get_tokens(hh_ctx* x, int32_t seq, int32_t* out, int32_t cap, int32_t* n_out, void* stream) {
   if (!x) return HH_EINVAL;
   if (x->phase == PH_CREATED) return fail(x, HH_ESTATE, "hh_get_tokens: nothing prefilled");
   if (seq < 0 || seq >= x->B || !out || !n_out || cap < 0) return fail(x, HH_EINVAL, "hh_get_tokens: bad argument");
-  hh_status st = sync_stream(x, stream);
-  if (st != HH_OK) return st;
-  // the count and the first tokens in one copy (33 -> 11 us per sequence), whatever is committed beyond them in a second one
+  // the count and the first tokens in one copy (33 -> 12 us per sequence), whatever is committed beyond them in a second one
   constexpr int kFirst = 4095;
   int row[kFirst + 1];
   const int* src = x->out_tok + (size_t)seq * out_stride(x->d);
   const int most = cap < x->G ? cap : x->G, first = most < kFirst ? most : kFirst;
-  HH_HIP(copy_out(row, src, (size_t)(first + 1) * sizeof(int)));
+  HH_HIP(copy_out(row, src, (size_t)(first + 1) * sizeof(int), stream));
   const int c = row[0] < most ? row[0] : most;
   std::copy_n(row + 1, c < first ? c : first, out);
-  if (c > first) HH_HIP(copy_out(out + first, src + 1 + first, (size_t)(c - first) * sizeof(int)));
+  if (c > first) HH_HIP(copy_out(out + first, src + 1 + first, (size_t)(c - first) * sizeof(int), stream));
   *n_out = c;
   return HH_OK;
 }
@@ -1112,11 +1110,9 @@ hh_status hh_get_tokens(hh_ctx* x, int32_t seq, int32_t* out, int32_t cap, int32
 hh_status hh_get_lengths(hh_ctx* x, int32_t* kv_len, int32_t* committed, int32_t* last_n, void* stream) {
   if (!x) return HH_EINVAL;
   if (x->phase == PH_CREATED) return fail(x, HH_ESTATE, "hh_get_lengths: nothing prefilled");
-  hh_status st = sync_stream(x, stream);
-  if (st != HH_OK) return st;
   const size_t n = x->B;
   int* v = x->read_back.data();
-  HH_HIP(copy_out(v, x->kv_len, (x->last_n - x->kv_len + n) * sizeof(int)));
+  HH_HIP(copy_out(v, x->kv_len, (x->last_n - x->kv_len + n) * sizeof(int), stream));
   auto bring = [&](const int* from, int32_t* to) { if (to) std::copy_n(v + (from - x->kv_len), n, to); };
   bring(x->kv_len, kv_len); bring(x->committed, committed); bring(x->last_n, last_n);
   return HH_OK;
@@ -1162,21 +1158,20 @@ hh_status hh_get_acceptance(hh_ctx* x, uint64_t* accepted, uint64_t* tested, voi
 hh_status hh_get_round(hh_ctx* x, int32_t* drafts, int32_t* targets, void* stream) {
   if (!x) return HH_EINVAL;
   if (x->phase == PH_CREATED) return fail(x, HH_ESTATE, "hh_get_round: nothing prefilled");
-  hh_status st = sync_stream(x, stream);
-  if (st != HH_OK) return st;
   const Dims& d = x->d;
-  // The rows of the batch, their k or k + 1 columns picked out here (as strided copies 870 us for 64 sequences at k = 8, now 11);
-  // both arrays in one copy unless what lies between them takes longer than a second copy (256 KB: 10 us).
+  // The rows of the batch, their k or k + 1 columns picked out here (as strided copies 870 us for 64 sequences at k = 8, now 12);
+  // both arrays in one copy unless what lies between them takes longer than a second copy (256 KB: 8 us).
   constexpr size_t kBetween = 65536;
   const size_t n_d = drafts && x->k > 0 ? (size_t)x->B * d.Kmax : 0, n_t = targets ? (size_t)x->B * (d.Kmax + 1) : 0;
   const size_t apart = x->targets - x->drafts;
   int *dr = x->read_back.data(), *tg = dr + n_d;
   if (n_d > 0 && n_t > 0 && apart - n_d <= kBetween) {
     tg = dr + apart;
-    HH_HIP(copy_out(dr, x->drafts, (apart + n_t) * sizeof(int)));
+    HH_HIP(copy_out(dr, x->drafts, (apart + n_t) * sizeof(int), stream));
   } else {
-    if (n_d > 0) HH_HIP(copy_out(dr, x->drafts, n_d * sizeof(int)));
-    if (n_t > 0) HH_HIP(copy_out(tg, x->targets, n_t * sizeof(int)));
+    if (n_d + n_t == 0) return sync_stream(x, stream);
+    if (n_d > 0) HH_HIP(copy_out(dr, x->drafts, n_d * sizeof(int), stream));
+    if (n_t > 0) HH_HIP(copy_out(tg, x->targets, n_t * sizeof(int), stream));
   }
   for (int b = 0; b < x->B; ++b) {
     if (n_d > 0) std::copy_n(dr + (size_t)b * d.Kmax, x->k, drafts + (size_t)b * x->k);
