@@ -474,6 +474,10 @@ static hipError_t launch_attention_f(const Dims& d, const AttnArgs& a, int row_c
 template <int BF16, int E>
 static hipError_t launch_attention_t(const Dims& d, const AttnArgs& a, int row_chunks, size_t lds, hipStream_t s) {
   // (a bf16 cache comes here with pages of 16 tokens, and for cross-checks)
+  // The registers of whole tiles (float32, 64: 211 against 155, two workgroups per compute unit instead of three) pay in large launches as
+  // well.  Item loads under a condition each, and now: 64 sequences x 3 positions over 300 keys, head dimension 64 73 -> 46 us, 128
+  // 104 -> 72; x 9 over 1000 keys 190 -> 93 and 374 -> 196; a prefill pass of 64 positions each over up to 300 keys 115 -> 83 and 270 -> 160;
+  // bf16 with 16-token pages, 128: 90 -> 65, 298 -> 167 and 228 -> 153.
   if (!BF16 && d.Dh == 64 * E) return launch_attention_f<BF16, E, !BF16, false>(d, a, row_chunks, lds, s);
   // Places of the items walked where the registers they take cost a workgroup per compute unit in launches of many.  Float32,
   // head dimensions 72 to 120 (256 + 41 registers against 213: one against two), head dimension 96: prefill of 64 x 300 positions

@@ -435,7 +435,8 @@ bool ssm_small_wide(const Dims& d, const SsmArgs& a) {   // 16 lanes per row: tw
   return d.N % 64 == 0 && waves8 < 1024;
 }
 
-// true if the pass was taken by the few-positions kernel
+// true if the pass was taken by the few-positions kernel.  (State size 8, the only other one that a model may have, keeps the
+// position-by-position kernel: 2 lanes per row of one float4 each were not built, no measured model has it.)
 static bool launch_ssm_small(const Dims& d, const SsmArgs& a, hipStream_t s, hipError_t* err) {
   if (!ssm_small_fits(d, a)) return false;
   const int tmax = ssm_small_tmax(a.T);
