@@ -37,8 +37,8 @@ struct LayerDev {
 // ---- skinny GEMM: Y[m][n] (op)= sum_k norm(X)[m][k] * W[n][k]
 enum { EPI_STORE = 0, EPI_ADD = 1, EPI_SWIGLU = 2 };
 // A bf16 matrix as the matrix-core kernels read it: scaled float16 tiles (packed_weight_elems 16-bit values) and its factors
-// (scaled_tiles_floats): scale[0] for the activations of a many-row product and its inverse scale[1], scale[kScaleHead + t] the
-// inverse of the factor that the 16 rows of tile t are held times.
+// (scaled_tiles_floats): scale[0] for the activations of a many-row product and its inverse scale[1], scale[kScaleHead + n] the
+// inverse of the factor that row n is held times.
 constexpr int kScaleHead = 4;
 struct HalfTiles { uint16_t* tiles; float* scale; };
 struct GemvSeg {
@@ -79,7 +79,7 @@ size_t packed_weight_elems(int N, int K);
 bool skinny_mfma_fits(const GemvArgs& a);
 hipError_t launch_skinny_mfma(const GemvArgs& a, float* partial, int* n_blocks_out, hipStream_t s);
 // row_best (EPI_STORE only): per-row argmax keys [M], zeroed by the caller, raised with atomic maxima; store = 0: Y is not written
-// f, f2: factors of the weight tiles of each matrix
+// f, f2: factors of the weight rows of each matrix
 hipError_t launch_gemm_reduce(int epi, float* partial, int ksplit, int M, int N, const float* f, const float* f2, float* Y, int ldy, const float* R2,
                               const float* ssq, int ssq_ld, float rnorm_k, float eps, unsigned long long* row_best, int store,
                               hipStream_t s);
