@@ -249,9 +249,12 @@ __device__ __forceinline__ void gemv_body(const GemvArgs& a, const int m0, const
     }
     if (owner && rg < nrg) {
       float v = mine * rstd;
-      if (EPI == EPI_SWIGLU) v = v / (1.0f + expf(-v)) * (mine2 * rstd);
-      if (EPI == EPI_ADD) v += resid;
       const int n = rg * R + out_r;
+      if (EPI == EPI_SWIGLU) {
+        v = v / (1.0f + expf(-v)) * (mine2 * rstd);
+        if (a.out_factor != nullptr) v *= a.out_factor[n];
+      }
+      if (EPI == EPI_ADD) v += resid;
       Yb[(size_t)out_m * ldy + n] = v;
       if (a.best != nullptr) {
         const unsigned long long key = argmax_key(v, n);

@@ -79,6 +79,7 @@ struct hh_ctx {
   uint16_t* planes_side; // the same two scratch areas for products enqueued on the side stream
   uint16_t* planes_act;  // SwiGLU result of a many-row pass, handed to the down projection as split planes
   float* gemm_partial_side;
+  float* row_factors;    // [Mmax] of the rows of a many-row pass's SwiGLU result
   float* ho;             // [Mmax][D] attention branch after its output projection (full mode)
   float *rope, *h, *zx, *qkv, *g, *o, *act, *logits_d, *logits_v, *logits_p, *lasth, *part_o, *part_ml, *export_buf, *seg_scratch, *ssd_shared;
   int max_passes;
@@ -93,7 +94,8 @@ struct hh_ctx {
   // optional per-launch timing (hh_profile): event pairs tagged phase*16 + kind
   bool prof_on = false;
   // library-owned copies of every matrix as the matrix-core kernels read it (bf16 weights)
-  struct LayerTiles { HalfTiles inqkv, out, o, gate, up, down; };
+  // (up_act: up with the factors of the SwiGLU result's columns in its row factors, act_inverse: those alone; see act_factors_kernel)
+  struct LayerTiles { HalfTiles inqkv, out, o, gate, up, up_act, down; float* act_inverse; };
   std::vector<LayerTiles> tiles;   // per layer
   HalfTiles tiles_lm_head{};
   int only_kind = -1;   // hh_time_kind: launch only this kind of kernel
@@ -226,6 +228,7 @@ size_t carve(hh_ctx* x, char* base) {
     x->planes_side = c.take<uint16_t>(gemm_planes_elems((int)Mmax, kmax));
     x->planes_act = d.bf16 && Mmax > 16 ? c.take<uint16_t>(gemm_planes_elems((int)Mmax, d.F)) : nullptr;
     x->gemm_partial_side = d.bf16 ? c.take<float>(gemm_partial_elems()) : nullptr;
+    x->row_factors = d.bf16 ? c.take<float>(Mmax) : nullptr;
   }
   x->rope = c.take<float>((size_t)d.max_seq * d.Dh);
   x->h = c.take<float>(Mmax * d.D);
@@ -274,6 +277,7 @@ size_t carve(hh_ctx* x, char* base) {
       hh_ctx::LayerTiles m;
       m.inqkv = tiles(d.ldzx, d.D); m.out = tiles(d.D, d.d_inner); m.o = tiles(d.D, d.dq);
       m.gate = tiles(d.F, d.D); m.up = tiles(d.F, d.D); m.down = tiles(d.D, d.F);
+      m.up_act = {m.up.tiles, c.take<float>(scaled_tiles_floats(d.F))}; m.act_inverse = c.take<float>(d.F);
       if (base) x->tiles[l] = m;
     }
     x->tiles_lm_head = tiles(d.V, d.D);
@@ -316,13 +320,15 @@ hh_status fail(hh_ctx* x, hh_status st, const std::string& msg) {
 constexpr int kMfmaMinRows = 9;
 constexpr int kSkinnyMinRows = 4;
 bool takes_skinny(const GemvArgs& a) { return a.bf16 && !(a.flags & HH_KF_SKINNY_OFF) && a.M >= kSkinnyMinRows && skinny_mfma_fits(a); }
+bool takes_many(const GemvArgs& a) { return !takes_skinny(a) && !mid_mfma_fits(a) && a.bf16 && a.M >= kMfmaMinRows && a.seg[0].H.tiles != nullptr; }
+bool takes_tiles(const GemvArgs& a) { return takes_skinny(a) || mid_mfma_fits(a) || takes_many(a); }
 // side: the product is enqueued on the side stream (its own scratch, so that it may overlap a product on the main stream)
 hipError_t product(hh_ctx* x, const GemvArgs& a, hipStream_t s, bool side = false) {
   if (a.planes_in != nullptr || a.planes_out != nullptr)   // hand-over between two many-row products
     return launch_gemm_mfma(a, side ? x->planes_side : x->planes, side ? x->gemm_partial_side : x->gemm_partial, s);
   if (takes_skinny(a)) return launch_skinny_mfma(a, side ? x->gemm_partial_side : x->gemm_partial, nullptr, s);
   if (mid_mfma_fits(a)) return launch_mid_mfma(a, side ? x->gemm_partial_side : x->gemm_partial, s);
-  if (a.bf16 && a.M >= kMfmaMinRows && a.seg[0].H.tiles != nullptr)
+  if (takes_many(a))
     return launch_gemm_mfma(a, side ? x->planes_side : x->planes, side ? x->gemm_partial_side : x->gemm_partial, s);
   return launch_gemv(a, nullptr, s);
 }
@@ -452,12 +458,13 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
       b.seg[0] = {w.w_down, nullptr, x->h, d.D, d.D, tiles.down, {}}; b.n_seg = 1;
       // many rows: the SwiGLU result goes to the down projection as split planes, without the float32
       // round trip through `act` and without a split kernel of its own
-      if (x->planes_act != nullptr && !(d.flags & HH_KF_NO_HANDOVER) && !mid_mfma_fits(a)) {
-        if (!takes_skinny(a) && gemm_hands_over_planes(a)) {
-          a.planes_out = x->planes_act; a.planes_out_scale = tiles.down.scale;
-          b.planes_in = x->planes_act;
-        }
+      const bool hand_over = x->planes_act != nullptr && !(d.flags & HH_KF_NO_HANDOVER) && !takes_skinny(a) && !mid_mfma_fits(a) && gemm_hands_over_planes(a);
+      if (hand_over || takes_tiles(b)) {   // its tiles hold the columns times the factors that the SwiGLU result is divided by
+        a.seg[0].H2 = tiles.up_act;
+        a.out_factor = tiles.act_inverse;
       }
+      if (hand_over || (takes_many(a) && takes_many(b))) { a.row_factors_out = x->row_factors; b.row_factors = x->row_factors; }
+      if (hand_over) { a.planes_out = x->planes_act; b.planes_in = x->planes_act; }
       HH_LAUNCH(HH_K_MLP_UP, product(x, a, s));
       HH_LAUNCH(HH_K_MLP_DOWN, product(x, b, s));
     }
@@ -672,28 +679,31 @@ hh_status hh_create(const hh_weights* weights, const hh_cfg* cfg, hh_ctx** out) 
   if (d.bf16) {   // copies of every matrix in the tile layout of the matrix-core kernels
     hipError_t pe = hipSuccess;
     // (the norms of the matrices' rows go to product scratch meanwhile)
-    float *n1 = ctx->gemm_partial, *n2 = n1 + 65536, *unused = n2 + 65536;
-    auto pack = [&](const void* W, int N, int K, const HalfTiles& h, float* norms) { if (pe == hipSuccess) pe = launch_scaled_tiles(W, N, K, (size_t)K, h, norms, nullptr); };
-    auto bound = [&](const void* norm_w, int K, const float* a, const float* b, int rows, const HalfTiles& h) {
-      if (pe == hipSuccess) pe = launch_input_bound(static_cast<const float*>(norm_w), K, a, b, rows, h, nullptr);
+    float *n1 = ctx->gemm_partial, *n2 = n1 + 65536, *col = n2 + 65536;
+    auto pack = [&](const void* W, int N, int K, const HalfTiles& h, float* norms, const float* columns = nullptr) {
+      if (pe == hipSuccess) pe = launch_scaled_tiles(W, N, K, (size_t)K, columns, h, norms, nullptr);
+    };
+    auto bound = [&](const void* norm_w, int K, int kind, const float* norms, int rows, const HalfTiles& h) {
+      if (pe == hipSuccess) pe = launch_input_bound(static_cast<const float*>(norm_w), K, kind, norms, rows, h, nullptr);
     };
     for (int l = 0; l < d.L; ++l) {
       const LayerDev& ld = ctx->layers_host[l];
       const hh_ctx::LayerTiles& t = ctx->tiles[l];
       pack(ld.w_inqkv, d.ldzx, d.D, t.inqkv, n1);
-      bound(ld.norm1, d.D, nullptr, nullptr, 0, t.inqkv);
-      pack(ld.w_o, d.D, d.dq, t.o, unused);
-      bound(ld.norm1, d.D, n1 + d.d_in_proj + d.dq + d.dkv, nullptr, d.dkv, t.o);   // (the rows of w_v)
-      pack(ld.w_out, d.D, d.d_inner, t.out, unused);
-      bound(ld.gnorm, d.d_inner, nullptr, nullptr, 0, t.out);
+      bound(ld.norm1, d.D, BOUND_NORMED, nullptr, 0, t.inqkv);
+      pack(ld.w_o, d.D, d.dq, t.o, nullptr);
+      bound(ld.norm1, d.D, BOUND_VALUES, n1 + d.d_in_proj + d.dq + d.dkv, d.dkv, t.o);   // (the rows of w_v)
+      pack(ld.w_out, d.D, d.d_inner, t.out, nullptr);
+      bound(ld.gnorm, d.d_inner, BOUND_NORMED, nullptr, 0, t.out);
       pack(ld.w_gate, d.F, d.D, t.gate, n1);
       pack(ld.w_up, d.F, d.D, t.up, n2);
-      bound(ld.norm2, d.D, nullptr, nullptr, 0, t.gate);
-      pack(ld.w_down, d.D, d.F, t.down, unused);
-      bound(ld.norm2, d.D, n1, n2, d.F, t.down);
+      bound(ld.norm2, d.D, BOUND_NORMED, nullptr, 0, t.gate);
+      if (pe == hipSuccess) pe = launch_act_factors(n1, n2, d.F, t.gate.scale, t.up.scale, t.up_act.scale, col, t.act_inverse, nullptr);
+      pack(ld.w_down, d.D, d.F, t.down, nullptr, col);
+      bound(ld.norm2, d.D, BOUND_ACT, nullptr, 0, t.down);
     }
     pack(ctx->lm_head, d.V, d.D, ctx->tiles_lm_head, nullptr);
-    bound(ctx->final_norm, d.D, nullptr, nullptr, 0, ctx->tiles_lm_head);
+    bound(ctx->final_norm, d.D, BOUND_NORMED, nullptr, 0, ctx->tiles_lm_head);
     if (pe == hipSuccess) pe = hipDeviceSynchronize();
     if (pe != hipSuccess) return bail(pe, "hh_create: packing the weights");
   }

@@ -22,9 +22,9 @@ FAMILIES = [(2, 4, ()), (3, 5, ()), (4, 10, ()), (6, 16, ()), (10, 16, ()), (10,
             (3, 5, ("HH_KF_SKINNY_OFF", "HH_KF_MID_OFF")), (4, 15, ("HH_KF_MID_OFF",)), (4, 10, ("HH_KF_MID_OFF", "HH_KF_ROWS_LDS"))]
 
 
-def _model(layers=2, seed=11):
-    cfg = W.scaled_config("products", n_layers=layers, d_model=264, vocab=160, m_heads=16, m_head_dim=16, d_state=64, n_q_heads=4, n_kv_heads=2,
-                          head_dim=32, d_ff=416, w_dtype=W.BF16)
+def _model(layers=2, seed=11, d_model=264, d_ff=416):
+    cfg = W.scaled_config("products", n_layers=layers, d_model=d_model, vocab=160, m_heads=16, m_head_dim=16, d_state=64, n_q_heads=4, n_kv_heads=2,
+                          head_dim=32, d_ff=d_ff, w_dtype=W.BF16)
     wts = W.make_lively_weights(cfg, seed)
     for i in range(layers):           # an MLP that counts beside the two branches
         for name, factor in (("w_gate", 4), ("w_up", 4), ("w_down", 2)):
@@ -103,6 +103,47 @@ def test_rows_of_very_different_size_in_one_tile(monkeypatch, batch, tokens, fla
     _scale(wts, "L0.w_in", rows[:, None])
     _scale(wts, "L0.conv_w", np.where(small, np.float32(2.0 ** 26), np.float32(1))[:, None])
     _check(monkeypatch, wts, batch, tokens, flags, per_channel=True)
+
+
+@pytest.mark.parametrize("batch,tokens,flags", FAMILIES)
+def test_mlp_columns_of_very_different_size(monkeypatch, batch, tokens, flags):
+    """One channel of the second norm times 2^13 and its columns of gate and up divided by it, rows of up times 2^-12 to 2^12 and the columns
+    of down divided by it: the same function, and the down projection's input keeps its accuracy."""
+    cfg, wts = _model()
+    r = np.random.default_rng(2)
+    for layer in range(cfg.n_layers):
+        c = np.ones(cfg.d_model, np.float32)
+        c[77] = 2.0 ** 13
+        _scale(wts, f"L{layer}.norm2", c)
+        for name in ("w_gate", "w_up"):
+            _scale(wts, f"L{layer}.{name}", 1 / c)
+        c = np.exp2(r.integers(-12, 13, cfg.d_ff)).astype(np.float32)
+        _scale(wts, f"L{layer}.w_up", c[:, None])
+        _scale(wts, f"L{layer}.w_down", 1 / c)
+    _check(monkeypatch, wts, batch, tokens, flags)
+
+
+@pytest.mark.parametrize("batch,tokens,flags", FAMILIES)
+def test_a_channel_that_outweighs_the_row(monkeypatch, batch, tokens, flags):
+    """One channel of the residual stream 2^18 times the others, its norm weights 2^-18: what the MLP sees of a row is 2^-14 of what the norm
+    allows, its result the square of that."""
+    cfg, wts = _model()
+    c = np.ones(cfg.d_model, np.float32)
+    c[77] = 2.0 ** 18
+    _scale(wts, "embed", c)
+    _scale(wts, "final_norm", 1 / c)
+    for layer in range(cfg.n_layers):
+        for name in ("norm1", "norm2"):
+            _scale(wts, f"L{layer}.{name}", 1 / c)
+        for name in ("w_gate", "w_up"):
+            _scale(wts, f"L{layer}.{name}", 2.0 ** 14)
+    _check(monkeypatch, wts, batch, tokens, flags)
+
+
+# widths at which gate/up and down of 8 rows take different kernels: the vector unit for the one, the matrix cores for the other
+@pytest.mark.parametrize("d_model,d_ff", [(2592, 416), (264, 5128), (2592, 5128)])
+def test_mlp_products_of_different_kernels(monkeypatch, d_model, d_ff):
+    _check(monkeypatch, _model(d_model=d_model, d_ff=d_ff)[1], 2, 4, ())
 
 
 @pytest.mark.parametrize("batch,tokens,flags", FAMILIES)
