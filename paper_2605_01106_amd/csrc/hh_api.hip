@@ -94,8 +94,9 @@ struct hh_ctx {
   // optional per-launch timing (hh_profile): event pairs tagged phase*16 + kind
   bool prof_on = false;
   // library-owned copies of every matrix as the matrix-core kernels read it (bf16 weights)
-  // (up_act: up with the factors of the SwiGLU result's columns in its row factors, act_inverse: those alone; see act_factors_kernel)
-  struct LayerTiles { HalfTiles inqkv, out, o, gate, up, up_act, down; float* act_inverse; };
+  // (up_act: up with the factors of the SwiGLU result's columns in its row factors, act_inverse: those alone, act_weights: what the
+  // factors of its rows come from; see act_factors_kernel, act_input_kernel)
+  struct LayerTiles { HalfTiles inqkv, out, o, gate, up, up_act, down; float *act_inverse, *act_weights; };
   std::vector<LayerTiles> tiles;   // per layer
   HalfTiles tiles_lm_head{};
   int only_kind = -1;   // hh_time_kind: launch only this kind of kernel
@@ -277,7 +278,7 @@ size_t carve(hh_ctx* x, char* base) {
       hh_ctx::LayerTiles m;
       m.inqkv = tiles(d.ldzx, d.D); m.out = tiles(d.D, d.d_inner); m.o = tiles(d.D, d.dq);
       m.gate = tiles(d.F, d.D); m.up = tiles(d.F, d.D); m.down = tiles(d.D, d.F);
-      m.up_act = {m.up.tiles, c.take<float>(scaled_tiles_floats(d.F))}; m.act_inverse = c.take<float>(d.F);
+      m.up_act = {m.up.tiles, c.take<float>(scaled_tiles_floats(d.F))}; m.act_inverse = c.take<float>(d.F); m.act_weights = c.take<float>(d.D);
       if (base) x->tiles[l] = m;
     }
     x->tiles_lm_head = tiles(d.V, d.D);
@@ -463,7 +464,7 @@ hh_status run_layers(hh_ctx* x, const std::vector<LayerDev>& table, bool all_ful
         a.seg[0].H2 = tiles.up_act;
         a.out_factor = tiles.act_inverse;
       }
-      if (hand_over || (takes_many(a) && takes_many(b))) { a.row_factors_out = x->row_factors; b.row_factors = x->row_factors; }
+      if (hand_over || (takes_many(a) && takes_many(b))) { a.row_factors_out = x->row_factors; a.row_weights = tiles.act_weights; b.row_factors = x->row_factors; }
       if (hand_over) { a.planes_out = x->planes_act; b.planes_in = x->planes_act; }
       HH_LAUNCH(HH_K_MLP_UP, product(x, a, s));
       HH_LAUNCH(HH_K_MLP_DOWN, product(x, b, s));
@@ -679,9 +680,9 @@ hh_status hh_create(const hh_weights* weights, const hh_cfg* cfg, hh_ctx** out) 
   if (d.bf16) {   // copies of every matrix in the tile layout of the matrix-core kernels
     hipError_t pe = hipSuccess;
     // (the norms of the matrices' rows go to product scratch meanwhile)
-    float *n1 = ctx->gemm_partial, *n2 = n1 + 65536, *col = n2 + 65536;
-    auto pack = [&](const void* W, int N, int K, const HalfTiles& h, float* norms, const float* columns = nullptr) {
-      if (pe == hipSuccess) pe = launch_scaled_tiles(W, N, K, (size_t)K, columns, h, norms, nullptr);
+    float *n1 = ctx->gemm_partial, *n2 = n1 + 65536, *col = n2 + 65536, *uinv = col + 65536;
+    auto pack = [&](const void* W, int N, int K, const HalfTiles& h, float* norms, const float* norm_col = nullptr, const float* columns = nullptr) {
+      if (pe == hipSuccess) pe = launch_scaled_tiles(W, N, K, (size_t)K, columns, h, norm_col, norms, nullptr);
     };
     auto bound = [&](const void* norm_w, int K, int kind, const float* norms, int rows, const HalfTiles& h) {
       if (pe == hipSuccess) pe = launch_input_bound(static_cast<const float*>(norm_w), K, kind, norms, rows, h, nullptr);
@@ -695,12 +696,13 @@ hh_status hh_create(const hh_weights* weights, const hh_cfg* cfg, hh_ctx** out) 
       bound(ld.norm1, d.D, BOUND_VALUES, n1 + d.d_in_proj + d.dq + d.dkv, d.dkv, t.o);   // (the rows of w_v)
       pack(ld.w_out, d.D, d.d_inner, t.out, nullptr);
       bound(ld.gnorm, d.d_inner, BOUND_NORMED, nullptr, 0, t.out);
-      pack(ld.w_gate, d.F, d.D, t.gate, n1);
-      pack(ld.w_up, d.F, d.D, t.up, n2);
+      if (pe == hipSuccess) pe = launch_act_input(ld.w_gate, ld.w_up, d.F, d.D, ld.norm2, t.act_weights, uinv, nullptr);
+      pack(ld.w_gate, d.F, d.D, t.gate, n1, uinv);
+      pack(ld.w_up, d.F, d.D, t.up, n2, uinv);
       bound(ld.norm2, d.D, BOUND_NORMED, nullptr, 0, t.gate);
-      if (pe == hipSuccess) pe = launch_act_factors(n1, n2, d.F, t.gate.scale, t.up.scale, t.up_act.scale, col, t.act_inverse, nullptr);
-      pack(ld.w_down, d.D, d.F, t.down, nullptr, col);
-      bound(ld.norm2, d.D, BOUND_ACT, nullptr, 0, t.down);
+      if (pe == hipSuccess) pe = launch_act_factors(n1, n2, d.F, t.up.scale, t.up_act.scale, col, t.act_inverse, nullptr);
+      pack(ld.w_down, d.D, d.F, t.down, nullptr, nullptr, col);
+      bound(t.act_weights, d.D, BOUND_ACT, nullptr, 0, t.down);
     }
     pack(ctx->lm_head, d.V, d.D, ctx->tiles_lm_head, nullptr);
     bound(ctx->final_norm, d.D, BOUND_NORMED, nullptr, 0, ctx->tiles_lm_head);

@@ -37,8 +37,8 @@ struct LayerDev {
 // ---- skinny GEMM: Y[m][n] (op)= sum_k norm(X)[m][k] * W[n][k]
 enum { EPI_STORE = 0, EPI_ADD = 1, EPI_SWIGLU = 2 };
 // A bf16 matrix as the matrix-core kernels read it: scaled float16 tiles (packed_weight_elems 16-bit values) and its factors
-// (scaled_tiles_floats): scale[0] for the activations of a many-row product and its inverse scale[1], scale[2] the unit of its norm
-// weights (see input_bound_kernel), scale[kScaleHead + n] the inverse of the factor that row n is held times.
+// (scaled_tiles_floats): scale[0] for the activations of a many-row product and its inverse scale[1], scale[kScaleHead + n] the
+// inverse of the factor that row n is held times.
 constexpr int kScaleHead = 4;
 struct HalfTiles { uint16_t* tiles; float* scale; };
 struct GemvSeg {
@@ -68,6 +68,7 @@ struct GemvArgs {
   // tiles hold their column times), and in a many-row pass each row times a power of two from the norm of its normed input.
   const float* out_factor;                 // EPI_SWIGLU on the vector unit: inverse factor per column, or nullptr (the matrix-core kernels have it in H2's factors)
   float* row_factors_out;                  // EPI_SWIGLU, many rows: the rows' factors [M], written by the split; those of planes_out
+  const float* row_weights;                // with row_factors_out: launch_act_input's weighted [K]
   const float* row_factors;                // many rows: the factors of X's rows or planes_in's, or nullptr (seg[0].H.scale[0])
   // Rows that the kernel and its K split are chosen for, where that is not M (0: M).  A prefill pass over prompts of unequal
   // length says batch x positions here: the order of its sums, and with it the bits of a sequence's results, then does not
@@ -109,12 +110,13 @@ hipError_t launch_mid_pair(const GemvArgs& a, const GemvArgs& b, float* partial_
 size_t gemm_planes_elems(int M, int K);   // 16-bit elements of scratch for the split activations
 size_t scaled_tiles_floats(int N);
 // tiles and factors (but for those of the activations) of W [N][K], column k times col[k] (nullptr: as it is); norms: the
-// 2-norms of its rows [N rounded up to 16]
-hipError_t launch_scaled_tiles(const void* W, int N, int K, size_t ldw, const float* col, const HalfTiles& h, float* norms, hipStream_t s);
+// 2-norms of its rows [N rounded up to 16], columns times norm_col[k] (nullptr: as they are)
+hipError_t launch_scaled_tiles(const void* W, int N, int K, size_t ldw, const float* col, const HalfTiles& h, const float* norm_col, float* norms, hipStream_t s);
+// norm weights of the gate/up product's input times column factors u, and 1 / u (see column_max_kernel)
+hipError_t launch_act_input(const void* gate, const void* up, int N, int K, const float* norm_w, float* weighted, float* inverse, hipStream_t s);
 // factors of the SwiGLU result's columns, from the 2-norms of the gate's and the up matrix's rows: col[j] (the down projection's
-// columns), inverse[j], and the up matrix's row factors times inverse[j] in up_out (its other values are up's); gate, up: the scales
-// of the two matrices, gate's with launch_input_bound's values
-hipError_t launch_act_factors(const float* n_gate, const float* n_up, int F, const float* gate, const float* up, float* up_out, float* col, float* inverse, hipStream_t s);
+// columns), inverse[j], and the up matrix's row factors times inverse[j] in up_out (its other values are up's)
+hipError_t launch_act_factors(const float* n_gate, const float* n_up, int F, const float* up, float* up_out, float* col, float* inverse, hipStream_t s);
 // factors of the activations, K columns normed with norm_w or products of them (see input_bound_kernel)
 enum { BOUND_NORMED = 0, BOUND_VALUES = 1, BOUND_ACT = 2 };
 hipError_t launch_input_bound(const float* norm_w, int K, int kind, const float* norms, int rows, const HalfTiles& h, hipStream_t s);

@@ -107,13 +107,13 @@ def test_rows_of_very_different_size_in_one_tile(monkeypatch, batch, tokens, fla
 
 @pytest.mark.parametrize("batch,tokens,flags", FAMILIES)
 def test_mlp_columns_of_very_different_size(monkeypatch, batch, tokens, flags):
-    """One channel of the second norm times 2^13 and its columns of gate and up divided by it, rows of up times 2^-12 to 2^12 and the columns
+    """One channel of the second norm times 2^22 and its columns of gate and up divided by it, rows of up times 2^-12 to 2^12 and the columns
     of down divided by it: the same function, and the down projection's input keeps its accuracy."""
     cfg, wts = _model()
     r = np.random.default_rng(2)
     for layer in range(cfg.n_layers):
         c = np.ones(cfg.d_model, np.float32)
-        c[77] = 2.0 ** 13
+        c[77] = 2.0 ** 22
         _scale(wts, f"L{layer}.norm2", c)
         for name in ("w_gate", "w_up"):
             _scale(wts, f"L{layer}.{name}", 1 / c)
