@@ -106,6 +106,21 @@ def test_rows_of_very_different_size_in_one_tile(monkeypatch, batch, tokens, fla
 
 
 @pytest.mark.parametrize("batch,tokens,flags", FAMILIES)
+def test_a_channel_that_outweighs_its_block(monkeypatch, batch, tokens, flags):
+    """Every 40th norm weight times 2^22 and the columns that it meets divided by it: the same function, and the values beside it keep their
+    accuracy."""
+    cfg, wts = _model()
+    for layer in range(cfg.n_layers):
+        for norm, mats, n in (("norm1", ("w_in", "w_q", "w_k", "w_v"), cfg.d_model), ("gnorm", ("w_out",), cfg.d_inner), ("norm2", ("w_gate", "w_up"), cfg.d_model)):
+            c = np.ones(n, np.float32)
+            c[7::40] = 2.0 ** 22
+            _scale(wts, f"L{layer}.{norm}", c)
+            for name in mats:
+                _scale(wts, f"L{layer}.{name}", 1 / c)
+    _check(monkeypatch, wts, batch, tokens, flags)
+
+
+@pytest.mark.parametrize("batch,tokens,flags", FAMILIES)
 def test_mlp_columns_of_very_different_size(monkeypatch, batch, tokens, flags):
     """One channel of the second norm times 2^22 and its columns of gate and up divided by it, rows of up times 2^-12 to 2^12 and the columns
     of down divided by it: the same function, and the down projection's input keeps its accuracy."""
