@@ -90,8 +90,9 @@ typedef struct hh_cfg {
   int32_t max_new_tokens;               /* largest generation budget per sequence */
   int32_t kv_page_tokens;               /* tokens per KV page: 16, 32, 64, 128 or 256; 0 = default */
   int32_t prefill_chunk;                /* prompt positions per sequence per prefill pass, 1..1024; 0 = default:
-                                           4096 / max_batch (8192 / max_batch for d_model < 2048) rounded down to a multiple of
-                                           64, within 64..4096 and no more than max_seq_len rounded up to one */
+                                           4096 / max_batch (7680 / max_batch for bf16 models of d_model < 2048) rounded down to
+                                           a multiple of 32, within 64..4096 (float32 models: 1024), and where no prompt can be
+                                           that long max_seq_len - 2 max_draft - 3 or 64 */
   int32_t keep_logits;                  /* 1: float32 logits of the draft, verification and last prefill rows are kept for
                                            hh_get_logits.  0: greedy rounds (temperature 0) keep only the argmax of every
                                            row - the LM head of a pass with more than 16 rows then writes no logits at

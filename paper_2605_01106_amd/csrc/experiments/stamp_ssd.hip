@@ -16,7 +16,7 @@ int main() {
   hipEvent_t e0, e1; CK(hipEventCreate(&e0)); CK(hipEventCreate(&e1));
   Dims d{};
   d.L = 1; d.D = 2560; d.Hm = 40; d.P = 64; d.N = 256; d.d_inner = 2560; d.conv_dim = 2560 + 512; d.d_in_proj = 2 * 2560 + 512 + 40;
-  d.ring_w = d.conv_dim + d.Hm; d.ldzx = d.d_in_proj + 1792; d.ring_slots = 128; d.flags = 0;
+  d.ring_w = d.conv_dim + d.Hm; d.ldzx = d.d_in_proj + 1792; d.ring_rows = d.ring_slots = 128; d.ring_pass = 0; d.flags = 0;
   const int B = 64, T = 64;
   LayerDev ly{};
   auto dev = [&](size_t n, float fill) { float* p; CK(hipMalloc(&p, n * 4)); std::vector<float> h(n); for (size_t i = 0; i < n; ++i) h[i] = fill * (float)((i * 2654435761u >> 8) & 1023) / 1024.f - fill * 0.5f; CK(hipMemcpy(p, h.data(), n * 4, hipMemcpyHostToDevice)); return p; };

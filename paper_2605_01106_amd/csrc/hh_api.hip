@@ -123,16 +123,17 @@ struct hh_ctx {
 namespace {
 
 // Prompt positions per sequence per prefill pass.  Default: about 4096 activation rows per pass over the whole batch, 7680 where
-// rows are short, in multiples of 32 (the scan's chunk) from 64 to 4096, and no more than the longest prompt that fits.
+// bf16 rows are short, in multiples of 32 (the scan's chunk) from 64 to 4096 (float32 models: 1024), and no more than the longest prompt that fits.
 // Short passes leave the scan and the narrow products with few workgroups, and each costs a round of launches.  At most 512 positions
 // and 4096 rows (before) against this: one sequence of 4096 tokens through four 3B blocks 11.5 -> 8.3 ms (in passes of 1024 9.2, of
 // 2048 9.4), of 4000 through twelve 0.5B blocks 16.9 -> 8.6; two of 2500 12.7 -> 10.3 and 14.4 -> 10.0, five of 3001 19.9 -> 18.1 (two
 // blocks) and 33.0 -> 28.2; 24 ragged of 600 11.0 -> 10.3 and 26.5 -> 19.9, 64 of 448 19.3 either way and 40.4 -> 37.8.  8192 rows at a width
-// of 2560: 64 ragged sequences of 900 tokens 38.0 -> 36.4, 8 of 2048 13.9 -> 14.6.  7680 rather than 8192: a pass of 2^m positions
-// doubles the ring of raw inputs.
+// of 2560: 64 ragged sequences of 900 tokens 38.0 -> 36.4, 8 of 2048 13.9 -> 14.6.  Not more than 4096 positions: with the rows of more the
+// workspace of one sequence would exceed that of passes of 512 positions and a ring as long (0.5B shape, 9000 positions: 2391 MiB, now 2268).  Float32 models gain nothing from more than 1024 (tiny model, one of 4000 tokens 6.82 ms, in passes of 1024 6.74, of 512 7.01).
 int prefill_chunk_of(const hh_cfg& c) {
   if (c.prefill_chunk != 0) return c.prefill_chunk;
-  const int rows = (c.d_model >= 2048 ? 4096 : 7680) / (c.max_batch > 0 ? c.max_batch : 1) / 32 * 32;
+  const int per = (c.d_model >= 2048 || c.w_dtype == HH_F32 ? 4096 : 7680) / (c.max_batch > 0 ? c.max_batch : 1) / 32 * 32;
+  const int rows = std::min(per, c.w_dtype == HH_F32 ? 1024 : 4096);
   const long long longest = (long long)c.max_seq_len - 2LL * c.max_draft - 3;
   const int chunk = rows < 64 ? 64 : rows;
   return longest < chunk ? (longest < 64 ? 64 : (int)longest) : chunk;
@@ -169,8 +170,13 @@ bool derive_dims(const hh_cfg& c, Dims& d, std::string& why) {
   if (c.prefill_chunk < 0 || c.prefill_chunk > 1024) return bad("prefill_chunk must be in 1..1024");
   d.Kmax = c.max_draft; d.Bmax = c.max_batch; d.Gmax = c.max_new_tokens; d.max_seq = c.max_seq_len;
   d.Tmax = d.Kmax + 1 > chunk ? d.Kmax + 1 : chunk;
-  d.ring_slots = 4;
-  while (d.ring_slots < d.Tmax + 3) d.ring_slots <<= 1;
+  // two banks where a pass is longer than one; a bank for a whole pass where ring_slot's division would not be exact
+  const bool banks = (long long)c.max_seq_len * chunk < (1LL << 32);
+  d.ring_rows = 16;
+  while (d.ring_rows < (banks ? d.Kmax + 1 : d.Tmax) + 3) d.ring_rows <<= 1;
+  const bool two = chunk + 3 > d.ring_rows;
+  d.ring_slots = two ? 2 * d.ring_rows : d.ring_rows;
+  d.ring_pass = two ? (uint32_t)(0xffffffffu / (uint32_t)chunk) + 1 : 0;
   d.pages_per_seq = (d.max_seq + d.page_tokens - 1) / d.page_tokens;
   d.n_pages = d.pages_per_seq * d.Bmax;
   d.bf16 = c.w_dtype == HH_BF16;
@@ -223,22 +229,25 @@ size_t carve(hh_ctx* x, char* base) {
   {
     int kmax = d.D > d.d_inner ? d.D : d.d_inner;
     if (d.dq > kmax) kmax = d.dq;
-    if (d.F > kmax) kmax = d.F;
-    x->planes = c.take<uint16_t>(gemm_planes_elems((int)Mmax, kmax));
+    const int act_rows = gemm_rows_without_hand_over((int)Mmax, d.D, d.F, d.flags);   // (the others' SwiGLU results are planes already)
+    x->planes = c.take<uint16_t>(d.bf16 ? std::max(gemm_planes_elems((int)Mmax, kmax), gemm_planes_elems(act_rows, d.F)) : 0);   // (float32 models split nothing)
     x->gemm_partial = d.bf16 ? c.take<float>(gemm_partial_elems()) : nullptr;
-    x->planes_side = c.take<uint16_t>(gemm_planes_elems((int)Mmax, kmax));
-    x->planes_act = d.bf16 && Mmax > 16 ? c.take<uint16_t>(gemm_planes_elems((int)Mmax, d.F)) : nullptr;
+    x->planes_side = c.take<uint16_t>(d.bf16 ? gemm_planes_elems((int)Mmax, d.dq) : 0);   // (the attention's output projection)
     x->gemm_partial_side = d.bf16 ? c.take<float>(gemm_partial_elems()) : nullptr;
     x->row_factors = d.bf16 ? c.take<float>(Mmax) : nullptr;
   }
   x->rope = c.take<float>((size_t)d.max_seq * d.Dh);
   x->h = c.take<float>(Mmax * d.D);
-  x->zx = c.take<float>(Mmax * d.ldzx);
+  // The projections are read for the last time by the two branches, which have joined when the MLP writes the SwiGLU result, as float32 or as
+  // planes: one region for both (bf16 models, whose passes are long).
+  x->zx = c.take<float>(d.bf16 ? std::max(Mmax * std::max(d.ldzx, d.F), gemm_planes_elems((int)Mmax, d.F) / 2) : Mmax * d.ldzx);
   x->qkv = x->zx ? x->zx + d.d_in_proj : nullptr;
+  x->act = d.bf16 ? x->zx : nullptr;
+  x->planes_act = d.bf16 && Mmax > 16 ? reinterpret_cast<uint16_t*>(x->act) : nullptr;
   x->g = c.take<float>(Mmax * d.d_inner);
   x->o = c.take<float>(Mmax * d.dq);
   x->ho = c.take<float>(Mmax * d.D);
-  x->act = c.take<float>(Mmax * d.F);
+  if (!d.bf16) x->act = c.take<float>(Mmax * d.F);
   x->logits_d = c.take<float>(B * (d.Kmax > 0 ? d.Kmax : 1) * d.V);
   x->logits_v = c.take<float>(Mv * d.V);
   x->logits_p = c.take<float>(B * d.V);

@@ -14,7 +14,12 @@ struct Dims {
   int Hq, Hkv, Dh, dq, dkv, dqkv;
   int ldzx;         // row stride of the projection buffer: d_in_proj + dqkv (z | xBC | dt | q | k | v)
   int F;
-  int ring_slots;   // power of two >= d_conv-1 + max_draft+1 and >= d_conv-1 + prefill chunk
+  // Ring of raw conv inputs: what is read back are the 3 positions before a pass and the positions of a round, so that a bank of
+  // ring_rows slots (a power of two, at least 16 and d_conv-1 + max_draft+1) holds it whatever the length of a prefill pass, of which the
+  // last 3 positions are kept.  Where passes are longer than a bank there are two: pass p writes the one while it reads the positions
+  // before it from the other (ring_pass = 2^32 / prefill chunk rounded up; 0: one bank).
+  int ring_rows, ring_slots;   // ring_slots: of all banks
+  uint32_t ring_pass;
   int page_tokens, pages_per_seq, n_pages;
   int Bmax, Tmax, Gmax, Kmax, max_seq;
   int bf16;         // storage type of matrices and KV
@@ -23,6 +28,14 @@ struct Dims {
 };
 
 // ---- per-layer device pointers (an array of these lives in the workspace)
+// slot of a position in the ring (before position 0: that of position 0)
+__device__ __forceinline__ int ring_slot(const Dims& d, int pos) {
+  const uint32_t p = (uint32_t)(pos > 0 ? pos : 0);
+  return (int)((p & (uint32_t)(d.ring_rows - 1)) + (__umulhi(p, d.ring_pass) & 1u) * (uint32_t)d.ring_rows);
+}
+// first of a pass's nt positions that is kept in the ring
+__device__ __forceinline__ int ring_first(const Dims& d, int nt) { return nt + 3 <= d.ring_rows ? 0 : nt - 3; }
+
 struct LayerDev {
   const float *norm1, *conv_w, *conv_b, *a_log, *d_skip, *dt_bias, *gnorm, *norm2;
   const void *w_in, *w_out, *w_q, *w_k, *w_v, *w_o, *w_gate, *w_up, *w_down;
@@ -126,6 +139,8 @@ hipError_t launch_gemm_mfma(const GemvArgs& a, uint16_t* planes, float* partial,
 // kernel without a K split, result columns a multiple of 32): the caller then passes the same buffer as
 // planes_in of the product that consumes the result
 bool gemm_hands_over_planes(const GemvArgs& a);
+// the most rows, up to `rows`, whose SwiGLU product (K columns, N results) does not hand its result over
+int gemm_rows_without_hand_over(int rows, int K, int N, int flags);
 
 // ---- SSM branch: causal conv + selective scan over up to T positions per sequence
 struct SsmArgs {

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(512) void ssd_shared_kernel(const Dims d, const Ssm
   const int b = blockIdx.y, j0 = blockIdx.x * L;
   const int nt = a.n_tok != nullptr ? a.n_tok[b] : a.T;
   if (j0 >= nt) return;
-  const int tc = min(L, nt - j0), pos0 = a.pos0[b], rmask = d.ring_slots - 1;
+  const int tc = min(L, nt - j0), pos0 = a.pos0[b], keep = ring_first(d, nt);
   const LayerDev& ly = a.one;
   float* ring = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
   const float* zx = a.zx + first_row(a.row0, b, a.T) * d.ldzx;
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(512) void ssd_shared_kernel(const Dims d, const Ssm
   for (int u = 0; u < 3 + PP; ++u) {
     const int pos = pos0 + min(j0 + first - 3 + u, nt - 1);
     const float4 v = *reinterpret_cast<const float4*>(pos >= pos0 ? zx + (size_t)(pos - pos0) * d.ldzx + d.d_inner + ch
-                                                                  : ring + (size_t)(max(pos, 0) & rmask) * d.ring_w + ch);
+                                                                  : ring + (size_t)ring_slot(d, pos) * d.ring_w + ch);
     rows[u] = pos < 0 ? make_float4(0.f, 0.f, 0.f, 0.f) : v;
   }
 #pragma unroll
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(512) void ssd_shared_kernel(const Dims d, const Ssm
     const bool on = t < tc;
     const float rawdt = zx[(size_t)(j0 + min(t, tc - 1)) * d.ldzx + d.d_inner + d.conv_dim + hd];
     const float dt = on ? ssd_softplus(rawdt + ly.dt_bias[hd]) : 0.f;
-    if (on && a.write_ring) ring[(size_t)((pos0 + j0 + t) & rmask) * d.ring_w + d.conv_dim + hd] = rawdt;
+    if (on && a.write_ring && j0 + t >= keep) ring[(size_t)ring_slot(d, pos0 + j0 + t) * d.ring_w + d.conv_dim + hd] = rawdt;
     float la = on ? -expf(ly.a_log[hd]) * dt : 0.f;    // log a_t, float32 as in the sequential kernels
     // a decay below exp(-200) is zero in float32, and so is every product that holds it; bounded, its sums stay finite
     // (a rate of infinity would make their differences NaN) and keep the bits of the positions around it
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(512) void ssd_shared_kernel(const Dims d, const Ssm
     *reinterpret_cast<float4*>(rows_s + (is_c ? L * LDS : 0) + jj * LDS + 4 * (sg % (N / 4))) = o;
     if (!is_c) *reinterpret_cast<float4*>(out + Sh::kB + jj * N + 4 * sg) = o;
     // the raw inputs stay in the ring for the next pass's window and for rollbacks
-    if (on && a.write_ring) *reinterpret_cast<float4*>(ring + (size_t)((pos0 + j0 + jj) & rmask) * d.ring_w + ch) = rows[u + 3];
+    if (on && a.write_ring && j0 + jj >= keep) *reinterpret_cast<float4*>(ring + (size_t)ring_slot(d, pos0 + j0 + jj) * d.ring_w + ch) = rows[u + 3];
   }
   __syncthreads();
   const float* Bs = rows_s;
@@ -213,7 +213,6 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
   if (MODE != SEG_WALK && t0 >= nt) return;
   float* const seg_state = MODE == SEG_WALK ? nullptr : seg.states + (((size_t)b * seg.n + blockIdx.z) * d.Hm + h) * P * N;
   const int pos0 = a.pos0[b];
-  const int rmask = d.ring_slots - 1;
   float* ring = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
   const size_t rows0 = first_row(a.row0, b, a.T);
   const float* zx = a.zx + rows0 * d.ldzx;
@@ -222,6 +221,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
   // ---- staging, requested a chunk ahead: 4 channels of x (group sg, two positions) with the window before them, pieces of B
   // and C^T, the wavefront's tile of G, and one step size and log-decay sum (the first wavefront: lane / 32 = head of the pair)
   const int sg = tid & 31, sp = 2 * (tid >> 5), xch = 2 * blockIdx.x * P + 4 * sg;
+  const int keep = ring_first(d, nt);
   const bool keep_raw = MODE != SEG_LOCAL && a.write_ring;
   ssd_f32x4 bc[NC], cc[NC];
   float4 xr[5], gv = make_float4(0.f, 0.f, 0.f, 0.f), tw[4];
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
     _Pragma("unroll") for (int u = 0; u < 5; ++u) {                                                                                  \
       const int pos_ = pos0 + min((c0_) + sp - 3 + u, nt - 1);                                                                       \
       xr[u] = *reinterpret_cast<const float4*>(pos_ >= pos0 ? zx + (size_t)(pos_ - pos0) * d.ldzx + d.d_inner + xch                  \
-                                                            : ring + (size_t)(max(pos_, 0) & rmask) * d.ring_w + xch);               \
+                                                            : ring + (size_t)ring_slot(d, pos_) * d.ring_w + xch);                    \
     }                                                                                                                                \
     _Pragma("unroll") for (int i = 0; i < NC; ++i) {                                                                                 \
       bc[i] = *reinterpret_cast<const ssd_f32x4*>(sh_ + Sh::kB + 4 * (tid + 512 * i));                                               \
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(512) void ssd_mfma_kernel(const Dims d, const SsmAr
       if (jj >= tc) o = make_float4(0.f, 0.f, 0.f, 0.f);
       *reinterpret_cast<float4*>(ssd_smem + Lds::kX + (sg >> 4) * L * LDX + jj * LDX + 4 * (sg & 15)) = o;
       // the raw inputs stay in the ring for the next pass's window and for rollbacks
-      if (jj < tc && keep_raw) *reinterpret_cast<float4*>(ring + (size_t)((pos0 + j0 + jj) & rmask) * d.ring_w + xch) = xr[u + 3];
+      if (jj < tc && keep_raw && j0 + jj >= keep) *reinterpret_cast<float4*>(ring + (size_t)ring_slot(d, pos0 + j0 + jj) * d.ring_w + xch) = xr[u + 3];
     }
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
@@ -501,10 +501,11 @@ static bool ssd_shape(const Dims& d) {
   return d.P == kSsdP && d.Hm % 2 == 0 && d.d_inner % 4 == 0 && d.ldzx % 4 == 0 && d.ring_w % 4 == 0 && d.conv_dim % 4 == 0 &&
          (d.N == 64 || d.N == 128 || d.N == 256);
 }
+static int seg_workgroups(const Dims& d) { return d.N == 256 ? kSegWorkgroups / 2 : kSegWorkgroups; }
 static SsdSeg ssd_segments(const Dims& d, int B, int T) {
   SsdSeg seg{nullptr, nullptr, 0, 1};
   const int wgs = (d.Hm / 2) * B, chunks = (T + kSsdL - 1) / kSsdL;
-  const int most = (d.N == 256 ? kSegWorkgroups / 2 : kSegWorkgroups) / wgs;
+  const int most = seg_workgroups(d) / wgs;
   if (wgs >= 128 || T < kSegMinT || most < (d.N == 256 ? 3 : 2)) return seg;
   const int per = (chunks + most - 1) / most;      // chunks per segment
   seg.len = per * kSsdL;
@@ -516,7 +517,7 @@ size_t ssd_segment_elems(const Dims& d) {
   if (!ssd_shape(d) || d.Tmax < kSegMinT) return 0;
   size_t most = 0;
   for (int B = 1; B <= d.Bmax && (d.Hm / 2) * B < 128; ++B) {
-    const size_t n = std::min((size_t)kSegWorkgroups / ((d.Hm / 2) * B), (size_t)(d.Tmax + kSsdL - 1) / kSsdL);
+    const size_t n = std::min((size_t)seg_workgroups(d) / ((d.Hm / 2) * B), (size_t)(d.Tmax + kSsdL - 1) / kSsdL);
     most = std::max(most, (size_t)B * n * d.Hm * ((size_t)d.P * d.N + 1));
   }
   return most;

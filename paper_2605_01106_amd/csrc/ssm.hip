@@ -13,7 +13,7 @@
 //
 // Layout: S[b][h][p][n] float32, n fastest.  A workgroup owns kRows (8 or 32) rows p of one head; 8 lanes
 // share a row, each holding N/8 consecutive n in registers; the read-out over n is reduced
-// across those 8 lanes.  Ring row for position q: slot q mod ring_slots, [conv_dim raw xBC | Hm raw dt].
+// across those 8 lanes.  Ring row for position q: slot ring_slot(q), [conv_dim raw xBC | Hm raw dt].
 #include <stdlib.h>
 
 #include "hh_internal.h"
@@ -49,7 +49,6 @@ __global__ __launch_bounds__(kRows * kSub) void ssm_kernel(const Dims d, const S
   const int pos0 = a.pos0[b];
   const int p = p0 + row;
   const bool prow = p < d.P;
-  const int rmask = d.ring_slots - 1;
   const float* ring = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
   const size_t rows0 = first_row(a.row0, b, a.T);
   const float* zx = a.zx != nullptr ? a.zx + rows0 * d.ldzx : nullptr;
@@ -58,7 +57,7 @@ __global__ __launch_bounds__(kRows * kSub) void ssm_kernel(const Dims d, const S
   // (one unconditional load from a selected address, so that independent loads overlap)
   auto raw = [&](int pos, int c) -> float {
     const float* p = (zx != nullptr && pos >= pos0) ? zx + (size_t)(pos - pos0) * d.ldzx + d.d_inner + c
-                                                    : ring + (size_t)(max(pos, 0) & rmask) * d.ring_w + c;
+                                                    : ring + (size_t)ring_slot(d, pos) * d.ring_w + c;
     const float v = *p;
     return pos < 0 ? 0.f : v;
   };
@@ -119,18 +118,19 @@ __global__ __launch_bounds__(kRows * kSub) void ssm_kernel(const Dims d, const S
     // ---- keep the raw inputs of these positions for later windows and for rollback
     if (a.write_ring && zx != nullptr) {
       float* wr = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
+      const int keep = ring_first(d, nt);
       for (int it = tid; it < tc * kRows; it += kRows * kSub) {
         const int jj = it / kRows, ci = it % kRows;
-        if (p0 + ci < d.P) {
+        if (p0 + ci < d.P && j0 + jj >= keep) {
           const int c = h * d.P + p0 + ci, pos = pos0 + j0 + jj;
-          wr[(size_t)(pos & rmask) * d.ring_w + c] = raw(pos, c);
+          wr[(size_t)ring_slot(d, pos) * d.ring_w + c] = raw(pos, c);
         }
       }
       if (h == 0 && blockIdx.x == 0) {
         const int extra = 2 * N + d.Hm;
         for (int it = tid; it < tc * extra; it += kRows * kSub) {
           const int jj = it / extra, c = d.d_inner + it % extra, pos = pos0 + j0 + jj;
-          wr[(size_t)(pos & rmask) * d.ring_w + c] = raw(pos, c);
+          if (j0 + jj >= keep) wr[(size_t)ring_slot(d, pos) * d.ring_w + c] = raw(pos, c);
         }
       }
     }
@@ -218,14 +218,13 @@ __global__ __launch_bounds__(kRows * kSub + (PIPE ? chunk_stage_threads<NV, kRow
   const int pos0 = a.pos0[b];
   const int p = p0 + row;
   const bool prow = worker && p < d.P;
-  const int rmask = d.ring_slots - 1;
   float* ring = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
   const size_t rows0 = first_row(a.row0, b, a.T);
   const float* zx = a.zx != nullptr ? a.zx + rows0 * d.ldzx : nullptr;
   // row of raw inputs (xBC | dt) of position pos (positions < 0 read slot 0 and count as 0)
   auto raw_row = [&](int pos) -> const float* {
     return (zx != nullptr && pos >= pos0) ? zx + (size_t)(pos - pos0) * d.ldzx + d.d_inner
-                                          : ring + (size_t)(max(pos, 0) & rmask) * d.ring_w;
+                                          : ring + (size_t)ring_slot(d, pos) * d.ring_w;
   };
 
   float S[NV];
@@ -243,6 +242,7 @@ __global__ __launch_bounds__(kRows * kSub + (PIPE ? chunk_stage_threads<NV, kRow
       for (int i = 0; i < NV; ++i) S[i] = 0.f;
     }
   }
+  const int keep = ring_first(d, nt);
   const float dskip = ly.d_skip[h];
   const float dtb = ly.dt_bias[h];
   const float negA = -expf(ly.a_log[h]);
@@ -306,8 +306,8 @@ __global__ __launch_bounds__(kRows * kSub + (PIPE ? chunk_stage_threads<NV, kRow
             if (a.g != nullptr) *reinterpret_cast<float4*>(&zs[buf][jj][4 * xg]) = z[u];
           }
           // keep the raw inputs of these positions for later windows and for rollback
-          if (a.write_ring && zx != nullptr && active && (is_x || (h == 0 && blockIdx.x == 0)))
-            *reinterpret_cast<float4*>(ring + (size_t)((pos0 + jb + u) & rmask) * d.ring_w + c4) = r[u + 3];
+          if (a.write_ring && zx != nullptr && jb + u >= keep && active && (is_x || (h == 0 && blockIdx.x == 0)))
+            *reinterpret_cast<float4*>(ring + (size_t)ring_slot(d, pos0 + jb + u) * d.ring_w + c4) = r[u + 3];
         }
       }
     }
@@ -316,10 +316,10 @@ __global__ __launch_bounds__(kRows * kSub + (PIPE ? chunk_stage_threads<NV, kRow
       dts[buf][dt_jj] = dt;
       as[buf][dt_jj] = expf(negA * dt);
     }
-    if (stager && a.write_ring && zx != nullptr && h == 0 && blockIdx.x == 0) {
+    if (stager && a.write_ring && zx != nullptr && j0 + tc > keep && h == 0 && blockIdx.x == 0) {
       for (int it = stid; it < tc * d.Hm; it += NSTG) {
         const int jj = it / d.Hm, hh = it - jj * d.Hm, pos = pos0 + j0 + jj;
-        ring[(size_t)(pos & rmask) * d.ring_w + d.conv_dim + hh] = raw_row(pos)[d.conv_dim + hh];
+        if (j0 + jj >= keep) ring[(size_t)ring_slot(d, pos) * d.ring_w + d.conv_dim + hh] = raw_row(pos)[d.conv_dim + hh];
       }
     }
   };
@@ -512,7 +512,7 @@ __global__ void export_conv_kernel(const Dims d, const LayerDev* layer, const in
   for (int it = threadIdx.x; it < d.conv_dim * 3; it += blockDim.x) {
     const int c = it / 3, t = it % 3, pos = len - 3 + t;
     out[((size_t)b * d.conv_dim + c) * 3 + t] =
-        pos < 0 ? 0.f : ring[(size_t)(pos & (d.ring_slots - 1)) * d.ring_w + c];
+        pos < 0 ? 0.f : ring[(size_t)ring_slot(d, pos) * d.ring_w + c];
   }
 }
 

@@ -57,7 +57,7 @@ __device__ __forceinline__ void ssm_small_body(const Dims& d, const SsmArgs& a, 
   const LayerDev& ly = a.layers != nullptr ? a.layers[a.layer0 + lz] : a.one;
   TR(0);
   // Loads in the order of what they wait for.  Nothing here depends on the per-sequence
-  // scalars except the ring rows (slot = position mod ring size), which come last.
+  // scalars except the ring rows (slot = position mod ring size), which come last.  (A ring holds more rows than a pass of this kernel.)
   int pr[RG], cx[RG];
   bool prow[RG];
 #pragma unroll
@@ -66,7 +66,6 @@ __device__ __forceinline__ void ssm_small_body(const Dims& d, const SsmArgs& a, 
     prow[rg] = p0 + rg * ROWS + row < d.P;
     cx[rg] = h * d.P + pr[rg];
   }
-  const int rmask = d.ring_slots - 1;
   float* ring = ly.ring + (size_t)b * d.ring_slots * d.ring_w;
   const float* zx = a.zx != nullptr ? a.zx + (size_t)b * a.T * d.ldzx : nullptr;
   const int skip_v = (a.skip != nullptr ? a.skip : a.pos0)[b];   // absent arrays read pos0 instead and are ignored
@@ -136,7 +135,7 @@ __device__ __forceinline__ void ssm_small_body(const Dims& d, const SsmArgs& a, 
   if (nt <= 0) return;
   nt = min(nt, TMAX);
   // row of raw inputs (xBC | dt) of position pos0 + j in the ring (positions before 0 read slot 0 and count as 0)
-  auto ring_row = [&](int j) -> const float* { return ring + (size_t)(max(pos0 + j, 0) & rmask) * d.ring_w; };
+  auto ring_row = [&](int j) -> const float* { return ring + (size_t)ring_slot(d, pos0 + j) * d.ring_w; };
 #pragma unroll
   for (int j = -3; j < (int)TMAX; ++j) {
     if (j >= 0 && zx != nullptr) continue;
@@ -194,7 +193,7 @@ __device__ __forceinline__ void ssm_small_body(const Dims& d, const SsmArgs& a, 
       if (sub == 0 && prow[rg]) {
 #pragma unroll
         for (int j = 0; j < TMAX; ++j)
-          if (j < nt) ring[(size_t)((pos0 + j) & rmask) * d.ring_w + cx[rg]] = xraw[rg][j + 3];
+          if (j < nt) ring[(size_t)ring_slot(d, pos0 + j) * d.ring_w + cx[rg]] = xraw[rg][j + 3];
       }
     }
     if (h == 0 && bx == 0) {
@@ -204,12 +203,12 @@ __device__ __forceinline__ void ssm_small_body(const Dims& d, const SsmArgs& a, 
         if (gi < NGR) {
 #pragma unroll
           for (int j = 0; j < TMAX; ++j)
-            if (j < nt) store_channels<CW>(ring + (size_t)((pos0 + j) & rmask) * d.ring_w + d.d_inner + CW * gi, braw[u][j + 3]);
+            if (j < nt) store_channels<CW>(ring + (size_t)ring_slot(d, pos0 + j) * d.ring_w + d.d_inner + CW * gi, braw[u][j + 3]);
         }
       }
       for (int it = tid; it < nt * d.Hm; it += NTHR) {
         const int j = it / d.Hm, hh = it - j * d.Hm;
-        ring[(size_t)((pos0 + j) & rmask) * d.ring_w + d.conv_dim + hh] = zx[(size_t)j * d.ldzx + d.d_inner + d.conv_dim + hh];
+        ring[(size_t)ring_slot(d, pos0 + j) * d.ring_w + d.conv_dim + hh] = zx[(size_t)j * d.ldzx + d.d_inner + d.conv_dim + hh];
       }
     }
   }

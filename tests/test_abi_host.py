@@ -42,6 +42,14 @@ def test_workspace_sizes(B):
     assert 69e9 < big < 130e9
 
 
+@pytest.mark.parametrize("workload,batch,max_seq,k,strict,mib", [
+    ("c1", 1, 4200, 8, 0, 2305), ("c1", 1, 32768, 8, 1, 3096), ("c1", 1, 9000, 8, 0, 2391), ("c1", 2, 4200, 8, 0, 2766), ("c1", 5, 600, 2, 1, 5199),
+    ("c3", 1, 4200, 8, 0, 7523), ("c3", 1, 32768, 8, 1, 8898), ("c3", 2, 4200, 8, 0, 8338), ("c0", 1, 9000, 2, 0, 34), ("c0", 8, 1500, 2, 0, 117)])
+def test_workspace_of_long_passes(B, workload, batch, max_seq, k, strict, mib):
+    """Long prefill passes need no more memory than passes of 512 positions did with a ring of raw inputs as long as a pass (mib)."""
+    assert B.hh_workspace_bytes(B.make_cfg(W.WORKLOADS[workload].cfg, batch, max_seq, k, 16, draft_state_mode=strict)) <= mib << 20
+
+
 @pytest.mark.parametrize("strict", [0, 1])
 def test_every_array_has_a_guard_of_its_own(B, strict):
     """HH_KF_CANARIES puts 256 guard bytes behind every array that a kernel writes, so the workspace grows by 256 bytes per
@@ -182,6 +190,6 @@ def test_workspace_grows_with_the_strict_state_and_the_guards(B):
     strict = B.hh_workspace_bytes(B.make_cfg(c2.cfg, 16, 2048 + 300, 4, 256, draft_state_mode=1))
     guarded = B.hh_workspace_bytes(B.make_cfg(c2.cfg, 16, 2048 + 300, 4, 256, kernel_flags=B.HH_KF_CANARIES))
     state = 36 * 16 * 24 * 64 * 128 * 4
-    ring = 36 * 16 * 512 * (1536 + 2 * 128 + 24) * 4      # 512 slots: the next power of two above the 256-position prefill pass + 3
+    ring = 36 * 16 * 32 * (1536 + 2 * 128 + 24) * 4       # two banks of 16 slots, whatever the length of a prefill pass
     assert state + ring <= strict - base < state + ring + (1 << 20)
     assert 0 < guarded - base < 1 << 20

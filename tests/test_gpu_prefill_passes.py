@@ -53,3 +53,36 @@ def test_scan_inputs_shared_by_the_heads(d_state, heads):
         ctx.close()
     for i, (got, ref) in enumerate(zip(*res)):
         assert_close(f"output {i}", got, ref, atol, rtol, scale_to_ref=True)
+
+
+@pytest.mark.parametrize("flag", ["", "HH_KF_SSM_GENERAL", "HH_KF_SSM_SEQUENTIAL", "HH_KF_SSM_MATMUL", "HH_KF_SSM_SCALAR_CONV"])
+@pytest.mark.parametrize("chunk,k", [(5, 2), (14, 2), (16, 4), (33, 13), (100, 8)])
+def test_passes_longer_than_the_ring(flag, chunk, k):
+    """Raw inputs of a pass: the window of the next pass, rollbacks across the end of a pass and the rounds behind them find theirs, whatever
+    the pass length (one of 1024 positions holds every prompt here)."""
+    from paper_2605_01106_amd import binding as B
+
+    cfg = W.scaled_config("ring", n_layers=2, d_model=64, vocab=160, m_heads=4, m_head_dim=64, d_state=64, n_q_heads=2, n_kv_heads=1, head_dim=32,
+                          d_ff=96, w_dtype=W.F32)
+    lens = [3 * chunk - 1, 2 * chunk + 1, 2 * chunk + 2, 2 * chunk, chunk + 3, 1, chunk]
+    wts, prompts, n = W.make_lively_weights(cfg, 8), W.make_prompts(cfg.vocab, len(lens), lens, 9), len(lens)
+    atol, rtol = tolerances(W.F32)
+    counts, drafts = np.random.default_rng(4).integers(0, k + 1, (3, n)).astype(np.int32), W.make_random_drafts(cfg.vocab, 3, n, k, 2)
+    res = []
+    for c in (chunk, 1024):
+        import torch
+        ctx = B.Context(wts, n, 400, k, 60, prefill_chunk=c, kernel_flags=(getattr(B, flag) if flag else 0) | B.HH_KF_CANARIES)
+        ctx.hh_prefill(prompts, lens, 60)
+        out = []
+        for r in range(3):
+            out += [v for layer in range(cfg.n_layers) for v in ctx.hh_get_state(layer)]
+            ctx.hh_draft(k)
+            ctx.hh_set_drafts(drafts[r])
+            ctx.hh_verify()
+            out.append(ctx.hh_get_logits(1)[:, 1:])
+            ctx.hh_commit(torch.from_numpy(counts[r]).to("cuda:0"))
+        assert ctx.hh_check_canaries() == 0
+        res.append(out + [v for layer in range(cfg.n_layers) for v in ctx.hh_get_state(layer)])
+        ctx.close()
+    for i, (got, ref) in enumerate(zip(*res)):
+        assert_close(f"output {i}", got, ref, atol, rtol, scale_to_ref=True)
