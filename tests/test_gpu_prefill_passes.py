@@ -1,5 +1,5 @@
 """Prefill passes (needs an MI355X).  How a prompt is cut into passes is a schedule: the default (up to 4096 positions per sequence and
-pass) gives what passes of 192 positions give, to rounding; the matmul-form scan gives what the sequential one gives."""
+pass, 1024 of float32 models) gives what passes of 192 positions give, to rounding; the matmul-form scan gives what the sequential one gives."""
 import numpy as np
 import pytest
 
@@ -9,12 +9,15 @@ from parity_util import assert_close, tolerances
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("dtype", [W.BF16, W.F32])
-@pytest.mark.parametrize("lens", [[4096 + 33], [2751, 2687, 64], [1025], [63, 1300, 1280, 1, 1215, 700]])   # (below, at and above a pass)
-def test_default_passes(dtype, lens):
+# below, at and above a pass: 4096 positions (one sequence; also at a width of 2048), 2560 (three), 1280 (six); 1024, 1024 and 672 in float32
+@pytest.mark.parametrize("dtype,d_model,d_state,lens", [
+    (W.BF16, 64, 64, [4096 + 33]), (W.BF16, 64, 128, [2561, 2560, 64]), (W.BF16, 64, 256, [1025]), (W.BF16, 64, 64, [63, 1300, 1280, 1, 1215, 700]),
+    (W.BF16, 2048, 128, [4096 + 33]), (W.BF16, 2048, 64, [2048 + 1, 2048]),
+    (W.F32, 64, 64, [2048 + 33]), (W.F32, 64, 256, [1025, 1024, 64]), (W.F32, 64, 128, [1025]), (W.F32, 64, 64, [63, 673, 672, 1, 660, 700])])
+def test_default_passes(dtype, d_model, d_state, lens):
     from paper_2605_01106_amd import binding as B
 
-    cfg = W.scaled_config("passes", n_layers=2, d_model=64, vocab=160, m_heads=2, m_head_dim=64, d_state=64, n_q_heads=2, n_kv_heads=1,
+    cfg = W.scaled_config("passes", n_layers=2, d_model=d_model, vocab=160, m_heads=4, m_head_dim=64, d_state=d_state, n_q_heads=2, n_kv_heads=1,
                           head_dim=32, d_ff=96, w_dtype=dtype)
     wts, prompts, n = W.make_lively_weights(cfg, 5), W.make_prompts(cfg.vocab, len(lens), lens, 4), len(lens)
     atol, rtol = tolerances(dtype)
@@ -35,7 +38,7 @@ def test_default_passes(dtype, lens):
         assert_close(f"output {i}", got, ref, atol, rtol, scale_to_ref=True)
 
 
-@pytest.mark.parametrize("d_state,heads", [(64, 2), (64, 18), (128, 16), (256, 34)])   # (heads are shared out by 16)
+@pytest.mark.parametrize("d_state,heads", [(64, 4), (64, 20), (128, 16), (256, 36)])   # (heads are shared out by 16)
 def test_scan_inputs_shared_by_the_heads(d_state, heads):
     from paper_2605_01106_amd import binding as B
 
@@ -51,6 +54,7 @@ def test_scan_inputs_shared_by_the_heads(d_state, heads):
         res.append([ctx.hh_get_logits(2)] + [v for layer in range(cfg.n_layers) for v in ctx.hh_get_state(layer)])
         assert ctx.hh_check_canaries() == 0
         ctx.close()
+    assert not np.array_equal(res[0][1], res[1][1])   # (two forms of the scan, not one compared with itself)
     for i, (got, ref) in enumerate(zip(*res)):
         assert_close(f"output {i}", got, ref, atol, rtol, scale_to_ref=True)
 
