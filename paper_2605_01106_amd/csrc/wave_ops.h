@@ -71,16 +71,18 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 }
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// 1 / d for d >= 1 (infinity counts as the largest finite value, below 2^-126 is zero): the hardware's reciprocal and one Newton
-// step, 4 instructions where the IEEE division takes 10.
-__device__ __forceinline__ float rcp_above_one(float d) {
-  d = fminf(d, 3.402823466e+38f);
-  const float r = __builtin_amdgcn_rcpf(d);
-  return fmaf(fmaf(-d, r, 1.0f), r, r);
+// v / d for d >= 1 (infinity counts as the largest finite value; above 2^126 the result is zero): the hardware's reciprocal and the
+// quotient corrected by its remainder, 5 instructions where the IEEE division takes 10, and the same bits on the 2^20 values each of
+// |v| < 0.5, 2, 8, 30 and 80 that were compared.  (The reciprocal corrected before it is multiplied, which rounds twice: rms error of the SiLU 5.0e-8 instead of
+// 4.3e-8 for |v| < 0.5, a quarter of the bits others.)
+__device__ __forceinline__ float div_above_one(float v, float d) {
+  constexpr float kMax = 3.402823466e+38f;
+  d = fminf(d, kMax);
+  const float r = __builtin_amdgcn_rcpf(d), q = v * r;
+  return fmaf(fminf(fmaf(-d, q, v), kMax), r, q);   // (the remainder of an infinite v is NaN)
 }
 // v * sigmoid(v) with the hardware exponential (within 1 ulp; the argument scaling adds |v| * 2^-24 relative): for every conv channel
-// of every position.  Error as with an IEEE division (rms 7.7e-7, largest 3.8e-6 for |v| < 80; 99.4 % the same bits); decode rounds 0.3 to 0.9 %
-// faster, a walk of the matmul-form scan 4 %.
-__device__ __forceinline__ float fast_silu(float v) { return v * rcp_above_one(1.0f + __expf(-v)); }
+// of every position.  Decode rounds 0.3 to 0.9 % faster than with the IEEE division, a walk of the matmul-form scan 4 %.
+__device__ __forceinline__ float fast_silu(float v) { return div_above_one(v, 1.0f + __expf(-v)); }
 
 }  // namespace hh
