@@ -705,7 +705,7 @@ hh_status hh_create(const hh_weights* weights, const hh_cfg* cfg, hh_ctx** out) 
       bound(ld.norm1, d.D, BOUND_VALUES, n1 + d.d_in_proj + d.dq + d.dkv, d.dkv, t.o);   // (the rows of w_v)
       pack(ld.w_out, d.D, d.d_inner, t.out, nullptr);
       bound(ld.gnorm, d.d_inner, BOUND_NORMED, nullptr, 0, t.out);
-      if (pe == hipSuccess) pe = launch_act_input(ld.w_gate, ld.w_up, d.F, d.D, ld.norm2, t.act_weights, uinv, nullptr);
+      if (pe == hipSuccess) pe = launch_act_input(ld.w_gate, ld.w_up, d.F, d.D, ld.norm2, n1, t.act_weights, uinv, nullptr);
       pack(ld.w_gate, d.F, d.D, t.gate, n1, uinv);
       pack(ld.w_up, d.F, d.D, t.up, n2, uinv);
       bound(ld.norm2, d.D, BOUND_NORMED, nullptr, 0, t.gate);
