@@ -37,16 +37,12 @@ __device__ __forceinline__ float row16_sum(float v) {
   v += dpp_move<0x140>(v);   // row_mirror
   return v;
 }
-// largest of each 8 / 16 lanes, left in every one of them
-__device__ __forceinline__ float lanes8_max(float v) {
-  v = fmaxf(v, dpp_move<0xB1>(v));
-  v = fmaxf(v, dpp_move<0x4E>(v));
-  return fmaxf(v, dpp_move<0x141>(v));
-}
-__device__ __forceinline__ float row16_max(float v) {
-  v = lanes8_max(v);
-  return fmaxf(v, dpp_move<0x140>(v));
-}
+// largest of each 8 / 16 lanes' values, none of them negative, left in every one of them (as unsigned words: one instruction per step where
+// the float maximum takes five, for moving and quieting its operands)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_max(uint32_t u) { return max(u, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xf, 0xf, false)); }
+__device__ __forceinline__ float lanes8_max(float v) { return __uint_as_float(dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(__float_as_uint(v))))); }
+__device__ __forceinline__ float row16_max(float v) { return __uint_as_float(dpp_max<0x140>(__float_as_uint(lanes8_max(v)))); }
 // sum over the 64 lanes (the four row totals added in row order), uniform result
 __device__ __forceinline__ float wave_sum64(float v) {
   v = row16_sum(v);
