@@ -1,5 +1,5 @@
 // Development aid: timing and in-kernel phase stamps (csrc/trace.h) of the many-row LDS-staged GEMM at the 3B shape
-// (576 verification rows, 4096 prefill rows).  Stamps: 0 start, 1 first copies issued, 2 end of the K loop, 3 end.
+// (576 verification rows, 4096 prefill rows) on normal weights and activations (on zeros the clock is a quarter higher).  Stamps: 0 start, 1 first copies issued, 2 end of the K loop, 3 end.
 // Build: hipcc --offload-arch=gfx950 -O3 -std=c++17 -Xclang -target-feature -Xclang -packed-fp32-ops -I../../../include -o stamp_gemm_lds stamp_gemm_lds.hip
 #define HH_KERNEL_TRACE 1
 #include <stdio.h>
@@ -9,6 +9,17 @@
 #include "../trace.h"
 #include "../skinny_mfma.hip"
 #include "../gemm_mfma.hip"
+// values like a normal distribution's (the sum of four uniform ones), as float32 or as float16 scaled to a tile's range
+template <class T>
+__global__ void fill_kernel(T* p, size_t n, float scale, uint32_t seed) {
+  for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+    uint64_t z = (i + 1) * 0x9E3779B97F4A7C15ull + seed;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull; z = (z ^ (z >> 27)) * 0x94D049BB133111EBull; z ^= z >> 31;
+    float v = 0.f;
+    for (int k = 0; k < 4; ++k) v += (float)((z >> (16 * k)) & 0xffff) * (1.f / 32768.f) - 1.f;
+    p[i] = (T)(v * 0.866f * scale);
+  }
+}
 namespace hh { int gemv_max_blocks() { return 1 << 15; } }
 using namespace hh;
 #define CK(x) do { hipError_t e=(x); if(e!=hipSuccess){printf("ERR %s line %d: %s\n",#x,__LINE__,hipGetErrorString(e)); exit(1);} } while(0)
@@ -27,13 +38,18 @@ int main() {
     const std::vector<float> ones(scaled_tiles_floats(c.N), 1.f);
     for (int l = 0; l < L; ++l)
       for (HalfTiles* h : {&P[l], &P2[l]}) {
-        CK(hipMalloc(&h->tiles, pe * 2)); CK(hipMemset(h->tiles, 0x3c, pe * 2));
+        CK(hipMalloc(&h->tiles, pe * 2));
+        hipLaunchKernelGGL(fill_kernel<_Float16>, dim3(1024), dim3(256), 0, s, reinterpret_cast<_Float16*>(h->tiles), pe, 4096.f, (uint32_t)(2 * l + (h == &P2[l])));
+        CK(hipGetLastError());
         CK(hipMalloc(&h->scale, ones.size() * 4)); CK(hipMemcpy(h->scale, ones.data(), ones.size() * 4, hipMemcpyHostToDevice));
       }
     float *X, *Y, *nw, *partial; uint16_t* planes;
-    CK(hipMalloc(&X, (size_t)c.M * c.K * 4)); CK(hipMemset(X, 0, (size_t)c.M * c.K * 4));
+    CK(hipMalloc(&X, (size_t)c.M * c.K * 4));
+    hipLaunchKernelGGL(fill_kernel<float>, dim3(1024), dim3(256), 0, s, X, (size_t)c.M * c.K, 1.f, 99u);
+    CK(hipGetLastError());
     CK(hipMalloc(&Y, (size_t)c.M * c.N * 4)); CK(hipMemset(Y, 0, (size_t)c.M * c.N * 4));
-    CK(hipMalloc(&nw, c.K * 4)); CK(hipMemset(nw, 0, c.K * 4));
+    CK(hipMalloc(&nw, c.K * 4));
+    { const std::vector<float> one(c.K, 1.f); CK(hipMemcpy(nw, one.data(), c.K * 4, hipMemcpyHostToDevice)); }
     CK(hipMalloc(&partial, gemm_partial_elems() * 4));
     CK(hipMalloc(&planes, gemm_planes_elems(c.M, c.K) * 2));
     auto run = [&](int it) {

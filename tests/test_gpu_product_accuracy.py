@@ -2,7 +2,7 @@
 makes it, also for weights and activations of very different size.
 
 A one- or two-block bf16 model is prefilled in one pass of batch x positions rows, which choose the kernels: 4..16 rows (activations
-split per wavefront), 17..96 (per window), more (split into planes beforehand, handed over or not), and the kernel of 9 rows and more
+split per wavefront), 17..96 (per window, in either shape), more (split into planes beforehand, handed over or not), and the kernel of 9 rows and more
 without LDS.  Compared are the raw convolution inputs, that is the input projection of each block, and the logits.  The reference
 is the oracle with the library's own cached keys and values, so that no 16-bit rounding lies between the two.
 
@@ -19,7 +19,8 @@ BOUND = 3e-6
 
 # rows of the pass, kernel flags by name
 FAMILIES = [(2, 4, ()), (3, 5, ()), (4, 10, ()), (6, 16, ()), (10, 16, ()), (10, 16, ("HH_KF_NO_HANDOVER",)), (12, 50, ()),
-            (3, 5, ("HH_KF_SKINNY_OFF", "HH_KF_MID_OFF")), (4, 15, ("HH_KF_MID_OFF",)), (4, 10, ("HH_KF_MID_OFF", "HH_KF_ROWS_LDS"))]
+            (3, 5, ("HH_KF_SKINNY_OFF", "HH_KF_MID_OFF")), (4, 15, ("HH_KF_MID_OFF",)), (4, 10, ("HH_KF_MID_OFF", "HH_KF_ROWS_LDS")),
+            (4, 5, ("HH_KF_MID_WIDE",)), (3, 11, ("HH_KF_MID_WIDE",)), (4, 15, ("HH_KF_MID_WIDE",)), (7, 11, ("HH_KF_MID_WIDE",)), (6, 16, ("HH_KF_MID_WIDE",))]
 
 
 def _model(layers=2, seed=11, d_model=264, d_ff=416):

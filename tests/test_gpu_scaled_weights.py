@@ -72,9 +72,10 @@ def test_whole_matrices_times_powers_of_two(B, batch, k, tokens):
 
 @pytest.mark.parametrize("batch,k,tokens", SIZES)
 def test_columns_times_powers_of_two(B, batch, k, tokens):
-    """The same column by column, a range of 2^12 in one row of activations and its inverse in the weights.  Both terms keep
-    24 bits of each value down to 2^-17 of a block's largest, so results move by float32 rounding alone: 2^-22 per product, times
-    what one cached key or value of the other 16-bit neighbour makes of it (one layer: 2e-5 seen).  A lost low term is 2^-12."""
+    """The same column by column, a range of 2^12 in one row of activations and its inverse in the weights: no factor of a column is
+    missed.  What a cached key or value of the other 16-bit neighbour makes of float32 rounding is 2e-5 at most here.  (A power of two
+    leaves a term's bits as they are, so a low term that is lost in both models alike does not show: the products against float64 are in
+    test_gpu_product_accuracy.py.)"""
     cfg, base = _model(4, d_ff=96, layers=1)
     r = np.random.default_rng(1)
     scaled = copy.deepcopy(base)
