@@ -170,8 +170,9 @@ bool derive_dims(const hh_cfg& c, Dims& d, std::string& why) {
   if (c.prefill_chunk < 0 || c.prefill_chunk > 1024) return bad("prefill_chunk must be in 1..1024");
   d.Kmax = c.max_draft; d.Bmax = c.max_batch; d.Gmax = c.max_new_tokens; d.max_seq = c.max_seq_len;
   d.Tmax = d.Kmax + 1 > chunk ? d.Kmax + 1 : chunk;
-  // two banks where a pass is longer than one; a bank for a whole pass where ring_slot's division would not be exact
-  const bool banks = (long long)c.max_seq_len * chunk < (1LL << 32);
+  // one bank of up to 512 slots where it holds a whole pass, as such contexts always had, two of a round's length behind longer passes; a
+  // bank for a whole pass again where ring_slot's division would not be exact
+  const bool banks = d.Tmax + 3 > 512 && (long long)c.max_seq_len * chunk < (1LL << 32);
   d.ring_rows = 16;
   while (d.ring_rows < (banks ? d.Kmax + 1 : d.Tmax) + 3) d.ring_rows <<= 1;
   const bool two = chunk + 3 > d.ring_rows;

@@ -16,8 +16,8 @@ struct Dims {
   int F;
   // Ring of raw conv inputs: what is read back are the 3 positions before a pass and the positions of a round, so that a bank of
   // ring_rows slots (a power of two, at least 16 and d_conv-1 + max_draft+1) holds it whatever the length of a prefill pass, of which the
-  // last 3 positions are kept.  Where passes are longer than a bank there are two: pass p writes the one while it reads the positions
-  // before it from the other (ring_pass = 2^32 / prefill chunk rounded up; 0: one bank).
+  // last 3 positions are kept.  Passes of up to 509 positions have one bank that holds all of theirs; behind longer ones there are two banks:
+  // pass p writes the one while it reads the positions before it from the other (ring_pass = 2^32 / prefill chunk rounded up; 0: one bank).
   int ring_rows, ring_slots;   // ring_slots: of all banks
   uint32_t ring_pass;
   int page_tokens, pages_per_seq, n_pages;

@@ -190,6 +190,6 @@ def test_workspace_grows_with_the_strict_state_and_the_guards(B):
     strict = B.hh_workspace_bytes(B.make_cfg(c2.cfg, 16, 2048 + 300, 4, 256, draft_state_mode=1))
     guarded = B.hh_workspace_bytes(B.make_cfg(c2.cfg, 16, 2048 + 300, 4, 256, kernel_flags=B.HH_KF_CANARIES))
     state = 36 * 16 * 24 * 64 * 128 * 4
-    ring = 36 * 16 * 32 * (1536 + 2 * 128 + 24) * 4       # two banks of 16 slots, whatever the length of a prefill pass
+    ring = 36 * 16 * 512 * (1536 + 2 * 128 + 24) * 4      # 512 slots: the next power of two above the 256-position prefill pass + 3
     assert state + ring <= strict - base < state + ring + (1 << 20)
     assert 0 < guarded - base < 1 << 20
