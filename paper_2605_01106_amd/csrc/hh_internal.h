@@ -125,7 +125,7 @@ size_t scaled_tiles_floats(int N);
 // tiles and factors (but for those of the activations) of W [N][K], column k times col[k] (nullptr: as it is); norms: the
 // 2-norms of its rows [N rounded up to 16], columns times norm_col[k] (nullptr: as they are)
 hipError_t launch_scaled_tiles(const void* W, int N, int K, size_t ldw, const float* col, const HalfTiles& h, const float* norm_col, float* norms, hipStream_t s);
-// norm weights of the gate/up product's input times column factors u, and 1 / u (see column_max_kernel); scratch [K]
+// norm weights of the gate/up product's input times column factors u, and 1 / u (see column_max_kernel); scratch [16][K]
 hipError_t launch_act_input(const void* gate, const void* up, int N, int K, const float* norm_w, float* scratch, float* weighted, float* inverse, hipStream_t s);
 // factors of the SwiGLU result's columns, from the 2-norms of the gate's and the up matrix's rows: col[j] (the down projection's
 // columns), inverse[j], and the up matrix's row factors times inverse[j] in up_out (its other values are up's)
